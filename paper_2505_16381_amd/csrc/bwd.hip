@@ -573,14 +573,14 @@ __global__ __launch_bounds__(256) void bwd_keyside2_kernel(BwdParams p) {
     // of chunk j + (w >> 1), both query halves in turn.
     constexpr int CPW = FAR ? 2 : 1, NPOS = SBC / CPW;
     const int NC = p.NC;                                        // chunks per head in the workspace arrays and the grid's numbering
-    const int nsb_g = (NC + SBC - 1) / SBC;
+    const int nsb_g = (NC + SBC - 1) / SBC - (FAR ? 1 : 0);      // (far: no queries right of the last super-block)
     const int xcd = blockIdx.x & 7, kk = blockIdx.x >> 3;
     // (the divisions run on the vector unit; their results go back to scalar registers)
     const int j = __builtin_amdgcn_readfirstlane((kk / NPOS % nsb_g) * SBC + (kk % NPOS) * CPW);       // first key chunk of the workgroup
     const int bh = __builtin_amdgcn_readfirstlane((kk / (NPOS * nsb_g)) * 8 + xcd);
     if (bh >= p.B * p.H) return;
     const int NCo = (seq_len(p.ul, bh, p.L) + CHUNK - 1) / CHUNK;      // this head's own chunks
-    if (j >= NCo) return;
+    if (j >= NCo || (FAR && is_last_sb(j / SBC, NCo))) return;
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), h = lane >> 5, l32 = lane & 31;
     const int kh = wv & 1;
     const int jw = FAR ? j + (wv >> 1) : j;                            // this wave's key chunk
@@ -972,6 +972,7 @@ __global__ __launch_bounds__(256) void bwd_ddp_kernel(BwdParams p) {
     const int sb_end = (cj / SBC + 1) * SBC;
     const int i0 = FAR ? sb_end : j + 1;
     const int i1 = FAR ? NCo : (sb_end < NCo ? sb_end : NCo);       // (no queries to the right: the sums are zero)
+    if (FAR && is_last_sb(j, NCo)) return;
     f32x16 acc[NOWN];
 #pragma unroll
     for (int o = 0; o < NOWN; ++o) acc[o] = zero16();
@@ -1012,7 +1013,8 @@ __global__ __launch_bounds__(256) void bwd_ddp_kernel(BwdParams p) {
 }
 
 // ---------------------------------------------------------------------------------------
-// Batched small product for the chunk-transform adjoint, one workgroup per (chunk, bh):
+// Batched small product for the adjoint of the second level (fp32 operands), one workgroup per (chunk, bh), the
+// chunks of a head's last super-block left out:
 //   C[m][n] = mask( alpha * sum_k A[m][k] B[n][k] + Cin[m][n] )
 // Operands are addressed with explicit strides (so either orientation of a stored
 // matrix can be used), converted to the operand type while being staged in LDS.
@@ -1109,6 +1111,7 @@ __global__ __launch_bounds__(256) void batched_gemm_kernel(GemmArgs a) {
     const int chunk = blockIdx.x * a.cmul + a.cadd, bh = blockIdx.y;
     const int Lown = seq_len(a.ul, bh, a.L);               // this head's own length (packed batches: may be shorter than a.L)
     if (chunk >= a.NC || chunk * CHUNK >= Lown) return;
+    if (is_last_sb(chunk / SBC, (Lown + CHUNK - 1) / CHUNK)) return;
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), h = lane >> 5, l32 = lane & 31;
     stage_mat<TIO>(a.A, a.ul, As, ld, a.M, a.K, bh, chunk, Lown, tid);
     stage_mat<TIO>(a.B, a.ul, Bs, ld, a.N, a.K, bh, chunk, Lown, tid);
@@ -1306,7 +1309,8 @@ static hipError_t launch_scan_t(const BwdParams& p, int stages, hipStream_t st) 
     const int ntiles = (p.NC + 1) / 2;
     const int BH = p.B * p.H, nsb = (p.NC + SBC - 1) / SBC;
     const dim3 grid_adj((unsigned)(8 * ((BH + 7) / 8) * ntiles));
-    const dim3 grid_key((unsigned)(8 * ((BH + 7) / 8) * nsb * SBC)), grid_key_far((unsigned)(8 * ((BH + 7) / 8) * nsb * (SBC / 2)));
+    const dim3 grid_key((unsigned)(8 * ((BH + 7) / 8) * nsb * SBC)), grid_key_far((unsigned)(8 * ((BH + 7) / 8) * (nsb - 1) * (SBC / 2)));
+    const bool has_far = nsb > 1;       // (one super-block per head: nothing is far)
     if (p.cum) {       // PaTH-FoX instantiations
         if (stages & BWD_STAGE_SCAN) {
             if constexpr (sizeof(typename Compute<TIO>::type) == 2) {
@@ -1323,7 +1327,7 @@ static hipError_t launch_scan_t(const BwdParams& p, int stages, hipStream_t st) 
         if ((e = set_smem(&bwd_keyside2_kernel<TIO, D, true, true>, key_bytes)) != hipSuccess) return e;
         if (stages & BWD_STAGE_KEYS_NEAR) hipLaunchKernelGGL((bwd_keyside2_kernel<TIO, D, false, true>), grid_key, dim3(256), key_bytes, st, p);
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        if (stages & BWD_STAGE_KEYS_FAR) hipLaunchKernelGGL((bwd_keyside2_kernel<TIO, D, true, true>), grid_key_far, dim3(256), key_bytes, st, p);
+        if (has_far && (stages & BWD_STAGE_KEYS_FAR)) hipLaunchKernelGGL((bwd_keyside2_kernel<TIO, D, true, true>), grid_key_far, dim3(256), key_bytes, st, p);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     } else {
         if (stages & BWD_STAGE_SCAN) {
@@ -1341,7 +1345,7 @@ static hipError_t launch_scan_t(const BwdParams& p, int stages, hipStream_t st) 
         if ((e = set_smem(&bwd_keyside2_kernel<TIO, D, true, false>, key_bytes)) != hipSuccess) return e;
         if (stages & BWD_STAGE_KEYS_NEAR) hipLaunchKernelGGL((bwd_keyside2_kernel<TIO, D, false, false>), grid_key, dim3(256), key_bytes, st, p);
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        if (stages & BWD_STAGE_KEYS_FAR) hipLaunchKernelGGL((bwd_keyside2_kernel<TIO, D, true, false>), grid_key_far, dim3(256), key_bytes, st, p);
+        if (has_far && (stages & BWD_STAGE_KEYS_FAR)) hipLaunchKernelGGL((bwd_keyside2_kernel<TIO, D, true, false>), grid_key_far, dim3(256), key_bytes, st, p);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     const size_t ddp_bytes = DdpCfg<TIO, D>::smem_bytes;
@@ -1351,7 +1355,8 @@ static hipError_t launch_scan_t(const BwdParams& p, int stages, hipStream_t st) 
     if (sizeof(typename Compute<TIO>::type) != 2)       // 16-bit operands: the near key-side kernel has written ddP
         hipLaunchKernelGGL((bwd_ddp_kernel<TIO, D, false>), grid, dim3(256), ddp_bytes, st, p);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    const dim3 grid_sb((p.NC + SBC - 1) / SBC, p.B * p.H);
+    if (!has_far) return hipSuccess;
+    const dim3 grid_sb(nsb - 1, p.B * p.H);
     hipLaunchKernelGGL((bwd_ddp_kernel<TIO, D, true>), grid_sb, dim3(256), ddp_bytes, st, p);
     return hipGetLastError();
 }

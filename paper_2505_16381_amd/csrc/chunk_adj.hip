@@ -425,8 +425,8 @@ __global__ __launch_bounds__(CA_NT) void sb_chain_kernel(SbChainArgs a) {
     const int L = seq_len(a.ul, bh, a.L), NCo = (L + CHUNK - 1) / CHUNK;   // this head's own length and chunks
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), h = lane >> 5, l32 = lane & 31;
     const int c0 = J * SBC;
-    if (c0 >= NCo) return;                            // (packed batch: a shorter sequence has fewer super-blocks)
-    const int clast = (c0 + SBC - 1 < NCo) ? c0 + SBC - 1 : NCo - 1;
+    if (is_last_sb(J, NCo)) return;                   // no gradient arrives there (packed batch: a shorter sequence has fewer super-blocks)
+    const int clast = c0 + SBC - 1;
     const int TS = STRIDED ? (int)a.ul.vt : D;        // token stride of W
     const bool act = wv < 2 * DB;                     // 64 x d and d x 64 results: one block per wave
     const int hb = act ? wv / DB : 0, db = wv % DB;   // ... block (hb, db) of a 64 x d result, (db, hb) of a d x 64 one
@@ -551,7 +551,7 @@ hipError_t launch_sb_s(const SbChainArgs& a, int BH, hipStream_t st) {
     static const hipError_t attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&sb_chain_kernel<TIO, D, STRIDED>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::TOTAL);
     if (attr_err != hipSuccess) return attr_err;
-    hipLaunchKernelGGL((sb_chain_kernel<TIO, D, STRIDED>), dim3((a.NC + SBC - 1) / SBC, BH), dim3(CA_NT), (size_t)C::TOTAL, st, a);
+    hipLaunchKernelGGL((sb_chain_kernel<TIO, D, STRIDED>), dim3((a.NC + SBC - 1) / SBC - 1, BH), dim3(CA_NT), (size_t)C::TOTAL, st, a);      // (NC > SBC)
     return hipGetLastError();
 }
 template <typename TIO, int D>

@@ -42,10 +42,11 @@ __global__ __launch_bounds__(256) void prep2_fwd_kernel(FwdParams p) {
 
     const int sb = blockIdx.x, bh = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), h = lane >> 5, l32 = lane & 31;
-    const int NC = p.NC;                                                   // chunks per head in the workspace arrays
+    const int NC = p.NC, nsb = (NC + SBC - 1) / SBC;                       // chunks and super-blocks per head in the workspace arrays
     const int NCown = (seq_len(p.ul, bh, p.L) + CHUNK - 1) / CHUNK;        // this head's own (packed batches: may be fewer)
     const int c0 = sb * SBC;
     if (c0 >= NCown) return;
+    if (BWD && is_last_sb(sb, NCown)) return;         // (a training step never looks at it from the right: see is_last_sb)
     const int clast = (c0 + SBC - 1 < NCown) ? c0 + SBC - 1 : NCown - 1;
 
     Frag idf[SPB];
@@ -165,14 +166,14 @@ __global__ __launch_bounds__(256) void prep2_fwd_kernel(FwdParams p) {
     }
     // -(I - P_superblock) as the sweep's tile (rows b, contraction a): E itself (rows a, lane b) is the
     // transpose of what the registers hold -- taken through the matrix unit.
-    Frag* dst = reinterpret_cast<Frag*>(reinterpret_cast<T*>(p.dp2) + ((size_t)bh * gridDim.x + sb) * (size_t)D * D);
+    Frag* dst = reinterpret_cast<Frag*>(reinterpret_cast<T*>(p.dp2) + ((size_t)bh * nsb + sb) * (size_t)D * D);
 #pragma unroll
     for (int o = 0; o < NE; ++o) {
         const int blk = wv + 4 * o, bb = blk / DB, ab = blk % DB;
         Frag fin[SPB];
         pack_block<T>(Fm[o], fin);                              // tile piece (rows a, contraction b)
         if (BWD && p.dpt2 && sizeof(T) == 4) {      // backward, fp32 operands only: -(I - P_superblock) in the arrangement (rows a, contraction b)
-            Frag* dt = reinterpret_cast<Frag*>(reinterpret_cast<T*>(p.dpt2) + ((size_t)bh * gridDim.x + sb) * (size_t)D * D);
+            Frag* dt = reinterpret_cast<Frag*>(reinterpret_cast<T*>(p.dpt2) + ((size_t)bh * nsb + sb) * (size_t)D * D);
 #pragma unroll
             for (int s = 0; s < SPB; ++s) {
                 Frag ng;
@@ -198,7 +199,9 @@ hipError_t launch_prep2_fwd_b(const FwdParams& p, hipStream_t stream) {
     static const hipError_t attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&prep2_fwd_kernel<TIO, D, BWD>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::smem_bytes);
     if (attr_err != hipSuccess) return attr_err;
-    dim3 grid((p.NC + SBC - 1) / SBC, p.B * p.H);
+    const int nsb = (p.NC + SBC - 1) / SBC - (BWD ? 1 : 0);      // (training: every super-block but the last)
+    if (nsb < 1) return hipSuccess;
+    dim3 grid(nsb, p.B * p.H);
     const size_t bytes = C::smem_bytes;
     hipLaunchKernelGGL((prep2_fwd_kernel<TIO, D, BWD>), grid, dim3(256), bytes, stream, p);
     return hipGetLastError();
