@@ -567,7 +567,7 @@ static path_status_t bwd_run(BwdMode mode, int stages, const UserLayout& ul, con
     if (bf) {      // 2-byte operand types: the hand-fused kernel
         ChunkFusedArgs ca{ul, q, k, v, w, beta, d_o, lse, bp.delta, fp.sdm, fp.gm, fp.fm, fp.gktm, fp.nm, fp.aim, fp.ytm,
                           base + ws.utm, bp.dqb, bp.dkb, bp.dvp, F(ws.ddp), dq, dk, dv, dw, dbeta, bp.cum, bp.dcol, bp.drow,
-                          L, NC, scale};
+                          L, NC, BH, scale};
         ok = hip_ok(launch_chunk_fused(ca, BH, d, st), "chunk-transform adjoint");
         if (ok && log_f) {
             ScanArgs sa{bp.dcol, bp.drow, dlog_f, (int)Lp, L, L, L, 0, 1.f, 0, 1, ul};

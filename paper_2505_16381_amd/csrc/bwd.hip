@@ -40,7 +40,8 @@ __global__ __launch_bounds__(256) void bwd_dotile_kernel(BwdParams p) {
     constexpr int VE = 16 / (int)sizeof(TIO), VPR = D / VE, LD = D + VE;      // vector length, vectors per row, LDS pitch
     typedef TIO Vec __attribute__((ext_vector_type(VE)));
     __shared__ __attribute__((aligned(16))) TIO sdo[CHUNK * LD];
-    const int i = blockIdx.x, bh = blockIdx.y;
+    int i, bh;
+    chunk_and_head(p.ul, p.NC, p.B * p.H, i, bh);
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), h = lane >> 5, l32 = lane & 31;
     const int L = seq_len(p.ul, bh, p.L), NC = p.NC;      // this head's own length; NC: chunks per head in the workspace arrays
     if (i * CHUNK >= L) return;                            // (packed batch: a shorter sequence has fewer chunks)
@@ -1298,11 +1299,11 @@ template <typename K> static hipError_t set_smem(K kernel, size_t bytes) {
 // stages: which of the kernels to launch (BWD_STAGE_* bits; all of them is the whole pass, in this order)
 template <typename TIO, int D>
 static hipError_t launch_scan_t(const BwdParams& p, int stages, hipStream_t st) {
-    dim3 grid(p.NC, p.B * p.H);
+    dim3 grid(p.NC, p.B * p.H), grid1((unsigned)(p.NC * p.B * p.H));
     hipError_t e = hipSuccess;
     if (stages & BWD_STAGE_SCAN) {
-        if (p.ul.vt != D) hipLaunchKernelGGL((bwd_dotile_kernel<TIO, D, true>), grid, dim3(256), 0, st, p);
-        else hipLaunchKernelGGL((bwd_dotile_kernel<TIO, D, false>), grid, dim3(256), 0, st, p);
+        if (p.ul.vt != D) hipLaunchKernelGGL((bwd_dotile_kernel<TIO, D, true>), grid1, dim3(256), 0, st, p);
+        else hipLaunchKernelGGL((bwd_dotile_kernel<TIO, D, false>), grid1, dim3(256), 0, st, p);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     const size_t adj_bytes = Adj2Cfg<TIO, D>::smem_bytes, key_bytes = Key2Cfg<TIO, D>::smem_bytes;

@@ -130,7 +130,7 @@ struct ChunkFusedArgs {
     void *dq, *dk, *dv, *dw, *dbeta;             // I/O type
     const float* cum;                            // PaTH-FoX only (else NULL)
     float *dcol, *drow;
-    int L, NC;
+    int L, NC, BH;
     float scale;
 };
 hipError_t launch_chunk_fused(const ChunkFusedArgs& a, int BH, int d, hipStream_t st);

@@ -107,7 +107,8 @@ __global__ __launch_bounds__(CA_NT) void chunk_fused_kernel(ChunkFusedArgs a) {
     float* misc = reinterpret_cast<float*>(smem + C::MISC);
     float *lse_s = misc, *delta_s = misc + 64, *beta_s = misc + 128, *rdiag = misc + 192, *colsum = misc + 256, *cum_s = misc + 384;
 
-    const int chunk = blockIdx.x, bh = blockIdx.y;
+    int chunk, bh;
+    chunk_and_head(a.ul, a.NC, a.BH, chunk, bh);
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, h = lane >> 5, l32 = lane & 31;
     const int L = seq_len(a.ul, bh, a.L), NC = a.NC;      // this head's own length; NC: chunks per head in the workspace arrays
     if (chunk * CHUNK >= L) return;                        // (packed batch: a shorter sequence has fewer chunks)
@@ -377,7 +378,7 @@ hipError_t launch_s(const ChunkFusedArgs& a, int BH, hipStream_t st) {
     static const hipError_t attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&chunk_fused_kernel<TIO, D, FOX, STRIDED>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::TOTAL);
     if (attr_err != hipSuccess) return attr_err;
-    hipLaunchKernelGGL((chunk_fused_kernel<TIO, D, FOX, STRIDED>), dim3(a.NC, BH), dim3(CA_NT), (size_t)C::TOTAL, st, a);
+    hipLaunchKernelGGL((chunk_fused_kernel<TIO, D, FOX, STRIDED>), dim3((unsigned)(a.NC * BH)), dim3(CA_NT), (size_t)C::TOTAL, st, a);
     return hipGetLastError();
 }
 template <typename TIO, int D, bool FOX>

@@ -305,6 +305,18 @@ __device__ __forceinline__ long long user_scl(const UserLayout& u, int bh, long 
     if (u.cu) return ((long long)u.cu[bh / u.H] + t) * u.st + (bh % u.H) * u.sh;
     return (bh / u.H) * u.sb + (bh % u.H) * u.sh + t * u.st;
 }
+// Numbering of the kernels that run one workgroup per (chunk, head), as a one-dimensional grid of NC * BH
+// workgroups.  One length: chunks first, neighbours read neighbouring memory (heads first costs a [B,L,H,d] batch of
+// 4 x 3000 tokens 5 % of the chunk transform).  Packed batch: heads first, chunk by chunk -- workgroup n runs on XCD
+// n % 8, and with chunks first an XCD would take the same chunk numbers of every sequence, of which the late ones
+// exist in the long sequences only.  64 sequences of 256 .. 2048 tokens, 8 heads, d = 128: chunk transform 799 ->
+// 584 us, with the backward's outputs 1042 -> 796, its adjoint 1610 -> 1128.
+__device__ __forceinline__ void chunk_and_head(const UserLayout& u, int NC, int BH, int& chunk, int& bh) {
+    const int n = blockIdx.x, m = u.cu ? BH : NC;
+    const int hi = __builtin_amdgcn_readfirstlane(n / m), lo = n - hi * m;       // (the division runs on the vector unit)
+    chunk = u.cu ? hi : lo;
+    bh = u.cu ? lo : hi;
+}
 // length of head bh's sequence: the launch's L, or the head's own in a packed batch
 __device__ __forceinline__ int seq_len(const UserLayout& u, int bh, int L) {
     if (!u.cu) return L;

@@ -99,7 +99,8 @@ __global__ __launch_bounds__(256, (PrepCfg<TIO, D>::WGS_PER_CU)) void prep_fwd_k
     constexpr int LDH = C::LDH;
     constexpr bool COMPACT = C::COMPACT;
 
-    const int chunk = blockIdx.x, bh = blockIdx.y;
+    int chunk, bh;
+    chunk_and_head(p.ul, p.NC, p.B * p.H, chunk, bh);
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, h = lane >> 5, l32 = lane & 31;
     const int L = seq_len(p.ul, bh, p.L), NC = p.NC;      // this head's own length; NC: chunks per head in the workspace arrays
     const int t0 = chunk * CHUNK;
@@ -537,7 +538,7 @@ hipError_t launch_prep_fwd_s(const FwdParams& p, hipStream_t stream) {
     static const hipError_t attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&prep_fwd_kernel<T, D, BWD, STRIDED>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::smem_bytes);
     if (attr_err != hipSuccess) return attr_err;
-    dim3 grid(p.NC, p.B * p.H);
+    dim3 grid((unsigned)(p.NC * p.B * p.H));
     hipLaunchKernelGGL((prep_fwd_kernel<T, D, BWD, STRIDED>), grid, dim3(256), C::smem_bytes, stream, p);
     return hipGetLastError();
 }
