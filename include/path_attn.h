@@ -234,7 +234,7 @@ enum {
     PATH_BWD_STAGE_SCAN = 1,       /* dO tiles and delta; adjoint scan over the key blocks (dQ-side)          */
     PATH_BWD_STAGE_KEYS_NEAR = 2,  /* key-side sums over the query chunks of the key's own super-block       */
     PATH_BWD_STAGE_KEYS_FAR = 4,   /* key-side sums over all queries right of the key's super-block          */
-    PATH_BWD_STAGE_DDP = 8,        /* gradients of the super-block products                                  */
+    PATH_BWD_STAGE_DDP = 8,        /* PATH_F32: gradients of the products (PATH_BF16: the key-side passes)   */
     PATH_BWD_STAGE_CHUNK = 16,     /* adjoint of the second level and of the chunk transform: the gradients  */
     PATH_BWD_STAGE_ALL = 31
 };

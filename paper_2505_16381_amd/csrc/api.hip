@@ -64,9 +64,11 @@ static BwdWorkspace bwd_workspace(int B, int H, int L, int d, size_t es) {
     auto take = [&](size_t& field, size_t bytes) { field = off; off = align256(off + bytes); };
     // (the transposed key tiles ktT, kt2T exist for fp32 operands only: the 16-bit adjoint scan transposes in LDS)
     take(w.ktT, (es == 4 ? 1 : 0) * BH * Lp * d * es);
-    for (size_t* f : {&w.vk, &w.doq, &w.doT}) take(*f, BH * Lp * d * es);
+    for (size_t* f : {&w.vk, &w.doq}) take(*f, BH * Lp * d * es);
+    take(w.doT, (es == 4 ? 1 : 0) * BH * Lp * d * es);           // (the transposed dO tiles and states: likewise)
     take(w.dpt, (es == 4 ? 1 : 0) * BH * NC * d * d * es);       // (fp32 operands only, like ktT)
-    for (size_t* f : {&w.xs, &w.xsT, &w.gs}) take(*f, BH * nslots * CHUNK * d * es);
+    for (size_t* f : {&w.xs, &w.gs}) take(*f, BH * nslots * CHUNK * d * es);
+    take(w.xsT, (es == 4 ? 1 : 0) * BH * nslots * CHUNK * d * es);
     take(w.kt2T, (es == 4 ? 1 : 0) * BH * Lp * d * es);
     take(w.dpt2, (es == 4 ? 1 : 0) * BH * NSB * d * d * es);
     take(w.kbm, BH * Lp * d * es);

@@ -51,7 +51,7 @@ __device__ __forceinline__ void wait_tiles_and_sync() {
 // EMIT (forward of a training pair): the query states the backward needs are written on the way,
 // in the arrangement of the backward's own states sweep (see states_bwd.hip): whenever a wave
 // meets a new key block -- a chunk j < cq of its own super-block, or a super-block further left --
-// it stores its state as the tiles xs and xsT of the pair (cq, block).
+// it stores its state as the tile xs (fp32 operands: and its transpose xsT) of the pair (cq, block).
 //
 // RING (sequence-parallel forward, Sec. 3.5): 1 = the sweep over a device's own segment; it also applies the
 // product of the segment's first chunk / super-block at the end (the query state then stands at the segment's left
@@ -180,8 +180,8 @@ __global__ __launch_bounds__(FWD2_THREADS, 512 / FWD2_THREADS) void attn_fwd2_ke
                 const size_t slot = ((size_t)bh * num_block_slots(NC) + block_slot(cq, j >= jsb ? j : j - (SBC - 1), NC)) * (size_t)CHUNK * D;
                 Frag* xd = reinterpret_cast<Frag*>(reinterpret_cast<T*>(p.xs) + slot);
 #pragma unroll
-                for (int s = 0; s < DS; ++s) __builtin_nontemporal_store(Xh[s], &xd[((size_t)qb * DS + s) * 64 + lane]);     // streamed: keep the key/value tiles in L2
-                if (sizeof(T) == 4 || j < jsb) {     // (16-bit operands: the near blocks' consumer transposes xs itself)
+                for (int s = 0; s < DS; ++s) __builtin_nontemporal_store(Xh[s], &xd[((size_t)qb * DS + s) * 64 + tile_lane(lane, s)]);     // streamed: keep the key/value tiles in L2
+                if (sizeof(T) == 4) {                // (16-bit operands: the consumers transpose xs themselves)
                     Frag* xt = reinterpret_cast<Frag*>(reinterpret_cast<T*>(p.xsT) + slot);
                     Frag idf[SPB];
                     identity_frags<T>(idf, l32, h);

@@ -29,15 +29,16 @@
 namespace path {
 
 // ---------------------------------------------------------------------------------------
-// Per query chunk: delta_t = dO_t . o_t, the row constants of the softmax, and dO as two
+// Per query chunk: delta_t = dO_t . o_t, the row constants of the softmax, and dO as
 // fragment-order tiles (I/O type; rows past L are zero):
-//   doq (rows q, contraction c)  and  doT (rows c, contraction q).
-// dO is read once, in 16-byte vectors, and staged in LDS; both tiles are built from there.
+//   doq (rows q, contraction c)  and, for fp32 operands,  doT (rows c, contraction q).
+// dO is read once, in 16-byte vectors, and staged in LDS; the tiles are built from there.
 template <typename TIO, int D, bool STRIDED>
 __global__ __launch_bounds__(256) void bwd_dotile_kernel(BwdParams p) {
     using FragV = typename Tr<TIO>::Frag;
     constexpr int KW = Tr<TIO>::KW, SPB = 32 / KW, DB = D / 32, QS = CHUNK / KW;
     constexpr int VE = 16 / (int)sizeof(TIO), VPR = D / VE, LD = D + VE;      // vector length, vectors per row, LDS pitch
+    constexpr bool WITH_T = sizeof(typename Compute<TIO>::type) == 4;         // (16-bit operands: the consumers read doq transposed)
     typedef TIO Vec __attribute__((ext_vector_type(VE)));
     __shared__ __attribute__((aligned(16))) TIO sdo[CHUNK * LD];
     int i, bh;
@@ -83,15 +84,15 @@ __global__ __launch_bounds__(256) void bwd_dotile_kernel(BwdParams p) {
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
             a[j] = (float)sdo[(32 * qb + l32) * LD + 32 * cb + acc_row(j, h)];      // registers rows c, lane q
-            b[j] = (float)sdo[(32 * qb + acc_row(j, h)) * LD + 32 * cb + l32];      // registers rows q, lane c
+            if (WITH_T) b[j] = (float)sdo[(32 * qb + acc_row(j, h)) * LD + 32 * cb + l32];      // registers rows q, lane c
         }
         FragV fa[SPB], fb[SPB];
         pack_block<TIO>(a, fa);
-        pack_block<TIO>(b, fb);
+        if (WITH_T) pack_block<TIO>(b, fb);
 #pragma unroll
         for (int s = 0; s < SPB; ++s) {
-            __builtin_nontemporal_store(fa[s], &dq[((size_t)qb * (D / KW) + cb * SPB + s) * 64 + lane]);
-            __builtin_nontemporal_store(fb[s], &dt[((size_t)cb * QS + qb * SPB + s) * 64 + lane]);
+            __builtin_nontemporal_store(fa[s], &dq[((size_t)qb * (D / KW) + cb * SPB + s) * 64 + tile_lane(lane, s)]);
+            if (WITH_T) __builtin_nontemporal_store(fb[s], &dt[((size_t)cb * QS + qb * SPB + s) * 64 + lane]);
         }
     }
 }
@@ -158,7 +159,7 @@ __global__ __launch_bounds__(256) void bwd_adjoint2_kernel(BwdParams p) {
     if (active) {
         const FragV* dq = reinterpret_cast<const FragV*>(reinterpret_cast<const TIO*>(p.doq) + ((size_t)bh * NC + cq) * CHUNK * D);
 #pragma unroll
-        for (int s = 0; s < DS; ++s) dOb[s] = dq[((size_t)qb * DS + s) * 64 + lane];
+        for (int s = 0; s < DS; ++s) dOb[s] = dq[((size_t)qb * DS + s) * 64 + tile_lane(lane, s)];
         // base-2 units (PaTH-FoX: minus the query's gate sum); rows past L hold a huge value, so that their
         // P = exp2(-huge) = 0 without a mask.  log2(scale) is folded in: the exponential then yields scale * P,
         // which is all the logit gradient dS = scale * P o (dP - delta) needs.
@@ -202,7 +203,7 @@ __global__ __launch_bounds__(256) void bwd_adjoint2_kernel(BwdParams p) {
         const size_t slot = ((size_t)bh * nslots + block_slot(cq, j, NC)) * (size_t)CHUNK * D;
         const Frag* xg = reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(p.xs) + slot);
 #pragma unroll
-        for (int s = 0; s < DS; ++s) x[s] = __builtin_nontemporal_load(&xg[((size_t)qb * DS + s) * 64 + lane]);     // read once: leave L2 to the key tiles
+        for (int s = 0; s < DS; ++s) x[s] = __builtin_nontemporal_load(&xg[((size_t)qb * DS + s) * 64 + tile_lane(lane, s)]);     // read once: leave L2 to the key tiles
     };
     Frag Xnext[DS], Xb[DS];
 #pragma unroll
@@ -330,24 +331,6 @@ __global__ __launch_bounds__(256) void bwd_adjoint2_kernel(BwdParams p) {
 }
 
 // ---------------------------------------------------------------------------------------
-// Fragment of the TRANSPOSE of a fragment-order tile (rows q in 32-row halves of DS slabs,
-// contraction c).  Element e of a fragment belongs to contraction index 16 s + acc_row(e, h) of
-// its slab s, in both tiles, so the lane needs tile[q = 16 qs + acc_row(e, h)][c = 32 b + l32],
-// e = 0..7: two transposing reads, of rows 16 qs + 4 h + 0..3 and the same + 8 (in each block of
-// 16 lanes, lane i points at 4 consecutive c of row .. + i/4 and receives column i of the four rows).
-template <typename E, int DS>
-__device__ __forceinline__ typename Tr<E>::Frag ld_tile_frag_tr(const E* tile, int qs, int b, int l32, int h) {
-    static_assert(sizeof(E) == 2, "16-bit transposing reads");
-    typedef short v4s __attribute__((ext_vector_type(4)));
-    const int i = l32 & 15;
-    const E* p = tile + (size_t)((((qs >> 1) * DS + 2 * b + (l32 >> 4)) * 64 + (i & 1) * 32 + 16 * (qs & 1) + 4 * h + (i >> 2)) * 8 + 4 * ((i >> 1) & 1));
-    union { v4s v[2]; typename Tr<E>::Frag f; } u;
-    u.v[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)(p));
-    u.v[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)(p + 64));
-    return u.f;
-}
-
-// ---------------------------------------------------------------------------------------
 // The adjoint scan for 16-bit operands with TWO workgroups per CU: the same arithmetic as
 // bwd_adjoint2_kernel, arranged to fit 256 registers per wave and one 80 KB stage per workgroup, so that
 // the second workgroup's waves fill the gaps of the first (tile requests, LDS latencies, the dependent
@@ -396,7 +379,7 @@ __global__ __launch_bounds__(256, 2) void bwd_adjoint2_lite_kernel(BwdParams p) 
     if (active) {
         const FragV* dq = reinterpret_cast<const FragV*>(reinterpret_cast<const TIO*>(p.doq) + ((size_t)bh * NC + cq) * CHUNK * D);
 #pragma unroll
-        for (int s = 0; s < DS; ++s) dOb[s] = dq[((size_t)qb * DS + s) * 64 + lane];
+        for (int s = 0; s < DS; ++s) dOb[s] = dq[((size_t)qb * DS + s) * 64 + tile_lane(lane, s)];
         lse2 = p.lse2p[(size_t)bh * Lp + tq] - __builtin_log2f(p.scale);     // the exponential then yields scale * P
         dl = p.delta[(size_t)bh * Lp + tq];
     }
@@ -427,7 +410,7 @@ __global__ __launch_bounds__(256, 2) void bwd_adjoint2_lite_kernel(BwdParams p) 
             const size_t xslot = ((size_t)bh * nslots + block_slot(cq, j, NC)) * (size_t)CHUNK * D;
             const Frag* xg = reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(p.xs) + xslot);
 #pragma unroll
-            for (int s = 0; s < DS; ++s) Xb[s] = __builtin_nontemporal_load(&xg[((size_t)qb * DS + s) * 64 + lane]);
+            for (int s = 0; s < DS; ++s) Xb[s] = __builtin_nontemporal_load(&xg[((size_t)qb * DS + s) * 64 + tile_lane(lane, s)]);
         }
         wait_async_and_sync();
         if (!mine) continue;
@@ -442,7 +425,7 @@ __global__ __launch_bounds__(256, 2) void bwd_adjoint2_lite_kernel(BwdParams p) 
                 for (int s0 = 0; s0 < DS; s0 += 4) {
                     Frag pa[4];
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) pa[u] = ld_tile_frag_tr<T, DS>(reinterpret_cast<const T*>(sDP), s0 + u, b, l32, h);
+                    for (int u = 0; u < 4; ++u) pa[u] = ld_tile_frag_tr<T, DS, false>(reinterpret_cast<const T*>(sDP), s0 + u, b, l32, h);
 #pragma unroll
                     for (int u = 0; u < 4; ++u) Gm[b] = Tr<T>::mma(pa[u], Gb[s0 + u], Gm[b]);
                 }
@@ -482,7 +465,7 @@ __global__ __launch_bounds__(256, 2) void bwd_adjoint2_lite_kernel(BwdParams p) 
             for (int b = 0; b < DB; ++b) {
                 Frag ta[SPB];
 #pragma unroll
-                for (int u = 0; u < SPB; ++u) ta[u] = ld_tile_frag_tr<T, DS>(reinterpret_cast<const T*>(sK), kb * SPB + u, b, l32, h);
+                for (int u = 0; u < SPB; ++u) ta[u] = ld_tile_frag_tr<T, DS, false>(reinterpret_cast<const T*>(sK), kb * SPB + u, b, l32, h);
 #pragma unroll
                 for (int u = 0; u < SPB; ++u) Gm[b] = Tr<T>::mma(ta[u], dSh[u], Gm[b]);
             }
@@ -559,6 +542,7 @@ __global__ __launch_bounds__(256) void bwd_keyside2_kernel(BwdParams p) {
     using FragV = typename Tr<TIO>::Frag;
     constexpr int KW = Tr<T>::KW, SPB = 32 / KW, DB = D / 32, DS = D / KW, QS = CHUNK / KW;
     constexpr int KVF = C::KV_FRAGS, NBUF = C::NBUF, STF = C::STAGE_FRAGS;
+    static_assert(!FAR || sizeof(T) == 4, "16-bit operands: bwd_far_kernel");
     constexpr bool NFUSE = !FAR && sizeof(T) == 2;          // the near part of ddP is taken here too
     constexpr int NOWN = NFUSE ? DB * DB / 4 : 1;           // its 32x32 blocks per wave
 
@@ -613,38 +597,31 @@ __global__ __launch_bounds__(256) void bwd_keyside2_kernel(BwdParams p) {
     float dcol = 0.f;
 
     // all operands of query chunk i, asynchronously, into stage buffer (i & (NBUF-1))
-    // part = -1: everything; 0..3: one tile each (the requests for the next chunk are spread over
-    // the current chunk's work, see the adjoint scan)
-    auto issue = [&](int i, int part) {
+    auto issue = [&](int i) {
         Frag* buf = sbase + (size_t)(i & (NBUF - 1)) * STF;
         const size_t slot = ((size_t)bh * nslots + block_slot(i, j, NC)) * (size_t)CHUNK * D;
         const size_t bhi = ((size_t)bh * NC + i) * CHUNK * D;
-        if (part < 0 || part == 0)
-            async_copy_tile<256, KVF>(reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(p.xs) + slot), buf, tid, wv);
-        if ((part < 0 || part == 2) && !NFUSE)       // (near, 16-bit: Xs^T fragments are read out of the xs tile)
+        async_copy_tile<256, KVF>(reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(p.xs) + slot), buf, tid, wv);
+        if (!NFUSE)       // (near, 16-bit: Xs^T fragments are read out of the xs tile)
             async_copy_tile<256, KVF>(reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(p.xsT) + slot), buf + KVF, tid, wv);
-        if (part < 0 || part == 1)
-            async_copy_tile<256, KVF>(reinterpret_cast<const Frag*>(reinterpret_cast<const TIO*>(p.doq) + bhi), buf + 2 * KVF, tid, wv);
-        if (part < 0 || part == 3) {
-            if (NFUSE) async_copy_tile<256, KVF>(reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(p.gs) + slot), buf + 3 * KVF, tid, wv);
-            else async_copy_tile<256, KVF>(reinterpret_cast<const Frag*>(reinterpret_cast<const TIO*>(p.doT) + bhi), buf + 3 * KVF, tid, wv);
-        }
-        if ((part < 0 || part == 0) && tid < 32) {     // 64 floats of lse2 (lanes 0-15) and of delta (lanes 16-31): 16 bytes per lane
+        async_copy_tile<256, KVF>(reinterpret_cast<const Frag*>(reinterpret_cast<const TIO*>(p.doq) + bhi), buf + 2 * KVF, tid, wv);
+        if (NFUSE) async_copy_tile<256, KVF>(reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(p.gs) + slot), buf + 3 * KVF, tid, wv);
+        else async_copy_tile<256, KVF>(reinterpret_cast<const Frag*>(reinterpret_cast<const TIO*>(p.doT) + bhi), buf + 3 * KVF, tid, wv);
+        if (tid < 32) {     // 64 floats of lse2 (lanes 0-15) and of delta (lanes 16-31): 16 bytes per lane
             const float* src = (tid < 16 ? p.lse2p : p.delta) + (size_t)bh * Lp + (size_t)i * CHUNK + 4 * (tid & 15);
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
                                              (__attribute__((address_space(3))) void*)(buf + 4 * KVF), 16, 0, 0);
         }
     };
 
-    if (i0 < i1 && NBUF == 2) issue(i0, -1);
+    if (i0 < i1 && NBUF == 2) issue(i0);
     for (int i = i0; i < i1; ++i) {
-        const bool spread = NBUF == 2 && i + 1 < i1 && FAR;       // far: two rounds of work per chunk to spread over
         if (NBUF == 2) {
             wait_async_and_sync();                 // chunk i has landed; everyone is done with chunk i-1
-            if (i + 1 < i1) issue(i + 1, spread ? 0 : -1);
+            if (i + 1 < i1) issue(i + 1);
         } else {
             __syncthreads();
-            issue(i, -1);
+            issue(i);
             wait_async_and_sync();
         }
         const Frag* sX = sbase + (size_t)(i & (NBUF - 1)) * STF;
@@ -664,7 +641,7 @@ __global__ __launch_bounds__(256) void bwd_keyside2_kernel(BwdParams p) {
                 Frag xa[4];
                 FragV da[4];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) { xa[u] = sX[(qh * DS + s0 + u) * 64 + lane]; da[u] = sDQ[(qh * DS + s0 + u) * 64 + lane]; }
+                for (int u = 0; u < 4; ++u) { xa[u] = sX[(qh * DS + s0 + u) * 64 + tile_lane(lane, u)]; da[u] = sDQ[(qh * DS + s0 + u) * 64 + tile_lane(lane, u)]; }
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     S = Tr<T>::mma(xa[u], Kb[s0 + u], S);
@@ -709,110 +686,7 @@ __global__ __launch_bounds__(256) void bwd_keyside2_kernel(BwdParams p) {
                 }
             }
         };
-        if (FAR && sizeof(T) == 2) {
-            // Both query halves, software-pipelined by hand: the element-wise part of one half is
-            // interleaved, element by element, with the products of the other (one wave per SIMD:
-            // nothing else hides it).  The scheduling barriers keep the compiler from undoing the order.
-            f32x16 S0 = zero16(), dP0 = zero16(), S1 = zero16(), dP1 = zero16(), Pm;
-            FragV Pb0[SPB], Pb1[SPB];
-            Frag dSb0[SPB], dSb1[SPB];
-            f32x4 ls0[4], dls0[4], ls1[4], dls1[4];
-            // Rows past L need no mask: their padded lse2p is huge, so P = exp2(-huge) = 0.
-            // The empty asm statements pin the element's arithmetic between the two products around it
-            // (they are ordered with the scheduling barriers; plain arithmetic alone is not).
-            auto elem = [&](int jj, f32x16& S, const f32x16& dP, const f32x4* ls, const f32x4* dls) {
-                float sv = S[jj], dv = dP[jj];
-                asm volatile("" : "+v"(sv), "+v"(dv));
-                const float P = __builtin_amdgcn_exp2f(__builtin_fmaf(sv, sl2, -ls[jj >> 2][jj & 3]) - ckj);
-                const float dz = P * (dv - dls[jj >> 2][jj & 3]);
-                if (FOX) dcol += dz;
-                float ds = dz, pv = P;      // the factor scale of dS is applied to the finished dKb sums
-                asm volatile("" : "+v"(ds), "+v"(pv));
-                Pm[jj] = pv;
-                S[jj] = ds;
-            };
-            Frag xa0[DS], xa1[DS], tb0[DB * SPB], tb1[DB * SPB];
-            FragV da0[DS], da1[DS], ta0[DB * SPB], ta1[DB * SPB];
-#pragma unroll
-            for (int u = 0; u < DS; ++u) { xa0[u] = sX[u * 64 + lane]; da0[u] = sDQ[u * 64 + lane]; }
-            __builtin_amdgcn_sched_barrier(0);
-            // logits and dP of half 0
-#pragma unroll
-            for (int u = 0; u < DS; ++u) {
-                S0 = Tr<T>::mma(xa0[u], Kb[u], S0);
-                dP0 = Tr<TIO>::mma(da0[u], Vb[u], dP0);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            if (spread) issue(i + 1, 1);
-            // logits and dP of half 1  ||  element-wise part of half 0
-#pragma unroll
-            for (int u = 0; u < DS; ++u) { xa1[u] = sX[(DS + u) * 64 + lane]; da1[u] = sDQ[(DS + u) * 64 + lane]; }
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                ls0[g] = *reinterpret_cast<const f32x4*>(lse2 + 8 * g + 4 * h);
-                dls0[g] = *reinterpret_cast<const f32x4*>(dl + 8 * g + 4 * h);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int u = 0; u < DS; ++u) {
-                S1 = Tr<T>::mma(xa1[u], Kb[u], S1);
-                __builtin_amdgcn_sched_barrier(0);
-                if (2 * u < 16) elem(2 * u, S0, dP0, ls0, dls0);
-                __builtin_amdgcn_sched_barrier(0);
-                dP1 = Tr<TIO>::mma(da1[u], Vb[u], dP1);
-                __builtin_amdgcn_sched_barrier(0);
-                if (2 * u + 1 < 16) elem(2 * u + 1, S0, dP0, ls0, dls0);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            if (DS < 8) {
-#pragma unroll
-                for (int jj = 2 * DS; jj < 16; ++jj) elem(jj, S0, dP0, ls0, dls0);
-            }
-            pack_block<TIO>(Pm, Pb0);
-            pack_block<T>(S0, dSb0);
-            if (spread) issue(i + 1, 3);
-            // dV^T, dKb^T of half 0  ||  element-wise part of half 1
-#pragma unroll
-            for (int u = 0; u < DB * SPB; ++u) {
-                ta0[u] = sDT[((u / SPB) * QS + u % SPB) * 64 + lane];
-                tb0[u] = sXT[((u / SPB) * QS + u % SPB) * 64 + lane];
-            }
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                ls1[g] = *reinterpret_cast<const f32x4*>(lse2 + 32 + 8 * g + 4 * h);
-                dls1[g] = *reinterpret_cast<const f32x4*>(dl + 32 + 8 * g + 4 * h);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int u = 0; u < DB * SPB; ++u) {
-                dVt[u / SPB] = Tr<TIO>::mma(ta0[u], Pb0[u % SPB], dVt[u / SPB]);
-                __builtin_amdgcn_sched_barrier(0);
-                if (2 * u < 16) elem(2 * u, S1, dP1, ls1, dls1);
-                __builtin_amdgcn_sched_barrier(0);
-                dKt[u / SPB] = Tr<T>::mma(tb0[u], dSb0[u % SPB], dKt[u / SPB]);
-                __builtin_amdgcn_sched_barrier(0);
-                if (2 * u + 1 < 16) elem(2 * u + 1, S1, dP1, ls1, dls1);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            if (DB * SPB < 8) {
-#pragma unroll
-                for (int jj = 2 * DB * SPB; jj < 16; ++jj) elem(jj, S1, dP1, ls1, dls1);
-            }
-            pack_block<TIO>(Pm, Pb1);
-            pack_block<T>(S1, dSb1);
-            if (spread) issue(i + 1, 2);
-            // dV^T, dKb^T of half 1
-#pragma unroll
-            for (int u = 0; u < DB * SPB; ++u) {
-                ta1[u] = sDT[((u / SPB) * QS + SPB + u % SPB) * 64 + lane];
-                tb1[u] = sXT[((u / SPB) * QS + SPB + u % SPB) * 64 + lane];
-            }
-#pragma unroll
-            for (int u = 0; u < DB * SPB; ++u) {
-                dVt[u / SPB] = Tr<TIO>::mma(ta1[u], Pb1[u % SPB], dVt[u / SPB]);
-                dKt[u / SPB] = Tr<T>::mma(tb1[u], dSb1[u % SPB], dKt[u / SPB]);
-            }
-        } else {
+        {
 #pragma unroll
             for (int qq = 0; qq < CPW; ++qq) {
                 const int qh = FAR ? qq : (wv >> 1);
@@ -820,7 +694,6 @@ __global__ __launch_bounds__(256) void bwd_keyside2_kernel(BwdParams p) {
                 FragV Pb[SPB];
                 Frag dSb[SPB];
                 sdp(qh, S, dP);
-                if (FAR && spread) issue(i + 1, qq == 0 ? 1 : 3);
                 soft(qh, S, dP, Pb, dSb);
                 if constexpr (NFUSE) {
                     // dV^T, dKb^T and the wave's ddP blocks, one 32-row block b of Xs^T at a time: its four
@@ -846,9 +719,9 @@ __global__ __launch_bounds__(256) void bwd_keyside2_kernel(BwdParams p) {
                         FragV ta[SPB];
 #pragma unroll
                         for (int u = 0; u < SPB; ++u) {
-                            fo[u] = ld_tile_frag_tr<T, DS>(reinterpret_cast<const T*>(sX), own + u, b, l32, h);
-                            fx[u] = ld_tile_frag_tr<T, DS>(reinterpret_cast<const T*>(sX), oth + u, b, l32, h);
-                            ta[u] = ld_tile_frag_tr<TIO, DS>(reinterpret_cast<const TIO*>(sDQ), own + u, b, l32, h);
+                            fo[u] = ld_tile_frag_tr<T, DS, true>(reinterpret_cast<const T*>(sX), own + u, b, l32, h);
+                            fx[u] = ld_tile_frag_tr<T, DS, true>(reinterpret_cast<const T*>(sX), oth + u, b, l32, h);
+                            ta[u] = ld_tile_frag_tr<TIO, DS, true>(reinterpret_cast<const TIO*>(sDQ), own + u, b, l32, h);
                         }
 #pragma unroll
                         for (int u = 0; u < SPB; ++u) {
@@ -871,7 +744,6 @@ __global__ __launch_bounds__(256) void bwd_keyside2_kernel(BwdParams p) {
                 } else {
                     upd(qh, Pb, dSb);
                 }
-                if (FAR && spread && qq == 0) issue(i + 1, 2);
             }
         }
     }
@@ -1292,89 +1164,78 @@ __global__ __launch_bounds__(256, 3) void chunk_adjoint_kernel(ChunkProgram pr) 
 }
 
 // ---------------------------------------------------------------------------------------
-template <typename K> static hipError_t set_smem(K kernel, size_t bytes) {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+// Set once per process and kernel; a function-local static is initialised under the language's own lock.
+template <auto Kernel> static hipError_t set_smem(size_t bytes) {
+    static const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(Kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    return e;
 }
 
 // stages: which of the kernels to launch (BWD_STAGE_* bits; all of them is the whole pass, in this order)
-template <typename TIO, int D>
+template <typename TIO, int D, bool FOX>
 static hipError_t launch_scan_t(const BwdParams& p, int stages, hipStream_t st) {
-    dim3 grid(p.NC, p.B * p.H), grid1((unsigned)(p.NC * p.B * p.H));
+    constexpr bool F32 = sizeof(typename Compute<TIO>::type) == 4;
+    const int BH = p.B * p.H, ntiles = (p.NC + 1) / 2, nsb = (p.NC + SBC - 1) / SBC;
+    const bool has_far = nsb > 1;       // (one super-block per head: nothing is far)
+    const unsigned rounds = 8 * (unsigned)((BH + 7) / 8);
     hipError_t e = hipSuccess;
     if (stages & BWD_STAGE_SCAN) {
-        if (p.ul.vt != D) hipLaunchKernelGGL((bwd_dotile_kernel<TIO, D, true>), grid1, dim3(256), 0, st, p);
-        else hipLaunchKernelGGL((bwd_dotile_kernel<TIO, D, false>), grid1, dim3(256), 0, st, p);
+        const dim3 grid((unsigned)(p.NC * BH)), grid_adj(rounds * ntiles);
+        if (p.ul.vt != D) hipLaunchKernelGGL((bwd_dotile_kernel<TIO, D, true>), grid, dim3(256), 0, st, p);
+        else hipLaunchKernelGGL((bwd_dotile_kernel<TIO, D, false>), grid, dim3(256), 0, st, p);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        if constexpr (F32) {
+            const size_t bytes = Adj2Cfg<TIO, D>::smem_bytes;
+            if ((e = set_smem<&bwd_adjoint2_kernel<TIO, D, FOX>>(bytes)) != hipSuccess) return e;
+            hipLaunchKernelGGL((bwd_adjoint2_kernel<TIO, D, FOX>), grid_adj, dim3(256), bytes, st, p);
+        } else {
+            const size_t bytes = (size_t)(2 * Adj2Cfg<TIO, D>::KV_FRAGS + Adj2Cfg<TIO, D>::DP_FRAGS) * 16;      // kt | vk | dpt
+            if ((e = set_smem<&bwd_adjoint2_lite_kernel<TIO, D, FOX>>(bytes)) != hipSuccess) return e;
+            hipLaunchKernelGGL((bwd_adjoint2_lite_kernel<TIO, D, FOX>), grid_adj, dim3(256), bytes, st, p);
+        }
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    const size_t adj_bytes = Adj2Cfg<TIO, D>::smem_bytes, key_bytes = Key2Cfg<TIO, D>::smem_bytes;
-    const int ntiles = (p.NC + 1) / 2;
-    const int BH = p.B * p.H, nsb = (p.NC + SBC - 1) / SBC;
-    const dim3 grid_adj((unsigned)(8 * ((BH + 7) / 8) * ntiles));
-    const dim3 grid_key((unsigned)(8 * ((BH + 7) / 8) * nsb * SBC)), grid_key_far((unsigned)(8 * ((BH + 7) / 8) * (nsb - 1) * (SBC / 2)));
-    const bool has_far = nsb > 1;       // (one super-block per head: nothing is far)
-    if (p.cum) {       // PaTH-FoX instantiations
-        if (stages & BWD_STAGE_SCAN) {
-            if constexpr (sizeof(typename Compute<TIO>::type) == 2) {
-                const size_t lite_bytes = (size_t)(2 * Adj2Cfg<TIO, D>::KV_FRAGS + Adj2Cfg<TIO, D>::DP_FRAGS) * 16;      // kt | vk | dpt
-                if ((e = set_smem(&bwd_adjoint2_lite_kernel<TIO, D, true>, lite_bytes)) != hipSuccess) return e;
-                hipLaunchKernelGGL((bwd_adjoint2_lite_kernel<TIO, D, true>), grid_adj, dim3(256), lite_bytes, st, p);
-            } else {
-                if ((e = set_smem(&bwd_adjoint2_kernel<TIO, D, true>, adj_bytes)) != hipSuccess) return e;
-                hipLaunchKernelGGL((bwd_adjoint2_kernel<TIO, D, true>), grid_adj, dim3(256), adj_bytes, st, p);
-            }
-            if ((e = hipGetLastError()) != hipSuccess) return e;
-        }
-        if ((e = set_smem(&bwd_keyside2_kernel<TIO, D, false, true>, key_bytes)) != hipSuccess) return e;
-        if ((e = set_smem(&bwd_keyside2_kernel<TIO, D, true, true>, key_bytes)) != hipSuccess) return e;
-        if (stages & BWD_STAGE_KEYS_NEAR) hipLaunchKernelGGL((bwd_keyside2_kernel<TIO, D, false, true>), grid_key, dim3(256), key_bytes, st, p);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        if (has_far && (stages & BWD_STAGE_KEYS_FAR)) hipLaunchKernelGGL((bwd_keyside2_kernel<TIO, D, true, true>), grid_key_far, dim3(256), key_bytes, st, p);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-    } else {
-        if (stages & BWD_STAGE_SCAN) {
-            if constexpr (sizeof(typename Compute<TIO>::type) == 2) {
-                const size_t lite_bytes = (size_t)(2 * Adj2Cfg<TIO, D>::KV_FRAGS + Adj2Cfg<TIO, D>::DP_FRAGS) * 16;      // kt | vk | dpt
-                if ((e = set_smem(&bwd_adjoint2_lite_kernel<TIO, D, false>, lite_bytes)) != hipSuccess) return e;
-                hipLaunchKernelGGL((bwd_adjoint2_lite_kernel<TIO, D, false>), grid_adj, dim3(256), lite_bytes, st, p);
-            } else {
-                if ((e = set_smem(&bwd_adjoint2_kernel<TIO, D, false>, adj_bytes)) != hipSuccess) return e;
-                hipLaunchKernelGGL((bwd_adjoint2_kernel<TIO, D, false>), grid_adj, dim3(256), adj_bytes, st, p);
-            }
-            if ((e = hipGetLastError()) != hipSuccess) return e;
-        }
-        if ((e = set_smem(&bwd_keyside2_kernel<TIO, D, false, false>, key_bytes)) != hipSuccess) return e;
-        if ((e = set_smem(&bwd_keyside2_kernel<TIO, D, true, false>, key_bytes)) != hipSuccess) return e;
-        if (stages & BWD_STAGE_KEYS_NEAR) hipLaunchKernelGGL((bwd_keyside2_kernel<TIO, D, false, false>), grid_key, dim3(256), key_bytes, st, p);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        if (has_far && (stages & BWD_STAGE_KEYS_FAR)) hipLaunchKernelGGL((bwd_keyside2_kernel<TIO, D, true, false>), grid_key_far, dim3(256), key_bytes, st, p);
+    const size_t key_bytes = Key2Cfg<TIO, D>::smem_bytes;
+    if (stages & BWD_STAGE_KEYS_NEAR) {
+        if ((e = set_smem<&bwd_keyside2_kernel<TIO, D, false, FOX>>(key_bytes)) != hipSuccess) return e;
+        hipLaunchKernelGGL((bwd_keyside2_kernel<TIO, D, false, FOX>), dim3(rounds * nsb * SBC), dim3(256), key_bytes, st, p);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    const size_t ddp_bytes = DdpCfg<TIO, D>::smem_bytes;
-    if ((e = set_smem(&bwd_ddp_kernel<TIO, D, false>, ddp_bytes)) != hipSuccess) return e;
-    if ((e = set_smem(&bwd_ddp_kernel<TIO, D, true>, ddp_bytes)) != hipSuccess) return e;
-    if (!(stages & BWD_STAGE_DDP)) return hipSuccess;
-    if (sizeof(typename Compute<TIO>::type) != 2)       // 16-bit operands: the near key-side kernel has written ddP
-        hipLaunchKernelGGL((bwd_ddp_kernel<TIO, D, false>), grid, dim3(256), ddp_bytes, st, p);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    if (!has_far) return hipSuccess;
-    const dim3 grid_sb(nsb - 1, p.B * p.H);
-    hipLaunchKernelGGL((bwd_ddp_kernel<TIO, D, true>), grid_sb, dim3(256), ddp_bytes, st, p);
-    return hipGetLastError();
+    if (has_far && (stages & BWD_STAGE_KEYS_FAR)) {
+        if constexpr (F32) {
+            if ((e = set_smem<&bwd_keyside2_kernel<TIO, D, true, FOX>>(key_bytes)) != hipSuccess) return e;
+            hipLaunchKernelGGL((bwd_keyside2_kernel<TIO, D, true, FOX>), dim3(rounds * (nsb - 1) * (SBC / 2)), dim3(256), key_bytes, st, p);
+            if ((e = hipGetLastError()) != hipSuccess) return e;
+        } else {
+            if ((e = launch_bwd_far(p, D, st)) != hipSuccess) return e;
+        }
+    }
+    if constexpr (F32) {       // (16-bit operands: the key-side kernels take ddP too)
+        if (stages & BWD_STAGE_DDP) {
+            const size_t bytes = DdpCfg<TIO, D>::smem_bytes;
+            if ((e = set_smem<&bwd_ddp_kernel<TIO, D, false>>(bytes)) != hipSuccess) return e;
+            if ((e = set_smem<&bwd_ddp_kernel<TIO, D, true>>(bytes)) != hipSuccess) return e;
+            hipLaunchKernelGGL((bwd_ddp_kernel<TIO, D, false>), dim3(p.NC, BH), dim3(256), bytes, st, p);
+            if ((e = hipGetLastError()) != hipSuccess || !has_far) return e;
+            hipLaunchKernelGGL((bwd_ddp_kernel<TIO, D, true>), dim3(nsb - 1, BH), dim3(256), bytes, st, p);
+            e = hipGetLastError();
+        }
+    }
+    return e;
 }
 
 hipError_t launch_bwd_scan(const BwdParams& p, int d, int is_bf16, int stages, hipStream_t st) {
-    if (is_bf16) return d == 64 ? launch_scan_t<bf16_t, 64>(p, stages, st) : launch_scan_t<bf16_t, 128>(p, stages, st);
-    return d == 64 ? launch_scan_t<float, 64>(p, stages, st) : launch_scan_t<float, 128>(p, stages, st);
+#define LAUNCH_SCAN(TT, DD) (p.cum ? launch_scan_t<TT, DD, true>(p, stages, st) : launch_scan_t<TT, DD, false>(p, stages, st))
+    if (is_bf16) return d == 64 ? LAUNCH_SCAN(bf16_t, 64) : LAUNCH_SCAN(bf16_t, 128);
+    return d == 64 ? LAUNCH_SCAN(float, 64) : LAUNCH_SCAN(float, 128);
+#undef LAUNCH_SCAN
 }
 
 hipError_t launch_batched_gemm(const GemmArgs& a, int BH, int is_bf16, hipStream_t st) {
     const size_t es = is_bf16 ? 2 : 4, fe = is_bf16 ? 8 : 4;
     const size_t bytes = (size_t)(a.M + a.N) * (a.K + fe) * es;
     dim3 grid(a.gridx, BH);
-    // set once per process; function-local statics are initialised under the language's own lock
-    static const hipError_t attr_bf = set_smem(&batched_gemm_kernel<bf16_t>, 160 * 1024);
-    static const hipError_t attr_f32 = set_smem(&batched_gemm_kernel<float>, 160 * 1024);
-    if ((is_bf16 ? attr_bf : attr_f32) != hipSuccess) return is_bf16 ? attr_bf : attr_f32;
+    const hipError_t e = is_bf16 ? set_smem<&batched_gemm_kernel<bf16_t>>(160 * 1024) : set_smem<&batched_gemm_kernel<float>>(160 * 1024);
+    if (e != hipSuccess) return e;
     if (is_bf16) hipLaunchKernelGGL((batched_gemm_kernel<bf16_t>), grid, dim3(256), bytes, st, a);
     else hipLaunchKernelGGL((batched_gemm_kernel<float>), grid, dim3(256), bytes, st, a);
     return hipGetLastError();
@@ -1393,7 +1254,7 @@ hipError_t launch_chunk_adjoint(const ChunkProgram& pr, int BH, int is_bf16, hip
     dim3 grid(pr.NC, BH);
 #define LAUNCH_CHUNK_ADJ(TT, FF)                                                                  \
     do {                                                                                          \
-        if ((e = set_smem(&chunk_adjoint_kernel<TT, FF>, 160 * 1024)) != hipSuccess) return e;    \
+        if ((e = set_smem<&chunk_adjoint_kernel<TT, FF>>(160 * 1024)) != hipSuccess) return e;   \
         hipLaunchKernelGGL((chunk_adjoint_kernel<TT, FF>), grid, dim3(256), bytes, st, pr);       \
     } while (0)
     if (is_bf16) { if (fox) LAUNCH_CHUNK_ADJ(bf16_t, true); else LAUNCH_CHUNK_ADJ(bf16_t, false); }

@@ -2,10 +2,10 @@
 // (paper Sec. 3.3 workflow) without logits or outputs.  For every query chunk i it writes the
 // state used against each key block of the backward -- the chunks of i's own super-block one
 // by one, the super-blocks further left as a whole (second blocking level, see prep2_fwd.hip) --
-// as two fragment-order tiles per (chunk, block) pair: xs (rows q, contraction c), which is
-// the operand copy of the state itself, and xsT (rows c, contraction q), its transpose taken
-// through the matrix unit (with 16-bit operands only for the far blocks: the near blocks'
-// consumer reads xs with the transposing LDS read instead).
+// as a fragment-order tile per (chunk, block) pair: xs (rows q, contraction c), which is
+// the operand copy of the state itself; for fp32 operands also xsT (rows c, contraction q), its
+// transpose taken through the matrix unit (16-bit operands: the consumers read xs with the
+// transposing LDS read instead).
 //
 // One workgroup = 4 waves = two query chunks; wave w owns the 32-query half (w & 1) of chunk
 // 2*tile + (w >> 1).  The state keeps an fp32 master; per step one -dP tile (chunk or
@@ -94,9 +94,9 @@ __global__ __launch_bounds__(256) void bwd_states_kernel(FwdParams p) {
             const size_t slot = ((size_t)bh * nslots + block_slot(cq, c, NC)) * (size_t)CHUNK * D;
             Frag* xd = reinterpret_cast<Frag*>(reinterpret_cast<T*>(p.xs) + slot);
 #pragma unroll
-            for (int s = 0; s < DS; ++s) __builtin_nontemporal_store(Xb[s], &xd[((size_t)qb * DS + s) * 64 + lane]);
+            for (int s = 0; s < DS; ++s) __builtin_nontemporal_store(Xb[s], &xd[((size_t)qb * DS + s) * 64 + tile_lane(lane, s)]);
             Frag* xt = reinterpret_cast<Frag*>(reinterpret_cast<T*>(p.xsT) + slot);
-            if (sizeof(T) == 4 || !near)       // (16-bit operands: the near blocks' consumer transposes xs itself)
+            if (sizeof(T) == 4)
 #pragma unroll
             for (int b = 0; b < DB; ++b) {
                 const f32x16 tr = transpose32<T>(Xb + b * SPB, idf);     // rows q, lane c (block b)

@@ -2,7 +2,7 @@
 
 A training step leaves parts of its workspace unwritten -- the second-level tiles of a head's last super-block and
 everything its adjoint would put there -- and no kernel may read them.  Lengths around the edges of a super-block
-(1024 tokens), dense and packed; the bars are those of the other backward tests (2e-2 bf16, 1e-4 fp32, of the
+(1024 tokens; one, two, three, four query chunks right of the first), dense and packed; the bars are those of the other backward tests (2e-2 bf16, 1e-4 fp32, of the
 tensor's maximum), which a single NaN fails.
 """
 import numpy as np
@@ -36,7 +36,8 @@ def _compare(ref, got, dtype, tag):
         assert np.isfinite(g).all() and e <= TOL[dtype], (tag, n, e)
 
 
-@pytest.mark.parametrize("dtype,L,d", [("bf16", 1024, 128), ("bf16", 1025, 64), ("bf16", 2048, 128), ("bf16", 2111, 64),
+@pytest.mark.parametrize("dtype,L,d", [("bf16", 1024, 128), ("bf16", 1025, 64), ("bf16", 1089, 128), ("bf16", 1153, 64),
+                                       ("bf16", 1217, 128), ("bf16", 2048, 128), ("bf16", 2111, 64),
                                        ("fp32", 1024, 64), ("fp32", 1089, 128)])
 def test_training_pair(gpu, oracle, dtype, L, d):
     torch, pa = gpu
