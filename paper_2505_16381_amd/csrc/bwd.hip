@@ -114,9 +114,7 @@ template <typename TIO, int D> struct Adj2Cfg {
     typedef typename Compute<TIO>::type T;
     static constexpr int FE = Tr<T>::FE;
     static constexpr int KV_FRAGS = CHUNK * D / FE, DP_FRAGS = D * D / FE;
-    static constexpr int NBUF = (sizeof(T) == 2) ? 2 : 1;
-    static constexpr int STAGE_FRAGS = 3 * KV_FRAGS + DP_FRAGS;                    // kt | vk | ktT | dpt
-    static constexpr size_t smem_bytes = (size_t)NBUF * STAGE_FRAGS * 16;
+    static constexpr size_t smem_bytes = (size_t)(3 * KV_FRAGS + DP_FRAGS) * 16;   // fp32: kt | vk | ktT | dpt
 };
 
 template <typename TIO, int D, bool FOX>
@@ -128,7 +126,7 @@ __global__ __launch_bounds__(256) void bwd_adjoint2_kernel(BwdParams p) {
     constexpr int KW = Tr<T>::KW, SPB = 32 / KW, DB = D / 32, DS = D / KW, QS = CHUNK / KW;
     constexpr int KVF = C::KV_FRAGS, DPF = C::DP_FRAGS;
 
-    constexpr int NBUF = C::NBUF, STF = C::STAGE_FRAGS;
+    static_assert(sizeof(T) == 4, "fp32 operands");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     Frag* sbase = reinterpret_cast<Frag*>(smem);
 
@@ -176,26 +174,17 @@ __global__ __launch_bounds__(256) void bwd_adjoint2_kernel(BwdParams p) {
     // Step j handles key chunk j: far (j < jsb: second-level keys, state and product of its
     // super-block) or near (chunk-level keys, state and product of the chunk).
     const int nsb = (NC + SBC - 1) / SBC;
-    // The four tiles of chunk j are requested in four parts (part = -1: all at once).  With two
-    // stage buffers the parts of the NEXT chunk are spread over the current chunk's work: the
-    // direct-to-LDS path takes about 32 B/clk per CU, and a wave that issues a whole stage at
-    // once sits in the issue queue for that long.
-    auto issue = [&](int j, int part) {
-        Frag* buf = sbase + (size_t)(j & (NBUF - 1)) * STF;
+    auto issue = [&](int j) {
         const size_t bhc = (size_t)bh * NC + j;
         const bool far = j < jsb;
-        if (part < 0 || part == 0)
-            async_copy_tile<256, KVF>(reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(far ? p.kt2 : p.kt) + bhc * CHUNK * D), buf, tid, wv);
-        if (part < 0 || part == 1)
-            async_copy_tile<256, KVF>(reinterpret_cast<const Frag*>(reinterpret_cast<const TIO*>(p.vk) + bhc * CHUNK * D), buf + KVF, tid, wv);
-        if (part < 0 || part == 2)
-            async_copy_tile<256, KVF>(reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(far ? p.kt2T : p.ktT) + bhc * CHUNK * D), buf + 2 * KVF, tid, wv);
-        if ((part < 0 || part == 3) && j > 0) {
-            if (!far)
-                async_copy_tile<256, DPF>(reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(p.dpt) + bhc * (size_t)D * D), buf + 3 * KVF, tid, wv);
-            else if (j % SBC == 0)
-                async_copy_tile<256, DPF>(reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(p.dpt2) + ((size_t)bh * nsb + j / SBC) * (size_t)D * D), buf + 3 * KVF, tid, wv);
-        }
+        async_copy_tile<256, KVF>(reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(far ? p.kt2 : p.kt) + bhc * CHUNK * D), sbase, tid, wv);
+        async_copy_tile<256, KVF>(reinterpret_cast<const Frag*>(reinterpret_cast<const TIO*>(p.vk) + bhc * CHUNK * D), sbase + KVF, tid, wv);
+        async_copy_tile<256, KVF>(reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(far ? p.kt2T : p.ktT) + bhc * CHUNK * D), sbase + 2 * KVF, tid, wv);
+        if (j == 0) return;
+        if (!far)
+            async_copy_tile<256, DPF>(reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(p.dpt) + bhc * (size_t)D * D), sbase + 3 * KVF, tid, wv);
+        else if (j % SBC == 0)
+            async_copy_tile<256, DPF>(reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(p.dpt2) + ((size_t)bh * nsb + j / SBC) * (size_t)D * D), sbase + 3 * KVF, tid, wv);
     };
     auto block_start = [&](int j) { return j >= jsb || j % SBC == 0; };
     // the wave's own state fragments of the block that starts at chunk j: fetched one step ahead
@@ -209,23 +198,13 @@ __global__ __launch_bounds__(256) void bwd_adjoint2_kernel(BwdParams p) {
 #pragma unroll
     for (int s = 0; s < DS; ++s) { Xnext[s] = Tr<T>::zero(); Xb[s] = Tr<T>::zero(); }
     if (active && cq > 0) load_x(0, Xnext);
-    if (jmax >= 0 && NBUF == 2) issue(0, -1);
 
     for (int j = 0; j <= jmax; ++j) {
-        const bool spread = NBUF == 2 && j + 1 <= jmax;     // request chunk j+1 while working on chunk j
-        if (NBUF == 2) {
-            wait_async_and_sync();                 // chunk j has landed; everyone is done with chunk j-1
-            if (spread) issue(j + 1, 0);
-        } else {
-            __syncthreads();
-            issue(j, -1);
-            wait_async_and_sync();
-        }
-        if (!active || j >= cq) {
-            if (spread) { issue(j + 1, 1); issue(j + 1, 2); issue(j + 1, 3); }
-            continue;
-        }
-        const Frag* sK = sbase + (size_t)(j & (NBUF - 1)) * STF;
+        __syncthreads();
+        issue(j);
+        wait_async_and_sync();
+        if (!active || j >= cq) continue;
+        const Frag* sK = sbase;
         const FragV* sV = reinterpret_cast<const FragV*>(sK + KVF);
         const Frag* sKT = sK + 2 * KVF;
         const Frag* sDP = sK + 3 * KVF;
@@ -270,9 +249,7 @@ __global__ __launch_bounds__(256) void bwd_adjoint2_kernel(BwdParams p) {
                     S[jj] = ds;
                 }
                 pack_block<T>(S, dSb + kb * SPB);
-                if (spread) issue(j + 1, 1 + kb);
             }
-            if (spread) issue(j + 1, 3);
     #pragma unroll
             for (int b = 0; b < DB; b += 2) {
                 Frag ta[2 * QS];
@@ -506,30 +483,23 @@ __global__ __launch_bounds__(256, 2) void bwd_adjoint2_lite_kernel(BwdParams p) 
 }
 
 // ---------------------------------------------------------------------------------------
-// Key-side reduction of dV and dKb.  One workgroup per key chunk j; wave w owns the 32 keys of
-// half (w & 1) (= the MFMA columns) and the 32-query half (w >> 1) of every query chunk i > j
-// of the kernel's range -- near (FAR = false): the chunks i > j of j's own super-block, keys Kb,
-// results dKb and dV; far (FAR = true): all chunks of the super-blocks to the right, keys Kb2,
-// results dKb2 and dV added to the near part (the near kernel runs first):
+// Key-side reduction of dV and dKb for fp32 operands (16-bit operands: bwd_keys.hip).  One workgroup per key chunk
+// j; wave w owns the 32 keys of half (w & 1) (= the MFMA columns) and the 32-query half (w >> 1) of every query
+// chunk i > j of the kernel's range -- near (FAR = false): the chunks i > j of j's own super-block, keys Kb, results
+// dKb and dV; far (FAR = true): all chunks of the super-blocks to the right, keys Kb2, results dKb2 and dV added to
+// the near part (the near kernel runs first):
 //     S  = Xs Kb_j^T              A = xs tile,   B = Kb fragments (resident)
 //     dP = dO V_j^T               A = doq tile,  B = V fragments (resident)
 //     dV^T  += dO^T P             A = doT tile,  B = P   (registers)
 //     dKb^T += Xs^T dS            A = xsT tile,  B = dS  (registers)
 // The two query halves are summed through LDS at the end (no atomics).
-//
-// With 16-bit operands the near kernel also takes the near part of ddP_j (see bwd_ddp_kernel):
-//     ddP_j -= Xs^T g               A = xsT tile,  B = gT tile
-// over the same pairs (i, j), whose xsT tile it has staged anyway.  The gT tile takes the LDS
-// space of the doT tile; the dO^T fragments are then read out of the doq tile with the
-// transposing LDS read.
-//
 template <typename TIO, int D> struct Key2Cfg {
     typedef typename Compute<TIO>::type T;
     static constexpr int FE = Tr<T>::FE;
     static constexpr int KV_FRAGS = CHUNK * D / FE;
-    static constexpr int NBUF = (sizeof(T) == 2) ? 2 : 1;                     // fp32 tiles are too big to double-buffer
-    static constexpr int STAGE_FRAGS = 4 * KV_FRAGS + 32;                     // xs | xsT | doq | doT (near, 16-bit: gT) | lse2 | delta
-    static constexpr size_t tile_bytes = (size_t)NBUF * STAGE_FRAGS * 16;
+    static_assert(sizeof(T) == 4, "fp32 operands");
+    static constexpr int STAGE_FRAGS = 4 * KV_FRAGS + 32;                     // xs | xsT | doq | doT | lse2 | delta (too big to double-buffer)
+    static constexpr size_t tile_bytes = (size_t)STAGE_FRAGS * 16;
     static constexpr size_t red_bytes = (size_t)2 * 2 * (D / 32) * 1024 * 4 + 256;   // dV, dKb (and FOX column sums) of the two upper waves
     static constexpr size_t smem_bytes = tile_bytes > red_bytes ? tile_bytes : red_bytes;
 };
@@ -541,10 +511,7 @@ __global__ __launch_bounds__(256) void bwd_keyside2_kernel(BwdParams p) {
     using Frag = typename Tr<T>::Frag;
     using FragV = typename Tr<TIO>::Frag;
     constexpr int KW = Tr<T>::KW, SPB = 32 / KW, DB = D / 32, DS = D / KW, QS = CHUNK / KW;
-    constexpr int KVF = C::KV_FRAGS, NBUF = C::NBUF, STF = C::STAGE_FRAGS;
-    static_assert(!FAR || sizeof(T) == 4, "16-bit operands: bwd_far_kernel");
-    constexpr bool NFUSE = !FAR && sizeof(T) == 2;          // the near part of ddP is taken here too
-    constexpr int NOWN = NFUSE ? DB * DB / 4 : 1;           // its 32x32 blocks per wave
+    constexpr int KVF = C::KV_FRAGS;
 
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     Frag* sbase = reinterpret_cast<Frag*>(smem);
@@ -588,48 +555,36 @@ __global__ __launch_bounds__(256) void bwd_keyside2_kernel(BwdParams p) {
     f32x16 dVt[DB], dKt[DB];
 #pragma unroll
     for (int b = 0; b < DB; ++b) { dVt[b] = zero16(); dKt[b] = zero16(); }
-    f32x16 ddPa[NOWN];
-#pragma unroll
-    for (int o = 0; o < NOWN; ++o) ddPa[o] = zero16();
     // PaTH-FoX: this lane's key has gate sum ckj; dcol collects the column sum of the logit gradient
     const int key_tok = (wactive ? jw : j) * CHUNK + 32 * kh + l32;
     const float ckj = FOX ? p.cum[(size_t)bh * Lp + key_tok] : 0.f;
     float dcol = 0.f;
 
-    // all operands of query chunk i, asynchronously, into stage buffer (i & (NBUF-1))
+    // all operands of query chunk i
+    Frag* const sX = sbase;
+    const Frag* sXT = sX + KVF;
+    const FragV* sDQ = reinterpret_cast<const FragV*>(sX + 2 * KVF);
+    const FragV* sDT = reinterpret_cast<const FragV*>(sX + 3 * KVF);
+    const float* lse2 = reinterpret_cast<const float*>(sX + 4 * KVF);
+    const float* dl = lse2 + CHUNK;
     auto issue = [&](int i) {
-        Frag* buf = sbase + (size_t)(i & (NBUF - 1)) * STF;
         const size_t slot = ((size_t)bh * nslots + block_slot(i, j, NC)) * (size_t)CHUNK * D;
         const size_t bhi = ((size_t)bh * NC + i) * CHUNK * D;
-        async_copy_tile<256, KVF>(reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(p.xs) + slot), buf, tid, wv);
-        if (!NFUSE)       // (near, 16-bit: Xs^T fragments are read out of the xs tile)
-            async_copy_tile<256, KVF>(reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(p.xsT) + slot), buf + KVF, tid, wv);
-        async_copy_tile<256, KVF>(reinterpret_cast<const Frag*>(reinterpret_cast<const TIO*>(p.doq) + bhi), buf + 2 * KVF, tid, wv);
-        if (NFUSE) async_copy_tile<256, KVF>(reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(p.gs) + slot), buf + 3 * KVF, tid, wv);
-        else async_copy_tile<256, KVF>(reinterpret_cast<const Frag*>(reinterpret_cast<const TIO*>(p.doT) + bhi), buf + 3 * KVF, tid, wv);
+        async_copy_tile<256, KVF>(reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(p.xs) + slot), sX, tid, wv);
+        async_copy_tile<256, KVF>(reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(p.xsT) + slot), sX + KVF, tid, wv);
+        async_copy_tile<256, KVF>(reinterpret_cast<const Frag*>(reinterpret_cast<const TIO*>(p.doq) + bhi), sX + 2 * KVF, tid, wv);
+        async_copy_tile<256, KVF>(reinterpret_cast<const Frag*>(reinterpret_cast<const TIO*>(p.doT) + bhi), sX + 3 * KVF, tid, wv);
         if (tid < 32) {     // 64 floats of lse2 (lanes 0-15) and of delta (lanes 16-31): 16 bytes per lane
             const float* src = (tid < 16 ? p.lse2p : p.delta) + (size_t)bh * Lp + (size_t)i * CHUNK + 4 * (tid & 15);
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
-                                             (__attribute__((address_space(3))) void*)(buf + 4 * KVF), 16, 0, 0);
+                                             (__attribute__((address_space(3))) void*)(sX + 4 * KVF), 16, 0, 0);
         }
     };
 
-    if (i0 < i1 && NBUF == 2) issue(i0);
     for (int i = i0; i < i1; ++i) {
-        if (NBUF == 2) {
-            wait_async_and_sync();                 // chunk i has landed; everyone is done with chunk i-1
-            if (i + 1 < i1) issue(i + 1);
-        } else {
-            __syncthreads();
-            issue(i);
-            wait_async_and_sync();
-        }
-        const Frag* sX = sbase + (size_t)(i & (NBUF - 1)) * STF;
-        const Frag* sXT = sX + KVF;
-        const FragV* sDQ = reinterpret_cast<const FragV*>(sX + 2 * KVF);
-        const FragV* sDT = reinterpret_cast<const FragV*>(sX + 3 * KVF);
-        const float* lse2 = reinterpret_cast<const float*>(sX + 4 * KVF);
-        const float* dl = lse2 + CHUNK;
+        __syncthreads();
+        issue(i);
+        wait_async_and_sync();
 
         // The three parts of the work on a 32-query half: logits and dP (16 products), the element-wise
         // part, and the updates of dV^T and dKb^T (32 products).
@@ -686,74 +641,15 @@ __global__ __launch_bounds__(256) void bwd_keyside2_kernel(BwdParams p) {
                 }
             }
         };
-        {
 #pragma unroll
-            for (int qq = 0; qq < CPW; ++qq) {
-                const int qh = FAR ? qq : (wv >> 1);
-                f32x16 S, dP;
-                FragV Pb[SPB];
-                Frag dSb[SPB];
-                sdp(qh, S, dP);
-                soft(qh, S, dP, Pb, dSb);
-                if constexpr (NFUSE) {
-                    // dV^T, dKb^T and the wave's ddP blocks, one 32-row block b of Xs^T at a time: its four
-                    // fragments (all 64 queries) serve ddP, and the two of the wave's own query half serve dKb^T --
-                    // every fragment is read from LDS once per step (the reads, not the products, bound this loop).
-                    // The wave's ddP blocks wv, wv + 4, ... all lie in column block bb of g (d = 128: one per row
-                    // block b; d = 64: the single block (wv / 2, wv % 2)), whose fragments are read once too.
-                    static_assert(DB == 4 || DB == 2, "block ownership below");
-                    // The wave's own query half comes first, the other one second, both by address (qh is uniform over
-                    // the wave): no selects between registers.  Chunk 0 has no transform to the left of it: its sums
-                    // are taken like the others (its adjoint-state tile is valid memory, whatever it holds) and
-                    // written as zeros at the end -- a test here would put the accumulators behind a branch, and
-                    // the compiler then copies them between the register files around every product.
-                    const Frag* sG = sX + 3 * KVF;
-                    const int bb = DB == 4 ? wv : (wv & 1);
-                    const int own = qh * SPB, oth = (1 - qh) * SPB;
-                    Frag fbo[SPB], fbx[SPB];
-#pragma unroll
-                    for (int u = 0; u < SPB; ++u) { fbo[u] = sG[(bb * QS + own + u) * 64 + lane]; fbx[u] = sG[(bb * QS + oth + u) * 64 + lane]; }
-#pragma unroll
-                    for (int b = 0; b < DB; ++b) {
-                        Frag fo[SPB], fx[SPB];
-                        FragV ta[SPB];
-#pragma unroll
-                        for (int u = 0; u < SPB; ++u) {
-                            fo[u] = ld_tile_frag_tr<T, DS, true>(reinterpret_cast<const T*>(sX), own + u, b, l32, h);
-                            fx[u] = ld_tile_frag_tr<T, DS, true>(reinterpret_cast<const T*>(sX), oth + u, b, l32, h);
-                            ta[u] = ld_tile_frag_tr<TIO, DS, true>(reinterpret_cast<const TIO*>(sDQ), own + u, b, l32, h);
-                        }
-#pragma unroll
-                        for (int u = 0; u < SPB; ++u) {
-                            dVt[b] = Tr<TIO>::mma(ta[u], Pb[u], dVt[b]);
-                            dKt[b] = Tr<T>::mma(fo[u], dSb[u], dKt[b]);
-                        }
-                        if (DB == 4 || b == (wv >> 1)) {
-                            constexpr int NO = DB == 4 ? DB : 1;
-#pragma unroll
-                            for (int o = 0; o < NO; ++o)
-                                if (DB != 4 || o == b) {
-#pragma unroll
-                                    for (int u = 0; u < SPB; ++u) {
-                                        ddPa[o] = Tr<T>::mma(fo[u], fbo[u], ddPa[o]);
-                                        ddPa[o] = Tr<T>::mma(fx[u], fbx[u], ddPa[o]);
-                                    }
-                                }
-                        }
-                    }
-                } else {
-                    upd(qh, Pb, dSb);
-                }
-            }
-        }
-    }
-    if (NFUSE) {
-#pragma unroll
-        for (int o = 0; o < NOWN; ++o) {
-            const int blk = wv + 4 * o, ab = blk / DB, bb = blk % DB;
-#pragma unroll
-            for (int jj = 0; jj < 16; ++jj)
-                __builtin_nontemporal_store(j >= 1 ? -ddPa[o][jj] : 0.f, &p.ddp[((size_t)bh * NC + j) * D * D + (size_t)(32 * ab + acc_row(jj, h)) * D + 32 * bb + l32]);
+        for (int qq = 0; qq < CPW; ++qq) {
+            const int qh = FAR ? qq : (wv >> 1);
+            f32x16 S, dP;
+            FragV Pb[SPB];
+            Frag dSb[SPB];
+            sdp(qh, S, dP);
+            soft(qh, S, dP, Pb, dSb);
+            upd(qh, Pb, dSb);
         }
     }
     if (FAR) {
@@ -1194,14 +1090,19 @@ static hipError_t launch_scan_t(const BwdParams& p, int stages, hipStream_t st) 
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    const size_t key_bytes = Key2Cfg<TIO, D>::smem_bytes;
     if (stages & BWD_STAGE_KEYS_NEAR) {
-        if ((e = set_smem<&bwd_keyside2_kernel<TIO, D, false, FOX>>(key_bytes)) != hipSuccess) return e;
-        hipLaunchKernelGGL((bwd_keyside2_kernel<TIO, D, false, FOX>), dim3(rounds * nsb * SBC), dim3(256), key_bytes, st, p);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
+        if constexpr (F32) {
+            const size_t key_bytes = Key2Cfg<TIO, D>::smem_bytes;
+            if ((e = set_smem<&bwd_keyside2_kernel<TIO, D, false, FOX>>(key_bytes)) != hipSuccess) return e;
+            hipLaunchKernelGGL((bwd_keyside2_kernel<TIO, D, false, FOX>), dim3(rounds * nsb * SBC), dim3(256), key_bytes, st, p);
+            if ((e = hipGetLastError()) != hipSuccess) return e;
+        } else {
+            if ((e = launch_bwd_near(p, D, st)) != hipSuccess) return e;
+        }
     }
     if (has_far && (stages & BWD_STAGE_KEYS_FAR)) {
         if constexpr (F32) {
+            const size_t key_bytes = Key2Cfg<TIO, D>::smem_bytes;
             if ((e = set_smem<&bwd_keyside2_kernel<TIO, D, true, FOX>>(key_bytes)) != hipSuccess) return e;
             hipLaunchKernelGGL((bwd_keyside2_kernel<TIO, D, true, FOX>), dim3(rounds * (nsb - 1) * (SBC / 2)), dim3(256), key_bytes, st, p);
             if ((e = hipGetLastError()) != hipSuccess) return e;
