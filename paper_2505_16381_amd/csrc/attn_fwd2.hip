@@ -180,7 +180,7 @@ __global__ __launch_bounds__(FWD2_THREADS, 512 / FWD2_THREADS) void attn_fwd2_ke
                 const size_t slot = ((size_t)bh * num_block_slots(NC) + block_slot(cq, j >= jsb ? j : j - (SBC - 1), NC)) * (size_t)CHUNK * D;
                 Frag* xd = reinterpret_cast<Frag*>(reinterpret_cast<T*>(p.xs) + slot);
 #pragma unroll
-                for (int s = 0; s < DS; ++s) __builtin_nontemporal_store(Xh[s], &xd[((size_t)qb * DS + s) * 64 + tile_lane(lane, s)]);     // streamed: keep the key/value tiles in L2
+                for (int s = 0; s < DS; ++s) __builtin_nontemporal_store(Xh[s], &xd[((size_t)qb * DS + s) * 64 + tile_lane<T>(lane, s)]);     // streamed: keep the key/value tiles in L2
                 if (sizeof(T) == 4) {                // (16-bit operands: the consumers transpose xs themselves)
                     Frag* xt = reinterpret_cast<Frag*>(reinterpret_cast<T*>(p.xsT) + slot);
                     Frag idf[SPB];
@@ -213,7 +213,7 @@ __global__ __launch_bounds__(FWD2_THREADS, 512 / FWD2_THREADS) void attn_fwd2_ke
         } else {
             S = zero16();
 #pragma unroll
-            for (int s = 0; s < DS; ++s) S = Tr<T>::mma(sK[s * 64 + lane], Xh[s], S);
+            for (int s = 0; s < DS; ++s) S = Tr<T>::mma(sK[s * 64 + tile_lane<T>(lane, s)], Xh[s], S);
         }
 
         // ---- online softmax.  Fast path: exponentiate against the current reference maximum
@@ -292,7 +292,7 @@ __global__ __launch_bounds__(FWD2_THREADS, 512 / FWD2_THREADS) void attn_fwd2_ke
 #pragma unroll
                 for (int b = 0; b < DB; ++b)
 #pragma unroll
-                    for (int s = 0; s < DS; ++s) Xn[b] = Tr<T>::mma(sP[(b * DS + s) * 64 + lane], Xh[s], Xn[b]);
+                    for (int s = 0; s < DS; ++s) Xn[b] = Tr<T>::mma(sP[(b * DS + s) * 64 + tile_lane<T>(lane, s)], Xh[s], Xn[b]);
 #pragma unroll
                 for (int b = 0; b < DB; ++b) {
                     if (HAS_MASTER) Xm[b] = Xn[b];

@@ -91,7 +91,7 @@ __global__ __launch_bounds__(256) void bwd_dotile_kernel(BwdParams p) {
         if (WITH_T) pack_block<TIO>(b, fb);
 #pragma unroll
         for (int s = 0; s < SPB; ++s) {
-            __builtin_nontemporal_store(fa[s], &dq[((size_t)qb * (D / KW) + cb * SPB + s) * 64 + tile_lane(lane, s)]);
+            __builtin_nontemporal_store(fa[s], &dq[((size_t)qb * (D / KW) + cb * SPB + s) * 64 + tile_lane<TIO>(lane, s)]);
             if (WITH_T) __builtin_nontemporal_store(fb[s], &dt[((size_t)cb * QS + qb * SPB + s) * 64 + lane]);
         }
     }
@@ -157,7 +157,7 @@ __global__ __launch_bounds__(256) void bwd_adjoint2_kernel(BwdParams p) {
     if (active) {
         const FragV* dq = reinterpret_cast<const FragV*>(reinterpret_cast<const TIO*>(p.doq) + ((size_t)bh * NC + cq) * CHUNK * D);
 #pragma unroll
-        for (int s = 0; s < DS; ++s) dOb[s] = dq[((size_t)qb * DS + s) * 64 + tile_lane(lane, s)];
+        for (int s = 0; s < DS; ++s) dOb[s] = dq[((size_t)qb * DS + s) * 64 + tile_lane<TIO>(lane, s)];
         // base-2 units (PaTH-FoX: minus the query's gate sum); rows past L hold a huge value, so that their
         // P = exp2(-huge) = 0 without a mask.  log2(scale) is folded in: the exponential then yields scale * P,
         // which is all the logit gradient dS = scale * P o (dP - delta) needs.
@@ -192,7 +192,7 @@ __global__ __launch_bounds__(256) void bwd_adjoint2_kernel(BwdParams p) {
         const size_t slot = ((size_t)bh * nslots + block_slot(cq, j, NC)) * (size_t)CHUNK * D;
         const Frag* xg = reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(p.xs) + slot);
 #pragma unroll
-        for (int s = 0; s < DS; ++s) x[s] = __builtin_nontemporal_load(&xg[((size_t)qb * DS + s) * 64 + tile_lane(lane, s)]);     // read once: leave L2 to the key tiles
+        for (int s = 0; s < DS; ++s) x[s] = __builtin_nontemporal_load(&xg[((size_t)qb * DS + s) * 64 + tile_lane<TIO>(lane, s)]);     // read once: leave L2 to the key tiles
     };
     Frag Xnext[DS], Xb[DS];
 #pragma unroll
@@ -228,7 +228,7 @@ __global__ __launch_bounds__(256) void bwd_adjoint2_kernel(BwdParams p) {
                     Frag ka[4];
                     FragV va[4];
     #pragma unroll
-                    for (int u = 0; u < 4; ++u) { ka[u] = sK[(kb * DS + s0 + u) * 64 + lane]; va[u] = sV[(kb * DS + s0 + u) * 64 + lane]; }
+                    for (int u = 0; u < 4; ++u) { ka[u] = sK[(kb * DS + s0 + u) * 64 + tile_lane<T>(lane, u)]; va[u] = sV[(kb * DS + s0 + u) * 64 + lane]; }
     #pragma unroll
                     for (int u = 0; u < 4; ++u) {
                         S = Tr<T>::mma(ka[u], Xb[s0 + u], S);
@@ -356,7 +356,7 @@ __global__ __launch_bounds__(256, 2) void bwd_adjoint2_lite_kernel(BwdParams p) 
     if (active) {
         const FragV* dq = reinterpret_cast<const FragV*>(reinterpret_cast<const TIO*>(p.doq) + ((size_t)bh * NC + cq) * CHUNK * D);
 #pragma unroll
-        for (int s = 0; s < DS; ++s) dOb[s] = dq[((size_t)qb * DS + s) * 64 + tile_lane(lane, s)];
+        for (int s = 0; s < DS; ++s) dOb[s] = dq[((size_t)qb * DS + s) * 64 + tile_lane<TIO>(lane, s)];
         lse2 = p.lse2p[(size_t)bh * Lp + tq] - __builtin_log2f(p.scale);     // the exponential then yields scale * P
         dl = p.delta[(size_t)bh * Lp + tq];
     }
@@ -387,7 +387,7 @@ __global__ __launch_bounds__(256, 2) void bwd_adjoint2_lite_kernel(BwdParams p) 
             const size_t xslot = ((size_t)bh * nslots + block_slot(cq, j, NC)) * (size_t)CHUNK * D;
             const Frag* xg = reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(p.xs) + xslot);
 #pragma unroll
-            for (int s = 0; s < DS; ++s) Xb[s] = __builtin_nontemporal_load(&xg[((size_t)qb * DS + s) * 64 + tile_lane(lane, s)]);
+            for (int s = 0; s < DS; ++s) Xb[s] = __builtin_nontemporal_load(&xg[((size_t)qb * DS + s) * 64 + tile_lane<TIO>(lane, s)]);
         }
         wait_async_and_sync();
         if (!mine) continue;
@@ -402,7 +402,7 @@ __global__ __launch_bounds__(256, 2) void bwd_adjoint2_lite_kernel(BwdParams p) 
                 for (int s0 = 0; s0 < DS; s0 += 4) {
                     Frag pa[4];
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) pa[u] = ld_tile_frag_tr<T, DS, false>(reinterpret_cast<const T*>(sDP), s0 + u, b, l32, h);
+                    for (int u = 0; u < 4; ++u) pa[u] = ld_tile_frag_tr<T, DS>(reinterpret_cast<const T*>(sDP), s0 + u, b, l32, h);
 #pragma unroll
                     for (int u = 0; u < 4; ++u) Gm[b] = Tr<T>::mma(pa[u], Gb[s0 + u], Gm[b]);
                 }
@@ -415,7 +415,7 @@ __global__ __launch_bounds__(256, 2) void bwd_adjoint2_lite_kernel(BwdParams p) 
                 Frag ka[2];
                 FragV va[2];
 #pragma unroll
-                for (int u = 0; u < 2; ++u) { ka[u] = sK[(kb * DS + s0 + u) * 64 + lane]; va[u] = sV[(kb * DS + s0 + u) * 64 + lane]; }
+                for (int u = 0; u < 2; ++u) { ka[u] = sK[(kb * DS + s0 + u) * 64 + tile_lane<T>(lane, u)]; va[u] = sV[(kb * DS + s0 + u) * 64 + lane]; }
 #pragma unroll
                 for (int u = 0; u < 2; ++u) {
                     S = Tr<T>::mma(ka[u], Xb[s0 + u], S);
@@ -442,7 +442,7 @@ __global__ __launch_bounds__(256, 2) void bwd_adjoint2_lite_kernel(BwdParams p) 
             for (int b = 0; b < DB; ++b) {
                 Frag ta[SPB];
 #pragma unroll
-                for (int u = 0; u < SPB; ++u) ta[u] = ld_tile_frag_tr<T, DS, false>(reinterpret_cast<const T*>(sK), kb * SPB + u, b, l32, h);
+                for (int u = 0; u < SPB; ++u) ta[u] = ld_tile_frag_tr<T, DS>(reinterpret_cast<const T*>(sK), kb * SPB + u, b, l32, h);
 #pragma unroll
                 for (int u = 0; u < SPB; ++u) Gm[b] = Tr<T>::mma(ta[u], dSh[u], Gm[b]);
             }
@@ -550,7 +550,7 @@ __global__ __launch_bounds__(256) void bwd_keyside2_kernel(BwdParams p) {
         const Frag* kg = reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(FAR ? p.kt2 : p.kt) + ((size_t)bh * NC + jl) * CHUNK * D);
         const FragV* vg = reinterpret_cast<const FragV*>(reinterpret_cast<const TIO*>(p.vk) + ((size_t)bh * NC + jl) * CHUNK * D);
 #pragma unroll
-        for (int s = 0; s < DS; ++s) { Kb[s] = kg[((size_t)kh * DS + s) * 64 + lane]; Vb[s] = vg[((size_t)kh * DS + s) * 64 + lane]; }
+        for (int s = 0; s < DS; ++s) { Kb[s] = kg[((size_t)kh * DS + s) * 64 + tile_lane<T>(lane, s)]; Vb[s] = vg[((size_t)kh * DS + s) * 64 + lane]; }
     }
     f32x16 dVt[DB], dKt[DB];
 #pragma unroll
@@ -596,7 +596,7 @@ __global__ __launch_bounds__(256) void bwd_keyside2_kernel(BwdParams p) {
                 Frag xa[4];
                 FragV da[4];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) { xa[u] = sX[(qh * DS + s0 + u) * 64 + tile_lane(lane, u)]; da[u] = sDQ[(qh * DS + s0 + u) * 64 + tile_lane(lane, u)]; }
+                for (int u = 0; u < 4; ++u) { xa[u] = sX[(qh * DS + s0 + u) * 64 + tile_lane<TIO>(lane, u)]; da[u] = sDQ[(qh * DS + s0 + u) * 64 + tile_lane<TIO>(lane, u)]; }
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     S = Tr<T>::mma(xa[u], Kb[s0 + u], S);

@@ -87,7 +87,7 @@ __global__ __launch_bounds__(512, 2) void bwd_far_kernel(BwdParams p) {
             const Frag* kg = reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(p.kt2) + ((size_t)bh * NC + jw) * CHUNK * D);
             const FragV* vg = reinterpret_cast<const FragV*>(reinterpret_cast<const TIO*>(p.vk) + ((size_t)bh * NC + jw) * CHUNK * D);
 #pragma unroll
-            for (int s = 0; s < DS; ++s) { Kb[s] = kg[((size_t)kh * DS + s) * 64 + lane]; Vb[s] = vg[((size_t)kh * DS + s) * 64 + lane]; }
+            for (int s = 0; s < DS; ++s) { Kb[s] = kg[((size_t)kh * DS + s) * 64 + tile_lane<T>(lane, s)]; Vb[s] = vg[((size_t)kh * DS + s) * 64 + lane]; }
         }
         const int key_tok = jw * CHUNK + 32 * kh + l32;
         const float ckj = FOX ? p.cum[(size_t)bh * Lp + key_tok] : 0.f;
@@ -103,7 +103,7 @@ __global__ __launch_bounds__(512, 2) void bwd_far_kernel(BwdParams p) {
             const Frag* sX = stages + st * STF;
             const FragV* sDQ = reinterpret_cast<const FragV*>(sX + KVF);
 #pragma unroll
-            for (int u = 0; u < DS; ++u) { xa[u] = sX[(qh * DS + u) * 64 + tile_lane(lane, u)]; da[u] = sDQ[(qh * DS + u) * 64 + tile_lane(lane, u)]; }
+            for (int u = 0; u < DS; ++u) { xa[u] = sX[(qh * DS + u) * 64 + tile_lane<T>(lane, u)]; da[u] = sDQ[(qh * DS + u) * 64 + tile_lane<T>(lane, u)]; }
         };
         // A half-step's work in four slices, each a quarter of its products, a quarter of the element-wise part of the
         // half-step before (half qh of the tile in stage st: P and dS -> its hand-over buffer) and a piece of the copies.
@@ -209,12 +209,12 @@ __global__ __launch_bounds__(512, 2) void bwd_far_kernel(BwdParams p) {
 #pragma unroll
             for (int b = 0; b < DB; ++b)
 #pragma unroll
-                for (int u = 0; u < SPB; ++u) ta[b * SPB + u] = ld_tile_frag_tr<E, DS, true>(tile, qh * SPB + u, b, l32, h);
+                for (int u = 0; u < SPB; ++u) ta[b * SPB + u] = ld_tile_frag_tr<E, DS>(tile, qh * SPB + u, b, l32, h);
             if constexpr (KEYS) {
 #pragma unroll
                 for (int u = 0; u < SPB; ++u) gf[u] = stages[st * STF + 2 * KVF + (qh * SPB + u) * 64 + lane];
 #pragma unroll
-                for (int u = 0; u < SPB; ++u) td[u] = ld_tile_frag_tr<E, DS, true>(tile, qh * SPB + u, ab, l32, h);
+                for (int u = 0; u < SPB; ++u) td[u] = ld_tile_frag_tr<E, DS>(tile, qh * SPB + u, ab, l32, h);
             }
         };
         int st = 0;
@@ -388,7 +388,7 @@ __global__ __launch_bounds__(512, 2 * (NearCfg<TIO, D>::WGS_PER_CU)) void bwd_ne
             const Frag* kg = reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(p.kt) + ((size_t)bh * NC + j) * CHUNK * D);
             const FragV* vg = reinterpret_cast<const FragV*>(reinterpret_cast<const TIO*>(p.vk) + ((size_t)bh * NC + j) * CHUNK * D);
 #pragma unroll
-            for (int s = 0; s < DS; ++s) { Kb[s] = kg[((size_t)kh * DS + s) * 64 + lane]; Vb[s] = vg[((size_t)kh * DS + s) * 64 + lane]; }
+            for (int s = 0; s < DS; ++s) { Kb[s] = kg[((size_t)kh * DS + s) * 64 + tile_lane<T>(lane, s)]; Vb[s] = vg[((size_t)kh * DS + s) * 64 + lane]; }
         }
         const int key_tok = j * CHUNK + 32 * kh + l32;
         const float ckj = FOX ? p.cum[(size_t)bh * Lp + key_tok] : 0.f;
@@ -401,7 +401,7 @@ __global__ __launch_bounds__(512, 2 * (NearCfg<TIO, D>::WGS_PER_CU)) void bwd_ne
             Frag xa[DS];
             FragV da[DS];
 #pragma unroll
-            for (int u = 0; u < DS; ++u) { xa[u] = sX[(qh * DS + u) * 64 + tile_lane(lane, u)]; da[u] = sDQ[(qh * DS + u) * 64 + tile_lane(lane, u)]; }
+            for (int u = 0; u < DS; ++u) { xa[u] = sX[(qh * DS + u) * 64 + tile_lane<T>(lane, u)]; da[u] = sDQ[(qh * DS + u) * 64 + tile_lane<T>(lane, u)]; }
             __builtin_amdgcn_sched_barrier(0);
             if (i + 1 < i1) issue(i + 1);
             __builtin_amdgcn_sched_barrier(0);
@@ -486,7 +486,7 @@ __global__ __launch_bounds__(512, 2 * (NearCfg<TIO, D>::WGS_PER_CU)) void bwd_ne
         for (int a = 0; a < NA; ++a)
 #pragma unroll
             for (int s = 0; s < QS; ++s) {
-                xt[a * QS + s] = ld_tile_frag_tr<T, DS, true>(reinterpret_cast<const T*>(sX), s, NA * rb + a, l32, h);
+                xt[a * QS + s] = ld_tile_frag_tr<T, DS>(reinterpret_cast<const T*>(sX), s, NA * rb + a, l32, h);
                 gf[a * QS + s] = sX[2 * KVF + ((NA * kb + a) * QS + s) * 64 + lane];
             }
         __builtin_amdgcn_sched_barrier(0);
@@ -500,7 +500,7 @@ __global__ __launch_bounds__(512, 2 * (NearCfg<TIO, D>::WGS_PER_CU)) void bwd_ne
 #pragma unroll
         for (int a = 0; a < NA; ++a)
 #pragma unroll
-            for (int s = 0; s < QS; ++s) dt[a * QS + s] = ld_tile_frag_tr<TIO, DS, true>(reinterpret_cast<const TIO*>(sX + KVF), s, NA * rb + a, l32, h);
+            for (int s = 0; s < QS; ++s) dt[a * QS + s] = ld_tile_frag_tr<TIO, DS>(reinterpret_cast<const TIO*>(sX + KVF), s, NA * rb + a, l32, h);
     };
     if (i0 < i1) {
         copies_landed();

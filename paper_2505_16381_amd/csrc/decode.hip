@@ -78,7 +78,7 @@ __global__ __launch_bounds__(256) void key_prefill_kernel(PrefillArgs a) {
                 f32x16 acc = zero16();
                 if (!lastsb) {
 #pragma unroll
-                    for (int s = 0; s < DS; ++s) acc = Tr<T>::mma(Es[(cb * DS + s) * 64 + lane], sK[((size_t)sb2 * DS + s) * 64 + lane], acc);
+                    for (int s = 0; s < DS; ++s) acc = Tr<T>::mma(Es[(cb * DS + s) * 64 + lane], sK[((size_t)sb2 * DS + s) * 64 + tile_lane<T>(lane, s)], acc);
                 }
                 const int s = 32 * sb2 + l32, tok = c * CHUNK + s;
                 if (tok < L) {
@@ -91,7 +91,7 @@ __global__ __launch_bounds__(256) void key_prefill_kernel(PrefillArgs a) {
 #pragma unroll
                         for (int r = 0; r < 4; ++r) {
                             const int jj = 4 * g + r;
-                            const Frag kf = sK[((size_t)sb2 * DS + cb * SPB + jj / FE) * 64 + lane];
+                            const Frag kf = sK[((size_t)sb2 * DS + cb * SPB + jj / FE) * 64 + tile_lane<T>(lane, jj / FE)];
                             o4[r] = (TIO)((float)kf[jj % FE] - acc[jj]);
                         }
                         *reinterpret_cast<OVec4*>(dst + 8 * g) = o4;
@@ -107,11 +107,11 @@ __global__ __launch_bounds__(256) void key_prefill_kernel(PrefillArgs a) {
             f32x16 acc = zero16();
             if (!lastsb) {
 #pragma unroll
-                for (int s = 0; s < DS; ++s) acc = Tr<T>::mma(sDP[((size_t)bb * DS + s) * 64 + lane], Es[(ab * DS + s) * 64 + lane], acc);
+                for (int s = 0; s < DS; ++s) acc = Tr<T>::mma(sDP[((size_t)bb * DS + s) * 64 + tile_lane<T>(lane, s)], Es[(ab * DS + s) * 64 + lane], acc);
             }
             Frag dfr[SPB];
 #pragma unroll
-            for (int s2 = 0; s2 < SPB; ++s2) dfr[s2] = sDP[((size_t)bb * DS + ab * SPB + s2) * 64 + lane];
+            for (int s2 = 0; s2 < SPB; ++s2) dfr[s2] = sDP[((size_t)bb * DS + ab * SPB + s2) * 64 + tile_lane<T>(lane, s2)];
             const f32x16 dpT = transpose32<T>(dfr, idf);
 #pragma unroll
             for (int jj = 0; jj < 16; ++jj) {

@@ -221,23 +221,26 @@ __device__ __forceinline__ void mm(f32x16& acc, const T* A, int lda, int ar0, co
     }
 }
 
-// Place of lane `lane`'s fragment inside slab s of the tiles that are also read transposed (see below): half 1 moves by
-// four rows and odd slabs by eight.  A linear read of a slab touches the same 1 KB either way.
-__device__ __forceinline__ int tile_lane(int lane, int s) { return lane ^ ((lane >> 5) << 2) ^ ((s & 1) << 3); }
+// Place of lane `lane`'s fragment inside slab s of the tiles that, with 16-bit operands, are also read transposed (see
+// below) -- keys and -dP of both levels, query states, dO: half 1 moves by four rows and odd slabs by eight.  A linear
+// read of a slab touches the same 1 KB either way.  fp32 tiles keep plain lane order.
+template <typename T> __device__ __forceinline__ int tile_lane(int lane, int s) {
+    return sizeof(T) == 2 ? lane ^ ((lane >> 5) << 2) ^ ((s & 1) << 3) : lane;
+}
 
 // Fragment of the TRANSPOSE of a fragment-order tile (rows q in 32-row halves of DS slabs, contraction c).  Element e
 // of a fragment belongs to contraction index 16 s + acc_row(e, h) of its slab s, in both tiles, so the lane needs
 // tile[q = 16 qs + acc_row(e, h)][c = 32 b + l32], e = 0..7: two transposing reads, of rows 16 qs + 4 h + 0..3 and the
 // same + 8 (in each block of 16 lanes, lane i points at 4 consecutive c of row .. + i/4 and receives column i of the
 // four rows).  The 32 lanes of a half-wave point at four rows of two slabs and both halves of each: with fragments
-// in plain lane order (SWZ = false) those lie 512 bytes apart, on the same banks -- 8.4 LDS cycles per read; the
-// order of tile_lane (SWZ = true) spreads them over all banks -- 2.4 cycles, the rate of a linear read.
-template <typename E, int DS, bool SWZ>
+// in plain lane order those would lie 512 bytes apart, on the same banks -- 8.4 LDS cycles per read; the order of
+// tile_lane spreads them over all banks -- 2.4 cycles, the rate of a linear read.
+template <typename E, int DS>
 __device__ __forceinline__ typename Tr<E>::Frag ld_tile_frag_tr(const E* tile, int qs, int b, int l32, int h) {
     static_assert(sizeof(E) == 2, "16-bit transposing reads");
     typedef short v4s __attribute__((ext_vector_type(4)));
     const int i = l32 & 15, sl = l32 >> 4, hh = i & 1;
-    const int row = (4 * h + (i >> 2)) ^ (SWZ ? 4 * hh : 0), odd = SWZ ? 8 * sl : 0;      // + 16 (qs & 1)
+    const int row = (4 * h + (i >> 2)) ^ (4 * hh), odd = 8 * sl;      // + 16 (qs & 1)
     const E* p = tile + (size_t)((((qs >> 1) * DS + 2 * b) * 64 + 16 * (qs & 1)) * 8) + (sl * 64 + hh * 32 + row) * 8 + 4 * ((i >> 1) & 1);
     union { v4s v[2]; typename Tr<E>::Frag f; } u;
     u.v[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)(p + odd * 8));

@@ -111,16 +111,16 @@ __global__ __launch_bounds__(256) void prep2_fwd_kernel(FwdParams p) {
                 const int blk = wv + 4 * o, cb = blk >> 1, sb2 = blk & 1;
                 f32x16 acc = zero16();
 #pragma unroll
-                for (int s = 0; s < DS; ++s) acc = Tr<T>::mma(Es[(cb * DS + s) * 64 + lane], k1[((size_t)sb2 * DS + s) * 64 + lane], acc);
+                for (int s = 0; s < DS; ++s) acc = Tr<T>::mma(Es[(cb * DS + s) * 64 + lane], k1[((size_t)sb2 * DS + s) * 64 + tile_lane<T>(lane, s)], acc);
                 Frag fr[SPB];
 #pragma unroll
                 for (int s2 = 0; s2 < SPB; ++s2) {
-                    const Frag kf = k1[((size_t)sb2 * DS + cb * SPB + s2) * 64 + lane];
+                    const Frag kf = k1[((size_t)sb2 * DS + cb * SPB + s2) * 64 + tile_lane<T>(lane, s2)];
 #pragma unroll
                     for (int e = 0; e < FE; ++e) fr[s2][e] = (T)((float)kf[e] - acc[s2 * FE + e]);
                 }
 #pragma unroll
-                for (int s2 = 0; s2 < SPB; ++s2) __builtin_nontemporal_store(fr[s2], &k2[((size_t)sb2 * DS + cb * SPB + s2) * 64 + lane]);
+                for (int s2 = 0; s2 < SPB; ++s2) __builtin_nontemporal_store(fr[s2], &k2[((size_t)sb2 * DS + cb * SPB + s2) * 64 + tile_lane<T>(lane, s2)]);
                 if (k2T) {     // backward only: the arrangement (rows cc, contraction s)
                     const f32x16 tr = transpose32<T>(fr, idf);      // rows s, lane cc
                     Frag ft[SPB];
@@ -137,13 +137,13 @@ __global__ __launch_bounds__(256) void prep2_fwd_kernel(FwdParams p) {
             f32x16 acc = zero16();
             if (c != clast) {
 #pragma unroll
-                for (int s = 0; s < DS; ++s) acc = Tr<T>::mma(dpn[((size_t)bb * DS + s) * 64 + lane], Es[(ab * DS + s) * 64 + lane], acc);
+                for (int s = 0; s < DS; ++s) acc = Tr<T>::mma(dpn[((size_t)bb * DS + s) * 64 + tile_lane<T>(lane, s)], Es[(ab * DS + s) * 64 + lane], acc);
             }
             // -dP[a][b] in this block's register layout (rows b, lane a): the tile piece (rows b,
             // contraction a) transposed through the matrix unit
             Frag dfr[SPB];
 #pragma unroll
-            for (int s2 = 0; s2 < SPB; ++s2) dfr[s2] = dpn[((size_t)bb * DS + ab * SPB + s2) * 64 + lane];
+            for (int s2 = 0; s2 < SPB; ++s2) dfr[s2] = dpn[((size_t)bb * DS + ab * SPB + s2) * 64 + tile_lane<T>(lane, s2)];
             const f32x16 dpT = transpose32<T>(dfr, idf);
 #pragma unroll
             for (int jj = 0; jj < 16; ++jj) {
@@ -188,7 +188,7 @@ __global__ __launch_bounds__(256) void prep2_fwd_kernel(FwdParams p) {
         Frag fr[SPB];
         pack_block<T>(tr, fr);
 #pragma unroll
-        for (int s = 0; s < SPB; ++s) __builtin_nontemporal_store(fr[s], &dst[((size_t)bb * DS + ab * SPB + s) * 64 + lane]);
+        for (int s = 0; s < SPB; ++s) __builtin_nontemporal_store(fr[s], &dst[((size_t)bb * DS + ab * SPB + s) * 64 + tile_lane<T>(lane, s)]);
     }
 }
 

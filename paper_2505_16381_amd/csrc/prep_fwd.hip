@@ -400,7 +400,7 @@ __global__ __launch_bounds__(256, (PrepCfg<TIO, D>::WGS_PER_CU)) void prep_fwd_k
             Frag fr[SPB];
             pack_block<T>(acc, fr);
 #pragma unroll
-            for (int s = 0; s < SPB; ++s) __builtin_nontemporal_store(fr[s], &dst[((size_t)bb * (D / KW) + ab * SPB + s) * 64 + lane]);
+            for (int s = 0; s < SPB; ++s) __builtin_nontemporal_store(fr[s], &dst[((size_t)bb * (D / KW) + ab * SPB + s) * 64 + tile_lane<T>(lane, s)]);
         }
     }
     // (c) Kb tile (rows = key s, contraction = c): acc rows c, cols s;  Kb^T = K^T - W^T Y.
@@ -425,7 +425,7 @@ __global__ __launch_bounds__(256, (PrepCfg<TIO, D>::WGS_PER_CU)) void prep_fwd_k
             Frag fr[SPB];
             pack_block<T>(acc, fr);
 #pragma unroll
-            for (int s2 = 0; s2 < SPB; ++s2) __builtin_nontemporal_store(fr[s2], &kdst[((size_t)sb * (D / KW) + cb * SPB + s2) * 64 + lane]);
+            for (int s2 = 0; s2 < SPB; ++s2) __builtin_nontemporal_store(fr[s2], &kdst[((size_t)sb * (D / KW) + cb * SPB + s2) * 64 + tile_lane<T>(lane, s2)]);
             if (BWD && p.kbm) {       // backward only: the same keys row-major [token][c]
                 typedef typename Tr<T>::Vec4 TVec4;
                 T* kb = reinterpret_cast<T*>(p.kbm) + (bhc * CHUNK + s) * (size_t)D + 32 * cb + 4 * h;

@@ -94,7 +94,7 @@ __global__ __launch_bounds__(256) void bwd_states_kernel(FwdParams p) {
             const size_t slot = ((size_t)bh * nslots + block_slot(cq, c, NC)) * (size_t)CHUNK * D;
             Frag* xd = reinterpret_cast<Frag*>(reinterpret_cast<T*>(p.xs) + slot);
 #pragma unroll
-            for (int s = 0; s < DS; ++s) __builtin_nontemporal_store(Xb[s], &xd[((size_t)qb * DS + s) * 64 + tile_lane(lane, s)]);
+            for (int s = 0; s < DS; ++s) __builtin_nontemporal_store(Xb[s], &xd[((size_t)qb * DS + s) * 64 + tile_lane<T>(lane, s)]);
             Frag* xt = reinterpret_cast<Frag*>(reinterpret_cast<T*>(p.xsT) + slot);
             if (sizeof(T) == 4)
 #pragma unroll
@@ -114,7 +114,7 @@ __global__ __launch_bounds__(256) void bwd_states_kernel(FwdParams p) {
                 for (int s0 = 0; s0 < DS; s0 += 4) {
                     Frag pa[4];
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) pa[u] = tp[(b * DS + s0 + u) * 64 + lane];
+                    for (int u = 0; u < 4; ++u) pa[u] = tp[(b * DS + s0 + u) * 64 + tile_lane<T>(lane, u)];
 #pragma unroll
                     for (int u = 0; u < 4; ++u) Xm[b] = Tr<T>::mma(pa[u], Xb[s0 + u], Xm[b]);
                 }
