@@ -83,8 +83,8 @@ static BwdWorkspace bwd_workspace(int B, int H, int L, int d, size_t es) {
     take(w.drow, BH * Lp * 4);
     for (size_t* f : {&w.fm, &w.gktm, &w.nm, &w.aim, &w.ytm}) take(*f, BH * NC * 4096 * es);
     take(w.utm, BH * NC * d * CHUNK * es);
-    take(w.gm, BH * NC * 4096 * 4);
-    take(w.sdm, BH * NC * 4096 * 4);
+    take(w.gm, staged * BH * NC * 4096 * 4);
+    take(w.sdm, staged * BH * NC * 4096 * 4);
     take(w.delta, BH * Lp * 4);
     take(w.lse2p, BH * Lp * 4);
     for (size_t* f : {&w.dqb, &w.dkb, &w.dvp}) take(*f, BH * Lp * d * 4);
@@ -459,7 +459,7 @@ static path_status_t bwd_run(BwdMode mode, int stages, const UserLayout& ul, con
     fp.B = B; fp.H = H; fp.L = L; fp.NC = NC; fp.scale = scale; fp.ul = ul;
     fp.ktT = base + ws.ktT; fp.vk = base + ws.vk; fp.dpt = base + ws.dpt; fp.xs = base + ws.xs; fp.xsT = base + ws.xsT;
     fp.fm = base + ws.fm; fp.gktm = base + ws.gktm; fp.nm = base + ws.nm; fp.aim = base + ws.aim;
-    fp.ytm = base + ws.ytm; fp.utm = base + ws.utm; fp.gm = F(ws.gm); fp.sdm = F(ws.sdm);
+    fp.ytm = base + ws.ytm; fp.utm = base + ws.utm; fp.gm = bf ? nullptr : F(ws.gm); fp.sdm = bf ? nullptr : F(ws.sdm);
     float* cum = log_f ? F(ws.f.cum) : nullptr;
     if (mode != BWD_RESUME && mode != BWD_FWD_SWEEP) {
         if (log_f && !hip_ok(launch_gate_sums(log_f, ul, cum, B, H, L, dt, st), "gate sums (backward)")) return PATH_ERR_HIP;
@@ -567,7 +567,7 @@ static path_status_t bwd_run(BwdMode mode, int stages, const UserLayout& ul, con
     // Chains of products that add into the same result are consecutive.
     if (!ok) return PATH_ERR_HIP;
     if (bf) {      // 2-byte operand types: the hand-fused kernel
-        ChunkFusedArgs ca{ul, q, k, v, w, beta, d_o, lse, bp.delta, fp.sdm, fp.gm, fp.fm, fp.gktm, fp.nm, fp.aim, fp.ytm,
+        ChunkFusedArgs ca{ul, q, k, v, w, beta, d_o, lse, bp.delta, fp.sd, fp.fm, fp.gktm, fp.nm, fp.aim, fp.ytm,
                           base + ws.utm, bp.dqb, bp.dkb, bp.dvp, F(ws.ddp), dq, dk, dv, dw, dbeta, bp.cum, bp.dcol, bp.drow,
                           L, NC, BH, scale};
         ok = hip_ok(launch_chunk_fused(ca, BH, d, st), "chunk-transform adjoint");

@@ -122,7 +122,7 @@ struct ChunkFusedArgs {
     UserLayout ul;                               // layout of q .. d_o, lse and of the outputs
     const void *q, *k, *v, *w, *beta, *d_o;      // I/O type, the caller's layout
     const float *lse, *delta;                    // the caller's layout; [BH][Lp]
-    const float *sdm, *gm;                       // [BH][NC][64][64]: raw diagonal logits, G
+    const float* sd;                             // raw diagonal logits as the sweep reads them (accumulator order)
     const void *fm, *gktm, *nm, *aim, *ytm;      // operand type, [BH][NC][64][64]
     const void* utm;                             // operand type, [BH][NC][d][64]
     const float *dqb, *dkb, *dvp;                // [BH][Lp][d]

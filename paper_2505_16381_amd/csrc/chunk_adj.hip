@@ -40,14 +40,17 @@ template <typename TIO, int D> struct CaCfg {
     static constexpr int BIG = (64 * LDD > D * LDC ? 64 * LDD : D * LDC) * 2;   // bytes of a 64 x D or D x 64 tile
     static constexpr int SMALL = 64 * LDC * 2;
     static constexpr int LDM = 65;             // pitch of the fp32 copy of M
-    // byte offsets: W | X0 X3 (adjacent: ddP spans both) | X1 | X2 | Y0..Y4 | misc
-    static constexpr int XW = 0, X0 = BIG, X3 = 2 * BIG, X1 = 3 * BIG, X2 = 4 * BIG;
-    static constexpr int Y0 = 5 * BIG, Y1 = Y0 + SMALL, Y2 = Y1 + SMALL, Y3 = Y2 + SMALL, Y4 = Y3 + SMALL;
-    static constexpr int MISC = Y4 + SMALL;
+    // byte offsets.  d = 128: W | X0 X3 (adjacent: ddP spans both, later the fp32 M) | X1 | X2 | Y0 Y1 Y2 | N | misc.
+    // d = 64, where all tiles have one size: W | X0 Y0 (adjacent: the fp32 M) | X1 | X2 | X3 = N | Y1 | Y2 | misc: 74 KB, two
+    // workgroups per CU (with ten tiles, 92 KB and one workgroup it took 0.63 ms at B=8, H=16, L=4096).
+    static constexpr int XW = 0, X0 = BIG, X3 = D == 64 ? 5 * BIG : 2 * BIG, X1 = 3 * BIG, X2 = 4 * BIG;
+    static constexpr int Y0 = D == 64 ? 2 * BIG : 5 * BIG, Y1 = D == 64 ? 6 * BIG : Y0 + SMALL, Y2 = Y1 + SMALL, YN = D == 64 ? X3 : Y2 + SMALL;
+    static constexpr int MISC = D == 64 ? Y2 + SMALL : YN + SMALL;
     static constexpr int TOTAL = MISC + 2048;
-    static_assert(D * LDD * 2 <= 2 * BIG, "ddP tile must fit X0+X3");
-    static_assert(64 * LDM * 4 <= 2 * BIG, "fp32 M must fit X0+X3");
-    static_assert(TOTAL <= 160 * 1024, "LDS budget");
+    static constexpr int WGS_PER_CU = D == 64 ? 2 : 1;
+    static_assert(D == 64 ? BIG == SMALL : D * LDD * 2 <= 2 * BIG, "ddP tile must fit X0 (d = 64) or X0 and X3");
+    static_assert(64 * LDM * 4 <= 2 * BIG, "fp32 M must fit X0 and its neighbour");
+    static_assert(WGS_PER_CU * TOTAL <= 160 * 1024, "LDS budget");
 };
 
 // ROWS x COLS elements of type S from global memory (row-major, `stride` elements between rows), 8 per
@@ -88,7 +91,7 @@ __device__ __forceinline__ void st_block(T* dst, int ld, int r0, int c0, const f
 }
 
 template <typename TIO, int D, bool FOX, bool STRIDED>
-__global__ __launch_bounds__(CA_NT) void chunk_fused_kernel(ChunkFusedArgs a) {
+__global__ __launch_bounds__(CA_NT, 2 * (CaCfg<TIO, D>::WGS_PER_CU)) void chunk_fused_kernel(ChunkFusedArgs a) {
     using C = CaCfg<TIO, D>;
     typedef typename C::T T;
     constexpr int LDD = C::LDD, LDC = C::LDC, LDM = C::LDM;
@@ -101,11 +104,10 @@ __global__ __launch_bounds__(CA_NT) void chunk_fused_kernel(ChunkFusedArgs a) {
     T* Y0 = reinterpret_cast<T*>(smem + C::Y0);
     T* Y1 = reinterpret_cast<T*>(smem + C::Y1);
     T* Y2 = reinterpret_cast<T*>(smem + C::Y2);
-    T* Y3 = reinterpret_cast<T*>(smem + C::Y3);
-    T* Y4 = reinterpret_cast<T*>(smem + C::Y4);
+    T* YN = reinterpret_cast<T*>(smem + C::YN);
     float* Mf = reinterpret_cast<float*>(smem + C::X0);      // fp32 M, after ddP is dead
     float* misc = reinterpret_cast<float*>(smem + C::MISC);
-    float *lse_s = misc, *delta_s = misc + 64, *beta_s = misc + 128, *rdiag = misc + 192, *colsum = misc + 256, *cum_s = misc + 384;
+    float *beta_s = misc, *rdiag = misc + 64, *rowsum = misc + 128, *colsum = misc + 256;
 
     int chunk, bh;
     chunk_and_head(a.ul, a.NC, a.BH, chunk, bh);
@@ -128,9 +130,10 @@ __global__ __launch_bounds__(CA_NT) void chunk_fused_kernel(ChunkFusedArgs a) {
     const T* utmg = reinterpret_cast<const T*>(a.utm) + ((size_t)bh * NC + chunk) * D * CHUNK;
     const float* ddpg = a.ddp + ((size_t)bh * NC + chunk) * D * D;
 
-    // wave -> 32x32 block of a 64 x D result (all 8 waves for D = 128) and of a 64 x 64 result (waves 0..3)
+    // wave -> 32x32 block of a 64 x D result (all 8 waves for D = 128; waves 0..3 for D = 64) and of a 64 x 64 result
+    // (waves 0..3; waves 4..7 for D = 64)
     constexpr int NBD = D / 32;
-    const bool actD = wv < 2 * NBD, act6 = wv < 4;
+    const bool actD = wv < 2 * NBD, act6 = D == 64 ? wv >= 4 : wv < 4;
     const int mbD = wv / NBD, cbD = wv % NBD, mb6 = (wv >> 1) & 1, cb6 = wv & 1;
 
     auto cin = [&](const float* g, f32x16& acc) {       // accumulator block (mbD, cbD) from a padded fp32 [64][D] tensor
@@ -152,16 +155,19 @@ __global__ __launch_bounds__(CA_NT) void chunk_fused_kernel(ChunkFusedArgs a) {
     tdO.load(dog, TS, ntok, tid);
     tV.load(vg, TS, ntok, tid);
     if (tid < CHUNK) {
-        const bool ok = tid < ntok;
-        lse_s[tid] = ok ? a.lse[user_scl(a.ul, bh, chunk * CHUNK + tid)] : 0.f;
-        delta_s[tid] = a.delta[tpad + tid];
-        beta_s[tid] = ok ? (float)reinterpret_cast<const TIO*>(a.beta)[user_scl(a.ul, bh, chunk * CHUNK + tid)] : 0.f;
-        if (FOX) { cum_s[tid] = a.cum[tpad + tid]; colsum[tid] = 0.f; colsum[CHUNK + tid] = 0.f; }
+        beta_s[tid] = tid < ntok ? (float)reinterpret_cast<const TIO*>(a.beta)[user_scl(a.ul, bh, chunk * CHUNK + tid)] : 0.f;
+        if (FOX) { colsum[tid] = 0.f; colsum[CHUNK + tid] = 0.f; }
     }
-    float sd[16];                                   // raw diagonal logits of this wave's block
+    // the diagonal block is taken transposed (rows s = keys in registers, lane = query t = 32 cb6 + l32), as the chunk
+    // transform left its raw logits for the sweep
+    f32x4 sd[4];
+    const int tq = 32 * cb6 + l32;
+    float lse_t = 0.f, delta_t = 0.f;
     if (act6) {
 #pragma unroll
-        for (int jj = 0; jj < 16; ++jj) sd[jj] = a.sdm[cbase + (size_t)(32 * mb6 + acc_row(jj, h)) * 64 + 32 * cb6 + l32];
+        for (int g = 0; g < 4; ++g) sd[g] = *reinterpret_cast<const f32x4*>(a.sd + (((size_t)bh * NC + chunk) * 4 + cb6 * 2 + mb6) * 1024 + (g * 64 + lane) * 4);
+        if (tq < ntok) lse_t = a.lse[user_scl(a.ul, bh, chunk * CHUNK + tq)];
+        delta_t = a.delta[tpad + tq];
     }
     tW.template store<T, false>(XW, LDD, tid);
     tdO.template store<T, false>(X0, LDD, tid);
@@ -181,25 +187,34 @@ __global__ __launch_bounds__(CA_NT) void chunk_fused_kernel(ChunkFusedArgs a) {
     // ---- dPd = dO V^T; P, dSd (diagonal block) -> Y0 = P, Y1 = dSd, both [query][key] ----------
     if (act6) {
         f32x16 acc = zero16();
-        mm<T, D, false, false>(acc, X0, LDD, 32 * mb6, X1, LDD, 32 * cb6, l32, h);
-        const int s = 32 * cb6 + l32;
-        float csum = 0.f;
+        mm<T, D, false, false>(acc, X1, LDD, 32 * mb6, X0, LDD, 32 * cb6, l32, h);
+        const float cum_t = FOX ? a.cum[tpad + tq] : 0.f;
+        float rsum = 0.f;
+        typedef typename Tr<T>::Vec4 TVec4;
 #pragma unroll
-        for (int jj = 0; jj < 16; ++jj) {
-            const int t = 32 * mb6 + acc_row(jj, h);
-            float P = 0.f, ds = 0.f;
-            if (s <= t && t < ntok) {
-                float z = a.scale * sd[jj] - lse_s[t];
-                if (FOX) z += (cum_s[t] - cum_s[s]) * 0.69314718055994530942f;     // gate sums are kept in base-2 units
-                P = __expf(z);
-                const float dz = P * (acc[jj] - delta_s[t]);
-                ds = a.scale * dz;
-                if (FOX) { csum += dz; atomicAdd(colsum + CHUNK + t, dz); }
+        for (int g = 0; g < 4; ++g) {
+            const int s0 = 32 * mb6 + 8 * g + 4 * h;
+            f32x4 cum_s4 = {0.f, 0.f, 0.f, 0.f};
+            if (FOX) cum_s4 = *reinterpret_cast<const f32x4*>(a.cum + tpad + s0);
+            TVec4 p4, d4;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                float P = 0.f, ds = 0.f;
+                if (s0 + r <= tq && tq < ntok) {
+                    float z = a.scale * sd[g][r] - lse_t;
+                    if (FOX) z += (cum_t - cum_s4[r]) * 0.69314718055994530942f;     // gate sums are kept in base-2 units
+                    P = __expf(z);
+                    const float dz = P * (acc[4 * g + r] - delta_t);
+                    ds = a.scale * dz;
+                    if (FOX) { rsum += dz; atomicAdd(colsum + s0 + r, dz); }
+                }
+                p4[r] = (T)P;
+                d4[r] = (T)ds;
             }
-            Y0[t * LDC + s] = (T)P;
-            Y1[t * LDC + s] = (T)ds;
+            *reinterpret_cast<TVec4*>(Y0 + tq * LDC + s0) = p4;
+            *reinterpret_cast<TVec4*>(Y1 + tq * LDC + s0) = d4;
         }
-        if (FOX) atomicAdd(colsum + s, csum);
+        if (FOX) atomicAdd(colsum + CHUNK + tq, rsum);
     }
     GTile<float, 64, D> tdKb;
     tdKb.load(a.dkb + pbase, D, 64, tid);
@@ -250,39 +265,39 @@ __global__ __launch_bounds__(CA_NT) void chunk_fused_kernel(ChunkFusedArgs a) {
     }
     __syncthreads();                 // Q (X0) and Y (Y0) are free
     tK.template store<T, false>(X0, LDD, tid);
-    tF.template store<T, false>(Y3, LDC, tid);
+    tF.template store<T, false>(Y0, LDC, tid);
     GTile<T, 64, 64> tN, tG;
     tN.load(reinterpret_cast<const T*>(a.nm) + cbase, 64, 64, tid);
     tG.load(reinterpret_cast<const T*>(a.gktm) + cbase, 64, 64, tid);
     __syncthreads();
 
-    // ---- dQ = dQb + dSd K + dF W;  dY = -(F^T dSd + W dKb^T) -> Y4 ---------------------------------
+    // ---- dQ = dQb + dSd K + dF W;  dY = -(F^T dSd + W dKb^T) ----------------------------------------
     if (actD) {
         mm<T, 64, false, true>(accQ, Y1, LDC, 32 * mbD, X0, LDD, 32 * cbD, l32, h);
         mm<T, 64, false, true>(accQ, Y2, LDC, 32 * mbD, XW, LDD, 32 * cbD, l32, h);
         out_user(a.dq, accQ);
     }
+    f32x16 accY = zero16();
     if (act6) {
-        f32x16 acc = zero16();
-        mm<T, 64, true, true>(acc, Y3, LDC, 32 * mb6, Y1, LDC, 32 * cb6, l32, h);
-        mm<T, D, false, false>(acc, XW, LDD, 32 * mb6, X3, LDD, 32 * cb6, l32, h);
+        mm<T, 64, true, true>(accY, Y0, LDC, 32 * mb6, Y1, LDC, 32 * cb6, l32, h);
+        mm<T, D, false, false>(accY, XW, LDD, 32 * mb6, X3, LDD, 32 * cb6, l32, h);
 #pragma unroll
-        for (int jj = 0; jj < 16; ++jj) acc[jj] = -acc[jj];
-        st_block<T>(Y4, LDC, 32 * mb6, 32 * cb6, acc, l32, h);
+        for (int jj = 0; jj < 16; ++jj) accY[jj] = -accY[jj];
     }
     GTile<T, 64, 64> tA;
     tA.load(reinterpret_cast<const T*>(a.aim) + cbase, 64, 64, tid);
     tK.load(kg, TS, ntok, tid);       // K once more, for dGk K at the end
     __syncthreads();                 // K (X0), dKb (X3), dSd (Y1), dF (Y2) are free
-    tDD.template store<T, false>(X0, LDD, tid);        // ddP [a][b], spans X0 and X3
-    tN.template store<T, false>(Y0, LDC, tid);
+    if (act6) st_block<T>(Y2, LDC, 32 * mb6, 32 * cb6, accY, l32, h);     // dY
+    tDD.template store<T, false>(X0, LDD, tid);        // ddP [a][b] (d = 128: spans X0 and X3)
+    tN.template store<T, false>(YN, LDC, tid);
     tG.template store<T, false>(Y1, LDC, tid);
     __syncthreads();
 
     // ---- dU = -F^T dQb + W ddP;  dW += U ddP^T ---------------------------------------------------
     f32x16 accU = zero16();
     if (actD) {
-        mm<T, 64, true, true>(accU, Y3, LDC, 32 * mbD, X1, LDD, 32 * cbD, l32, h);
+        mm<T, 64, true, true>(accU, Y0, LDC, 32 * mbD, X1, LDD, 32 * cbD, l32, h);
         mm<T, D, false, true>(accU, XW, LDD, 32 * mbD, X0, LDD, 32 * cbD, l32, h);
         mm<T, D, true, false>(accW, X2, LDC, 32 * mbD, X0, LDD, 32 * cbD, l32, h);
     }
@@ -291,40 +306,34 @@ __global__ __launch_bounds__(CA_NT) void chunk_fused_kernel(ChunkFusedArgs a) {
     tK.template store<T, false>(X2, LDD, tid);
     __syncthreads();
 
-    // ---- dW += N^T dU;  dN = dY Gk^T + dU W^T -> Y3 ------------------------------------------------
-    if (actD) mm<T, 64, true, true>(accW, Y0, LDC, 32 * mbD, X1, LDD, 32 * cbD, l32, h);
+    // ---- dW += N^T dU;  dN = dY Gk^T + dU W^T -> Y0 ------------------------------------------------
+    if (actD) mm<T, 64, true, true>(accW, YN, LDC, 32 * mbD, X1, LDD, 32 * cbD, l32, h);
     if (act6) {
         f32x16 acc = zero16();
-        mm<T, 64, false, true>(acc, Y4, LDC, 32 * mb6, Y1, LDC, 32 * cb6, l32, h);
+        mm<T, 64, false, true>(acc, Y2, LDC, 32 * mb6, Y1, LDC, 32 * cb6, l32, h);
         mm<T, D, false, false>(acc, X1, LDD, 32 * mb6, XW, LDD, 32 * cb6, l32, h);
-        st_block<T>(Y3, LDC, 32 * mb6, 32 * cb6, acc, l32, h);
-    }
-    float gv[8];                     // G of the rows this wave reduces for dbeta (row wv + 8 i, column lane)
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const int r = wv + 8 * i;
-        gv[i] = (lane < r) ? a.gm[cbase + (size_t)r * 64 + lane] : 0.f;
+        st_block<T>(Y0, LDC, 32 * mb6, 32 * cb6, acc, l32, h);
     }
     __syncthreads();                 // dN visible; Gk (Y1) is free
 
     // ---- dGk = sl(N^T dY) -> Y1 ----------------------------------------------------------------------
     if (act6) {
         f32x16 acc = zero16();
-        mm<T, 64, true, true>(acc, Y0, LDC, 32 * mb6, Y4, LDC, 32 * cb6, l32, h);
+        mm<T, 64, true, true>(acc, YN, LDC, 32 * mb6, Y2, LDC, 32 * cb6, l32, h);
 #pragma unroll
         for (int jj = 0; jj < 16; ++jj)
             if (32 * cb6 + l32 >= 32 * mb6 + acc_row(jj, h)) acc[jj] = 0.f;
         st_block<T>(Y1, LDC, 32 * mb6, 32 * cb6, acc, l32, h);
     }
-    __syncthreads();                 // dY (Y4) is free
-    tA.template store<T, false>(Y4, LDC, tid);
+    __syncthreads();                 // dY (Y2) is free
+    tA.template store<T, false>(Y2, LDC, tid);
     __syncthreads();
 
-    // ---- R = A^-T dN -> Y2 (operand) and its diagonal (fp32) ----------------------------------------
+    // ---- R = A^-T dN -> X1 (operand) and its diagonal (fp32) ----------------------------------------
     if (act6) {
         f32x16 acc = zero16();
-        mm<T, 64, true, true>(acc, Y4, LDC, 32 * mb6, Y3, LDC, 32 * cb6, l32, h);
-        st_block<T>(Y2, LDC, 32 * mb6, 32 * cb6, acc, l32, h);
+        mm<T, 64, true, true>(acc, Y2, LDC, 32 * mb6, Y0, LDC, 32 * cb6, l32, h);
+        st_block<T>(X1, LDC, 32 * mb6, 32 * cb6, acc, l32, h);
         if (mb6 == cb6) {
 #pragma unroll
             for (int jj = 0; jj < 16; ++jj)
@@ -333,39 +342,47 @@ __global__ __launch_bounds__(CA_NT) void chunk_fused_kernel(ChunkFusedArgs a) {
     }
     __syncthreads();
 
-    // ---- M = sl(-R N^T) -> fp32 in LDS ---------------------------------------------------------------
+    // ---- M = sl(-R N^T) -> fp32 in LDS; row sums of M o G for dbeta ----------------------------------
     if (act6) {
-        f32x16 acc = zero16();
-        mm<T, 64, false, false>(acc, Y2, LDC, 32 * mb6, Y0, LDC, 32 * cb6, l32, h);
+        f32x16 acc = zero16(), gacc = zero16();
+        mm<T, 64, false, false>(acc, X1, LDC, 32 * mb6, YN, LDC, 32 * cb6, l32, h);
+        mm<T, D, false, false>(gacc, XW, LDD, 32 * mb6, XW, LDD, 32 * cb6, l32, h);       // G = W W^T, as the transform forms it
 #pragma unroll
         for (int jj = 0; jj < 16; ++jj) {
             const int m = 32 * mb6 + acc_row(jj, h), n = 32 * cb6 + l32;
-            Mf[m * LDM + n] = (n >= m) ? 0.f : -acc[jj];
+            const float mv = (n >= m) ? 0.f : -acc[jj];
+            Mf[m * LDM + n] = mv;
+            gacc[jj] *= mv;
         }
+        // sums over the 32 columns: in four rounds a lane passes on half of its rows, one round adds the last pair up
+        float v8[8], v4[4], v2[2];
+        const bool b4 = l32 & 16, b3 = l32 & 8, b2 = l32 & 4, b1 = l32 & 2;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v8[i] = (b4 ? gacc[i + 8] : gacc[i]) + __shfl_xor(b4 ? gacc[i] : gacc[i + 8], 16);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v4[i] = (b3 ? v8[i + 4] : v8[i]) + __shfl_xor(b3 ? v8[i] : v8[i + 4], 8);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) v2[i] = (b2 ? v4[i + 2] : v4[i]) + __shfl_xor(b2 ? v4[i] : v4[i + 2], 4);
+        float v = (b1 ? v2[1] : v2[0]) + __shfl_xor(b1 ? v2[0] : v2[1], 2);
+        v += __shfl_xor(v, 1);
+        if (!(l32 & 1)) rowsum[cb6 * CHUNK + 32 * mb6 + acc_row(8 * b4 + 4 * b3 + 2 * b2 + b1, h)] = v;
     }
     __syncthreads();
 
-    // ---- dGs = diag(beta) M + (diag(beta) M)^T -> Y3;  dbeta ------------------------------------------
+    // ---- dGs = diag(beta) M + (diag(beta) M)^T -> Y2;  dbeta ------------------------------------------
     for (int idx = tid; idx < 4096; idx += CA_NT) {
         const int r = idx >> 6, c = idx & 63;
-        Y3[r * LDC + c] = (T)(beta_s[r] * Mf[r * LDM + c] + beta_s[c] * Mf[c * LDM + r]);
+        Y2[r * LDC + c] = (T)(beta_s[r] * Mf[r * LDM + c] + beta_s[c] * Mf[c * LDM + r]);
     }
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const int r = wv + 8 * i;
-        float s = Mf[r * LDM + lane] * gv[i];           // M is zero on and above the diagonal, gv outside lane < r
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off);
-        if (lane == 0 && r < ntok)
-            reinterpret_cast<TIO*>(a.dbeta)[user_scl(a.ul, bh, chunk * CHUNK + r)] = (TIO)(s + rdiag[r]);
-    }
+    if (tid < ntok)
+        reinterpret_cast<TIO*>(a.dbeta)[user_scl(a.ul, bh, chunk * CHUNK + tid)] = (TIO)(rowsum[tid] + rowsum[CHUNK + tid] + rdiag[tid]);
     __syncthreads();
 
     // ---- dK += dGk^T W;  dW += dGs W + dGk K ------------------------------------------------------------
     if (actD) {
         mm<T, 64, true, true>(accK, Y1, LDC, 32 * mbD, XW, LDD, 32 * cbD, l32, h);
         out_user(a.dk, accK);
-        mm<T, 64, false, true>(accW, Y3, LDC, 32 * mbD, XW, LDD, 32 * cbD, l32, h);
+        mm<T, 64, false, true>(accW, Y2, LDC, 32 * mbD, XW, LDD, 32 * cbD, l32, h);
         mm<T, 64, false, true>(accW, Y1, LDC, 32 * mbD, X2, LDD, 32 * cbD, l32, h);
         out_user(a.dw, accW);
     }
