@@ -50,7 +50,7 @@ static FwdWorkspace fwd_workspace(int B, int H, int L, int d, size_t es) {
 struct BwdWorkspace {
     FwdWorkspace f;
     size_t ktT, vk, dpt, doq, doT, xs, xsT, gs, fm, gktm, nm, aim, ytm, utm, gm, sdm, delta, lse2p, dqb, dkb, dvp, ddp;
-    size_t kt2T, dpt2, kbm, rm, dk2, dchain, t1;       // second level and its adjoint
+    size_t kt2T, dpt2, kbm, rm, dr, dk2, dchain, t1;   // second level and its adjoint
     size_t dcol, drow;                                 // PaTH-FoX: column and row sums of the logit gradient
     size_t dpd, pd, dsd, df, dy, dn, dgk, rr, mm, dgs, du, dqf, dkf, dwf, dbf, total;
 };
@@ -71,10 +71,11 @@ static BwdWorkspace bwd_workspace(int B, int H, int L, int d, size_t es) {
     take(w.xsT, (es == 4 ? 1 : 0) * BH * nslots * CHUNK * d * es);
     take(w.kt2T, (es == 4 ? 1 : 0) * BH * Lp * d * es);
     take(w.dpt2, (es == 4 ? 1 : 0) * BH * NSB * d * d * es);
-    take(w.kbm, BH * Lp * d * es);
+    take(w.kbm, (es == 4 ? 1 : 0) * BH * Lp * d * es);
     take(w.rm, BH * NC * d * d * es);
+    take(w.dr, (es == 2 ? 1 : 0) * BH * NC * d * d * es);
     take(w.dk2, BH * Lp * d * 4);
-    take(w.dchain, BH * (NC + 1) * d * d * 4);
+    take(w.dchain, BH * (es == 4 ? NC + 1 : NSB) * d * d * 4);
     // (regions only the fp32-operand path uses -- the second level's chain and the chunk-transform adjoint as
     //  staged products -- have size zero for 2-byte operands, whose fused kernels keep these in LDS)
     const size_t staged = es == 4 ? 1 : 0;
@@ -534,7 +535,7 @@ static path_status_t bwd_run(BwdMode mode, int stages, const UserLayout& ul, con
     //     D_c     = D_{c-1} (I - dP_c)^T + dKb2_c^T Kb_c          dP_c = W_c^T U_c
     //     dKb_c  += dKb2_c R_c
     if (NC > SBC && bf) {         // fused kernel (2-byte operand types)
-        SbChainArgs sa{base + ws.rm, base + ws.kbm, base + ws.utm, w, F(ws.dk2), F(ws.dchain), F(ws.ddp), dkb, L, NC, ul};
+        SbChainArgs sa{fp.kt, base + ws.utm, w, F(ws.dk2), F(ws.dchain), base + ws.dr, L, NC, ul};
         ok = hip_ok(launch_bwd_sb_chain(sa, BH, d, st), "second-level adjoint");
     } else if (NC > SBC) {        // the same chain as a sequence of batched products (fp32 operands)
         const long long dd = (long long)d * d, dd_bh = (long long)NC * dd, ch_bh = (long long)(NC + 1) * dd;
@@ -568,7 +569,7 @@ static path_status_t bwd_run(BwdMode mode, int stages, const UserLayout& ul, con
     if (!ok) return PATH_ERR_HIP;
     if (bf) {      // 2-byte operand types: the hand-fused kernel
         ChunkFusedArgs ca{ul, q, k, v, w, beta, d_o, lse, bp.delta, fp.sd, fp.fm, fp.gktm, fp.nm, fp.aim, fp.ytm,
-                          base + ws.utm, bp.dqb, bp.dkb, bp.dvp, F(ws.ddp), dq, dk, dv, dw, dbeta, bp.cum, bp.dcol, bp.drow,
+                          base + ws.utm, bp.dqb, bp.dkb, bp.dvp, F(ws.ddp), NC > SBC ? base + ws.rm : nullptr, base + ws.dr, F(ws.dk2), dq, dk, dv, dw, dbeta, bp.cum, bp.dcol, bp.drow,
                           L, NC, BH, scale};
         ok = hip_ok(launch_chunk_fused(ca, BH, d, st), "chunk-transform adjoint");
         if (ok && log_f) {

@@ -18,7 +18,8 @@ struct BwdParams {
     float *dqb, *dkb, *dvp;   // [BH][Lp][d] fp32: dQb, dKb, dV (off-diagonal part)
     float *ddp;               // [BH][NC][d][d] fp32: ddP[a][b]
     float *dk2;               // [BH][Lp][d] fp32: dKb2 (gradient of the second-level keys)
-    float *dchain;            // [BH][NC+1][d][d] fp32: chain of the second level's adjoint, entry c+1 for chunk c
+    float *dchain;            // gradients of P_superblock, fp32 [d][d]: 16-bit operands [BH][NSB]; fp32 operands the whole chain
+                              // of the second level's adjoint, [BH][NC+1], entry c+1 for chunk c
     const float* cum;         // PaTH-FoX only (else NULL): [BH][Lp] cumulative log2 gates
     float* dcol;              // PaTH-FoX only: [BH][Lp] column sums of the logit gradient
     float* drow;              // PaTH-FoX only: [BH][Lp] row sums of the logit gradient (zero in exact arithmetic)
@@ -54,14 +55,12 @@ struct GemmArgs {
 
 // Adjoint of the second blocking level, one workgroup per (super-block, head).
 struct SbChainArgs {
-    const void* rm;      // [BH][NC][d][d] operand type: R_c row-major
-    const void* kbm;     // [BH][Lp][d] operand type: Kb
+    const void* kt;      // [BH][NC] key tiles (operand type)
     const void* utm;     // [BH][NC][d][64] operand type: utm[c][t] = U[t][c]
     const void* w;       // [BH][L][d] I/O type
     const float* dk2;    // [BH][Lp][d]
-    const float* dchain; // [BH][NC+1][d][d]: entry 4J = gradient of P_superblock J
-    float* ddp;          // [BH][NC][d][d]   (updated)
-    float* dkb;          // [BH][Lp][d]      (updated)
+    const float* dchain; // [BH][NSB][d][d]: gradient of P_superblock J
+    void* dr;            // [BH][NC] tiles (operand type, rows a, contraction b): gradient of R_{c-1}, written
     int L, NC;
     UserLayout ul;       // layout of w
 };
@@ -126,7 +125,9 @@ struct ChunkFusedArgs {
     const void *fm, *gktm, *nm, *aim, *ytm;      // operand type, [BH][NC][64][64]
     const void* utm;                             // operand type, [BH][NC][d][64]
     const float *dqb, *dkb, *dvp;                // [BH][Lp][d]
-    const float* ddp;                            // [BH][NC][d][d]
+    const float* ddp;                            // [BH][NC][d][d]: its near part
+    const void *rm, *dr;                         // second level: tiles of R_c and of the gradient of R_{c-1} (NULL: one super-block)
+    const float* dk2;                            // [BH][Lp][d]: gradient of the second-level keys
     void *dq, *dk, *dv, *dw, *dbeta;             // I/O type
     const float* cum;                            // PaTH-FoX only (else NULL)
     float *dcol, *drow;

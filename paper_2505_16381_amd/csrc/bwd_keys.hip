@@ -305,7 +305,7 @@ __global__ __launch_bounds__(512, 2) void bwd_far_kernel(BwdParams p) {
                 }
         if (KEYS && (DB == 4 || (pos < 4 && ck == 0))) {
             // the gradient of P_superblock starts the second level's chain (nothing lies left of super-block 0)
-            float* dst = p.dchain + ((size_t)bh * (NC + 1) + (size_t)J * SBC) * D * D;
+            float* dst = p.dchain + ((size_t)bh * nsb + J) * D * D;
 #pragma unroll
             for (int jj = 0; jj < 16; ++jj) dst[(size_t)(32 * ab + acc_row(jj, h)) * D + 32 * bb + l32] = J >= 1 ? dd[jj] : 0.f;
         }

@@ -12,6 +12,7 @@
 //   dV  = dV' + P^T dO
 //   dF  = tril(-dSd Y^T - dQb U^T)            dY = -F^T dSd - W dKb^T
 //   dU  = -F^T dQb + W ddP                     dN = dY Gk^T + dU W^T
+//   (ddP, dKb: what the key-side kernels left plus the second level's share, see sb_chain_kernel below)
 //   dGk = sl(N^T dY)     R = A^-T dN     M = sl(-R N^T)     dGs = diag(beta) M + (diag(beta) M)^T
 //   dbeta_a = R_aa + sum_s M_as G_as
 //   dQ  = dQb + dSd K + dF W
@@ -55,15 +56,15 @@ template <typename TIO, int D> struct CaCfg {
 
 // ROWS x COLS elements of type S from global memory (row-major, `stride` elements between rows), 8 per
 // thread and step, held in registers between load() and store(); rows >= nvalid are zero.
-template <typename S, int ROWS, int COLS> struct GTile {
-    static constexpr int NV = ROWS * COLS / 8 / CA_NT;
-    static_assert(NV >= 1 && NV * 8 * CA_NT == ROWS * COLS, "tile must be a multiple of the workgroup's reach");
+template <typename S, int ROWS, int COLS, int NT = CA_NT> struct GTile {
+    static constexpr int NV = ROWS * COLS / 8 / NT;
+    static_assert(NV >= 1 && NV * 8 * NT == ROWS * COLS, "tile must be a multiple of the workgroup's reach");
     typedef S Vec8 __attribute__((ext_vector_type(8)));
     Vec8 v[NV];
     __device__ __forceinline__ void load(const S* src, int stride, int nvalid, int tid) {
 #pragma unroll
         for (int u = 0; u < NV; ++u) {
-            const int idx = tid + u * CA_NT, r = idx / (COLS / 8), c = (idx % (COLS / 8)) * 8;
+            const int idx = tid + u * NT, r = idx / (COLS / 8), c = (idx % (COLS / 8)) * 8;
             if (r < nvalid) v[u] = *reinterpret_cast<const Vec8*>(src + r * stride + c);
             else
 #pragma unroll
@@ -74,7 +75,7 @@ template <typename S, int ROWS, int COLS> struct GTile {
         typedef T TVec8 __attribute__((ext_vector_type(8)));
 #pragma unroll
         for (int u = 0; u < NV; ++u) {
-            const int idx = tid + u * CA_NT, r = idx / (COLS / 8), c = (idx % (COLS / 8)) * 8;
+            const int idx = tid + u * NT, r = idx / (COLS / 8), c = (idx % (COLS / 8)) * 8;
             TVec8 o;
 #pragma unroll
             for (int e = 0; e < 8; ++e) o[e] = (T)(NEG ? -(float)v[u][e] : (float)v[u][e]);
@@ -149,11 +150,79 @@ __global__ __launch_bounds__(CA_NT, 2 * (CaCfg<TIO, D>::WGS_PER_CU)) void chunk_
         }
     };
 
-    // ---- stage W, dO, V; per-token scalars ---------------------------------------------------
+    // ---- the second level's share: ddP -= R^T D, dKb += dKb2 R (D = gradient of R_{c-1}) -------------------
+    // blocks of ddP: wave -> wv, wv + 8 (d = 128), one on waves 4..7 (d = 64)
+    constexpr int NDD = D == 128 ? 2 : 1;
+    const bool actP = D == 128 || wv >= 4;
+    const int blk0 = D == 128 ? wv : wv & 3;
+    f32x16 accV, accQ, accK = zero16();
+    // (d = 64: waves 0..3 and 4..7 hold different things, and two workgroups per CU leave 128 registers: one place
+    // each for dV / ddP, dK / its near part, dQ / dY)
+    f32x16 dd_own[NDD], ddn_own[NDD], y_own;
+    auto dd = [&](int o) -> f32x16& { if constexpr (D == 64) return accV; else return dd_own[o]; };
+    auto ddn = [&](int o) -> f32x16& { if constexpr (D == 64) return accK; else return ddn_own[o]; };
+    f32x16& accY = D == 64 ? accQ : y_own;
+#pragma unroll
+    for (int o = 0; o < NDD; ++o) dd(o) = zero16();
     GTile<TIO, 64, D> tW, tdO, tV;
-    tW.load(wg, TS, ntok, tid);
-    tdO.load(dog, TS, ntok, tid);
-    tV.load(vg, TS, ntok, tid);
+    if (a.rm && !is_last_sb(chunk / SBC, (L + CHUNK - 1) / CHUNK)) {
+        constexpr int DPF = D * D / 8, DS = D / 16;
+        typedef typename Tr<T>::Frag Frag;
+        const size_t bhc = (size_t)bh * NC + chunk;
+        T* sR = X0;                                  // R | D in X0 .. X2 (d = 64: in X0, Y0), dKb2 in Y0 (d = 64: X1)
+        T* sD = sR + D * D;
+        T* sK2 = D == 64 ? X1 : Y0;
+        GTile<float, 64, D> tK2;
+        tK2.load(a.dk2 + bhc * CHUNK * D, D, 64, tid);
+        async_copy_tile<CA_NT, DPF>(reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(a.rm) + bhc * D * D), reinterpret_cast<Frag*>(sR), tid, wv);
+        async_copy_tile<CA_NT, DPF>(reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(a.dr) + bhc * D * D), reinterpret_cast<Frag*>(sD), tid, wv);
+        tW.load(wg, TS, ntok, tid);
+        tdO.load(dog, TS, ntok, tid);
+        tV.load(vg, TS, ntok, tid);
+        tK2.template store<T, false>(sK2, LDD, tid);
+        wait_async_and_sync();
+#pragma unroll
+        for (int o = 0; o < NDD; ++o) {
+            const int blk = blk0 + 8 * o, xb = blk / NBD, bb = blk % NBD;
+            if (actP) {
+                f32x16 acc = zero16();
+#pragma unroll
+                for (int s0 = 0; s0 < DS; s0 += 4) {
+                    Frag fa[4], fb[4];
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) { fa[s] = ld_tile_frag_tr<T, DS>(sR, s0 + s, xb, l32, h); fb[s] = ld_tile_frag_tr<T, DS>(sD, s0 + s, bb, l32, h); }
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) acc = Tr<T>::mma(fa[s], fb[s], acc);
+                }
+#pragma unroll
+                for (int jj = 0; jj < 16; ++jj) dd(o)[jj] = -acc[jj];
+            }
+        }
+        if (actD) {
+            typedef typename Tr<T>::Vec4 TVec4;
+#pragma unroll
+            for (int s0 = 0; s0 < DS; s0 += 4) {
+                Frag fa[4], fb[4];
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                    const T* kp = sK2 + (32 * mbD + l32) * LDD + 16 * (s0 + s) + 4 * h;        // contraction index in accumulator order
+                    const TVec4 lo = *reinterpret_cast<const TVec4*>(kp), hi = *reinterpret_cast<const TVec4*>(kp + 8);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) { fa[s][e] = lo[e]; fa[s][4 + e] = hi[e]; }
+                    fb[s] = ld_tile_frag_tr<T, DS>(sR, s0 + s, cbD, l32, h);
+                }
+#pragma unroll
+                for (int s = 0; s < 4; ++s) accK = Tr<T>::mma(fa[s], fb[s], accK);
+            }
+        }
+        __syncthreads();
+    } else {
+        tW.load(wg, TS, ntok, tid);
+        tdO.load(dog, TS, ntok, tid);
+        tV.load(vg, TS, ntok, tid);
+    }
+
+    // ---- stage W, dO, V; per-token scalars ---------------------------------------------------
     if (tid < CHUNK) {
         beta_s[tid] = tid < ntok ? (float)reinterpret_cast<const TIO*>(a.beta)[user_scl(a.ul, bh, chunk * CHUNK + tid)] : 0.f;
         if (FOX) { colsum[tid] = 0.f; colsum[CHUNK + tid] = 0.f; }
@@ -172,14 +241,12 @@ __global__ __launch_bounds__(CA_NT, 2 * (CaCfg<TIO, D>::WGS_PER_CU)) void chunk_
     tW.template store<T, false>(XW, LDD, tid);
     tdO.template store<T, false>(X0, LDD, tid);
     tV.template store<T, false>(X1, LDD, tid);
-    f32x16 accV, accK, accQ, accW = zero16();
+    f32x16 accW = zero16();
     if (actD) cin(a.dvp + pbase, accV);
     GTile<TIO, 64, D> tQ;
     tQ.load(qg, TS, ntok, tid);
     GTile<T, 64, 64> tY;
     tY.load(reinterpret_cast<const T*>(a.ytm) + cbase, 64, 64, tid);
-    GTile<float, 64, D> tdQb;
-    tdQb.load(a.dqb + pbase, D, 64, tid);
     GTile<T, D, 64> tU;
     tU.load(utmg, 64, D, tid);
     __syncthreads();
@@ -216,8 +283,7 @@ __global__ __launch_bounds__(CA_NT, 2 * (CaCfg<TIO, D>::WGS_PER_CU)) void chunk_
         }
         if (FOX) atomicAdd(colsum + CHUNK + tq, rsum);
     }
-    GTile<float, 64, D> tdKb;
-    tdKb.load(a.dkb + pbase, D, 64, tid);
+    if (actD) cin(a.dqb + pbase, accQ);
     __syncthreads();
     if (FOX && tid < CHUNK) {        // the diagonal block's column and row sums of the logit gradient
         a.dcol[tpad + tid] += colsum[tid];
@@ -228,14 +294,22 @@ __global__ __launch_bounds__(CA_NT, 2 * (CaCfg<TIO, D>::WGS_PER_CU)) void chunk_
     if (actD) {
         mm<T, 64, true, true>(accV, Y0, LDC, 32 * mbD, X0, LDD, 32 * cbD, l32, h);
         out_user(a.dv, accV);
-        cin(a.dkb + pbase, accK);
+        f32x16 kin;
+        cin(a.dkb + pbase, kin);
+#pragma unroll
+        for (int jj = 0; jj < 16; ++jj) accK[jj] += kin[jj];
     }
     __syncthreads();                 // dO (X0), V (X1), P (Y0) are free
     tQ.template store<T, false>(X0, LDD, tid);
     tY.template store<T, true>(Y0, LDC, tid);          // -Y^T as stored ([r][s])
-    tdQb.template store<T, true>(X1, LDD, tid);        // -dQb
+    if (actD) {
+        f32x16 neg;
+#pragma unroll
+        for (int jj = 0; jj < 16; ++jj) neg[jj] = -accQ[jj];
+        st_block<T>(X1, LDD, 32 * mbD, 32 * cbD, neg, l32, h);                // -dQb
+        st_block<T>(X3, LDD, 32 * mbD, 32 * cbD, accK, l32, h);               // dKb
+    }
     tU.template store<T, false>(X2, LDC, tid);         // U as stored: [feature][token]
-    if (actD) cin(a.dqb + pbase, accQ);
     GTile<TIO, 64, D> tK;
     tK.load(kg, TS, ntok, tid);
     GTile<T, 64, 64> tF;
@@ -253,9 +327,14 @@ __global__ __launch_bounds__(CA_NT, 2 * (CaCfg<TIO, D>::WGS_PER_CU)) void chunk_
             if (32 * cb6 + l32 > 32 * mb6 + acc_row(jj, h)) acc[jj] = 0.f;
         st_block<T>(Y2, LDC, 32 * mb6, 32 * cb6, acc, l32, h);
     }
-    tdKb.template store<T, false>(X3, LDD, tid);
-    GTile<float, D, D> tDD;
-    tDD.load(ddpg, D, D, tid);
+    if (actP) {                      // the near part of ddP, in flight until it is stored
+#pragma unroll
+        for (int o = 0; o < NDD; ++o) {
+            const int blk = blk0 + 8 * o, xb = blk / NBD, bb = blk % NBD;
+#pragma unroll
+            for (int jj = 0; jj < 16; ++jj) ddn(o)[jj] = ddpg[(size_t)(32 * xb + acc_row(jj, h)) * D + 32 * bb + l32];
+        }
+    }
     __syncthreads();
 
     // ---- dW = dF^T Q - Y dKb (kept open) ----------------------------------------------------------
@@ -277,8 +356,8 @@ __global__ __launch_bounds__(CA_NT, 2 * (CaCfg<TIO, D>::WGS_PER_CU)) void chunk_
         mm<T, 64, false, true>(accQ, Y2, LDC, 32 * mbD, XW, LDD, 32 * cbD, l32, h);
         out_user(a.dq, accQ);
     }
-    f32x16 accY = zero16();
     if (act6) {
+        accY = zero16();
         mm<T, 64, true, true>(accY, Y0, LDC, 32 * mb6, Y1, LDC, 32 * cb6, l32, h);
         mm<T, D, false, false>(accY, XW, LDD, 32 * mb6, X3, LDD, 32 * cb6, l32, h);
 #pragma unroll
@@ -289,7 +368,15 @@ __global__ __launch_bounds__(CA_NT, 2 * (CaCfg<TIO, D>::WGS_PER_CU)) void chunk_
     tK.load(kg, TS, ntok, tid);       // K once more, for dGk K at the end
     __syncthreads();                 // K (X0), dKb (X3), dSd (Y1), dF (Y2) are free
     if (act6) st_block<T>(Y2, LDC, 32 * mb6, 32 * cb6, accY, l32, h);     // dY
-    tDD.template store<T, false>(X0, LDD, tid);        // ddP [a][b] (d = 128: spans X0 and X3)
+    if (actP) {                      // ddP [a][b] (d = 128: spans X0 and X3)
+#pragma unroll
+        for (int o = 0; o < NDD; ++o) {
+            const int blk = blk0 + 8 * o, xb = blk / NBD, bb = blk % NBD;
+#pragma unroll
+            for (int jj = 0; jj < 16; ++jj) ddn(o)[jj] += dd(o)[jj];
+            st_block<T>(X0, LDD, 32 * xb, 32 * bb, ddn(o), l32, h);
+        }
+    }
     tN.template store<T, false>(YN, LDC, tid);
     tG.template store<T, false>(Y1, LDC, tid);
     __syncthreads();
@@ -405,160 +492,120 @@ hipError_t launch_t(const ChunkFusedArgs& a, int BH, hipStream_t st) {
 
 
 // ---------------------------------------------------------------------------------------
-// Adjoint of the second blocking level (Kb2_c = Kb_c R_c^T, R_{c-1} = R_c P_c with R_last = I,
-// P_superblock = R_{first-1}; P_c = I - dP_c, dP_c = W_c^T U_c), fused: one workgroup per
-// (super-block J, head) walks the chunks c = first .. last with the gradient G of R_{c-1} in
-// accumulator registers (start: the gradient of P_superblock from the far ddP kernel),
-//     ddP_c -= R_c^T G                              (d x d x d)
-//     dKb_c += dKb2_c R_c                           (64 x d x d)
-//     G     <- G - (G U_c^T) W_c + dKb2_c^T Kb_c     (c < last)
-// The five operands of a chunk are fetched into registers one chunk ahead and staged in LDS as
-// they lie in memory (16-byte writes, no bank conflicts); products that contract along the rows
-// of a stored matrix take their fragments with transposing LDS reads.
+// The chain of the second blocking level's adjoint (Kb2_c = Kb_c R_c^T, R_{c-1} = R_c P_c with R_last = I,
+// P_superblock = R_{first-1}; P_c = I - dP_c, dP_c = W_c^T U_c): with G the gradient of R_{c-1}, starting from the
+// gradient of P_superblock (far key-side kernel), chunks first .. last,
+//     G <- G - (G U_c^T) W_c + dKb2_c^T Kb_c .
+// G before chunk c is left as a tile; what it is for -- ddP_c -= R_c^T G, dKb_c += dKb2_c R_c -- the chunk-transform
+// adjoint does, where ddP_c and dKb_c are read anyway.  The rows of G do not depend on each other: a wave keeps 32 of
+// them, transposed, in accumulator registers (lane = row), its operand copy is those registers packed, and the only
+// thing the waves share is the tiles of U, W and Kb, fetched one chunk ahead.
+// What bounds it: memory (112 KB per chunk at d = 128), and the chain's latency when there are few heads.  As one
+// workgroup of eight waves that exchanged G through LDS and updated ddP and dKb in memory itself (304 KB per chunk)
+// it took 0.50 ms at B=4, H=16, L=8192, d=128.
 template <typename TIO, int D> struct SbCfg {
     typedef typename Compute<TIO>::type T;
+    static constexpr int NT = 64 * (D / 32);                          // one wave per 32 rows of G
     static constexpr int LDD = D + 8, LDC = CHUNK + 8;
-    static constexpr int DD = D * LDD * 2, TD = 64 * LDD * 2, DT = D * LDC * 2;     // bytes: d x d, 64 x d, d x 64 tiles
-    static constexpr int R_ = 0, G_ = DD, K2 = 2 * DD, U_ = K2 + TD, W_ = U_ + DT, KB = W_ + TD, T1 = KB + TD;
-    static constexpr int TOTAL = T1 + DT;
-    static_assert(TOTAL <= 160 * 1024, "LDS budget");
+    static constexpr int U_ = 0, W_ = D * LDC * 2, KB = W_ + 64 * LDD * 2, TOTAL = KB + 64 * D * 2;    // bytes: U | W | Kb tile
 };
 
 template <typename TIO, int D, bool STRIDED>
-__global__ __launch_bounds__(CA_NT) void sb_chain_kernel(SbChainArgs a) {
+__global__ __launch_bounds__((SbCfg<TIO, D>::NT), 2) void sb_chain_kernel(SbChainArgs a) {
     using C = SbCfg<TIO, D>;
     typedef typename C::T T;
-    constexpr int LDD = C::LDD, LDC = C::LDC, DB = D / 32;
-    constexpr int NOWN = (DB * DB + 7) / 8;          // d x d blocks per wave: blocks wv, wv + 8, ...
+    using Frag = typename Tr<T>::Frag;
+    constexpr int LDD = C::LDD, LDC = C::LDC, DB = D / 32, DS = D / 16, NT = C::NT;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    T* sR = reinterpret_cast<T*>(smem + C::R_);       // R_c [k][x]
-    T* sG = reinterpret_cast<T*>(smem + C::G_);       // G [a][b]
-    T* sK2 = reinterpret_cast<T*>(smem + C::K2);      // dKb2_c [s][a]
     T* sU = reinterpret_cast<T*>(smem + C::U_);       // U_c as stored: [feature][token]
     T* sW = reinterpret_cast<T*>(smem + C::W_);       // W_c [t][b]
-    T* sKb = reinterpret_cast<T*>(smem + C::KB);      // Kb_c [s][b]
-    T* sT1 = reinterpret_cast<T*>(smem + C::T1);      // -(G U^T) [a][t]
+    T* sKb = reinterpret_cast<T*>(smem + C::KB);      // Kb_c, a tile (rows s, contraction b)
 
     const int J = blockIdx.x, bh = blockIdx.y, NC = a.NC;           // NC: chunks per head in the workspace arrays
-    const int L = seq_len(a.ul, bh, a.L), NCo = (L + CHUNK - 1) / CHUNK;   // this head's own length and chunks
+    const int L = seq_len(a.ul, bh, a.L), NCo = (L + CHUNK - 1) / CHUNK, nsb = (NC + SBC - 1) / SBC;   // this head's own length and chunks
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), h = lane >> 5, l32 = lane & 31;
     const int c0 = J * SBC;
     if (is_last_sb(J, NCo)) return;                   // no gradient arrives there (packed batch: a shorter sequence has fewer super-blocks)
-    const int clast = c0 + SBC - 1;
     const int TS = STRIDED ? (int)a.ul.vt : D;        // token stride of W
-    const bool act = wv < 2 * DB;                     // 64 x d and d x 64 results: one block per wave
-    const int hb = act ? wv / DB : 0, db = wv % DB;   // ... block (hb, db) of a 64 x d result, (db, hb) of a d x 64 one
 
-    f32x16 G[NOWN];
+    f32x16 G[DB];                                     // G^T: rows b, lane = row a = 32 wv + l32
     {
-        const float* src = a.dchain + ((size_t)bh * (NC + 1) + c0) * D * D;
+        const float* src = a.dchain + (((size_t)bh * nsb + J) * D + 32 * wv + l32) * D + 4 * h;
 #pragma unroll
-        for (int o = 0; o < NOWN; ++o) {
-            const int blk = wv + 8 * o, ab = blk / DB, bb = blk % DB;
-            if (blk < DB * DB) {
+        for (int b = 0; b < DB; ++b)
 #pragma unroll
-                for (int jj = 0; jj < 16; ++jj) G[o][jj] = src[(size_t)(32 * ab + acc_row(jj, h)) * D + 32 * bb + l32];
+            for (int g = 0; g < 4; ++g) {
+                const f32x4 v4 = *reinterpret_cast<const f32x4*>(src + 32 * b + 8 * g);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) G[b][4 * g + r] = v4[r];
             }
-        }
     }
-    GTile<T, D, D> tR;
-    GTile<float, 64, D> tK2;
-    GTile<T, D, 64> tU;
-    GTile<TIO, 64, D> tW;
-    GTile<T, 64, D> tKb;
+    GTile<T, D, 64, NT> tU;
+    GTile<TIO, 64, D, NT> tW;
+    Frag tKb[64 * D / 8 / NT];
     auto fetch = [&](int c) {
         const size_t bhc = (size_t)bh * NC + c;
-        const int ntok = (L - c * CHUNK < CHUNK) ? L - c * CHUNK : CHUNK;
-        tR.load(reinterpret_cast<const T*>(a.rm) + bhc * D * D, D, D, tid);
-        tK2.load(a.dk2 + bhc * CHUNK * D, D, 64, tid);
-        if (c < clast) {
-            tU.load(reinterpret_cast<const T*>(a.utm) + bhc * D * CHUNK, 64, D, tid);
-            tW.load(reinterpret_cast<const TIO*>(a.w) + user_vec(a.ul, bh, (long long)c * CHUNK), TS, ntok, tid);
-            tKb.load(reinterpret_cast<const T*>(a.kbm) + bhc * CHUNK * D, D, 64, tid);
-        }
+        tU.load(reinterpret_cast<const T*>(a.utm) + bhc * D * CHUNK, 64, D, tid);
+        tW.load(reinterpret_cast<const TIO*>(a.w) + user_vec(a.ul, bh, (long long)c * CHUNK), TS, 64, tid);     // (a whole chunk: not the head's last)
+        const Frag* kg = reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(a.kt) + bhc * CHUNK * D);
+#pragma unroll
+        for (int u = 0; u < 64 * D / 8 / NT; ++u) tKb[u] = kg[tid + u * NT];
     };
     fetch(c0);
-    for (int c = c0; c <= clast; ++c) {
-        const size_t bhc = (size_t)bh * NC + c;
+    for (int c = c0; ; ++c) {
+        Frag Gb[DS];
+#pragma unroll
+        for (int b = 0; b < DB; ++b) pack_block<T>(G[b], Gb + 2 * b);
+        Frag* dst = reinterpret_cast<Frag*>(reinterpret_cast<T*>(a.dr) + ((size_t)bh * NC + c) * D * D) + (size_t)wv * DS * 64;
+#pragma unroll
+        for (int s = 0; s < DS; ++s) __builtin_nontemporal_store(Gb[s], &dst[s * 64 + tile_lane<T>(lane, s)]);
+        if (c == c0 + SBC - 1) break;
         __syncthreads();                              // the previous chunk's reads are done
-        tR.template store<T, false>(sR, LDD, tid);
-        tK2.template store<T, false>(sK2, LDD, tid);
-        if (c < clast) {
-            tU.template store<T, false>(sU, LDC, tid);
-            tW.template store<T, false>(sW, LDD, tid);
-            tKb.template store<T, false>(sKb, LDD, tid);
-        }
+        tU.template store<T, false>(sU, LDC, tid);
+        tW.template store<T, false>(sW, LDD, tid);
 #pragma unroll
-        for (int o = 0; o < NOWN; ++o) {
-            const int blk = wv + 8 * o, ab = blk / DB, bb = blk % DB;
-            if (blk < DB * DB) st_block<T>(sG, LDD, 32 * ab, 32 * bb, G[o], l32, h);
-        }
-        if (c < clast) fetch(c + 1);
-        // The two results of this step are added to what the key-side kernels left in ddP_c and dKb_c: every
-        // element has exactly one writer here, so a plain read-modify-write does (hardware atomic adds, tried
-        // first because they need no old value, ran at the L2's atomic rate and doubled the kernel's time).
-        // The old values are requested well before they are used: those of the wave's first ddP block and of
-        // its dKb block now, those of its second ddP block after the first is stored -- that block's product
-        // is taken last, after the update of G (R and this step's G stay in LDS until the next step).
-        static_assert(NOWN <= 2, "two d x d blocks per wave at most");
-        float* const ddp_dst = a.ddp + bhc * (size_t)D * D;
-        float* const dkb_dst = a.dkb + (bhc * CHUNK) * (size_t)D;
-        auto ddp_load = [&](int o, f32x16& old) {
-            const int blk = wv + 8 * o, xb = blk / DB, bb = blk % DB;
-            if (blk < DB * DB) {
+        for (int u = 0; u < 64 * D / 8 / NT; ++u) reinterpret_cast<Frag*>(sKb)[tid + u * NT] = tKb[u];
+        float k2[32];                                 // dKb2_c[s][a], s = 16 i + acc_row(e, h): needed after T1
+        const float* kp = a.dk2 + (((size_t)bh * NC + c) * CHUNK + 4 * h) * D + 32 * wv + l32;
 #pragma unroll
-                for (int jj = 0; jj < 16; ++jj) old[jj] = ddp_dst[(size_t)(32 * xb + acc_row(jj, h)) * D + 32 * bb + l32];
-            }
-        };
-        // ddP_c[x][b] -= sum_k R[k][x] G[k][b]
-        auto ddp_block = [&](int o, const f32x16& old) {
-            const int blk = wv + 8 * o, xb = blk / DB, bb = blk % DB;
-            if (blk < DB * DB) {
-                f32x16 acc = zero16();
-                mm<T, D, true, true>(acc, sR, LDD, 32 * xb, sG, LDD, 32 * bb, l32, h);
+        for (int i = 0; i < 4; ++i)
 #pragma unroll
-                for (int jj = 0; jj < 16; ++jj) ddp_dst[(size_t)(32 * xb + acc_row(jj, h)) * D + 32 * bb + l32] = old[jj] - acc[jj];
-            }
-        };
-        f32x16 ddp_old, dkb_old;
-        ddp_load(0, ddp_old);
-        if (act) {
-#pragma unroll
-            for (int jj = 0; jj < 16; ++jj) dkb_old[jj] = dkb_dst[(size_t)(32 * hb + acc_row(jj, h)) * D + 32 * db + l32];
-        }
+            for (int e = 0; e < 8; ++e) k2[8 * i + e] = kp[(16 * i + acc_row(e, 0)) * D];
         __syncthreads();
-        ddp_block(0, ddp_old);
-        if (NOWN > 1) ddp_load(1, ddp_old);
-        // dKb_c[s][b] += sum_a dKb2[s][a] R[a][b]
-        if (act) {
-            f32x16 acc = zero16();
-            mm<T, D, false, true>(acc, sK2, LDD, 32 * hb, sR, LDD, 32 * db, l32, h);
+        // T1^T[t][a] = -sum_k U[t][k] G[a][k]
+        Frag t1[4];
 #pragma unroll
-            for (int jj = 0; jj < 16; ++jj) dkb_dst[(size_t)(32 * hb + acc_row(jj, h)) * D + 32 * db + l32] = dkb_old[jj] + acc[jj];
-        }
-        if (c == clast) {
-            if (NOWN > 1) ddp_block(1, ddp_old);
-            break;
-        }
-        // T1[a][t] = sum_k G[a][k] U[t][k]
-        if (act) {
+        for (int tb = 0; tb < 2; ++tb) {
             f32x16 acc = zero16();
-            mm<T, D, false, true>(acc, sG, LDD, 32 * db, sU, LDC, 32 * hb, l32, h);
+#pragma unroll
+            for (int s0 = 0; s0 < DS; s0 += 4) {
+                Frag f[4];
+#pragma unroll
+                for (int s = 0; s < 4; ++s) f[s] = ld_frag_tr_acc<T>(sU, LDC, 16 * (s0 + s), 32 * tb, l32, h);
+#pragma unroll
+                for (int s = 0; s < 4; ++s) acc = Tr<T>::mma(f[s], Gb[s0 + s], acc);
+            }
 #pragma unroll
             for (int jj = 0; jj < 16; ++jj) acc[jj] = -acc[jj];
-            st_block<T>(sT1, LDC, 32 * db, 32 * hb, acc, l32, h);
+            pack_block<T>(acc, t1 + 2 * tb);
         }
-        __syncthreads();
-        // G += -T1 W + dKb2^T Kb
+        if (c + 1 < c0 + SBC - 1) fetch(c + 1);
+        Frag kf[4];
 #pragma unroll
-        for (int o = 0; o < NOWN; ++o) {
-            const int blk = wv + 8 * o, ab = blk / DB, bb = blk % DB;
-            if (blk < DB * DB) {
-                mm<T, 64, false, true>(G[o], sT1, LDC, 32 * ab, sW, LDD, 32 * bb, l32, h);
-                mm<T, 64, true, true>(G[o], sK2, LDD, 32 * ab, sKb, LDD, 32 * bb, l32, h);
-            }
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) kf[i][e] = (T)k2[8 * i + e];
+        // G^T += W^T T1^T + Kb^T dKb2
+#pragma unroll
+        for (int b = 0; b < DB; ++b) {
+            Frag f[4], k[4];
+#pragma unroll
+            for (int s = 0; s < 4; ++s) { k[s] = ld_tile_frag_tr<T, DS>(sKb, s, b, l32, h); f[s] = ld_frag_tr_acc<T>(sW, LDD, 16 * s, 32 * b, l32, h); }
+#pragma unroll
+            for (int s = 0; s < 4; ++s) G[b] = Tr<T>::mma(k[s], kf[s], G[b]);
+#pragma unroll
+            for (int s = 0; s < 4; ++s) G[b] = Tr<T>::mma(f[s], t1[s], G[b]);
         }
-        if (NOWN > 1) ddp_block(1, ddp_old);
     }
 }
 
@@ -569,7 +616,7 @@ hipError_t launch_sb_s(const SbChainArgs& a, int BH, hipStream_t st) {
     static const hipError_t attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&sb_chain_kernel<TIO, D, STRIDED>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::TOTAL);
     if (attr_err != hipSuccess) return attr_err;
-    hipLaunchKernelGGL((sb_chain_kernel<TIO, D, STRIDED>), dim3((a.NC + SBC - 1) / SBC - 1, BH), dim3(CA_NT), (size_t)C::TOTAL, st, a);      // (NC > SBC)
+    hipLaunchKernelGGL((sb_chain_kernel<TIO, D, STRIDED>), dim3((a.NC + SBC - 1) / SBC - 1, BH), dim3(C::NT), (size_t)C::TOTAL, st, a);      // (NC > SBC)
     return hipGetLastError();
 }
 template <typename TIO, int D>

@@ -194,6 +194,20 @@ __device__ __forceinline__ typename Tr<T>::Frag ld_frag_tr(const T* X, int ld, i
     return u.f;
 }
 
+// The same with the contraction index in accumulator order: the values X[kk + acc_row(e, h)][r0 + l32], e = 0..7, which
+// is how a packed accumulator block orders them.
+template <typename T>
+__device__ __forceinline__ typename Tr<T>::Frag ld_frag_tr_acc(const T* X, int ld, int kk, int r0, int l32, int h) {
+    static_assert(sizeof(T) == 2, "16-bit transposing reads");
+    typedef short v4s __attribute__((ext_vector_type(4)));
+    const int j = l32 & 15;
+    const T* p = X + (kk + 4 * h + (j >> 2)) * ld + r0 + (l32 & 16) + 4 * (j & 3);
+    union { v4s v[2]; typename Tr<T>::Frag f; } u;
+    u.v[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)(p));
+    u.v[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)(p + 8 * ld));
+    return u.f;
+}
+
 // acc[m][n] += sum_k A(m,k) B(n,k) for one 32x32 block (rows ar0.., columns br0..).
 // TA == false: A is stored [m][k] (16-byte fragment reads); TA == true: A is stored [k][m] (transposing reads).  Same for B.
 template <typename T, int K, bool TA, bool TB>
@@ -374,8 +388,8 @@ struct FwdParams {
     // Backward only: per-chunk matrices of the transform, row-major 64x64 (operand type) --
     // fm = F[t][t'], gktm[s][t'] = strictLower(W K^T)[t'][s], nm = N, aim = A^{-1},
     // ytm[s][t] = Y[t][s]; utm [d][64]: utm[c][t] = U[t][c]; fp32: gm = W W^T, sdm[t][s] = Sd;
-    // kbm [Lp][d]: boundary-adjusted keys Kb (rows past L zero); rm [d][d] per chunk: R_c of
-    // the second level (operand type).
+    // kbm [Lp][d]: boundary-adjusted keys Kb (rows past L zero; fp32 operands only); rm [d][d] per chunk: R_c of
+    // the second level (operand type; fp32 operands row-major, 16-bit operands as a tile with rows a, contraction b).
     void *fm, *gktm, *nm, *aim, *ytm, *utm, *kbm, *rm;
     float *gm, *sdm;
     // Sequence-parallel forward (one device's share of the ring of Sec. 3.5): the sweep's per-query registers --

@@ -78,7 +78,21 @@ __global__ __launch_bounds__(256) void prep2_fwd_kernel(FwdParams p) {
         Frag* k2 = reinterpret_cast<Frag*>(reinterpret_cast<T*>(p.kt2) + bhc * (size_t)CHUNK * D);
         // (the transposed arrangement of the second-level keys: fp32 operands only, as for the chunk-level ones)
         Frag* k2T = (BWD && p.kt2T && sizeof(T) == 4) ? reinterpret_cast<Frag*>(reinterpret_cast<T*>(p.kt2T) + bhc * (size_t)CHUNK * D) : nullptr;
-        if (BWD && p.rm) {      // backward only: R_c = I - E_c, row-major [a][b]
+        if (BWD && sizeof(T) == 2) {      // backward only: R_c = I - E_c as a tile (rows a, contraction b)
+            Frag* rdst = reinterpret_cast<Frag*>(reinterpret_cast<T*>(p.rm) + bhc * (size_t)D * D);
+#pragma unroll
+            for (int o = 0; o < NE; ++o) {
+                const int blk = wv + 4 * o, bb = blk / DB, ab = blk % DB;
+                f32x16 rc;
+#pragma unroll
+                for (int jj = 0; jj < 16; ++jj)
+                    rc[jj] = (32 * ab + l32 == 32 * bb + acc_row(jj, h) ? 1.f : 0.f) - (c == clast ? 0.f : Fm[o][jj]);
+                Frag fr[SPB];
+                pack_block<T>(rc, fr);
+#pragma unroll
+                for (int s2 = 0; s2 < SPB; ++s2) __builtin_nontemporal_store(fr[s2], &rdst[((size_t)ab * DS + bb * SPB + s2) * 64 + tile_lane<T>(lane, s2)]);
+            }
+        } else if (BWD) {                 // (fp32 operands: row-major [a][b])
             typedef typename Tr<T>::Vec4 TVec4;
             T* rdst = reinterpret_cast<T*>(p.rm) + bhc * (size_t)D * D;
 #pragma unroll

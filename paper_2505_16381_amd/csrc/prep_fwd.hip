@@ -426,7 +426,7 @@ __global__ __launch_bounds__(256, (PrepCfg<TIO, D>::WGS_PER_CU)) void prep_fwd_k
             pack_block<T>(acc, fr);
 #pragma unroll
             for (int s2 = 0; s2 < SPB; ++s2) __builtin_nontemporal_store(fr[s2], &kdst[((size_t)sb * (D / KW) + cb * SPB + s2) * 64 + tile_lane<T>(lane, s2)]);
-            if (BWD && p.kbm) {       // backward only: the same keys row-major [token][c]
+            if (BWD && sizeof(T) == 4) {       // backward with fp32 operands only: the same keys row-major [token][c]
                 typedef typename Tr<T>::Vec4 TVec4;
                 T* kb = reinterpret_cast<T*>(p.kbm) + (bhc * CHUNK + s) * (size_t)D + 32 * cb + 4 * h;
 #pragma unroll
