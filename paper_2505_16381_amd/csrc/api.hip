@@ -235,9 +235,8 @@ static path_status_t fwd_impl(int stage, const UserLayout& ul, const void* q, co
     if (stage != 2) {
         p.q = q; p.k = k; p.v = v; p.w = w; p.beta = beta;
         if (!hip_ok(launch_prep_fwd(p, d, dt == PATH_BF16, hs), "chunk transform")) return PATH_ERR_HIP;
-        // (the sweep reads the second level only when there is a super-block to the left; the key
-        // prefill of the decode path reads it always)
-        if (!hip_ok(launch_prep2_fwd(p, d, dt == PATH_BF16, hs), "second-level transform")) return PATH_ERR_HIP;
+        // (one super-block: nobody reads the second level, neither the sweep nor the key prefill of the decode path)
+        if (p.NC > SBC && !hip_ok(launch_prep2_fwd(p, d, dt == PATH_BF16, hs), "second-level transform")) return PATH_ERR_HIP;
         if (log_f && !hip_ok(launch_gate_sums(log_f, ul, cum, B, H, L, dt, hs), "gate sums")) return PATH_ERR_HIP;
     }
     if (stage != 1) {
@@ -658,13 +657,16 @@ extern "C" path_status_t path_key_prefill(const void* v, int B, int H, int L, in
     const unsigned char* base = static_cast<const unsigned char*>(fws);
     hipStream_t st = static_cast<hipStream_t>(stream);
     clear_inherited_error();
-    PrefillArgs a{base + ws.kt2, base + ws.dp2, kcache, L, (L + CHUNK - 1) / CHUNK, Lmax};
-    if (!hip_ok(launch_key_prefill(a, B * H, d, dt == PATH_BF16, st), "key prefill")) return PATH_ERR_HIP;
-    // values: rows [0, L) of every head, unchanged
-    if (!hip_ok(hipMemcpy2DAsync(vcache, (size_t)Lmax * d * es, v, (size_t)L * d * es, (size_t)L * d * es, (size_t)B * H,
-                                 hipMemcpyDeviceToDevice, st), "value cache copy"))
-        return PATH_ERR_HIP;
-    return PATH_OK;
+    const int NC = (L + CHUNK - 1) / CHUNK;
+    if (NC <= SBC) {      // one super-block: its second-level keys are the prompt's (the forward has not formed them)
+        FwdParams p = {};
+        const path_status_t ps = fwd_setup(p, layout_of(PATH_LAYOUT_BHLD, H, L, d), B, H, L, d, dt, const_cast<void*>(fws), fws_bytes);
+        if (ps != PATH_OK) return ps;
+        p.v = v; p.kcache = kcache; p.vcache = vcache; p.Lmax = Lmax;
+        return hip_ok(launch_prep2_fwd(p, d, dt == PATH_BF16, st), "key prefill") ? PATH_OK : PATH_ERR_HIP;
+    }
+    PrefillArgs a{base + ws.kt2, base + ws.dp2, v, kcache, vcache, L, NC, Lmax};
+    return hip_ok(launch_key_prefill(a, B * H, d, dt == PATH_BF16, st), "key prefill") ? PATH_OK : PATH_ERR_HIP;
 }
 
 extern "C" path_status_t path_decode_step(const void* q, const void* k, const void* v, const void* w,

@@ -10,7 +10,9 @@
 //    linear in l.  One workgroup per (head, super-block): it runs the d x d recurrence from the
 //    right end down to its own super-block (a few small products per step, the same for every
 //    workgroup of the head, hence the same E) and carries only its own super-block's keys.
-//    Results go row-major into the key cache, in the cache's storage type.
+//    Results go row-major into the key cache, in the cache's storage type.  (A prompt of one super-block
+//    has nothing to carry beyond it: its keys take the second level's own step straight to the cache,
+//    see prep2_fwd.hip.)  Further workgroups copy the values.
 //
 //  * Decode step (the section's first equation): when token t arrives every cached key is
 //    refreshed in place, k_i <- k_i - beta_t (w_t . k_i) w_t, and attention of q_t over the
@@ -52,7 +54,7 @@ __global__ __launch_bounds__(256) void key_prefill_kernel(PrefillArgs a) {
     const int bh = blockIdx.x, Jme = blockIdx.y;   // this workgroup carries the keys of super-block Jme
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, h = lane >> 5, l32 = lane & 31;
     const int NC = a.NC, L = a.L, nsb = (NC + SBC - 1) / SBC;
-    if (Jme >= nsb) return;
+    if (Jme >= nsb) { copy_value_rows<TIO, D, 256>(a.v, a.vcache, L, a.Lmax, bh, Jme - nsb, tid); return; }
 
     Frag idf[SPB];
     identity_frags<T>(idf, l32, h);
@@ -268,10 +270,10 @@ __global__ __launch_bounds__(D) void decode_combine_kernel(DecodeArgs a, int nsp
 template <typename TIO, int D>
 static hipError_t launch_prefill_t(const PrefillArgs& a, int BH, hipStream_t st) {
     const size_t bytes = PrefillCfg<TIO, D>::smem_bytes;
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&key_prefill_kernel<TIO, D>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    static const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&key_prefill_kernel<TIO, D>),
+                                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((key_prefill_kernel<TIO, D>), dim3(BH, (a.NC + SBC - 1) / SBC), dim3(256), bytes, st, a);
+    hipLaunchKernelGGL((key_prefill_kernel<TIO, D>), dim3(BH, (a.NC + SBC - 1) / SBC + value_row_pieces(a.L)), dim3(256), bytes, st, a);
     return hipGetLastError();
 }
 hipError_t launch_key_prefill(const PrefillArgs& a, int BH, int d, int is_bf16, hipStream_t st) {

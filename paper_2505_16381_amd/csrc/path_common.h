@@ -400,6 +400,9 @@ struct FwdParams {
     // attended, and they are stored again.  NCq: chunks of the query side (ring = 2 only; else NC).
     float* ring_state;
     int ring, NCq;
+    // Key prefill of a prompt of one super-block (second-level kernel only): the decode path's caches [BH][Lmax][d].
+    void *kcache, *vcache;
+    int Lmax;
 };
 // ring_state: per (head, query chunk, 32-query half) one record of RING_REC(d) floats, each quantity as the sweep
 // holds it: [X: d/32 blocks][O: d/32 blocks] of 1024 floats (register g*4+r of lane l at g*256 + l*4 + r), then the

@@ -10,38 +10,53 @@
 // per chunk.  With E_c = I - R_c:  E_{c-1} = E_c + dP_c - E_c dP_c  and
 // Kb2_c = Kb_c - Kb_c E_c^T.
 //
-// One workgroup per (batch*head, super-block).  E is kept TRANSPOSED in fp32
-// registers (rows b, lane a): in that layout its operand copy is directly the
-// fragment-order tile (rows a, contraction b) that both products need -- as the
-// A operand of the key transport and as the B operand of the update -- and the
-// other operands are the fragment tiles the chunk kernel already wrote (keys and
-// -dP), read straight from global memory; where -dP is needed element-wise in the
-// transposed register layout it is transposed through the matrix unit.
+// One workgroup per (batch*head, super-block), one wave per 32 rows of E: the rows of E do not depend on each other
+// (E dP takes a row of E to a row), and column c of Kb2 needs row c of E alone.  A wave keeps its rows transposed in
+// fp32 registers (rows b, lane = row a); those registers packed are the operand of both products, so the waves share
+// nothing but the chunk's key and -dP tiles, copied to LDS as the chunk kernel wrote them.  Where -dP is needed
+// element-wise in the transposed register layout it is transposed through the matrix unit.
+//
+// What bounds it: memory where there are many super-blocks (64 KB per chunk at d = 128, 96 with the backward's
+// outputs), the chain of 16 chunks where there are few.  Hence two shapes: more than one workgroup per CU, one stage of
+// tiles each, and a single workgroup per CU with the next chunk's tiles on their way during the current one's products.
+// At d = 128: 64 heads of 7 super-blocks with the backward's outputs 160 us (4.3 TB/s), 512 heads of 2 without them
+// 154 us, one super-block per head into the cache 38 us.  (Waves that each took all of E's blocks from LDS, two
+// fragments per product: 171, 226 and, with the rows turned and copied afterwards, 84 us.)
 #include "path_common.h"
+#include "decode_decl.h"
 
 namespace path {
 
-template <typename TIO, int D> struct Prep2Cfg {
+enum { P2_FWD = 0, P2_BWD = 1, P2_CACHE = 2 };
+// P2_BWD: also write the backward-only outputs.  P2_CACHE: the key prefill of a prompt of one super-block -- the keys,
+// carried to the super-block's right edge, which is the prompt's end, go to the decode path's cache (row-major, its
+// storage type), and further workgroups copy the values.
+template <typename TIO, int D, int NBUF> struct Prep2Cfg {
     typedef typename Compute<TIO>::type T;
     static constexpr int KV_FRAGS = CHUNK * D / Tr<T>::FE, DP_FRAGS = D * D / Tr<T>::FE;
-    static constexpr int NBUF = sizeof(T) == 2 ? 2 : 1;      // fp32 tiles: one stage only fits
-    // operand copy of E (fragment order) + NBUF stages of (key tile | -dP tile) of a chunk
-    static constexpr size_t smem_bytes = (size_t)D * D * sizeof(T) + (size_t)NBUF * (KV_FRAGS + DP_FRAGS) * 16;
+    static constexpr int NT = 64 * (D / 32);
+    static constexpr size_t smem_bytes = (size_t)NBUF * (KV_FRAGS + DP_FRAGS) * 16;      // stages of (key tile | -dP tile)
+    static constexpr int WAVES_PER_SIMD = sizeof(T) == 2 && NBUF == 1 ? (D == 64 ? 3 : 2) : 1;
 };
 
-// BWD: also write the backward-only outputs (compile-time, so the forward carries none of that code).
-template <typename TIO, int D, bool BWD>
-__global__ __launch_bounds__(256) void prep2_fwd_kernel(FwdParams p) {
-    using T = typename Compute<TIO>::type;
+template <typename TIO, int D, int MODE, int NBUF>
+__global__ __launch_bounds__((Prep2Cfg<TIO, D, NBUF>::NT), (Prep2Cfg<TIO, D, NBUF>::WAVES_PER_SIMD)) void prep2_fwd_kernel(FwdParams p) {
+    using C = Prep2Cfg<TIO, D, NBUF>;
+    using T = typename C::T;
     using Frag = typename Tr<T>::Frag;
     constexpr int FE = Tr<T>::FE, KW = Tr<T>::KW;
-    constexpr int SPB = 32 / KW, DB = D / 32, DS = D / KW, NE = DB * DB / 4, NK = 2 * DB / 4;
+    constexpr int SPB = 32 / KW, DB = D / 32, DS = D / KW, KVF = C::KV_FRAGS, DPF = C::DP_FRAGS, NT = C::NT;
+    constexpr bool BWD = MODE == P2_BWD;
 
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    Frag* Es = reinterpret_cast<Frag*>(smem);      // tile (rows a, contraction b) of E
+    Frag* const stage = reinterpret_cast<Frag*>(smem);
 
     const int sb = blockIdx.x, bh = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), h = lane >> 5, l32 = lane & 31;
+    if (MODE == P2_CACHE && sb > 0) {
+        copy_value_rows<TIO, D, NT>(p.v, p.vcache, p.L, p.Lmax, bh, sb - 1, tid);
+        return;
+    }
     const int NC = p.NC, nsb = (NC + SBC - 1) / SBC;                       // chunks and super-blocks per head in the workspace arrays
     const int NCown = (seq_len(p.ul, bh, p.L) + CHUNK - 1) / CHUNK;        // this head's own (packed batches: may be fewer)
     const int c0 = sb * SBC;
@@ -49,18 +64,17 @@ __global__ __launch_bounds__(256) void prep2_fwd_kernel(FwdParams p) {
     if (BWD && is_last_sb(sb, NCown)) return;         // (a training step never looks at it from the right: see is_last_sb)
     const int clast = (c0 + SBC - 1 < NCown) ? c0 + SBC - 1 : NCown - 1;
 
-    Frag idf[SPB];
+    Frag idf[SPB], Eb[DS];
     identity_frags<T>(idf, l32, h);
-    f32x16 Fm[NE];      // E^T: block o = (rows b-block bb, lane a-block ab), blk = wv + 4*o, bb = blk / DB, ab = blk % DB
+    f32x16 Fm[DB];      // E^T of the wave's rows: rows b, lane a = 32 wv + l32
+#pragma unroll
+    for (int b = 0; b < DB; ++b) Fm[b] = zero16();
 
-    // the chunk's key and -dP tiles are copied to LDS (direct-to-LDS), one chunk ahead where two stages fit
-    constexpr int KVF = Prep2Cfg<TIO, D>::KV_FRAGS, DPF = Prep2Cfg<TIO, D>::DP_FRAGS, NBUF = Prep2Cfg<TIO, D>::NBUF;
-    Frag* stage = Es + DPF;
     auto issue = [&](int c) {
         const size_t bhc = (size_t)bh * NC + c;
         Frag* buf = stage + (size_t)(c & (NBUF - 1)) * (KVF + DPF);
-        async_copy_tile<256, KVF>(reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(p.kt) + bhc * (size_t)CHUNK * D), buf, tid, wv);
-        async_copy_tile<256, DPF>(reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(p.dp) + bhc * (size_t)D * D), buf + KVF, tid, wv);
+        async_copy_tile<NT, KVF>(reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(p.kt) + bhc * (size_t)CHUNK * D), buf, tid, wv);
+        async_copy_tile<NT, DPF>(reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(p.dp) + bhc * (size_t)D * D), buf + KVF, tid, wv);
     };
     if (NBUF == 2) issue(clast);
     for (int c = clast; c >= c0; --c) {
@@ -75,125 +89,117 @@ __global__ __launch_bounds__(256) void prep2_fwd_kernel(FwdParams p) {
         }
         const Frag* k1 = stage + (size_t)(c & (NBUF - 1)) * (KVF + DPF);
         const Frag* dpn = k1 + KVF;                                                                                  // (rows b, contr a) = -dP[a][b]
-        Frag* k2 = reinterpret_cast<Frag*>(reinterpret_cast<T*>(p.kt2) + bhc * (size_t)CHUNK * D);
-        // (the transposed arrangement of the second-level keys: fp32 operands only, as for the chunk-level ones)
-        Frag* k2T = (BWD && p.kt2T && sizeof(T) == 4) ? reinterpret_cast<Frag*>(reinterpret_cast<T*>(p.kt2T) + bhc * (size_t)CHUNK * D) : nullptr;
-        if (BWD && sizeof(T) == 2) {      // backward only: R_c = I - E_c as a tile (rows a, contraction b)
-            Frag* rdst = reinterpret_cast<Frag*>(reinterpret_cast<T*>(p.rm) + bhc * (size_t)D * D);
 #pragma unroll
-            for (int o = 0; o < NE; ++o) {
-                const int blk = wv + 4 * o, bb = blk / DB, ab = blk % DB;
+        for (int b = 0; b < DB; ++b) pack_block<T>(Fm[b], Eb + b * SPB);
+        if (BWD) {      // backward only: R_c = I - E_c (16-bit operands: a tile with rows a, contraction b; fp32: row-major [a][b])
+#pragma unroll
+            for (int b = 0; b < DB; ++b) {
+                int diag = b == wv ? l32 - 4 * h : -1;
+                asm volatile("" : "+v"(diag));            // compared here: sixteen masks kept over the loop would spill
                 f32x16 rc;
 #pragma unroll
-                for (int jj = 0; jj < 16; ++jj)
-                    rc[jj] = (32 * ab + l32 == 32 * bb + acc_row(jj, h) ? 1.f : 0.f) - (c == clast ? 0.f : Fm[o][jj]);
-                Frag fr[SPB];
-                pack_block<T>(rc, fr);
+                for (int jj = 0; jj < 16; ++jj) rc[jj] = (acc_row(jj, 0) == diag ? 1.f : 0.f) - Fm[b][jj];
+                if (sizeof(T) == 2) {
+                    Frag* rdst = reinterpret_cast<Frag*>(reinterpret_cast<T*>(p.rm) + bhc * (size_t)D * D);
+                    Frag fr[SPB];
+                    pack_block<T>(rc, fr);
 #pragma unroll
-                for (int s2 = 0; s2 < SPB; ++s2) __builtin_nontemporal_store(fr[s2], &rdst[((size_t)ab * DS + bb * SPB + s2) * 64 + tile_lane<T>(lane, s2)]);
+                    for (int s2 = 0; s2 < SPB; ++s2) __builtin_nontemporal_store(fr[s2], &rdst[((size_t)wv * DS + b * SPB + s2) * 64 + tile_lane<T>(lane, s2)]);
+                } else {
+                    float* rdst = reinterpret_cast<float*>(p.rm) + bhc * (size_t)D * D + (size_t)(32 * wv + l32) * D + 32 * b + 4 * h;
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) *reinterpret_cast<f32x4*>(rdst + 8 * g) = f32x4{rc[4 * g], rc[4 * g + 1], rc[4 * g + 2], rc[4 * g + 3]};
+                }
             }
-        } else if (BWD) {                 // (fp32 operands: row-major [a][b])
-            typedef typename Tr<T>::Vec4 TVec4;
-            T* rdst = reinterpret_cast<T*>(p.rm) + bhc * (size_t)D * D;
+        }
+        // The products in groups of DS fragments (the two halves of the key tile, the DB row blocks of -dP), each group's
+        // read from LDS while the one before is multiplied; the scheduling barriers keep it to two groups in registers.
+        Frag f[2][DS], dfr[2][SPB];
+        auto read_group = [&](int g) {
+            const Frag* src = g < 2 ? k1 + (size_t)g * DS * 64 : dpn + (size_t)(g - 2) * DS * 64;
 #pragma unroll
-            for (int o = 0; o < NE; ++o) {
-                const int blk = wv + 4 * o, bb = blk / DB, ab = blk % DB;
-                const int a = 32 * ab + l32;
+            for (int s = 0; s < DS; ++s) f[g & 1][s] = src[s * 64 + tile_lane<T>(lane, s)];
 #pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    TVec4 o4;
+            for (int s2 = 0; s2 < SPB; ++s2) dfr[g & 1][s2] = src[(wv * SPB + s2) * 64 + tile_lane<T>(lane, s2)];
+        };
+        read_group(0);
+        // Kb2^T[cc][s] = Kb^T[cc][s] - sum_b E[cc][b] Kb[s][b]   (registers rows cc of the wave, lane s)
+        Frag* k2 = reinterpret_cast<Frag*>(reinterpret_cast<T*>(p.kt2) + bhc * (size_t)CHUNK * D);
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int b = 32 * bb + 8 * g + 4 * h + r;
-                        const float e = (c == clast) ? 0.f : Fm[o][4 * g + r];
-                        o4[r] = (T)((a == b ? 1.f : 0.f) - e);
+        for (int sb2 = 0; sb2 < 2; ++sb2) {
+            read_group(sb2 + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            f32x16 acc = zero16();
+#pragma unroll
+            for (int s = 0; s < DS; ++s) acc = Tr<T>::mma(Eb[s], f[sb2][s], acc);      // (last chunk: E = 0)
+            if (MODE == P2_CACHE) {
+                typedef typename Tr<TIO>::Vec4 OVec4;
+                const int tok = c * CHUNK + 32 * sb2 + l32;
+                if (tok < p.L) {
+                    TIO* dst = reinterpret_cast<TIO*>(p.kcache) + ((size_t)bh * p.Lmax + tok) * D + 32 * wv + 4 * h;
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) {
+                        OVec4 o4;
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            const int jj = 4 * g + r;
+                            o4[r] = (TIO)((float)dfr[sb2][jj / FE][jj % FE] - acc[jj]);
+                        }
+                        *reinterpret_cast<OVec4*>(dst + 8 * g) = o4;
                     }
-                    *reinterpret_cast<TVec4*>(rdst + (size_t)a * D + 32 * bb + 8 * g + 4 * h) = o4;
                 }
+                continue;
+            }
+            Frag fr[SPB];
+#pragma unroll
+            for (int s2 = 0; s2 < SPB; ++s2) {
+#pragma unroll
+                for (int e = 0; e < FE; ++e) fr[s2][e] = (T)((float)dfr[sb2][s2][e] - acc[s2 * FE + e]);
+            }
+#pragma unroll
+            for (int s2 = 0; s2 < SPB; ++s2) __builtin_nontemporal_store(fr[s2], &k2[((size_t)sb2 * DS + wv * SPB + s2) * 64 + tile_lane<T>(lane, s2)]);
+            if (BWD && sizeof(T) == 4) {     // backward with fp32 operands only: the arrangement (rows cc, contraction s)
+                Frag* k2T = reinterpret_cast<Frag*>(reinterpret_cast<T*>(p.kt2T) + bhc * (size_t)CHUNK * D);
+                const f32x16 tr = transpose32<T>(fr, idf);      // rows s, lane cc
+                Frag ft[SPB];
+                pack_block<T>(tr, ft);
+#pragma unroll
+                for (int s2 = 0; s2 < SPB; ++s2) __builtin_nontemporal_store(ft[s2], &k2T[((size_t)wv * (CHUNK / KW) + sb2 * SPB + s2) * 64 + lane]);
             }
         }
-        if (c == clast) {
-            for (int idx = tid; idx < CHUNK * D / FE; idx += 256) k2[idx] = k1[idx];
-            if (k2T) {
-                const Frag* k1T = reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(p.ktT) + bhc * (size_t)CHUNK * D);
-                for (int idx = tid; idx < CHUNK * D / FE; idx += 256) __builtin_nontemporal_store(k1T[idx], &k2T[idx]);
-            }
-        } else {
-            // Kb2^T[cc][s] = Kb^T[cc][s] - sum_b E[cc][b] Kb[s][b]   (registers rows cc, lane s)
-#pragma unroll
-            for (int o = 0; o < NK; ++o) {
-                const int blk = wv + 4 * o, cb = blk >> 1, sb2 = blk & 1;
-                f32x16 acc = zero16();
-#pragma unroll
-                for (int s = 0; s < DS; ++s) acc = Tr<T>::mma(Es[(cb * DS + s) * 64 + lane], k1[((size_t)sb2 * DS + s) * 64 + tile_lane<T>(lane, s)], acc);
-                Frag fr[SPB];
-#pragma unroll
-                for (int s2 = 0; s2 < SPB; ++s2) {
-                    const Frag kf = k1[((size_t)sb2 * DS + cb * SPB + s2) * 64 + tile_lane<T>(lane, s2)];
-#pragma unroll
-                    for (int e = 0; e < FE; ++e) fr[s2][e] = (T)((float)kf[e] - acc[s2 * FE + e]);
-                }
-#pragma unroll
-                for (int s2 = 0; s2 < SPB; ++s2) __builtin_nontemporal_store(fr[s2], &k2[((size_t)sb2 * DS + cb * SPB + s2) * 64 + tile_lane<T>(lane, s2)]);
-                if (k2T) {     // backward only: the arrangement (rows cc, contraction s)
-                    const f32x16 tr = transpose32<T>(fr, idf);      // rows s, lane cc
-                    Frag ft[SPB];
-                    pack_block<T>(tr, ft);
-#pragma unroll
-                    for (int s2 = 0; s2 < SPB; ++s2) __builtin_nontemporal_store(ft[s2], &k2T[((size_t)cb * (CHUNK / KW) + sb2 * SPB + s2) * 64 + lane]);
-                }
-            }
-        }
+        if (MODE == P2_CACHE && c == c0) break;
         // E^T <- E^T + dP^T - dP^T E^T   (registers rows b, lane a)
 #pragma unroll
-        for (int o = 0; o < NE; ++o) {
-            const int blk = wv + 4 * o, bb = blk / DB, ab = blk % DB;
+        for (int b = 0; b < DB; ++b) {
+            if (b + 1 < DB) read_group(b + 3);
+            __builtin_amdgcn_sched_barrier(0);
             f32x16 acc = zero16();
-            if (c != clast) {
 #pragma unroll
-                for (int s = 0; s < DS; ++s) acc = Tr<T>::mma(dpn[((size_t)bb * DS + s) * 64 + tile_lane<T>(lane, s)], Es[(ab * DS + s) * 64 + lane], acc);
-            }
+            for (int s = 0; s < DS; ++s) acc = Tr<T>::mma(f[b & 1][s], Eb[s], acc);
             // -dP[a][b] in this block's register layout (rows b, lane a): the tile piece (rows b,
             // contraction a) transposed through the matrix unit
-            Frag dfr[SPB];
+            const f32x16 dpT = transpose32<T>(dfr[b & 1], idf);
 #pragma unroll
-            for (int s2 = 0; s2 < SPB; ++s2) dfr[s2] = dpn[((size_t)bb * DS + ab * SPB + s2) * 64 + tile_lane<T>(lane, s2)];
-            const f32x16 dpT = transpose32<T>(dfr, idf);
-#pragma unroll
-            for (int jj = 0; jj < 16; ++jj) {
-                const float prev = (c == clast) ? 0.f : Fm[o][jj];
-                Fm[o][jj] = prev - dpT[jj] + acc[jj];
-            }
+            for (int jj = 0; jj < 16; ++jj) Fm[b][jj] = Fm[b][jj] - dpT[jj] + acc[jj];
+            __builtin_amdgcn_sched_barrier(0);
         }
-        __syncthreads();      // every read of the old operand copy is done
-        if (c > c0) {
-#pragma unroll
-            for (int o = 0; o < NE; ++o) {
-                const int blk = wv + 4 * o, bb = blk / DB, ab = blk % DB;
-                Frag fr[SPB];
-                pack_block<T>(Fm[o], fr);
-#pragma unroll
-                for (int s2 = 0; s2 < SPB; ++s2) Es[(ab * DS + bb * SPB + s2) * 64 + lane] = fr[s2];
-            }
-        }
-        __syncthreads();
     }
+    if (MODE == P2_CACHE) return;
     // -(I - P_superblock) as the sweep's tile (rows b, contraction a): E itself (rows a, lane b) is the
     // transpose of what the registers hold -- taken through the matrix unit.
     Frag* dst = reinterpret_cast<Frag*>(reinterpret_cast<T*>(p.dp2) + ((size_t)bh * nsb + sb) * (size_t)D * D);
 #pragma unroll
-    for (int o = 0; o < NE; ++o) {
-        const int blk = wv + 4 * o, bb = blk / DB, ab = blk % DB;
+    for (int b = 0; b < DB; ++b) {
         Frag fin[SPB];
-        pack_block<T>(Fm[o], fin);                              // tile piece (rows a, contraction b)
-        if (BWD && p.dpt2 && sizeof(T) == 4) {      // backward, fp32 operands only: -(I - P_superblock) in the arrangement (rows a, contraction b)
+        pack_block<T>(Fm[b], fin);                              // tile piece (rows a, contraction b)
+        if (BWD && sizeof(T) == 4) {      // backward, fp32 operands only: -(I - P_superblock) in the arrangement (rows a, contraction b)
             Frag* dt = reinterpret_cast<Frag*>(reinterpret_cast<T*>(p.dpt2) + ((size_t)bh * nsb + sb) * (size_t)D * D);
 #pragma unroll
             for (int s = 0; s < SPB; ++s) {
                 Frag ng;
 #pragma unroll
                 for (int e = 0; e < FE; ++e) ng[e] = (T)(-(float)fin[s][e]);
-                __builtin_nontemporal_store(ng, &dt[((size_t)ab * DS + bb * SPB + s) * 64 + lane]);
+                __builtin_nontemporal_store(ng, &dt[((size_t)wv * DS + b * SPB + s) * 64 + lane]);
             }
         }
         f32x16 tr = transpose32<T>(fin, idf);                   // rows a, lane b
@@ -202,27 +208,42 @@ __global__ __launch_bounds__(256) void prep2_fwd_kernel(FwdParams p) {
         Frag fr[SPB];
         pack_block<T>(tr, fr);
 #pragma unroll
-        for (int s = 0; s < SPB; ++s) __builtin_nontemporal_store(fr[s], &dst[((size_t)bb * DS + ab * SPB + s) * 64 + tile_lane<T>(lane, s)]);
+        for (int s = 0; s < SPB; ++s) __builtin_nontemporal_store(fr[s], &dst[((size_t)b * DS + wv * SPB + s) * 64 + tile_lane<T>(lane, s)]);
     }
 }
 
-template <typename TIO, int D, bool BWD>
-hipError_t launch_prep2_fwd_b(const FwdParams& p, hipStream_t stream) {
-    using C = Prep2Cfg<TIO, D>;
+template <typename TIO, int D, int MODE, int NBUF>
+hipError_t launch_prep2_b(const FwdParams& p, dim3 grid, hipStream_t stream) {
+    using C = Prep2Cfg<TIO, D, NBUF>;
     // set once per process; a function-local static is initialised under the language's own lock
-    static const hipError_t attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&prep2_fwd_kernel<TIO, D, BWD>),
+    static const hipError_t attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&prep2_fwd_kernel<TIO, D, MODE, NBUF>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::smem_bytes);
     if (attr_err != hipSuccess) return attr_err;
-    const int nsb = (p.NC + SBC - 1) / SBC - (BWD ? 1 : 0);      // (training: every super-block but the last)
-    if (nsb < 1) return hipSuccess;
-    dim3 grid(nsb, p.B * p.H);
-    const size_t bytes = C::smem_bytes;
-    hipLaunchKernelGGL((prep2_fwd_kernel<TIO, D, BWD>), grid, dim3(256), bytes, stream, p);
+    hipLaunchKernelGGL((prep2_fwd_kernel<TIO, D, MODE, NBUF>), grid, dim3(C::NT), C::smem_bytes, stream, p);
     return hipGetLastError();
+}
+template <typename TIO, int D, int MODE>
+hipError_t launch_prep2_m(const FwdParams& p, hipStream_t stream) {
+    const int BH = p.B * p.H, nsb = (p.NC + SBC - 1) / SBC - (MODE == P2_BWD ? 1 : 0);      // (training: every super-block but the last)
+    if (nsb < 1) return hipSuccess;
+    if constexpr (MODE == P2_CACHE) {
+        const dim3 grid(1 + value_row_pieces(p.L), BH);
+        return launch_prep2_b<TIO, D, MODE, sizeof(TIO) == 2 ? 2 : 1>(p, grid, stream);
+    } else {
+        const dim3 grid(nsb, BH);
+        // (fp32 operands: two stages of tiles do not fit)
+        if constexpr (sizeof(TIO) == 2) {
+            // one workgroup for every CU or less; above that the second workgroup hides more than the second stage does
+            // (one stage against two, us: d = 128, 128 workgroups 59 / 52, 192 59 / 50, 512 106 / 127; d = 64, 256 30 / 24, 384 47 / 50)
+            if ((long long)nsb * BH <= 256) return launch_prep2_b<TIO, D, MODE, 2>(p, grid, stream);
+        }
+        return launch_prep2_b<TIO, D, MODE, 1>(p, grid, stream);
+    }
 }
 template <typename TIO, int D>
 hipError_t launch_prep2_fwd_t(const FwdParams& p, hipStream_t stream) {
-    return p.rm ? launch_prep2_fwd_b<TIO, D, true>(p, stream) : launch_prep2_fwd_b<TIO, D, false>(p, stream);
+    if (p.kcache) return launch_prep2_m<TIO, D, P2_CACHE>(p, stream);
+    return p.rm ? launch_prep2_m<TIO, D, P2_BWD>(p, stream) : launch_prep2_m<TIO, D, P2_FWD>(p, stream);
 }
 
 hipError_t launch_prep2_fwd(const FwdParams& p, int d, int is_bf16, hipStream_t stream) {
