@@ -19,11 +19,13 @@
 //    refreshed cache is ordinary softmax attention.  Both happen in ONE pass over the key cache
 //    (read k, write k, read v: 3 n d elements per head -- HBM-bound), split over the cached
 //    positions; a second small kernel merges the splits, adds the arriving token's own key and
-//    value, and appends them to the caches.
+//    value, and appends them to the caches.  Short caches are not split: one kernel does it all.
 //
 //  * PaTH-FoX at decode time (Sec. 2.2 extension): with the running sums c_i of the log gates kept beside the
 //    caches, key i's logit gets c_t - c_i, c_t = c_{t-1} + log f_t; the arriving token's own logit gets nothing
 //    and its sum is appended (GATES instantiations of the two kernels).
+#include <type_traits>
+
 #include "path_common.h"
 #include "decode_decl.h"
 
@@ -134,21 +136,91 @@ __global__ __launch_bounds__(256) void key_prefill_kernel(PrefillArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------
-// One pass over the cached keys of a split: refresh, logit, online softmax, P V.
-// A key is handled by LPK = D/8 consecutive lanes (8 elements each); a wave takes 64/LPK keys
-// per round.  Partial results (m, l, o[D]) per split go to the workspace.
+// The last part of a step, by D threads (whole waves), thread c for component c: the arriving token's own key and value
+// join the cached keys' maximum M, row sum Ls and unnormalised output O; the caches grow by one.
 template <typename TIO, int D, bool GATES>
-__global__ __launch_bounds__(256) void decode_partial_kernel(DecodeArgs a) {
-    constexpr int LPK = D / 8, KPW = 64 / LPK, GROUPS = 4 * KPW;
+struct DecodeTail {
+    TIO kt, vt;
+    float qk, gate;
+    __device__ __forceinline__ void load(const DecodeArgs& a, int bh, int c) {
+        const TIO* q = reinterpret_cast<const TIO*>(a.q) + (size_t)bh * D;
+        const TIO* k = reinterpret_cast<const TIO*>(a.k) + (size_t)bh * D;
+        kt = k[c];
+        vt = reinterpret_cast<const TIO*>(a.v)[(size_t)bh * D + c];
+        qk = 0.f;
+#pragma unroll
+        for (int b = 0; b < D; b += 64) qk += (float)q[b + (c & 63)] * (float)k[b + (c & 63)];
+        // the token's running gate sum, which joins the cache (its own logit carries no gate)
+        gate = GATES ? (a.n > 0 ? a.ccache[(size_t)bh * a.Lmax + a.n - 1] : 0.f) + (float)reinterpret_cast<const TIO*>(a.log_f)[bh] : 0.f;
+    }
+    __device__ __forceinline__ void finish(const DecodeArgs& a, int bh, int c, float M, float Ls, float O) const {
+        float s_new = qk;
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) s_new += __shfl_xor(s_new, off);
+        s_new *= a.scale;
+        const float Mn = fmaxf(M, s_new);
+        const float old = M == -INFINITY ? 0.f : __expf(M - Mn), own = __expf(s_new - Mn);
+        Ls = Ls * old + own;
+        O = O * old + own * (float)vt;
+        reinterpret_cast<TIO*>(a.o)[(size_t)bh * D + c] = (TIO)(O / Ls);
+        if (c == 0) a.lse[bh] = Mn + __logf(Ls);
+        reinterpret_cast<TIO*>(a.kcache)[((size_t)bh * a.Lmax + a.n) * D + c] = kt;
+        reinterpret_cast<TIO*>(a.vcache)[((size_t)bh * a.Lmax + a.n) * D + c] = vt;
+        if (GATES && c == 0) a.ccache[(size_t)bh * a.Lmax + a.n] = gate;
+    }
+};
+
+// One pass over the cached keys of a split: refresh, logit, online softmax, P V.  DIRECT: the split is the whole head
+// and the workgroup ends the step itself; else partial results (m, l, o[D]) per split go to the workspace.
+// A key is handled by LPK = D/8 consecutive lanes (8 elements each); a wave takes 64/LPK keys at a time and UN such
+// rounds per step, whose rows it has requested a step ahead.  The sums over a key's lanes are DPP moves (a shuffle
+// through LDS costs its latency eight times per key).
+// What bounds it: HBM (3 n d elements per head), for few heads the latency of a step.  Values are read and refreshed
+// keys written past the caches' replacement (non-temporal), which leaves the Infinity Cache (256 MB) to the keys, the
+// one stream that is both read and written; the same hint on the key reads costs 15 %.  B=4, H=16, n=8192,
+// d=128: 96 -> 67 us (6.0 TB/s; without the hints 91); one sequence of 16 heads, n=32768: 116 -> 68.
+template <int LPK> __device__ __forceinline__ float group_sum(float x) {      // over the LPK lanes of a key, in all of them
+    static_assert(LPK == 8 || LPK == 16, "within a row of 16 lanes");
+    auto add = [&](auto ctrl) { x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), decltype(ctrl)::value, 0xf, 0xf, true)); };
+    add(std::integral_constant<int, 0xB1>{});                     // quad_perm [1,0,3,2]
+    add(std::integral_constant<int, 0x4E>{});                     // quad_perm [2,3,0,1]
+    add(std::integral_constant<int, 0x141>{});                    // row_half_mirror: the other quad of the eight
+    if (LPK == 16) add(std::integral_constant<int, 0x140>{});     // row_mirror: the other eight
+    return x;
+}
+
+template <typename TIO, int D, bool GATES, int NT, bool DIRECT>
+__global__ __launch_bounds__(NT) void decode_partial_kernel(DecodeArgs a) {
+    constexpr int LPK = D / 8, KPW = 64 / LPK, NW = NT / 64, UN = 4 / (int)sizeof(TIO), STEP = NW * UN * KPW;
     typedef TIO Vec8 __attribute__((ext_vector_type(8)));
-    __shared__ float red_m[GROUPS], red_l[GROUPS];
-    __shared__ float red_o[GROUPS][D];
+    __shared__ float red_m[NW], red_l[NW];
+    __shared__ float red_o[NW][D];
 
     const int split = blockIdx.x, bh = blockIdx.y, nsplit = gridDim.x;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int grp = lane / LPK, sub = lane % LPK;                 // key within the wave's round; 8-element slice
     const int n = a.n;
     const int i_begin = (int)((long long)n * split / nsplit), i_end = (int)((long long)n * (split + 1) / nsplit);
+
+    TIO* kc = reinterpret_cast<TIO*>(a.kcache) + (size_t)bh * a.Lmax * D + 8 * sub;
+    const TIO* vc = reinterpret_cast<const TIO*>(a.vcache) + (size_t)bh * a.Lmax * D + 8 * sub;
+    const float* cc = GATES ? a.ccache + (size_t)bh * a.Lmax : nullptr;
+    Vec8 kn[UN], vn[UN];                              // the next step's rows, requested a step ahead
+    float cn[UN];
+    auto request = [&](int i0) {                      // (positions past the end repeat the last one)
+#pragma unroll
+        for (int r = 0; r < UN; ++r) {
+            int i = i0 + r * KPW + grp;
+            i = i < i_end ? i : i_end - 1;
+            kn[r] = *reinterpret_cast<const Vec8*>(kc + (size_t)i * D);
+            vn[r] = __builtin_nontemporal_load(reinterpret_cast<const Vec8*>(vc + (size_t)i * D));
+            cn[r] = GATES ? cc[i] : 0.f;
+        }
+    };
+    int i0 = i_begin + wv * (UN * KPW);
+    if (i0 < i_end) request(i0);
+    DecodeTail<TIO, D, GATES> tail;
+    if (DIRECT && tid < D) tail.load(a, bh, tid);
 
     float q8[8], w8[8];
     {
@@ -158,112 +230,134 @@ __global__ __launch_bounds__(256) void decode_partial_kernel(DecodeArgs a) {
         for (int e = 0; e < 8; ++e) { q8[e] = (float)qv[e]; w8[e] = (float)wv8[e]; }
     }
     const float beta = (float)reinterpret_cast<const TIO*>(a.beta)[bh];
-    const float* cc = GATES ? a.ccache + (size_t)bh * a.Lmax : nullptr;
     const float c_t = GATES ? (n > 0 ? cc[n - 1] : 0.f) + (float)reinterpret_cast<const TIO*>(a.log_f)[bh] : 0.f;
-    auto group_sum = [&](float x) {
-#pragma unroll
-        for (int off = 1; off < LPK; off <<= 1) x += __shfl_xor(x, off);
-        return x;
-    };
-
-    TIO* kc = reinterpret_cast<TIO*>(a.kcache) + (size_t)bh * a.Lmax * D + 8 * sub;
-    const TIO* vc = reinterpret_cast<const TIO*>(a.vcache) + (size_t)bh * a.Lmax * D + 8 * sub;
     float m = -INFINITY, l = 0.f, acc[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[e] = 0.f;
 
-    for (int i0 = i_begin + wv * KPW; i0 < i_end; i0 += GROUPS) {
-        const int i = i0 + grp;
-        const bool ok = i < i_end;
-        float k8[8], v8[8];
-        if (ok) {
-            const Vec8 kv = *reinterpret_cast<const Vec8*>(kc + (size_t)i * D);
-            const Vec8 vv = *reinterpret_cast<const Vec8*>(vc + (size_t)i * D);
+    for (; i0 < i_end; i0 += STEP) {
+        Vec8 kv[UN], vv[UN];
+        float ci[UN], s[UN];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) { k8[e] = (float)kv[e]; v8[e] = (float)vv[e]; }
-        } else {
+        for (int r = 0; r < UN; ++r) { kv[r] = kn[r]; vv[r] = vn[r]; ci[r] = cn[r]; }
+        if (i0 + STEP < i_end) request(i0 + STEP);
+        float wk[UN];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) { k8[e] = 0.f; v8[e] = 0.f; }
+        for (int r = 0; r < UN; ++r) {
+            wk[r] = 0.f;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) wk[r] += w8[e] * (float)kv[r][e];
         }
-        float wk = 0.f;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) wk += w8[e] * k8[e];
-        wk = group_sum(wk);
-        // refreshed key, rounded to the cache's storage type: the stored value is the state, and
+        for (int r = 0; r < UN; ++r) wk[r] = group_sum<LPK>(wk[r]);
+        // refreshed keys, rounded to the cache's storage type: the stored value is the state, and
         // the logit is taken against it
-        Vec8 kn;
-        float qk = 0.f;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            kn[e] = (TIO)(k8[e] - beta * wk * w8[e]);
-            qk += q8[e] * (float)kn[e];
+        for (int r = 0; r < UN; ++r) {
+            const int i = i0 + r * KPW + grp;
+            s[r] = 0.f;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                kv[r][e] = (TIO)((float)kv[r][e] - beta * wk[r] * w8[e]);
+                s[r] += q8[e] * (float)kv[r][e];
+            }
+            if (i < i_end) __builtin_nontemporal_store(kv[r], reinterpret_cast<Vec8*>(kc + (size_t)i * D));
         }
-        qk = group_sum(qk);
-        if (ok) {
-            *reinterpret_cast<Vec8*>(kc + (size_t)i * D) = kn;
-            const float s = GATES ? a.scale * qk + (c_t - cc[i]) : a.scale * qk;
-            const float mn = fmaxf(m, s);
-            const float alpha = __expf(m - mn), pr = __expf(s - mn);      // m = -inf first time: alpha = 0
-            l = l * alpha + pr;
+        float mn = m;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) acc[e] = acc[e] * alpha + pr * v8[e];
-            m = mn;
+        for (int r = 0; r < UN; ++r) {
+            s[r] = a.scale * group_sum<LPK>(s[r]);
+            if (GATES) s[r] += c_t - ci[r];
+            if (i0 + r * KPW + grp >= i_end) s[r] = -INFINITY;
+            mn = fmaxf(mn, s[r]);
+        }
+        const float ref = mn == -INFINITY ? 0.f : mn;             // nothing yet: every weight below is exp(-inf)
+        const float alpha = __expf(m - ref);
+        m = mn;
+        l *= alpha;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[e] *= alpha;
+#pragma unroll
+        for (int r = 0; r < UN; ++r) {
+            const float pr = __expf(s[r] - ref);
+            l += pr;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) acc[e] += pr * (float)vv[r][e];
         }
     }
-    // merge the lane groups of the workgroup
-    const int g = wv * KPW + grp;
-    if (sub == 0) { red_m[g] = m; red_l[g] = l; }
+    // merge the keys of the wave's lanes, then the waves
+    {
+        float M = m;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) red_o[g][8 * sub + e] = acc[e];
+        for (int off = LPK; off < 64; off <<= 1) M = fmaxf(M, __shfl_xor(M, off));
+        const float sc = m == -INFINITY ? 0.f : __expf(m - M);
+        l *= sc;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[e] *= sc;
+#pragma unroll
+        for (int off = LPK; off < 64; off <<= 1) {
+            l += __shfl_xor(l, off);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) acc[e] += __shfl_xor(acc[e], off);
+        }
+        if (lane == 0) { red_m[wv] = M; red_l[wv] = l; }
+        if (grp == 0) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) red_o[wv][8 * sub + e] = acc[e];
+        }
+    }
     __syncthreads();
-    if (tid < D) {
-        float M = -INFINITY;
-        for (int gg = 0; gg < GROUPS; ++gg) M = fmaxf(M, red_m[gg]);
-        float Ls = 0.f, O = 0.f;
-        for (int gg = 0; gg < GROUPS; ++gg) {
-            const float sc = (red_m[gg] == -INFINITY) ? 0.f : __expf(red_m[gg] - M);
-            Ls += red_l[gg] * sc;
-            O += red_o[gg][tid] * sc;
-        }
-        float* part = a.partial + ((size_t)bh * nsplit + split) * (D + 2);
-        part[2 + tid] = O;
-        if (tid == 0) { part[0] = M; part[1] = Ls; }
+    if (tid >= D) return;
+    float M = -INFINITY;
+#pragma unroll
+    for (int g = 0; g < NW; ++g) M = fmaxf(M, red_m[g]);
+    float Ls = 0.f, O = 0.f;
+#pragma unroll
+    for (int g = 0; g < NW; ++g) {
+        const float sc = red_m[g] == -INFINITY ? 0.f : __expf(red_m[g] - M);
+        Ls += red_l[g] * sc;
+        O += red_o[g][tid] * sc;
     }
+    if (DIRECT) { tail.finish(a, bh, tid, M, Ls, O); return; }
+    float* part = a.partial + ((size_t)bh * nsplit + split) * (D + 2);
+    part[2 + tid] = O;
+    if (tid == 0) { part[0] = M; part[1] = Ls; }
 }
 
-// Merge the splits, add the arriving token's own key/value, normalise; append to the caches.
+// Merge the splits (at most 64: lane s holds the maximum and the row sum of split s), then the step's last part.
 template <typename TIO, int D, bool GATES>
 __global__ __launch_bounds__(D) void decode_combine_kernel(DecodeArgs a, int nsplit) {
-    __shared__ float sq[D];
-    const int bh = blockIdx.x, c = threadIdx.x;
-    const float qc = (float)reinterpret_cast<const TIO*>(a.q)[(size_t)bh * D + c];
-    const TIO kt = reinterpret_cast<const TIO*>(a.k)[(size_t)bh * D + c];
-    const TIO vt = reinterpret_cast<const TIO*>(a.v)[(size_t)bh * D + c];
-    sq[c] = qc * (float)kt;
-    __syncthreads();
-    for (int off = D / 2; off > 0; off >>= 1) {
-        if (c < off) sq[c] += sq[c + off];
-        __syncthreads();
-    }
-    const float s_new = a.scale * sq[0];
+    static_assert(DECODE_MAX_SPLITS <= 64, "one split per lane");
+    constexpr int NB = 16;                            // outputs of so many splits requested at once
+    const int bh = blockIdx.x, c = threadIdx.x, lane = c & 63;
     const float* part = a.partial + (size_t)bh * nsplit * (D + 2);
-    float M = s_new;
-    for (int s = 0; s < nsplit; ++s) M = fmaxf(M, part[(size_t)s * (D + 2)]);
-    float Ls = __expf(s_new - M), O = Ls * (float)vt;
-    for (int s = 0; s < nsplit; ++s) {
-        const float ms = part[(size_t)s * (D + 2)];
-        const float sc = (ms == -INFINITY) ? 0.f : __expf(ms - M);
-        Ls += part[(size_t)s * (D + 2) + 1] * sc;
-        O += part[(size_t)s * (D + 2) + 2 + c] * sc;
+    float on[NB];
+    auto request = [&](int s0) {                      // (splits past the last one repeat it, with weight zero)
+#pragma unroll
+        for (int r = 0; r < NB; ++r) on[r] = part[(size_t)(s0 + r < nsplit ? s0 + r : nsplit - 1) * (D + 2) + 2 + c];
+    };
+    const float ms = lane < nsplit ? part[(size_t)lane * (D + 2)] : -INFINITY;
+    float Ls = lane < nsplit ? part[(size_t)lane * (D + 2) + 1] : 0.f;
+    request(0);
+    DecodeTail<TIO, D, GATES> tail;
+    tail.load(a, bh, c);
+    float M = ms;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) M = fmaxf(M, __shfl_xor(M, off));
+    const float wt = ms == -INFINITY ? 0.f : __expf(ms - M);
+    Ls *= wt;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) Ls += __shfl_xor(Ls, off);
+    float O = 0.f;
+    for (int s0 = 0; s0 < nsplit; s0 += NB) {
+        float oc[NB];
+#pragma unroll
+        for (int r = 0; r < NB; ++r) oc[r] = on[r];
+        if (s0 + NB < nsplit) request(s0 + NB);
+#pragma unroll
+        for (int r = 0; r < NB; ++r) O += oc[r] * __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wt), s0 + r));
     }
-    reinterpret_cast<TIO*>(a.o)[(size_t)bh * D + c] = (TIO)(O / Ls);
-    if (c == 0) a.lse[bh] = M + __logf(Ls);
-    reinterpret_cast<TIO*>(a.kcache)[((size_t)bh * a.Lmax + a.n) * D + c] = kt;
-    reinterpret_cast<TIO*>(a.vcache)[((size_t)bh * a.Lmax + a.n) * D + c] = vt;
-    if (GATES && c == 0) {      // the arriving token's running gate sum joins the cache (its own logit carries no gate)
-        float* cc = a.ccache + (size_t)bh * a.Lmax;
-        cc[a.n] = (a.n > 0 ? cc[a.n - 1] : 0.f) + (float)reinterpret_cast<const TIO*>(a.log_f)[bh];
-    }
+    tail.finish(a, bh, c, M, Ls, O);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -281,18 +375,33 @@ hipError_t launch_key_prefill(const PrefillArgs& a, int BH, int d, int is_bf16, 
     return d == 64 ? launch_prefill_t<float, 64>(a, BH, st) : launch_prefill_t<float, 128>(a, BH, st);
 }
 
+// Splits of the cached positions.  About four workgroups per CU: three rows per 16 lanes in flight in each of their
+// 16 waves cover the latency of HBM (two per CU: 3 % slower at B=4, H=16, n=8192, eight: the same).  At least 64 keys
+// each: with 32 a single sequence of 16 heads takes 13.1 us for 2000 keys against 12.0, with 128 10.7 against 9.6 for
+// 1000 (d = 128).
 int decode_num_splits(int BH, int n) {
-    int s = (1024 + BH - 1) / BH;                 // about four workgroups per CU
+    int s = (1024 + BH - 1) / BH;
     if (s > DECODE_MAX_SPLITS) s = DECODE_MAX_SPLITS;
-    const int by_len = (n + 127) / 128;           // at least ~128 keys per split
+    const int by_len = (n + 63) / 64;
     if (s > by_len) s = by_len;
     return s < 1 ? 1 : s;
 }
 
+// Heads of up to 128 KB of keys are not split: one workgroup, one launch.  On the GPU the split pays from about 64 KB
+// on, where one CU's share of the memory bandwidth starts to count -- 16 heads of 200 keys, d = 128 (51 KB) 6.9 us against
+// 8.2 split and merged, 16 heads of 500 (128 KB) 11.0 against 9.0 -- but a launch costs the host about 3 us and a step
+// that short is bound by it: called one after the other, steps of 500 keys take 11.9 us against 14.7.  At 256 KB the
+// one workgroup takes 17.9 us, the two launches 14.5.  Up to 128 keys four waves do: 512 heads of 100 keys, d = 64,
+// 7.9 us against 10.7 with sixteen.
 template <typename TIO, int D, bool GATES>
 static hipError_t launch_decode_g(const DecodeArgs& a, int BH, hipStream_t st) {
+    if ((size_t)a.n * D * sizeof(TIO) <= 131072) {
+        if (a.n <= 128) hipLaunchKernelGGL((decode_partial_kernel<TIO, D, GATES, 256, true>), dim3(1, BH), dim3(256), 0, st, a);
+        else hipLaunchKernelGGL((decode_partial_kernel<TIO, D, GATES, 1024, true>), dim3(1, BH), dim3(1024), 0, st, a);
+        return hipGetLastError();
+    }
     const int nsplit = decode_num_splits(BH, a.n);
-    hipLaunchKernelGGL((decode_partial_kernel<TIO, D, GATES>), dim3(nsplit, BH), dim3(256), 0, st, a);
+    hipLaunchKernelGGL((decode_partial_kernel<TIO, D, GATES, 256, false>), dim3(nsplit, BH), dim3(256), 0, st, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((decode_combine_kernel<TIO, D, GATES>), dim3(BH), dim3(D), 0, st, a, nsplit);
