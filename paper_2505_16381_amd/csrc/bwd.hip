@@ -109,7 +109,7 @@ __global__ __launch_bounds__(256) void bwd_dotile_kernel(BwdParams p) {
 // After step j the state is also written, transposed through the matrix unit, as the tile
 // gT (rows b, contraction q) of pair (cq, j+1) for the key-side kernels.
 // This kernel runs fp32 operands (one workgroup per CU, one stage of tiles); 16-bit operands use
-// bwd_adjoint2_lite_kernel below (two workgroups per CU).
+// bwd_adjoint2_lite_kernel below (two workgroups per CU) or bwd_adjoint_kernel.
 template <typename TIO, int D> struct Adj2Cfg {
     typedef typename Compute<TIO>::type T;
     static constexpr int FE = Tr<T>::FE;
@@ -308,7 +308,8 @@ __global__ __launch_bounds__(256) void bwd_adjoint2_kernel(BwdParams p) {
 }
 
 // ---------------------------------------------------------------------------------------
-// The adjoint scan for 16-bit operands with TWO workgroups per CU: the same arithmetic as
+// The adjoint scan for 16-bit operands, d = 64 and short sequences (d = 128, more than eight chunks: bwd_adjoint.hip, to
+// the same bits), with TWO workgroups per CU: the same arithmetic as
 // bwd_adjoint2_kernel, arranged to fit 256 registers per wave and one 80 KB stage per workgroup, so that
 // the second workgroup's waves fill the gaps of the first (tile requests, LDS latencies, the dependent
 // chain logits -> exponentials -> update) instead of hand-interleaved halves of one wave.  Per step: one
@@ -1084,9 +1085,16 @@ static hipError_t launch_scan_t(const BwdParams& p, int stages, hipStream_t st) 
             if ((e = set_smem<&bwd_adjoint2_kernel<TIO, D, FOX>>(bytes)) != hipSuccess) return e;
             hipLaunchKernelGGL((bwd_adjoint2_kernel<TIO, D, FOX>), grid_adj, dim3(256), bytes, st, p);
         } else {
-            const size_t bytes = (size_t)(2 * Adj2Cfg<TIO, D>::KV_FRAGS + Adj2Cfg<TIO, D>::DP_FRAGS) * 16;      // kt | vk | dpt
-            if ((e = set_smem<&bwd_adjoint2_lite_kernel<TIO, D, FOX>>(bytes)) != hipSuccess) return e;
-            hipLaunchKernelGGL((bwd_adjoint2_lite_kernel<TIO, D, FOX>), grid_adj, dim3(256), bytes, st, p);
+            // d = 128 from nine chunks on: eight waves split by kind of work (bwd_adjoint.hip).  Training step with 2 and with
+            // 128 heads: 4096 tokens 596 -> 591 us and 5650 -> 5583, 1024 tokens 187 -> 186 and 930 -> 922, but 512
+            // tokens 119 -> 124 and 385 -> 382, 256 tokens 88 -> 92 and 177 -> 179: short chains feel the half-step it lags.
+            if (D == 128 && p.NC > 8) {
+                if ((e = launch_bwd_adjoint(p, st)) != hipSuccess) return e;
+            } else {
+                const size_t bytes = (size_t)(2 * Adj2Cfg<TIO, D>::KV_FRAGS + Adj2Cfg<TIO, D>::DP_FRAGS) * 16;      // kt | vk | dpt
+                if ((e = set_smem<&bwd_adjoint2_lite_kernel<TIO, D, FOX>>(bytes)) != hipSuccess) return e;
+                hipLaunchKernelGGL((bwd_adjoint2_lite_kernel<TIO, D, FOX>), grid_adj, dim3(256), bytes, st, p);
+            }
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }

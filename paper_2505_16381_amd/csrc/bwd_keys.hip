@@ -40,15 +40,6 @@ template <typename TIO, int D> struct FarCfg {
     static_assert(smem_bytes <= 160 * 1024, "LDS budget");
 };
 
-// This wave's LDS writes are done; then everybody's.  Loads and direct-to-LDS copies stay in flight.
-__device__ __forceinline__ void lds_barrier() {
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-}
-// This wave's direct-to-LDS copies have landed.
-__device__ __forceinline__ void copies_landed() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-
 template <typename TIO, int D, bool FOX>
 __global__ __launch_bounds__(512, 2) void bwd_far_kernel(BwdParams p) {
     using C = FarCfg<TIO, D>;

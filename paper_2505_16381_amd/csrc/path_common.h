@@ -293,6 +293,15 @@ __device__ __forceinline__ void wait_async_and_sync() {
     __syncthreads();
 }
 
+// This wave's LDS writes are done; then everybody's.  Loads and direct-to-LDS copies stay in flight.
+__device__ __forceinline__ void lds_barrier() {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+// This wave's direct-to-LDS copies have landed.
+__device__ __forceinline__ void copies_landed() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // Identity operand for transposing a 32x32 block through the matrix unit: with the block given as
 // an A operand (rows r, contraction k; i.e. packed from accumulators that hold it as rows k, lane r),
 // D = A * I comes out with rows r, lane k -- the transposed register layout.  Slab s of the identity
