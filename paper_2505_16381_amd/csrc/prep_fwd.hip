@@ -33,36 +33,41 @@ template <typename TIO, int D> struct PrepCfg {
     // Q and K are not staged: their operand fragments come straight from global memory (the chunk's rows are
     // read a few times, out of L2), converted to the operand type on the way.
     //
-    // 2-byte operands use a compact map (81 KB: TWO workgroups per CU, so that the barriers and the
-    // half-empty phases of one overlap the work of the other -- the kernel is a chain of short dependent
-    // phases, not a stream): U^T has the space a transposed copy of W would take; where it is large enough
-    // (d = 128) the fp32 inverse A^{-1} lives there before U^T is written; F, needed only by the output phase,
-    // is computed there and takes the place of the fp32 matrix A, which is dead by then.
+    // 2-byte operands use a compact map (50 KB at d = 64: THREE workgroups per CU; 67 KB at d = 128: two), so that the
+    // barriers and the half-empty phases of one overlap the work of the others -- the kernel is a chain of short dependent
+    // phases, not a stream.  W | Gk | U^T | Y^T | N | helper of the inverse, and in turn: the fp32 matrix A and its
+    // inverse, their three 32x32 blocks, lie where U^T, Y^T and N come to lie when they are done with (N passes
+    // through registers); F, needed only by the output phase, is computed there in place of Gk.  (With the
+    // inverse beside the rest, 79 KB and two workgroups per CU at d = 64: forward at B=8, H=16, L=2048 305 us against 281,
+    // training step at L=4096 2.92 ms against 2.87; the same at d = 128.)
     // fp32 operands keep separate blocks (N overwrites A^{-1} in place; one workgroup per CU).
     static constexpr bool COMPACT = sizeof(T) == 2;
+    static constexpr int LDB = COMPACT ? LDH : LDA;    // pitch of the 32x32 blocks of A and A^{-1}
+    static constexpr int BLK21 = COMPACT ? 32 * LDH : 32 * LDA, BLK22 = COMPACT ? 2 * 32 * LDH : 32 * LDA + 32;     // their places
     static constexpr int WSUT = COMPACT ? CHUNK * LDD : ((CHUNK * LDD > D * LDC) ? CHUNK * LDD : D * LDC);   // fp32: U^T re-uses W's rows
     // element offsets (in T) -- every block is a multiple of 16 bytes
     static constexpr size_t off_ws = 0;                               // W rows (fp32: later U^T)
-    static constexpr size_t off_wt = off_ws + WSUT;                   // fp32: W^T; 2-byte: U^T
-    static constexpr size_t off_f_sep = off_wt + (size_t)D * LDC;     // F (fp32 map)
-    static constexpr size_t off_gk = COMPACT ? off_wt + (size_t)D * LDC : off_f_sep + (size_t)CHUNK * LDC;     // (strictLower(W K^T))^T
-    static constexpr size_t off_yt = off_gk + (size_t)CHUNK * LDC;    // Y^T
+    static constexpr size_t off_gk = COMPACT ? off_ws + WSUT : off_ws + WSUT + (size_t)D * LDC + (size_t)CHUNK * LDC;     // (strictLower(W K^T))^T
+    static constexpr size_t off_wt = COMPACT ? off_gk + (size_t)CHUNK * LDC : off_ws + WSUT;    // fp32: W^T; 2-byte: U^T
+    static constexpr size_t off_f = COMPACT ? off_gk : off_wt + (size_t)D * LDC;                // F (2-byte: in Gk's place, from phase 4 on)
+    static constexpr size_t off_yt = COMPACT ? off_wt + (size_t)D * LDC : off_gk + (size_t)CHUNK * LDC;    // Y^T
     static constexpr size_t off_nt = off_yt + (size_t)CHUNK * LDC;    // N (operand precision)
     static constexpr bool NT_IN_XF = sizeof(T) == 4;                  // fp32: N overwrites A^{-1} in place (same shape)
     static constexpr size_t t_elems = off_nt + (NT_IN_XF ? 0 : (size_t)CHUNK * LDC);
-    static constexpr size_t off_af_bytes = ((t_elems * sizeof(T) + 15) / 16) * 16;   // fp32 A / solve
-    static constexpr size_t off_f = COMPACT ? off_af_bytes / sizeof(T) : off_f_sep;  // F (2-byte: in A's place, from phase 4 on)
-    static constexpr size_t off_beta_bytes = off_af_bytes + (size_t)CHUNK * LDA * 4;
-    static constexpr bool XF_IN_UT = COMPACT && (size_t)D * LDC * sizeof(T) >= (size_t)CHUNK * LDA * 4;
-    static constexpr size_t off_xf_bytes = XF_IN_UT ? off_wt * sizeof(T) : off_beta_bytes + CHUNK * 4;   // A^{-1}, fp32 [64][LDA]
-    // the two 32x32 fp32 helpers live in Y^T's space (Y^T is written only after the inverse is done)
-    static constexpr size_t off_xt1_bytes = off_yt * sizeof(T);                       // (A^{-1})_11^T
-    static constexpr size_t off_tt_bytes = off_xt1_bytes + (size_t)32 * LDH * 4;      // (A_21 (A^{-1})_11)^T
-    static_assert(2 * 32 * LDH * 4 <= CHUNK * LDC * sizeof(T), "helpers must fit in Y^T");
-    static_assert(!COMPACT || (size_t)CHUNK * LDC * sizeof(T) <= (size_t)CHUNK * LDA * 4, "F must fit in A's place");
-    static constexpr size_t smem_bytes = XF_IN_UT ? off_beta_bytes + CHUNK * 4 : off_xf_bytes + (size_t)CHUNK * LDA * 4;
-    static_assert(!COMPACT || smem_bytes <= 80 * 1024, "two workgroups per CU");
-    static constexpr int WGS_PER_CU = COMPACT ? 2 : 1;
+    static constexpr size_t t_bytes = ((t_elems * sizeof(T) + 15) / 16) * 16;
+    static constexpr size_t a_bytes = COMPACT ? 3 * 32 * LDH * 4 : (size_t)CHUNK * LDA * 4;
+    static constexpr size_t off_af_bytes = COMPACT ? off_wt * sizeof(T) : t_bytes;                // fp32 A / solve
+    static constexpr size_t off_beta_bytes = COMPACT ? t_bytes + (size_t)32 * LDH * 4 : off_af_bytes + a_bytes;
+    static constexpr size_t off_xf_bytes = COMPACT ? off_af_bytes + a_bytes : off_beta_bytes + CHUNK * 4;   // A^{-1}, fp32
+    // the two 32x32 fp32 helpers: (A^{-1})_11^T and (A_21 (A^{-1})_11)^T; 2-byte operands: one place, the second takes
+    // the first's, fp32: in Y^T's space (Y^T is written only after the inverse is done)
+    static constexpr size_t off_xt1_bytes = COMPACT ? t_bytes : off_yt * sizeof(T);
+    static constexpr size_t off_tt_bytes = COMPACT ? off_xt1_bytes : off_xt1_bytes + (size_t)32 * LDH * 4;
+    static_assert(COMPACT || 2 * 32 * LDH * 4 <= CHUNK * LDC * sizeof(T), "helpers must fit in Y^T");
+    static_assert(!COMPACT || off_xf_bytes + a_bytes <= t_bytes, "A and its inverse lie in U^T, Y^T and N");
+    static constexpr size_t smem_bytes = COMPACT ? off_beta_bytes + CHUNK * 4 : off_xf_bytes + a_bytes;
+    static constexpr int WGS_PER_CU = COMPACT ? (D == 64 ? 3 : 2) : 1;
+    static_assert(!COMPACT || WGS_PER_CU * smem_bytes <= 160 * 1024, "LDS budget");
 };
 
 // BWD: also write the backward-only outputs (all of them; their pointers are set).  A compile-time
@@ -96,7 +101,7 @@ __global__ __launch_bounds__(256, (PrepCfg<TIO, D>::WGS_PER_CU)) void prep_fwd_k
     float* Xf = reinterpret_cast<float*>(smem + C::off_xf_bytes);
     float* XT1 = reinterpret_cast<float*>(smem + C::off_xt1_bytes);
     float* TT = reinterpret_cast<float*>(smem + C::off_tt_bytes);
-    constexpr int LDH = C::LDH;
+    constexpr int LDH = C::LDH, LDB = C::LDB, BLK21 = C::BLK21, BLK22 = C::BLK22;
     constexpr bool COMPACT = C::COMPACT;
 
     int chunk, bh;
@@ -224,7 +229,8 @@ __global__ __launch_bounds__(256, (PrepCfg<TIO, D>::WGS_PER_CU)) void prep_fwd_k
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
             const int t = 32 * bi + acc_row(j, h);
-            Af[t * LDA + s] = (s < t) ? bs[t] * acc[j] : 0.f;
+            if (!COMPACT) Af[t * LDA + s] = (s < t) ? bs[t] * acc[j] : 0.f;
+            else if (bi >= bj) Af[(bi + bj) * BLK21 + (t & 31) * LDB + l32] = (s < t) ? bs[t] * acc[j] : 0.f;
             if (BWD && p.gm) p.gm[bhc * 4096 + t * 64 + s] = acc[j];
         }
     }
@@ -263,7 +269,7 @@ __global__ __launch_bounds__(256, (PrepCfg<TIO, D>::WGS_PER_CU)) void prep_fwd_k
     // block X_21 = -X_22 (A_21 X_11) by two fp32 MFMA products.
     if (wv < 2) {
         if (lane < 32) {
-            const int r0 = 32 * wv, c = lane;
+            const int c = lane, r0 = wv ? BLK22 : 0;       // the wave's diagonal block
             float n[32];
 #pragma unroll
             for (int t = 0; t < 32; ++t) n[t] = 0.f;
@@ -272,7 +278,7 @@ __global__ __launch_bounds__(256, (PrepCfg<TIO, D>::WGS_PER_CU)) void prep_fwd_k
                 float a0 = (t == c) ? 1.f : 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
 #pragma unroll
                 for (int s4 = 0; s4 < (t + 3) / 4; ++s4) {
-                    const f32x4 a4 = *reinterpret_cast<const f32x4*>(Af + (r0 + t) * LDA + r0 + 4 * s4);   // zeros for s >= t
+                    const f32x4 a4 = *reinterpret_cast<const f32x4*>(Af + r0 + t * LDB + 4 * s4);   // zeros for s >= t
                     a0 -= a4[0] * n[4 * s4 + 0];
                     a1 -= a4[1] * n[4 * s4 + 1];
                     a2 -= a4[2] * n[4 * s4 + 2];
@@ -280,16 +286,16 @@ __global__ __launch_bounds__(256, (PrepCfg<TIO, D>::WGS_PER_CU)) void prep_fwd_k
                 }
                 const float acc = (a0 + a1) + (a2 + a3);
                 n[t] = acc;
-                Xf[(r0 + t) * LDA + r0 + c] = acc;
+                Xf[r0 + t * LDB + c] = acc;
                 if (wv == 0) XT1[c * LDH + t] = acc;
             }
         }
-    } else if (wv == 2) {
+    } else if (!COMPACT && wv == 2) {
         for (int idx = lane; idx < 32 * 32; idx += 64) Xf[(idx >> 5) * LDA + 32 + (idx & 31)] = 0.f;   // upper-right block
     }
     __syncthreads();
     if (wv == 0) {      // T = A_21 X_11, stored transposed
-        f32x16 acc = gemm32<float, 32>(Af + 32 * LDA, LDA, 0, XT1, LDH, 0, l32, h, zero16());
+        f32x16 acc = gemm32<float, 32>(Af + BLK21, LDB, 0, XT1, LDH, 0, l32, h, zero16());
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
             f32x4 v4;
@@ -300,16 +306,28 @@ __global__ __launch_bounds__(256, (PrepCfg<TIO, D>::WGS_PER_CU)) void prep_fwd_k
     }
     __syncthreads();
     if (wv == 0) {      // X_21 = -X_22 T
-        f32x16 acc = gemm32<float, 32>(Xf + 32 * LDA + 32, LDA, 0, TT, LDH, 0, l32, h, zero16());
+        f32x16 acc = gemm32<float, 32>(Xf + BLK22, LDB, 0, TT, LDH, 0, l32, h, zero16());
 #pragma unroll
-        for (int j = 0; j < 16; ++j) Xf[(32 + acc_row(j, h)) * LDA + l32] = -acc[j];
+        for (int j = 0; j < 16; ++j) Xf[BLK21 + acc_row(j, h) * LDB + l32] = -acc[j];
     }
     __syncthreads();
-    for (int idx = tid; idx < CHUNK * CHUNK; idx += 256) {
-        const int t = idx >> 6, c = idx & 63;
-        const float x = Xf[t * LDA + c];
-        Nt[t * LDC + c] = (T)(x * bs[c]);
-        if (BWD && p.aim) reinterpret_cast<T*>(p.aim)[bhc * 4096 + idx] = (T)x;
+    {
+        constexpr int NX = CHUNK * CHUNK / 256;
+        float x[NX];
+        const int c = tid & 63;
+#pragma unroll
+        for (int it = 0; it < NX; ++it) {
+            const int t = (tid >> 6) + 4 * it, tb = it / (NX / 2), cb = c >> 5;
+            if (!COMPACT) x[it] = Xf[t * LDA + c];
+            else x[it] = tb >= cb ? Xf[(tb + cb) * BLK21 + (t & 31) * LDB + (c & 31)] : 0.f;
+        }
+        if (COMPACT) __syncthreads();                    // (N takes the inverse's place)
+#pragma unroll
+        for (int it = 0; it < NX; ++it) {
+            const int t = (tid >> 6) + 4 * it;
+            Nt[t * LDC + c] = (T)(x[it] * bs[c]);
+            if (BWD && p.aim) reinterpret_cast<T*>(p.aim)[bhc * 4096 + t * 64 + c] = (T)x[it];
+        }
     }
     __syncthreads();
 
@@ -347,24 +365,30 @@ __global__ __launch_bounds__(256, (PrepCfg<TIO, D>::WGS_PER_CU)) void prep_fwd_k
     __syncthreads();
 
     // ---- phase 4: outputs -----------------------------------------------------------
-    if (COMPACT) {       // F, into the space of the fp32 matrix A (dead since the inverse)
+    // 16 bytes per lane (the LDS rows are 16-byte aligned: LDC * sizeof(T) is a multiple of 16)
+    typedef T RowVec __attribute__((ext_vector_type(16 / sizeof(T))));
+    constexpr int VE = 16 / (int)sizeof(T), VPR = 64 / VE;
+    static_assert((LDC * sizeof(T)) % 16 == 0, "aligned rows");
+    if (BWD && p.fm) {
+        T* gk = reinterpret_cast<T*>(p.gktm) + bhc * 4096;
+        for (int idx = tid; idx < 64 * VPR; idx += 256) {
+            const int r = idx / VPR, c = (idx % VPR) * VE;
+            __builtin_nontemporal_store(*reinterpret_cast<const RowVec*>(Gk + r * LDC + c), reinterpret_cast<RowVec*>(gk + r * 64 + c));
+        }
+        if (COMPACT) __syncthreads();
+    }
+    if (COMPACT) {       // F, in Gk's place
         f_block();
         __syncthreads();
     }
     if (BWD && p.fm) {   // backward: keep the chunk's matrices (row-major, operand type)
         T* fm = reinterpret_cast<T*>(p.fm) + bhc * 4096;
-        T* gk = reinterpret_cast<T*>(p.gktm) + bhc * 4096;
         T* nm = reinterpret_cast<T*>(p.nm) + bhc * 4096;
         T* yt = reinterpret_cast<T*>(p.ytm) + bhc * 4096;
         T* ut = reinterpret_cast<T*>(p.utm) + bhc * (size_t)D * 64;
-        // 16 bytes per lane (the LDS rows are 16-byte aligned: LDC * sizeof(T) is a multiple of 16)
-        typedef T RowVec __attribute__((ext_vector_type(16 / sizeof(T))));
-        constexpr int VE = 16 / (int)sizeof(T), VPR = 64 / VE;
-        static_assert((LDC * sizeof(T)) % 16 == 0, "aligned rows");
         for (int idx = tid; idx < 64 * VPR; idx += 256) {
             const int r = idx / VPR, c = (idx % VPR) * VE;
             __builtin_nontemporal_store(*reinterpret_cast<const RowVec*>(Fs + r * LDC + c), reinterpret_cast<RowVec*>(fm + r * 64 + c));
-            __builtin_nontemporal_store(*reinterpret_cast<const RowVec*>(Gk + r * LDC + c), reinterpret_cast<RowVec*>(gk + r * 64 + c));
             __builtin_nontemporal_store(*reinterpret_cast<const RowVec*>(Nt + r * LDC + c), reinterpret_cast<RowVec*>(nm + r * 64 + c));
             __builtin_nontemporal_store(*reinterpret_cast<const RowVec*>(Yt + r * LDC + c), reinterpret_cast<RowVec*>(yt + r * 64 + c));
         }
