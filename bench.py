@@ -426,9 +426,9 @@ def main():
     single = {"attn_fwd2_kernel (forward sweep" + ("; in the training pair it also writes the backward's query states)" if do_bwd else ")"):
               (sweep_ms, fl_f, "4*d flops per (query, key <= query) pair")}
     if do_bwd:
-        single["bwd_keyside2_kernel<FAR> (key-side sums over the queries right of the key's super-block)"] = (
+        single["bwd_far_kernel (key-side sums over the queries right of the key's super-block)"] = (
             stage_ms["keys_far"], 8.0 * d * far_pairs * B * H, "8*d flops per (query, key) pair with the key in a super-block left of the query's")
-        single["bwd_keyside2_kernel<near> (key-side sums inside the key's super-block; also the near product gradients)"] = (
+        single["bwd_near_kernel (key-side sums inside the key's super-block; also the near product gradients)"] = (
             stage_ms["keys_near"], 8.0 * d * near_pairs * B * H, "8*d flops per (query, key) pair of one super-block, key chunk left of the query chunk")
     dom = max(single, key=lambda kname: single[kname][0])
     dom_ms, dom_fl, dom_note = single[dom]
