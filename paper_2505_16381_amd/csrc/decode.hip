@@ -268,9 +268,14 @@ __global__ __launch_bounds__(NT) void decode_partial_kernel(DecodeArgs a) {
         for (int r = 0; r < UN; ++r) {
             s[r] = a.scale * group_sum<LPK>(s[r]);
             if (GATES) s[r] += c_t - ci[r];
-            if (i0 + r * KPW + grp >= i_end) s[r] = -INFINITY;
-            mn = fmaxf(mn, s[r]);
         }
+        if (i0 + UN * KPW > i_end) {                      // past the end: weight zero, and a zero to weigh (the repeated row may hold infinities)
+#pragma unroll
+            for (int r = 0; r < UN; ++r)
+                if (i0 + r * KPW + grp >= i_end) { s[r] = -INFINITY; vv[r] = Vec8{}; }
+        }
+#pragma unroll
+        for (int r = 0; r < UN; ++r) mn = fmaxf(mn, s[r]);
         const float ref = mn == -INFINITY ? 0.f : mn;             // nothing yet: every weight below is exp(-inf)
         const float alpha = __expf(m - ref);
         m = mn;
@@ -332,7 +337,7 @@ __global__ __launch_bounds__(D) void decode_combine_kernel(DecodeArgs a, int nsp
     const int bh = blockIdx.x, c = threadIdx.x, lane = c & 63;
     const float* part = a.partial + (size_t)bh * nsplit * (D + 2);
     float on[NB];
-    auto request = [&](int s0) {                      // (splits past the last one repeat it, with weight zero)
+    auto request = [&](int s0) {                      // (splits past the last one repeat it, and count as zero)
 #pragma unroll
         for (int r = 0; r < NB; ++r) on[r] = part[(size_t)(s0 + r < nsplit ? s0 + r : nsplit - 1) * (D + 2) + 2 + c];
     };
@@ -354,6 +359,10 @@ __global__ __launch_bounds__(D) void decode_combine_kernel(DecodeArgs a, int nsp
 #pragma unroll
         for (int r = 0; r < NB; ++r) oc[r] = on[r];
         if (s0 + NB < nsplit) request(s0 + NB);
+        if (s0 + NB > nsplit) {
+#pragma unroll
+            for (int r = 0; r < NB; ++r) oc[r] = s0 + r < nsplit ? oc[r] : 0.f;
+        }
 #pragma unroll
         for (int r = 0; r < NB; ++r) O += oc[r] * __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wt), s0 + r));
     }
