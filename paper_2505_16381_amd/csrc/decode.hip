@@ -153,11 +153,15 @@ struct DecodeTail {
         // the token's running gate sum, which joins the cache (its own logit carries no gate)
         gate = GATES ? (a.n > 0 ? a.ccache[(size_t)bh * a.Lmax + a.n - 1] : 0.f) + (float)reinterpret_cast<const TIO*>(a.log_f)[bh] : 0.f;
     }
-    __device__ __forceinline__ void finish(const DecodeArgs& a, int bh, int c, float M, float Ls, float O) const {
-        float s_new = qk;
+    // The token's own logit.  Every wave of the head takes it -- all of q and k -- before a barrier, and no wave writes o
+    // before that barrier: o may be one of the inputs.
+    __device__ __forceinline__ void logit(float scale) {
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) s_new += __shfl_xor(s_new, off);
-        s_new *= a.scale;
+        for (int off = 32; off > 0; off >>= 1) qk += __shfl_xor(qk, off);
+        qk *= scale;
+    }
+    __device__ __forceinline__ void finish(const DecodeArgs& a, int bh, int c, float M, float Ls, float O) const {
+        const float s_new = qk;
         const float Mn = fmaxf(M, s_new);
         const float old = M == -INFINITY ? 0.f : __expf(M - Mn), own = __expf(s_new - Mn);
         Ls = Ls * old + own;
@@ -311,6 +315,7 @@ __global__ __launch_bounds__(NT) void decode_partial_kernel(DecodeArgs a) {
             for (int e = 0; e < 8; ++e) red_o[wv][8 * sub + e] = acc[e];
         }
     }
+    if (DIRECT && wv < D / 64) tail.logit(a.scale);
     __syncthreads();
     if (tid >= D) return;
     float M = -INFINITY;
@@ -346,6 +351,8 @@ __global__ __launch_bounds__(D) void decode_combine_kernel(DecodeArgs a, int nsp
     request(0);
     DecodeTail<TIO, D, GATES> tail;
     tail.load(a, bh, c);
+    tail.logit(a.scale);
+    if (D > 64) __syncthreads();
     float M = ms;
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) M = fmaxf(M, __shfl_xor(M, off));
