@@ -13,9 +13,9 @@
 // two per SIMD, that meet at one barrier per 32 queries:
 //   waves 0..3  32 keys each (keys and values resident): logits, dP, the element-wise part; P and dS leave as
 //               operand fragments through LDS, double-buffered;
-//   waves 4, 5  dV^T and waves 6, 7 dKb2^T, of 64 keys each, two half-steps behind (and one each of the sixteen 32x32
-//               blocks of dP_superblock, whose state fragments are in registers anyway: the eight workgroups of a
-//               super-block cover all of it, which saves the pass over the states that it was before).
+//   waves 4, 5  dV^T and waves 6, 7 dKb2^T, of 64 keys each, two half-steps behind (the latter also take one each of the
+//               sixteen 32x32 blocks of dP_superblock, whose state fragments are in registers anyway: the workgroups of a
+//               super-block cover all of it, see far_blocks.h, which saves the pass over the states that it was before).
 // The first kind's vector work then runs under the second kind's products.  The second kind, which has issue slots to
 // spare, requests the tiles (a direct-to-LDS request holds its wave for about 70 cycles) and reads dO^T and Xs^T out
 // of the untransposed ones with transposing LDS reads: a step stages two tiles instead of four, in a ring of three,
@@ -27,6 +27,7 @@
 
 #include "path_common.h"
 #include "bwd_decl.h"
+#include "far_blocks.h"
 
 namespace path {
 
@@ -34,7 +35,9 @@ template <typename TIO, int D> struct FarCfg {
     typedef typename Compute<TIO>::type T;
     static constexpr int KVF = CHUNK * D / Tr<T>::FE;                 // fragments of a tile
     static constexpr int GF = CHUNK / Tr<T>::KW * 64;                 // ... of 32 rows of a g tile
-    static constexpr int STF = 2 * KVF + GF + 32;                     // a stage: xs | doq | the workgroup's rows of gT | lse2, delta
+    typedef FarBlocks<SBC, D> Blocks;
+    static constexpr int GTF = Blocks::COLS * GF;
+    static constexpr int STF = 2 * KVF + GTF + 32;                    // a stage: xs | doq | the workgroup's rows of gT | lse2, delta
     static constexpr int PDF = 2 * 4 * 2 * 64;                        // a hand-over buffer: (P | dS) x 4 key blocks x 2 slabs
     static constexpr size_t smem_bytes = (size_t)(3 * STF + 2 * PDF) * 16;
     static_assert(smem_bytes <= 160 * 1024, "LDS budget");
@@ -47,14 +50,15 @@ __global__ __launch_bounds__(512, 2) void bwd_far_kernel(BwdParams p) {
     using Frag = typename Tr<T>::Frag;
     using FragV = typename Tr<TIO>::Frag;
     constexpr int KW = Tr<T>::KW, SPB = 32 / KW, DB = D / 32, DS = D / KW, QS = CHUNK / KW;
-    constexpr int KVF = C::KVF, GF = C::GF, STF = C::STF, PDF = C::PDF;
+    constexpr int KVF = C::KVF, GF = C::GF, GTF = C::GTF, STF = C::STF, PDF = C::PDF;
+    using Blocks = typename C::Blocks;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     Frag* const stages = reinterpret_cast<Frag*>(smem);
     Frag* const hand = stages + 3 * STF;
 
     // XCD x takes the heads bh = x (mod 8); the workgroups of a super-block get consecutive numbers on it (they
     // stream the same states and dO tiles at the same time, out of that XCD's L2), the left-most super-block first.
-    constexpr int NPOS = SBC / 2;
+    constexpr int NPOS = Blocks::NPOS;
     const int NC = p.NC, nsb = (NC + SBC - 1) / SBC;
     const int xcd = blockIdx.x & 7, kk = blockIdx.x >> 3, pos = kk % NPOS;
     const int J = __builtin_amdgcn_readfirstlane(kk / NPOS % (nsb - 1));
@@ -66,7 +70,7 @@ __global__ __launch_bounds__(512, 2) void bwd_far_kernel(BwdParams p) {
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), h = lane >> 5, l32 = lane & 31;
     const size_t Lp = (size_t)NC * CHUNK, nslots = num_block_slots(NC);
     const int i0 = (J + 1) * SBC, i1 = NCo;
-    const int bb = DB == 4 ? pos >> 1 : (pos >> 1) & 1;                // column block of the workgroup's blocks of dP_superblock
+    const int bb = Blocks::first_col(pos);                             // first column block of the workgroup's blocks of dP_superblock
 
     if (wv < 4) {
         // ---- logits and the element-wise part of 32 keys ------------------------------------------------------
@@ -108,7 +112,7 @@ __global__ __launch_bounds__(512, 2) void bwd_far_kernel(BwdParams p) {
         FragV Pb;
         Frag dSb;
         auto element_wise = [&](int st, int qh, const f32x16& S, const f32x16& dP, int g) {
-            const float* lse2 = reinterpret_cast<const float*>(stages + st * STF + 2 * KVF + GF) + 32 * qh + 4 * h;
+            const float* lse2 = reinterpret_cast<const float*>(stages + st * STF + 2 * KVF + GTF) + 32 * qh + 4 * h;
             const f32x4 ls = *reinterpret_cast<const f32x4*>(lse2 + 8 * g), dls = *reinterpret_cast<const f32x4*>(lse2 + CHUNK + 8 * g);
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
@@ -188,13 +192,17 @@ __global__ __launch_bounds__(512, 2) void bwd_far_kernel(BwdParams p) {
         f32x16 acc[DB][2];
 #pragma unroll
         for (int b = 0; b < DB; ++b) { acc[b][0] = zero16(); acc[b][1] = zero16(); }
-        // dP_superblock: this wave's block has row block ab.  (d = 64: four
-        // blocks in all, so the eight workgroups compute each of them twice per wave and the first four write it.)
-        const int ab = DB == 4 ? 2 * (pos & 1) + ck : pos & 1;
-        f32x16 dd = zero16();
+        // dP_superblock: this wave's blocks have row blocks ab ..
+        constexpr int NR = Blocks::ROWS, NCB = Blocks::COLS;
+        const int ab = Blocks::first_row(pos, ck);
+        f32x16 dd[NR][NCB];
+#pragma unroll
+        for (int a = 0; a < NR; ++a)
+#pragma unroll
+            for (int b = 0; b < NCB; ++b) dd[a][b] = zero16();
         // the tile's transposed fragments of a half-step, read before the barrier that P and dS wait for
-        FragE ta[DB * SPB], td[SPB];
-        Frag gf[SPB];
+        FragE ta[DB * SPB], td[NR * SPB];
+        Frag gf[NCB * SPB];
         auto read_tile = [&](int st, int qh) {
             const E* tile = reinterpret_cast<const E*>(stages + st * STF + (KEYS ? 0 : KVF));
 #pragma unroll
@@ -203,9 +211,13 @@ __global__ __launch_bounds__(512, 2) void bwd_far_kernel(BwdParams p) {
                 for (int u = 0; u < SPB; ++u) ta[b * SPB + u] = ld_tile_frag_tr<E, DS>(tile, qh * SPB + u, b, l32, h);
             if constexpr (KEYS) {
 #pragma unroll
-                for (int u = 0; u < SPB; ++u) gf[u] = stages[st * STF + 2 * KVF + (qh * SPB + u) * 64 + lane];
+                for (int b = 0; b < NCB; ++b)
 #pragma unroll
-                for (int u = 0; u < SPB; ++u) td[u] = ld_tile_frag_tr<E, DS>(tile, qh * SPB + u, ab, l32, h);
+                    for (int u = 0; u < SPB; ++u) gf[b * SPB + u] = stages[st * STF + 2 * KVF + b * GF + (qh * SPB + u) * 64 + lane];
+#pragma unroll
+                for (int a = 0; a < NR; ++a)
+#pragma unroll
+                    for (int u = 0; u < SPB; ++u) td[a * SPB + u] = ld_tile_frag_tr<E, DS>(tile, qh * SPB + u, ab + a, l32, h);
             }
         };
         int st = 0;
@@ -225,7 +237,11 @@ __global__ __launch_bounds__(512, 2) void bwd_far_kernel(BwdParams p) {
                     for (int k = 0; k < 2; ++k) acc[b][k] = Tr<E>::mma(ta[b * SPB + u], f[k][u], acc[b][k]);
             if constexpr (KEYS) {
 #pragma unroll
-                for (int u = 0; u < SPB; ++u) dd = Tr<T>::mma(td[u], gf[u], dd);
+                for (int u = 0; u < SPB; ++u)
+#pragma unroll
+                    for (int a = 0; a < NR; ++a)
+#pragma unroll
+                        for (int b = 0; b < NCB; ++b) dd[a][b] = Tr<T>::mma(td[a * SPB + u], gf[b * SPB + u], dd[a][b]);
             }
             __builtin_amdgcn_sched_barrier(0);
         };
@@ -244,14 +260,14 @@ __global__ __launch_bounds__(512, 2) void bwd_far_kernel(BwdParams p) {
             if (tid4 < 32) {    // 64 floats of lse2 (lanes 0-15) and of delta (lanes 16-31): 16 bytes per lane
                 const float* src = (tid4 < 16 ? p.lse2p : p.delta) + (size_t)bh * Lp + (size_t)i * CHUNK + 4 * (tid4 & 15);
                 __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
-                                                 (__attribute__((address_space(3))) void*)(buf + 2 * KVF + GF), 16, 0, 0);
+                                                 (__attribute__((address_space(3))) void*)(buf + 2 * KVF + GTF), 16, 0, 0);
             }
         };
         auto issue_b = [&](int i, int st) {               // doq, gT
             if (i >= i1) return;
             Frag* buf = stages + st * STF;
             async_copy_tile<256, KVF>(reinterpret_cast<const Frag*>(reinterpret_cast<const TIO*>(p.doq) + ((size_t)bh * NC + i) * CHUNK * D), buf + KVF, tid4, wv4);
-            async_copy_tile<256, GF>(reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(p.gs) + slot_of(i)) + bb * GF, buf + 2 * KVF, tid4, wv4);
+            async_copy_tile<256, GTF>(reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(p.gs) + slot_of(i)) + bb * GF, buf + 2 * KVF, tid4, wv4);
         };
         issue_a(i0, 0);
         issue_b(i0, 0);
@@ -294,11 +310,16 @@ __global__ __launch_bounds__(512, 2) void bwd_far_kernel(BwdParams p) {
                     for (int r = 0; r < 4; ++r) v4[r] = KEYS ? p.scale * acc[b][k][4 * g + r] : v4[r] + acc[b][k][4 * g + r];
                     *reinterpret_cast<f32x4*>(dst) = v4;
                 }
-        if (KEYS && (DB == 4 || (pos < 4 && ck == 0))) {
+        if (KEYS && Blocks::writes(pos, ck)) {
             // the gradient of P_superblock starts the second level's chain (nothing lies left of super-block 0)
             float* dst = p.dchain + ((size_t)bh * nsb + J) * D * D;
 #pragma unroll
-            for (int jj = 0; jj < 16; ++jj) dst[(size_t)(32 * ab + acc_row(jj, h)) * D + 32 * bb + l32] = J >= 1 ? dd[jj] : 0.f;
+            for (int a = 0; a < NR; ++a)
+#pragma unroll
+                for (int b = 0; b < NCB; ++b)
+#pragma unroll
+                    for (int jj = 0; jj < 16; ++jj)
+                        dst[(size_t)(32 * (ab + a) + acc_row(jj, h)) * D + 32 * (bb + b) + l32] = J >= 1 ? dd[a][b][jj] : 0.f;
         }
     };
     if (wv < 6) sums(std::false_type{});

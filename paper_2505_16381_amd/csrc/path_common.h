@@ -41,7 +41,8 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int CHUNK = 64;      // tokens per chunk (UT transform block)
 #ifndef PATH_SBC
-#define PATH_SBC 16            // measured at B=4, H=16, L=8192, d=128: 8 -> +0.35 ms per training step, 32 -> +0.65 ms
+#define PATH_SBC 16            // a power of two from 4 on.  Training step at B=4, H=16, L=8192, d=128: 8.14 ms; with 8 chunks 8.11, 32 8.79,
+                               // 4 11.4; 16 heads of 2048 tokens 498 us, 422, 406, 484 (the path_attn_ring_* contract is stated for 16)
 #endif
 constexpr int SBC = PATH_SBC;  // chunks per super-block (second blocking level of the forward sweep)
 
