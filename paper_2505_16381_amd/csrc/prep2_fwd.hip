@@ -14,7 +14,10 @@
 // (E dP takes a row of E to a row), and column c of Kb2 needs row c of E alone.  A wave keeps its rows transposed in
 // fp32 registers (rows b, lane = row a); those registers packed are the operand of both products, so the waves share
 // nothing but the chunk's key and -dP tiles, copied to LDS as the chunk kernel wrote them.  Where -dP is needed
-// element-wise in the transposed register layout it is transposed through the matrix unit.
+// element-wise in the transposed register layout it is transposed through the matrix unit.  (fp32 operands at d = 64: two
+// waves per 32 rows, half of the columns and half of the keys each, that pass each other their half of E through LDS.  With
+// two waves in all, half of the CU's matrix pipes idle: transform and key prefill of 16 heads of 2000 tokens 184 us,
+// with four 150.)
 //
 // What bounds it: memory where there are many super-blocks (64 KB per chunk at d = 128, 96 with the backward's
 // outputs), the chain of 16 chunks where there are few.  Hence two shapes: more than one workgroup per CU, one stage of
@@ -34,8 +37,10 @@ enum { P2_FWD = 0, P2_BWD = 1, P2_CACHE = 2 };
 template <typename TIO, int D, int NBUF> struct Prep2Cfg {
     typedef typename Compute<TIO>::type T;
     static constexpr int KV_FRAGS = CHUNK * D / Tr<T>::FE, DP_FRAGS = D * D / Tr<T>::FE;
-    static constexpr int NT = 64 * (D / 32);
-    static constexpr size_t smem_bytes = (size_t)NBUF * (KV_FRAGS + DP_FRAGS) * 16;      // stages of (key tile | -dP tile)
+    static constexpr int SPLIT = sizeof(T) == 4 && D == 64 ? 2 : 1;      // waves per 32 rows of E
+    static constexpr int NT = 64 * (D / 32) * SPLIT;
+    static constexpr int XCH_FRAGS = SPLIT == 1 ? 0 : DP_FRAGS;          // E as operand fragments
+    static constexpr size_t smem_bytes = ((size_t)NBUF * (KV_FRAGS + DP_FRAGS) + XCH_FRAGS) * 16;      // stages of (key tile | -dP tile)
     static constexpr int WAVES_PER_SIMD = sizeof(T) == 2 && NBUF == 1 ? (D == 64 ? 3 : 2) : 1;
 };
 
@@ -47,9 +52,12 @@ __global__ __launch_bounds__((Prep2Cfg<TIO, D, NBUF>::NT), (Prep2Cfg<TIO, D, NBU
     constexpr int FE = Tr<T>::FE, KW = Tr<T>::KW;
     constexpr int SPB = 32 / KW, DB = D / 32, DS = D / KW, KVF = C::KV_FRAGS, DPF = C::DP_FRAGS, NT = C::NT;
     constexpr bool BWD = MODE == P2_BWD;
+    constexpr int SPLIT = C::SPLIT, NB = DB / SPLIT, NKH = 2 / SPLIT;      // the wave's column blocks of E and halves of the key tile
+    static_assert(SPLIT == 1 || NBUF == 1, "the exchange takes its barriers from the single stage");
 
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     Frag* const stage = reinterpret_cast<Frag*>(smem);
+    Frag* const xch = stage + NBUF * (KVF + DPF);
 
     const int sb = blockIdx.x, bh = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), h = lane >> 5, l32 = lane & 31;
@@ -64,11 +72,14 @@ __global__ __launch_bounds__((Prep2Cfg<TIO, D, NBUF>::NT), (Prep2Cfg<TIO, D, NBU
     if (BWD && is_last_sb(sb, NCown)) return;         // (a training step never looks at it from the right: see is_last_sb)
     const int clast = (c0 + SBC - 1 < NCown) ? c0 + SBC - 1 : NCown - 1;
 
+    const int ra = wv / SPLIT, part = SPLIT == 1 ? 0 : wv % SPLIT;         // row block of E; which half of the work on it
+    const int b0 = part * NB, h0 = part * NKH;                             // first column block, first half of the key tile
+
     Frag idf[SPB], Eb[DS];
     identity_frags<T>(idf, l32, h);
-    f32x16 Fm[DB];      // E^T of the wave's rows: rows b, lane a = 32 wv + l32
+    f32x16 Fm[NB];      // E^T of the wave's rows: rows b of column block b0 + o, lane a = 32 ra + l32
 #pragma unroll
-    for (int b = 0; b < DB; ++b) Fm[b] = zero16();
+    for (int o = 0; o < NB; ++o) Fm[o] = zero16();
 
     auto issue = [&](int c) {
         const size_t bhc = (size_t)bh * NC + c;
@@ -85,67 +96,83 @@ __global__ __launch_bounds__((Prep2Cfg<TIO, D, NBUF>::NT), (Prep2Cfg<TIO, D, NBU
         } else {
             __syncthreads();
             issue(c);
+            if (SPLIT > 1) {
+#pragma unroll
+                for (int o = 0; o < NB; ++o) {
+                    Frag fr[SPB];
+                    pack_block<T>(Fm[o], fr);
+#pragma unroll
+                    for (int s2 = 0; s2 < SPB; ++s2) xch[(ra * DS + (b0 + o) * SPB + s2) * 64 + lane] = fr[s2];
+                }
+            }
             wait_async_and_sync();
         }
         const Frag* k1 = stage + (size_t)(c & (NBUF - 1)) * (KVF + DPF);
         const Frag* dpn = k1 + KVF;                                                                                  // (rows b, contr a) = -dP[a][b]
+        if constexpr (SPLIT == 1) {
 #pragma unroll
-        for (int b = 0; b < DB; ++b) pack_block<T>(Fm[b], Eb + b * SPB);
+            for (int b = 0; b < DB; ++b) pack_block<T>(Fm[b], Eb + b * SPB);
+        } else {
+#pragma unroll
+            for (int s = 0; s < DS; ++s) Eb[s] = xch[(ra * DS + s) * 64 + lane];
+        }
         if (BWD) {      // backward only: R_c = I - E_c (16-bit operands: a tile with rows a, contraction b; fp32: row-major [a][b])
 #pragma unroll
-            for (int b = 0; b < DB; ++b) {
-                int diag = b == wv ? l32 - 4 * h : -1;
+            for (int o = 0; o < NB; ++o) {
+                const int b = b0 + o;
+                int diag = b == ra ? l32 - 4 * h : -1;
                 asm volatile("" : "+v"(diag));            // compared here: sixteen masks kept over the loop would spill
                 f32x16 rc;
 #pragma unroll
-                for (int jj = 0; jj < 16; ++jj) rc[jj] = (acc_row(jj, 0) == diag ? 1.f : 0.f) - Fm[b][jj];
+                for (int jj = 0; jj < 16; ++jj) rc[jj] = (acc_row(jj, 0) == diag ? 1.f : 0.f) - Fm[o][jj];
                 if (sizeof(T) == 2) {
                     Frag* rdst = reinterpret_cast<Frag*>(reinterpret_cast<T*>(p.rm) + bhc * (size_t)D * D);
                     Frag fr[SPB];
                     pack_block<T>(rc, fr);
 #pragma unroll
-                    for (int s2 = 0; s2 < SPB; ++s2) __builtin_nontemporal_store(fr[s2], &rdst[((size_t)wv * DS + b * SPB + s2) * 64 + tile_lane<T>(lane, s2)]);
+                    for (int s2 = 0; s2 < SPB; ++s2) __builtin_nontemporal_store(fr[s2], &rdst[((size_t)ra * DS + b * SPB + s2) * 64 + tile_lane<T>(lane, s2)]);
                 } else {
-                    float* rdst = reinterpret_cast<float*>(p.rm) + bhc * (size_t)D * D + (size_t)(32 * wv + l32) * D + 32 * b + 4 * h;
+                    float* rdst = reinterpret_cast<float*>(p.rm) + bhc * (size_t)D * D + (size_t)(32 * ra + l32) * D + 32 * b + 4 * h;
 #pragma unroll
                     for (int g = 0; g < 4; ++g) *reinterpret_cast<f32x4*>(rdst + 8 * g) = f32x4{rc[4 * g], rc[4 * g + 1], rc[4 * g + 2], rc[4 * g + 3]};
                 }
             }
         }
-        // The products in groups of DS fragments (the two halves of the key tile, the DB row blocks of -dP), each group's
+        // The products in groups of DS fragments (halves of the key tile, then row blocks of -dP), each group's
         // read from LDS while the one before is multiplied; the scheduling barriers keep it to two groups in registers.
         Frag f[2][DS], dfr[2][SPB];
         auto read_group = [&](int g) {
-            const Frag* src = g < 2 ? k1 + (size_t)g * DS * 64 : dpn + (size_t)(g - 2) * DS * 64;
+            const Frag* src = g < NKH ? k1 + (size_t)(h0 + g) * DS * 64 : dpn + (size_t)(b0 + g - NKH) * DS * 64;
 #pragma unroll
             for (int s = 0; s < DS; ++s) f[g & 1][s] = src[s * 64 + tile_lane<T>(lane, s)];
 #pragma unroll
-            for (int s2 = 0; s2 < SPB; ++s2) dfr[g & 1][s2] = src[(wv * SPB + s2) * 64 + tile_lane<T>(lane, s2)];
+            for (int s2 = 0; s2 < SPB; ++s2) dfr[g & 1][s2] = src[(ra * SPB + s2) * 64 + tile_lane<T>(lane, s2)];
         };
         read_group(0);
         // Kb2^T[cc][s] = Kb^T[cc][s] - sum_b E[cc][b] Kb[s][b]   (registers rows cc of the wave, lane s)
         Frag* k2 = reinterpret_cast<Frag*>(reinterpret_cast<T*>(p.kt2) + bhc * (size_t)CHUNK * D);
 #pragma unroll
-        for (int sb2 = 0; sb2 < 2; ++sb2) {
-            read_group(sb2 + 1);
+        for (int g = 0; g < NKH; ++g) {
+            const int sb2 = h0 + g;
+            read_group(g + 1);
             __builtin_amdgcn_sched_barrier(0);
             f32x16 acc = zero16();
 #pragma unroll
-            for (int s = 0; s < DS; ++s) acc = Tr<T>::mma(Eb[s], f[sb2][s], acc);      // (last chunk: E = 0)
+            for (int s = 0; s < DS; ++s) acc = Tr<T>::mma(Eb[s], f[g][s], acc);      // (last chunk: E = 0)
             if (MODE == P2_CACHE) {
                 typedef typename Tr<TIO>::Vec4 OVec4;
                 const int tok = c * CHUNK + 32 * sb2 + l32;
                 if (tok < p.L) {
-                    TIO* dst = reinterpret_cast<TIO*>(p.kcache) + ((size_t)bh * p.Lmax + tok) * D + 32 * wv + 4 * h;
+                    TIO* dst = reinterpret_cast<TIO*>(p.kcache) + ((size_t)bh * p.Lmax + tok) * D + 32 * ra + 4 * h;
 #pragma unroll
-                    for (int g = 0; g < 4; ++g) {
+                    for (int q = 0; q < 4; ++q) {
                         OVec4 o4;
 #pragma unroll
                         for (int r = 0; r < 4; ++r) {
-                            const int jj = 4 * g + r;
-                            o4[r] = (TIO)((float)dfr[sb2][jj / FE][jj % FE] - acc[jj]);
+                            const int jj = 4 * q + r;
+                            o4[r] = (TIO)((float)dfr[g][jj / FE][jj % FE] - acc[jj]);
                         }
-                        *reinterpret_cast<OVec4*>(dst + 8 * g) = o4;
+                        *reinterpret_cast<OVec4*>(dst + 8 * q) = o4;
                     }
                 }
                 continue;
@@ -154,33 +181,34 @@ __global__ __launch_bounds__((Prep2Cfg<TIO, D, NBUF>::NT), (Prep2Cfg<TIO, D, NBU
 #pragma unroll
             for (int s2 = 0; s2 < SPB; ++s2) {
 #pragma unroll
-                for (int e = 0; e < FE; ++e) fr[s2][e] = (T)((float)dfr[sb2][s2][e] - acc[s2 * FE + e]);
+                for (int e = 0; e < FE; ++e) fr[s2][e] = (T)((float)dfr[g][s2][e] - acc[s2 * FE + e]);
             }
 #pragma unroll
-            for (int s2 = 0; s2 < SPB; ++s2) __builtin_nontemporal_store(fr[s2], &k2[((size_t)sb2 * DS + wv * SPB + s2) * 64 + tile_lane<T>(lane, s2)]);
+            for (int s2 = 0; s2 < SPB; ++s2) __builtin_nontemporal_store(fr[s2], &k2[((size_t)sb2 * DS + ra * SPB + s2) * 64 + tile_lane<T>(lane, s2)]);
             if (BWD && sizeof(T) == 4) {     // backward with fp32 operands only: the arrangement (rows cc, contraction s)
                 Frag* k2T = reinterpret_cast<Frag*>(reinterpret_cast<T*>(p.kt2T) + bhc * (size_t)CHUNK * D);
                 const f32x16 tr = transpose32<T>(fr, idf);      // rows s, lane cc
                 Frag ft[SPB];
                 pack_block<T>(tr, ft);
 #pragma unroll
-                for (int s2 = 0; s2 < SPB; ++s2) __builtin_nontemporal_store(ft[s2], &k2T[((size_t)wv * (CHUNK / KW) + sb2 * SPB + s2) * 64 + lane]);
+                for (int s2 = 0; s2 < SPB; ++s2) __builtin_nontemporal_store(ft[s2], &k2T[((size_t)ra * (CHUNK / KW) + sb2 * SPB + s2) * 64 + lane]);
             }
         }
         if (MODE == P2_CACHE && c == c0) break;
         // E^T <- E^T + dP^T - dP^T E^T   (registers rows b, lane a)
 #pragma unroll
-        for (int b = 0; b < DB; ++b) {
-            if (b + 1 < DB) read_group(b + 3);
+        for (int o = 0; o < NB; ++o) {
+            const int g = NKH + o;
+            if (o + 1 < NB) read_group(g + 1);
             __builtin_amdgcn_sched_barrier(0);
             f32x16 acc = zero16();
 #pragma unroll
-            for (int s = 0; s < DS; ++s) acc = Tr<T>::mma(f[b & 1][s], Eb[s], acc);
+            for (int s = 0; s < DS; ++s) acc = Tr<T>::mma(f[g & 1][s], Eb[s], acc);
             // -dP[a][b] in this block's register layout (rows b, lane a): the tile piece (rows b,
             // contraction a) transposed through the matrix unit
-            const f32x16 dpT = transpose32<T>(dfr[b & 1], idf);
+            const f32x16 dpT = transpose32<T>(dfr[g & 1], idf);
 #pragma unroll
-            for (int jj = 0; jj < 16; ++jj) Fm[b][jj] = Fm[b][jj] - dpT[jj] + acc[jj];
+            for (int jj = 0; jj < 16; ++jj) Fm[o][jj] = Fm[o][jj] - dpT[jj] + acc[jj];
             __builtin_amdgcn_sched_barrier(0);
         }
     }
@@ -189,9 +217,10 @@ __global__ __launch_bounds__((Prep2Cfg<TIO, D, NBUF>::NT), (Prep2Cfg<TIO, D, NBU
     // transpose of what the registers hold -- taken through the matrix unit.
     Frag* dst = reinterpret_cast<Frag*>(reinterpret_cast<T*>(p.dp2) + ((size_t)bh * nsb + sb) * (size_t)D * D);
 #pragma unroll
-    for (int b = 0; b < DB; ++b) {
+    for (int o = 0; o < NB; ++o) {
+        const int b = b0 + o;
         Frag fin[SPB];
-        pack_block<T>(Fm[b], fin);                              // tile piece (rows a, contraction b)
+        pack_block<T>(Fm[o], fin);                              // tile piece (rows a, contraction b)
         if (BWD && sizeof(T) == 4) {      // backward, fp32 operands only: -(I - P_superblock) in the arrangement (rows a, contraction b)
             Frag* dt = reinterpret_cast<Frag*>(reinterpret_cast<T*>(p.dpt2) + ((size_t)bh * nsb + sb) * (size_t)D * D);
 #pragma unroll
@@ -199,7 +228,7 @@ __global__ __launch_bounds__((Prep2Cfg<TIO, D, NBUF>::NT), (Prep2Cfg<TIO, D, NBU
                 Frag ng;
 #pragma unroll
                 for (int e = 0; e < FE; ++e) ng[e] = (T)(-(float)fin[s][e]);
-                __builtin_nontemporal_store(ng, &dt[((size_t)wv * DS + b * SPB + s) * 64 + lane]);
+                __builtin_nontemporal_store(ng, &dt[((size_t)ra * DS + b * SPB + s) * 64 + lane]);
             }
         }
         f32x16 tr = transpose32<T>(fin, idf);                   // rows a, lane b
@@ -208,7 +237,7 @@ __global__ __launch_bounds__((Prep2Cfg<TIO, D, NBUF>::NT), (Prep2Cfg<TIO, D, NBU
         Frag fr[SPB];
         pack_block<T>(tr, fr);
 #pragma unroll
-        for (int s = 0; s < SPB; ++s) __builtin_nontemporal_store(fr[s], &dst[((size_t)b * DS + wv * SPB + s) * 64 + tile_lane<T>(lane, s)]);
+        for (int s = 0; s < SPB; ++s) __builtin_nontemporal_store(fr[s], &dst[((size_t)b * DS + ra * SPB + s) * 64 + tile_lane<T>(lane, s)]);
     }
 }
 
