@@ -529,9 +529,13 @@ __global__ __launch_bounds__(256) void bwd_keyside2_kernel(BwdParams p) {
     const int nsb_g = (NC + SBC - 1) / SBC - (FAR ? 1 : 0);      // (far: no queries right of the last super-block)
     const int xcd = blockIdx.x & 7, kk = blockIdx.x >> 3;
     // (the divisions run on the vector unit; their results go back to scalar registers)
-    const int j = __builtin_amdgcn_readfirstlane((kk / NPOS % nsb_g) * SBC + (kk % NPOS) * CPW);       // first key chunk of the workgroup
+    int j = __builtin_amdgcn_readfirstlane((kk / NPOS % nsb_g) * SBC + (kk % NPOS) * CPW);       // first key chunk of the workgroup
     const int bh = __builtin_amdgcn_readfirstlane((kk / (NPOS * nsb_g)) * 8 + xcd);
     if (bh >= p.B * p.H) return;
+    // Far at d = 64, where a CU holds two workgroups: every second head of an XCD the other way round.  The XCD's CUs take
+    // workgroups in turn, and in one order the long ones of two heads came to lie on the same CUs: 16 heads of 5000
+    // tokens 985 us, so 666; 64 of 4096 1772 / 1694.  (d = 128 holds one, and wants the long ones first: 1359, so 1925.)
+    if (FAR && D == 64 && ((bh >> 3) & 1)) j = (nsb_g - 1 - j / SBC) * SBC + j % SBC;
     const int NCo = (seq_len(p.ul, bh, p.L) + CHUNK - 1) / CHUNK;      // this head's own chunks
     if (j >= NCo || (FAR && is_last_sb(j / SBC, NCo))) return;
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), h = lane >> 5, l32 = lane & 31;
