@@ -138,6 +138,9 @@ __global__ __launch_bounds__((Prep2Cfg<TIO, D, NBUF>::NT), (Prep2Cfg<TIO, D, NBU
                 }
             }
         }
+        // The last chunk has E = 0.  fp32 products take so long that they are left out there (the own segment of a ring, 3 heads
+        // of one chunk, d = 128: 62.0 us, without them 52.2); 16-bit products take a sixteenth of that.
+        const bool products = sizeof(T) == 2 || c != clast;
         // The products in groups of DS fragments (halves of the key tile, then row blocks of -dP), each group's
         // read from LDS while the one before is multiplied; the scheduling barriers keep it to two groups in registers.
         Frag f[2][DS], dfr[2][SPB];
@@ -157,8 +160,10 @@ __global__ __launch_bounds__((Prep2Cfg<TIO, D, NBUF>::NT), (Prep2Cfg<TIO, D, NBU
             read_group(g + 1);
             __builtin_amdgcn_sched_barrier(0);
             f32x16 acc = zero16();
+            if (products) {
 #pragma unroll
-            for (int s = 0; s < DS; ++s) acc = Tr<T>::mma(Eb[s], f[g][s], acc);      // (last chunk: E = 0)
+                for (int s = 0; s < DS; ++s) acc = Tr<T>::mma(Eb[s], f[g][s], acc);
+            }
             if (MODE == P2_CACHE) {
                 typedef typename Tr<TIO>::Vec4 OVec4;
                 const int tok = c * CHUNK + 32 * sb2 + l32;
@@ -202,8 +207,10 @@ __global__ __launch_bounds__((Prep2Cfg<TIO, D, NBUF>::NT), (Prep2Cfg<TIO, D, NBU
             if (o + 1 < NB) read_group(g + 1);
             __builtin_amdgcn_sched_barrier(0);
             f32x16 acc = zero16();
+            if (products) {
 #pragma unroll
-            for (int s = 0; s < DS; ++s) acc = Tr<T>::mma(f[g & 1][s], Eb[s], acc);
+                for (int s = 0; s < DS; ++s) acc = Tr<T>::mma(f[g & 1][s], Eb[s], acc);
+            }
             // -dP[a][b] in this block's register layout (rows b, lane a): the tile piece (rows b,
             // contraction a) transposed through the matrix unit
             const f32x16 dpT = transpose32<T>(dfr[g & 1], idf);
