@@ -528,14 +528,17 @@ __global__ __launch_bounds__(256) void bwd_keyside2_kernel(BwdParams p) {
     const int NC = p.NC;                                        // chunks per head in the workspace arrays and the grid's numbering
     const int nsb_g = (NC + SBC - 1) / SBC - (FAR ? 1 : 0);      // (far: no queries right of the last super-block)
     const int xcd = blockIdx.x & 7, kk = blockIdx.x >> 3;
+    // Far at d = 64, where a CU holds two workgroups: the super-blocks of all heads of the XCD together, longest first, and
+    // if that is one or two for each of its 32 CUs, which take them in turn, the second ones shortest first -- else a CU's two
+    // may both be the longest.  Heads one after the other / so, us: 16 heads of 5000 tokens 982 / 658, 24 of 2457 364 / 253, 64 of
+    // 4096 1762 / 1573; 128 of 2000 529 / 542, 24 of 4000 613 / 626.  (d = 128 holds one workgroup per CU: heads one after the other.)
+    constexpr bool BY_LENGTH = FAR && D == 64;
+    const int nh = BY_LENGTH ? (p.B * p.H + 7) / 8 : 1, M = NPOS * nsb_g * nh;
+    const int rank = BY_LENGTH && kk >= 32 && M <= 64 ? M + 31 - kk : kk;
     // (the divisions run on the vector unit; their results go back to scalar registers)
-    int j = __builtin_amdgcn_readfirstlane((kk / NPOS % nsb_g) * SBC + (kk % NPOS) * CPW);       // first key chunk of the workgroup
-    const int bh = __builtin_amdgcn_readfirstlane((kk / (NPOS * nsb_g)) * 8 + xcd);
+    const int j = __builtin_amdgcn_readfirstlane((BY_LENGTH ? rank / (NPOS * nh) : rank / NPOS % nsb_g) * SBC + (rank % NPOS) * CPW);       // first key chunk of the workgroup
+    const int bh = __builtin_amdgcn_readfirstlane((BY_LENGTH ? rank / NPOS % nh : rank / (NPOS * nsb_g)) * 8 + xcd);
     if (bh >= p.B * p.H) return;
-    // Far at d = 64, where a CU holds two workgroups: every second head of an XCD the other way round.  The XCD's CUs take
-    // workgroups in turn, and in one order the long ones of two heads came to lie on the same CUs: 16 heads of 5000
-    // tokens 985 us, so 666; 64 of 4096 1772 / 1694.  (d = 128 holds one, and wants the long ones first: 1359, so 1925.)
-    if (FAR && D == 64 && ((bh >> 3) & 1)) j = (nsb_g - 1 - j / SBC) * SBC + j % SBC;
     const int NCo = (seq_len(p.ul, bh, p.L) + CHUNK - 1) / CHUNK;      // this head's own chunks
     if (j >= NCo || (FAR && is_last_sb(j / SBC, NCo))) return;
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), h = lane >> 5, l32 = lane & 31;
