@@ -361,17 +361,23 @@ __device__ __forceinline__ long long user_scl(const UserLayout& u, int bh, long 
 // 4 x 3000 tokens 5 % of the chunk transform).  Packed batch: heads first, chunk by chunk -- workgroup n runs on XCD
 // n % 8, and with chunks first an XCD would take the same chunk numbers of every sequence, of which the late ones
 // exist in the long sequences only.  64 sequences of 256 .. 2048 tokens, 8 heads, d = 128: chunk transform 799 ->
-// 584 us, with the backward's outputs 1042 -> 796, its adjoint 1610 -> 1128.  The heads are turned by one per chunk: with a
-// multiple of eight of them in all, the chunks of a head would go to one XCD and to half of its CUs, a balance only if
-// every sequence by itself has eight heads.  Forward and backward, turned / not, us: one sequence of 4096 tokens and 31 of
-// 100, 2 heads, d = 128 770 / 1097, 8 heads 1304 / 1430; the 64 sequences above 5449 / 5498, with 1 head 992 / 1090; 8 of
-// 456 .. 1300, 3 heads, fp32, d = 64 1777 / 1860 (chunks first 1799).
+// 584 us, with the backward's outputs 1042 -> 796, its adjoint 1610 -> 1128.
+// Where a sequence has no multiple of eight heads, they are turned by one per chunk: else, with a multiple of eight in all,
+// the chunks of a head go to one XCD and to half of its CUs, and sequences of different lengths do not balance each other.
+// Not if an XCD has a CU for each of its chunks anyway: then a head's chunks had better lie in the L2 of the XCD that its
+// sweeps run on (4 sequences of 56 .. 292 tokens, 2 heads, d = 128, forward and backward: turned 127 us, not 118).  Turned / not,
+// us: one sequence of 4096 tokens and 31 of 100, 2 heads, d = 128 768 / 1096; the 64 sequences above with 1 head 1003 / 1095;
+// 8 of 456 .. 1300, 4 heads, fp32, d = 64 1903 / 1988 (chunks first 1881).
 __device__ __forceinline__ void chunk_and_head(const UserLayout& u, int NC, int BH, int& chunk, int& bh) {
     const int n = blockIdx.x, m = u.cu ? BH : NC;
     const int hi = __builtin_amdgcn_readfirstlane(n / m), lo = n - hi * m;       // (the division runs on the vector unit)
-    chunk = u.cu ? hi : lo;
-    bh = u.cu ? lo + __builtin_amdgcn_readfirstlane(hi % m) : hi;
-    if (u.cu && bh >= m) bh -= m;
+    if (!u.cu) { chunk = lo; bh = hi; return; }
+    chunk = hi;
+    bh = lo;
+    if ((u.H & 7) && NC * ((BH + 7) >> 3) > 32) {
+        bh += __builtin_amdgcn_readfirstlane(hi % m);
+        if (bh >= m) bh -= m;
+    }
 }
 // length of head bh's sequence: the launch's L, or the head's own in a packed batch
 __device__ __forceinline__ int seq_len(const UserLayout& u, int bh, int L) {
