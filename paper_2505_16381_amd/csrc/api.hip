@@ -519,7 +519,7 @@ static path_status_t bwd_run(BwdMode mode, int stages, const UserLayout& ul, con
         }
         a.M = M; a.N = N; a.K = K; a.alpha = alpha; a.mask = mask; a.NC = NC; a.L = L;
         a.cmul = cmul; a.cadd = cadd; a.gridx = cmul == 1 ? NC : (NC + cmul - 1) / cmul; a.ul = ul;
-        ok = hip_ok(launch_batched_gemm(a, BH, bf, st), "chunk-transform adjoint product");
+        ok = hip_ok(launch_batched_gemm(a, BH, st), "chunk-transform adjoint product");
     };
     float *dpd = F(ws.dpd), *pd = F(ws.pd), *dsd = F(ws.dsd), *df = F(ws.df), *dy = F(ws.dy), *dn = F(ws.dn);
     float *dgk = F(ws.dgk), *rr = F(ws.rr), *mm = F(ws.mm), *dgs = F(ws.dgs), *du = F(ws.du);
@@ -628,13 +628,13 @@ static path_status_t bwd_run(BwdMode mode, int stages, const UserLayout& ul, con
     prod(dkf, OUT_TOK, dkf, chunk_t(dgk, EL_OP), user_t(w), 64, d, 64, 1.f, MASK_NONE, true, true);          // dK += dGk^T W
     special(OP_STORE);                                                                                         // to the I/O dtype
     if (chain_open || pr.n > MAX_CHUNK_OPS) return PATH_ERR_HIP;
-    ok = hip_ok(launch_chunk_adjoint(pr, BH, bf, st), "chunk-transform adjoint");
+    ok = hip_ok(launch_chunk_adjoint(pr, BH, st), "chunk-transform adjoint");
     if (ok && log_f) {
         // dlog f_s = sum over the pairs j < s <= i of the logit gradient = (column sums left of s) - (row sums
         // above s).  The row sums vanish in exact arithmetic; subtracting them as computed removes the error that
         // delta = dO . o (o rounded to the I/O type) puts into every row, which the prefix sum would pile up.
         ScanArgs sa{bp.dcol, bp.drow, dlog_f, (int)Lp, L, L, L, 0, 1.f, 0, 1, ul};
-        ok = hip_ok(launch_fox_scan(sa, BH, 0, bf ? 1 : 0, st), "gate gradient");
+        ok = hip_ok(launch_fox_scan(sa, BH, 0, 0, st), "gate gradient");
     }
     return ok ? PATH_OK : PATH_ERR_HIP;
 }

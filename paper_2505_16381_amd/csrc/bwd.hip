@@ -1146,36 +1146,29 @@ hipError_t launch_bwd_scan(const BwdParams& p, int d, int is_bf16, int stages, h
 #undef LAUNCH_SCAN
 }
 
-hipError_t launch_batched_gemm(const GemmArgs& a, int BH, int is_bf16, hipStream_t st) {
-    const size_t es = is_bf16 ? 2 : 4, fe = is_bf16 ? 8 : 4;
-    const size_t bytes = (size_t)(a.M + a.N) * (a.K + fe) * es;
+// (the second level's adjoint and the chunk-transform adjoint as products: fp32 operands)
+hipError_t launch_batched_gemm(const GemmArgs& a, int BH, hipStream_t st) {
+    const size_t bytes = (size_t)(a.M + a.N) * (a.K + 4) * 4;
     dim3 grid(a.gridx, BH);
-    const hipError_t e = is_bf16 ? set_smem<&batched_gemm_kernel<bf16_t>>(160 * 1024) : set_smem<&batched_gemm_kernel<float>>(160 * 1024);
+    const hipError_t e = set_smem<&batched_gemm_kernel<float>>(160 * 1024);
     if (e != hipSuccess) return e;
-    if (is_bf16) hipLaunchKernelGGL((batched_gemm_kernel<bf16_t>), grid, dim3(256), bytes, st, a);
-    else hipLaunchKernelGGL((batched_gemm_kernel<float>), grid, dim3(256), bytes, st, a);
+    hipLaunchKernelGGL((batched_gemm_kernel<float>), grid, dim3(256), bytes, st, a);
     return hipGetLastError();
 }
 
-hipError_t launch_chunk_adjoint(const ChunkProgram& pr, int BH, int is_bf16, hipStream_t st) {
-    const size_t es = is_bf16 ? 2 : 4, fe = is_bf16 ? 8 : 4;
+hipError_t launch_chunk_adjoint(const ChunkProgram& pr, int BH, hipStream_t st) {
     size_t bytes = 1024;
     for (int i = 0; i < pr.n; ++i) {
         if (pr.ops[i].kind != OP_PRODUCT) continue;
-        const size_t b = (size_t)(CHUNK + CHUNK) * (pr.ops[i].K + fe) * es;      // A and half of B
+        const size_t b = (size_t)(CHUNK + CHUNK) * (pr.ops[i].K + 4) * 4;      // A and half of B
         if (b > bytes) bytes = b;
     }
     const bool fox = pr.diag.cum != nullptr;
     hipError_t e;
     dim3 grid(pr.NC, BH);
-#define LAUNCH_CHUNK_ADJ(TT, FF)                                                                  \
-    do {                                                                                          \
-        if ((e = set_smem<&chunk_adjoint_kernel<TT, FF>>(160 * 1024)) != hipSuccess) return e;   \
-        hipLaunchKernelGGL((chunk_adjoint_kernel<TT, FF>), grid, dim3(256), bytes, st, pr);       \
-    } while (0)
-    if (is_bf16) { if (fox) LAUNCH_CHUNK_ADJ(bf16_t, true); else LAUNCH_CHUNK_ADJ(bf16_t, false); }
-    else { if (fox) LAUNCH_CHUNK_ADJ(float, true); else LAUNCH_CHUNK_ADJ(float, false); }
-#undef LAUNCH_CHUNK_ADJ
+    if ((e = fox ? set_smem<&chunk_adjoint_kernel<float, true>>(160 * 1024) : set_smem<&chunk_adjoint_kernel<float, false>>(160 * 1024)) != hipSuccess) return e;
+    if (fox) hipLaunchKernelGGL((chunk_adjoint_kernel<float, true>), grid, dim3(256), bytes, st, pr);
+    else hipLaunchKernelGGL((chunk_adjoint_kernel<float, false>), grid, dim3(256), bytes, st, pr);
     return hipGetLastError();
 }
 

@@ -114,7 +114,7 @@ struct ChunkProgram {
     OutArgs out;
     int L, NC;
 };
-hipError_t launch_chunk_adjoint(const ChunkProgram& pr, int BH, int is_bf16, hipStream_t st);
+hipError_t launch_chunk_adjoint(const ChunkProgram& pr, int BH, hipStream_t st);                    // fp32 operands only
 
 // The same steps as one hand-fused kernel (2-byte operand types): every input is a plain pointer.
 struct ChunkFusedArgs {
@@ -144,7 +144,7 @@ hipError_t launch_bwd_scan(const BwdParams& p, int d, int is_bf16, int stages, h
 hipError_t launch_bwd_near(const BwdParams& p, int d, hipStream_t st);                   // 2-byte operand types only
 hipError_t launch_bwd_adjoint(const BwdParams& p, hipStream_t st);                       // 2-byte operand types, d = 128
 hipError_t launch_bwd_far(const BwdParams& p, int d, hipStream_t st);                    // 2-byte operand types only
-hipError_t launch_batched_gemm(const GemmArgs& a, int BH, int is_bf16, hipStream_t st);
+hipError_t launch_batched_gemm(const GemmArgs& a, int BH, hipStream_t st);                          // fp32 operands only
 hipError_t launch_bwd_sb_chain(const SbChainArgs& a, int BH, int d, hipStream_t st);    // 2-byte operand types only
 
 }  // namespace path
