@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
     ("bf16", 128, 1, 3, 0), ("bf16", 64, 1, 2, 1), ("bf16", 128, 2, 2, 33), ("bf16", 64, 1, 3, 128), ("bf16", 64, 1, 3, 129),
     ("bf16", 128, 1, 2, 512), ("bf16", 128, 1, 2, 513), ("bf16", 64, 2, 2, 1024), ("bf16", 64, 2, 2, 1025), ("bf16", 128, 1, 2, 1089),
     ("bf16", 128, 1, 1, 8200), ("bf16", 64, 16, 65, 1100), ("fp32", 128, 1, 2, 129), ("fp32", 128, 1, 2, 256),
-    ("fp32", 128, 1, 2, 257), ("fp32", 64, 1, 2, 513), ("fp32", 64, 1, 1, 5000)])
+    ("fp32", 128, 1, 2, 257), ("fp32", 64, 1, 2, 513), ("fp32", 64, 1, 1, 5000), ("fp32", 128, 1, 1, 4100), ("fp32", 128, 1, 2, 8200)])
 def test_one_step_from_random_caches(dtype, d, B, H, n, gates):
     import torch
     import paper_2505_16381_amd as pa
@@ -45,7 +45,10 @@ def test_one_step_from_random_caches(dtype, d, B, H, n, gates):
     e_o, e_l = np.abs(f(o) - ref[0]).max(), np.abs(f(lse) - ref[1]).max()
     e_k = (np.abs(f(gk)[:, :, :n + 1] - ref[2]) - (0 if dtype == "fp32" else 2.0 ** -7) * np.abs(ref[2])).max()
     print(f"[decode {dtype} d={d} B={B} H={H} n={n} gates={gates}] max|do|={e_o:.2e} max|dlse|={e_l:.2e} keys {e_k:.2e}", flush=True)
-    assert e_o <= (1e-4 if dtype == "fp32" else 2e-2) and e_l <= 1e-3 and e_k <= 1e-5
+    # outputs shrink with the number of keys (a mean of n values): the bar is a share of the largest one.  bf16: 2^-9 from the
+    # rounding of o, and as much again at most from the logits; of 64 splits a single one left out moves o by 5e-2 of it or more
+    e_r = e_o / np.abs(ref[0]).max()
+    assert e_r <= (1e-4 if dtype == "fp32" else 1e-2) and e_l <= 1e-3 and e_k <= 1e-5
     assert torch.equal(gv[:, :, :n].cpu(), vc[:, :, :n]) and torch.equal(gv[:, :, n].cpu(), v) and torch.equal(gk[:, :, n].cpu(), k)
     assert torch.equal(gk[:, :, n + 1:].cpu(), kc[:, :, n + 1:]) and torch.equal(gv[:, :, n + 1:].cpu(), vc[:, :, n + 1:])
     want_c = cc.clone()
