@@ -181,8 +181,10 @@ struct DecodeTail {
 // through LDS costs its latency eight times per key).
 // What bounds it: HBM (3 n d elements per head), for few heads the latency of a step.  Values are read and refreshed
 // keys written past the caches' replacement (non-temporal), which leaves the Infinity Cache (256 MB) to the keys, the
-// one stream that is both read and written; the same hint on the key reads costs 15 %.  B=4, H=16, n=8192,
-// d=128: 96 -> 67 us (6.0 TB/s; without the hints 91); one sequence of 16 heads, n=32768: 116 -> 68.
+// one stream that is both read and written; the same hint on the key reads costs 15 %.  d = 128, replayed from a graph,
+// against a pass without prefetch, hints and DPP sums: B=4, H=16, n=8192 with one cache step after step, whose keys stay in
+// that cache, 81.6 -> 65.3 us (without the hints a third slower), with six caches in turn, as a model's layers have them, 96.6
+// -> 84.0 (4.8 TB/s); 16 heads of 32768 keys 101.8 -> 67.3 and 117.6 -> 85.6.
 template <int LPK> __device__ __forceinline__ float group_sum(float x) {      // over the LPK lanes of a key, in all of them
     static_assert(LPK == 8 || LPK == 16, "within a row of 16 lanes");
     auto add = [&](auto ctrl) { x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), decltype(ctrl)::value, 0xf, 0xf, true)); };
@@ -403,12 +405,13 @@ int decode_num_splits(int BH, int n) {
     return s < 1 ? 1 : s;
 }
 
-// Heads of up to 128 KB of keys are not split: one workgroup, one launch.  On the GPU the split pays from about 64 KB
-// on, where one CU's share of the memory bandwidth starts to count -- 16 heads of 200 keys, d = 128 (51 KB) 6.9 us against
-// 8.2 split and merged, 16 heads of 500 (128 KB) 11.0 against 9.0 -- but a launch costs the host about 3 us and a step
-// that short is bound by it: called one after the other, steps of 500 keys take 11.9 us against 14.7.  At 256 KB the
-// one workgroup takes 17.9 us, the two launches 14.5.  Up to 128 keys four waves do: 512 heads of 100 keys, d = 64,
-// 7.9 us against 10.7 with sixteen.
+// Heads of up to 128 KB of keys are not split: one workgroup, one launch.  The choice favours steps that are launched one by
+// one, where a second launch costs the host about 3 us and a step that short is bound by it: 16 heads, d = 128, 12.9 us whatever
+// their length, against 15.9 split and merged.  On the GPU alone -- a step replayed from a graph -- one workgroup is ahead up to
+// 70 KB for up to 64 heads (200 keys 5.9 us against 6.6) and behind above (320: 7.1 / 6.8, 450: 8.6 / 6.8, 512: 9.1 / 6.9), for 256
+// heads and more always ahead (512 keys 16.8 / 21.0).  One rule for all callers: a replayed step, the step with static scratch
+// and the eager one give the same bits.  Up to 128 keys four waves do: 512 heads of 100 keys, d = 64, 7.9 us against 10.7 with
+// sixteen.
 template <typename TIO, int D, bool GATES>
 static hipError_t launch_decode_g(const DecodeArgs& a, int BH, hipStream_t st) {
     if ((size_t)a.n * D * sizeof(TIO) <= 131072) {
