@@ -298,7 +298,9 @@ path_status_t path_attn_varlen_bwd(const void* q, const void* k, const void* v, 
  * path_key_prefill: fills positions [0, L) of both caches after a prompt of L tokens (the
  * section's key-prefill formula, with suffix products: linear in L).  It reads the forward
  * workspace of the SAME prompt, i.e. call it after path_attn_fwd / path_attn_fwd_prep on
- * (q, k, v, w, beta) with that workspace (device, read-only here); v [B,H,L,d] is copied.
+ * (q, k, v, w, beta) with that workspace (device, read-only here); v [B,H,L,d] is copied.  (The workspace of a
+ * training pair will not do: nothing to the right of a prompt is ever asked of a training step, which leaves the last
+ * 1024 tokens' keys where the chunk transform put them.)
  * Errors: PATH_ERR_SHAPE also for L > Lmax.
  *
  * path_decode_step: one arriving token per (batch, head): q, k, v, w [B,H,d], beta [B,H] (dt,
@@ -353,7 +355,9 @@ path_status_t path_decode_step_fox(const void* q, const void* k, const void* v, 
  *                          elements per head).
  *   path_attn_ring_hop     attends the Lq queries of `state` to every key of an EARLIER segment of Lk tokens,
  *                          given as the workspace path_attn_ring_local filled on that segment (same B, H, d, dt),
- *                          and carries the state across that segment.  Hops are made nearest segment first.  Lk
+ *                          and carries the state across that segment.  (Not a workspace of another entry point: the
+ *                          ordinary forward of up to 1024 tokens and training pairs leave the second level out where
+ *                          nobody else reads it.)  Hops are made nearest segment first.  Lk
  *                          must be a multiple of 64 (PATH_ERR_SHAPE): only the last segment of a sequence may be
  *                          ragged, and it is nobody's earlier segment.  with_gates != 0: PaTH-FoX (the earlier
  *                          segment's gate sums are in its workspace; every segment of a sequence uses gates or none).

@@ -7,15 +7,16 @@
 //      Kb, product dP_j), the super-blocks further left as a whole ("far": one state for the
 //      super-block's SBC chunks, second-level keys Kb2, product dP2 = I - P_superblock).
 //   2. bwd_dotile:   delta_t = dO_t . o_t, and dO as operand tiles.
-//   3. bwd_adjoint2: per query chunk i, left-to-right over key chunks j:
+//   3. bwd_adjoint (bwd_adjoint.hip; d = 64 and short sequences bwd_adjoint2_lite, fp32 operands bwd_adjoint2): per query chunk i,
+//      left-to-right over key chunks j:
 //        dS = scale * P o (dO V_j^T - delta),   P = exp(scale * Xs Kb_j^T - lse)
 //        g(i,j) = dS Kb_j + g(i,j-1) (I - dP_j)^T          (g(i,-1) = 0)
 //      g(i,i-1) is the gradient of the boundary-adjusted queries Qb_i.
-//   4. bwd_keyside2 / bwd_ddp: per key chunk j, over query chunks i > j (no atomics):
+//   4. bwd_near / bwd_far (bwd_keys.hip; fp32 operands: bwd_keyside2 / bwd_ddp): per key chunk j, over query chunks i > j (no atomics):
 //        dV_j += P^T dO_i,  dKb_j += dS^T Xs(i,j),  ddP_j -= Xs(i,j)^T g(i,j-1).
 //   5. adjoint of the second level (dKb2, ddP2 -> dKb, ddP) and of the chunk transform
-//      (Qb, Kb, dP, Sd -> q, k, w, beta): short sequences of batched products (batched_gemm)
-//      and elementwise steps, driven from the host code.
+//      (Qb, Kb, dP, Sd -> q, k, w, beta): fused kernels (chunk_adj.hip); fp32 operands: short sequences of
+//      batched products (batched_gemm) and elementwise steps, driven from the host code.
 //
 // Steps 3 and 4 follow the forward's scheme: activations stay in registers in
 // transposed form, streamed operands are fragment-order tiles (written by prep, the

@@ -346,7 +346,8 @@ template <typename TIO, int D> struct NearCfg {
     static constexpr int STF = 3 * KVF + 32;                          // a stage: xs | doq | gT | lse2, delta
     static constexpr int PDF = 2 * 2 * 4 * 64;                        // a hand-over buffer: (P | dS) x 2 key halves x 4 slabs
     // d = 64: one hand-over buffer (and a second barrier per pair), so that two workgroups share a CU: a pair has half
-    // the products of d = 128 but the same element-wise part, and one workgroup alone leaves the matrix pipes idle.
+    // the products of d = 128 but the same element-wise part, and one workgroup alone leaves the matrix pipes idle.  (Two of
+    // the 128 registers that this leaves lie in scratch.)
     static constexpr int WGS_PER_CU = D == 64 ? 2 : 1, HB = D == 64 ? 1 : 2;
     static constexpr size_t smem_bytes = (size_t)(2 * STF + HB * PDF) * 16;
     static_assert(WGS_PER_CU * smem_bytes <= 160 * 1024, "LDS budget");

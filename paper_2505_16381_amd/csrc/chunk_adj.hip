@@ -42,7 +42,7 @@ template <typename TIO, int D> struct CaCfg {
     static constexpr int SMALL = 64 * LDC * 2;
     static constexpr int LDM = 65;             // pitch of the fp32 copy of M
     // byte offsets.  d = 128: W | X0 X3 (adjacent: ddP spans both, later the fp32 M) | X1 | X2 | Y0 Y1 Y2 | N | misc.
-    // d = 64, where all tiles have one size: W | X0 Y0 (adjacent: the fp32 M) | X1 | X2 | X3 = N | Y1 | Y2 | misc: 74 KB, two
+    // d = 64 (with gates 1 to 6 of the 128 registers lie in scratch), where all tiles have one size: W | X0 Y0 (adjacent: the fp32 M) | X1 | X2 | X3 = N | Y1 | Y2 | misc: 74 KB, two
     // workgroups per CU (with ten tiles, 92 KB and one workgroup it took 0.63 ms at B=8, H=16, L=4096).
     static constexpr int XW = 0, X0 = BIG, X3 = D == 64 ? 5 * BIG : 2 * BIG, X1 = 3 * BIG, X2 = 4 * BIG;
     static constexpr int Y0 = D == 64 ? 2 * BIG : 5 * BIG, Y1 = D == 64 ? 6 * BIG : Y0 + SMALL, Y2 = Y1 + SMALL, YN = D == 64 ? X3 : Y2 + SMALL;
@@ -500,7 +500,8 @@ hipError_t launch_t(const ChunkFusedArgs& a, int BH, hipStream_t st) {
 // adjoint does, where ddP_c and dKb_c are read anyway.  The rows of G do not depend on each other: a wave keeps 32 of
 // them, transposed, in accumulator registers (lane = row), its operand copy is those registers packed, and the only
 // thing the waves share is the tiles of U, W and Kb, fetched one chunk ahead.
-// What bounds it: memory (112 KB per chunk at d = 128), and the chain's latency when there are few heads.  As one
+// What bounds it: memory (112 KB per chunk at d = 128), and the chain's latency when there are few heads.  (At d = 128 it keeps
+// 8 to 14 registers in scratch: two workgroups per CU leave 256.)  As one
 // workgroup of eight waves that exchanged G through LDS and updated ddP and dKb in memory itself (304 KB per chunk)
 // it took 0.50 ms at B=4, H=16, L=8192, d=128.
 template <typename TIO, int D> struct SbCfg {

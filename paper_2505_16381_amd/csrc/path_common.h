@@ -23,7 +23,9 @@
 // is stored by the preprocessing kernel in exactly that order ("fragment
 // order"): fragment ((rb*(Kc/KW) + slab)*64 + lane) of a tile with rows
 // 32*rb + c and Kc contraction indices.  Lanes then read consecutive 16-byte
-// fragments: conflict-free LDS reads and linear global->LDS copies.
+// fragments: conflict-free LDS reads and linear global->LDS copies.  (16-bit
+// tiles of keys, -dP, query states, dO, R_c and its gradient exchange lanes
+// inside a slab, tile_lane() for lane, so that they can be read transposed too.)
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -436,8 +438,9 @@ __host__ __device__ constexpr size_t ring_rec_floats(int d) { return (size_t)2 *
 // transform nor its adjoint nor the far sums on it -- one super-block of eight at 8192 tokens, half of the chunks
 // of a batch of sequences of 256 to 2048 tokens, everything up to 1024 tokens.  Measured,
 // forward + backward: 64 packed sequences of 256 .. 2048 tokens (8 heads, d = 128) 7.50 -> 6.99 ms, one fp32 step of
-// 256 tokens 282 -> 253 us (three launches fewer).  (The plain forward fills it: the key
-// prefill of the decode path and the ring's hops carry keys beyond the head's end.)
+// 256 tokens 282 -> 253 us (three launches fewer).  (The forward of more than one super-block
+// and the ring fill it: the key prefill of the decode path and the ring's hops carry keys beyond the head's end.  A prompt of one
+// super-block is prefilled straight from the chunk tiles.)
 __host__ __device__ __forceinline__ bool is_last_sb(int sb, int NCown) { return (sb + 1) * SBC >= NCown; }
 
 // Key blocks of the backward, for query chunk i (own super-block I = i / SBC): the chunks

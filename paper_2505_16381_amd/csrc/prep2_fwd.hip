@@ -24,7 +24,8 @@
 // tiles each, and a single workgroup per CU with the next chunk's tiles on their way during the current one's products.
 // At d = 128: 64 heads of 7 super-blocks with the backward's outputs 160 us (4.3 TB/s), 512 heads of 2 without them
 // 154 us, one super-block per head into the cache 38 us.  (Waves that each took all of E's blocks from LDS, two
-// fragments per product: 171, 226 and, with the rows turned and copied afterwards, 84 us.)
+// fragments per product: 171, 226 and, with the rows turned and copied afterwards, 84 us.)  With the backward's outputs and
+// one stage, d = 128 keeps 8 registers in scratch.
 #include "path_common.h"
 #include "decode_decl.h"
 
