@@ -42,8 +42,9 @@ template <typename TIO, int D> struct CaCfg {
     static constexpr int SMALL = 64 * LDC * 2;
     static constexpr int LDM = 65;             // pitch of the fp32 copy of M
     // byte offsets.  d = 128: W | X0 X3 (adjacent: ddP spans both, later the fp32 M) | X1 | X2 | Y0 Y1 Y2 | N | misc.
-    // d = 64 (with gates 1 to 6 of the 128 registers lie in scratch), where all tiles have one size: W | X0 Y0 (adjacent: the fp32 M) | X1 | X2 | X3 = N | Y1 | Y2 | misc: 74 KB, two
-    // workgroups per CU (with ten tiles, 92 KB and one workgroup it took 0.63 ms at B=8, H=16, L=4096).
+    // d = 64, where all tiles have one size: W | X0 Y0 (adjacent: the fp32 M) | X1 | X2 | X3 = N | Y1 | Y2 | misc: 74 KB, two
+    // workgroups per CU (with ten tiles, 92 KB and one workgroup it took 0.63 ms at B=8, H=16, L=4096).  With gates 1 to 6 of
+    // its 128 registers lie in scratch.
     static constexpr int XW = 0, X0 = BIG, X3 = D == 64 ? 5 * BIG : 2 * BIG, X1 = 3 * BIG, X2 = 4 * BIG;
     static constexpr int Y0 = D == 64 ? 2 * BIG : 5 * BIG, Y1 = D == 64 ? 6 * BIG : Y0 + SMALL, Y2 = Y1 + SMALL, YN = D == 64 ? X3 : Y2 + SMALL;
     static constexpr int MISC = D == 64 ? Y2 + SMALL : YN + SMALL;
