@@ -420,16 +420,14 @@ def main():
     fwd_tflops = fl_f / ((prep_ms + sweep_ms) * 1e-3) / 1e12
     sweep_tflops = fl_f / (sweep_ms * 1e-3) / 1e12
     # Roofline of the dominant kernel of the timed step.  The stages that are ONE kernel launch each are the sweep
-    # and the two key-side passes; their algorithmic flops: sweep 4d per (query, key <= query) pair; key-side 8d
+    # and the far key-side pass; their algorithmic flops: sweep 4d per (query, key <= query) pair; key-side 8d
     # per pair of its range (logit and dP recomputed, dV and dK accumulated: four d-long dot products).
-    near_pairs, far_pairs = pair_counts(L)
+    _, far_pairs = pair_counts(L)
     single = {"attn_fwd2_kernel (forward sweep" + ("; in the training pair it also writes the backward's query states)" if do_bwd else ")"):
               (sweep_ms, fl_f, "4*d flops per (query, key <= query) pair")}
     if do_bwd:
         single["bwd_far_kernel (key-side sums over the queries right of the key's super-block)"] = (
             stage_ms["keys_far"], 8.0 * d * far_pairs * B * H, "8*d flops per (query, key) pair with the key in a super-block left of the query's")
-        single["bwd_near_kernel (key-side sums inside the key's super-block; also the near product gradients)"] = (
-            stage_ms["keys_near"], 8.0 * d * near_pairs * B * H, "8*d flops per (query, key) pair of one super-block, key chunk left of the query chunk")
     dom = max(single, key=lambda kname: single[kname][0])
     dom_ms, dom_fl, dom_note = single[dom]
     traffic = profiled_traffic(dom.split(" ")[0]) if (args.config == 2 and not args.shape) else None

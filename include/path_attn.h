@@ -232,10 +232,11 @@ path_status_t path_attn_train_bwd(const void* q, const void* k, const void* v, c
  * a later stage reads what the earlier ones left in the workspace.  Unknown or no bits: PATH_ERR_UNSUPPORTED. */
 enum {
     PATH_BWD_STAGE_SCAN = 1,       /* dO tiles and delta; adjoint scan over the key blocks (dQ-side)          */
-    PATH_BWD_STAGE_KEYS_NEAR = 2,  /* key-side sums over the query chunks of the key's own super-block       */
+    PATH_BWD_STAGE_KEYS_NEAR = 2,  /* PATH_F32: key-side sums inside a super-block (PATH_BF16: in _CHUNK)     */
     PATH_BWD_STAGE_KEYS_FAR = 4,   /* key-side sums over all queries right of the key's super-block          */
     PATH_BWD_STAGE_DDP = 8,        /* PATH_F32: gradients of the products (PATH_BF16: the key-side passes)   */
-    PATH_BWD_STAGE_CHUNK = 16,     /* adjoint of the second level and of the chunk transform: the gradients  */
+    PATH_BWD_STAGE_CHUNK = 16,     /* adjoint of the second level and of the chunk transform: the gradients;
+                                    * PATH_BF16: first the key-side sums inside the key's own super-block    */
     PATH_BWD_STAGE_ALL = 31
 };
 path_status_t path_attn_train_bwd_stages(int stages, const void* q, const void* k, const void* v, const void* w,

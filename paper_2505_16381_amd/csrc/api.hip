@@ -88,8 +88,9 @@ static BwdWorkspace bwd_workspace(int B, int H, int L, int d, size_t es) {
     take(w.sdm, staged * BH * NC * 4096 * 4);
     take(w.delta, BH * Lp * 4);
     take(w.lse2p, BH * Lp * 4);
-    for (size_t* f : {&w.dqb, &w.dkb, &w.dvp}) take(*f, BH * Lp * d * 4);
-    take(w.ddp, BH * NC * d * d * 4);
+    for (size_t* f : {&w.dqb, &w.dvp}) take(*f, BH * Lp * d * 4);
+    take(w.dkb, staged * BH * Lp * d * 4);
+    take(w.ddp, staged * BH * NC * d * d * 4);
     for (size_t* f : {&w.dpd, &w.pd, &w.dsd, &w.df, &w.dy, &w.dn, &w.dgk, &w.rr, &w.mm, &w.dgs}) take(*f, staged * BH * NC * 4096 * 4);
     for (size_t* f : {&w.du, &w.dqf, &w.dkf, &w.dwf}) take(*f, staged * BH * Lp * d * 4);
     take(w.dbf, staged * BH * Lp * 4);
@@ -568,7 +569,7 @@ static path_status_t bwd_run(BwdMode mode, int stages, const UserLayout& ul, con
     if (!ok) return PATH_ERR_HIP;
     if (bf) {      // 2-byte operand types: the hand-fused kernel
         ChunkFusedArgs ca{ul, q, k, v, w, beta, d_o, lse, bp.delta, fp.sd, fp.fm, fp.gktm, fp.nm, fp.aim, fp.ytm,
-                          base + ws.utm, bp.dqb, bp.dkb, bp.dvp, F(ws.ddp), NC > SBC ? base + ws.rm : nullptr, base + ws.dr, F(ws.dk2), dq, dk, dv, dw, dbeta, bp.cum, bp.dcol, bp.drow,
+                          base + ws.utm, fp.kt, fp.vk, bp.doq, fp.xs, bp.gs, bp.lse2p, bp.dqb, bp.dvp, base + ws.rm, base + ws.dr, F(ws.dk2), dq, dk, dv, dw, dbeta, bp.cum, bp.dcol, bp.drow,
                           L, NC, BH, scale};
         ok = hip_ok(launch_chunk_fused(ca, BH, d, st), "chunk-transform adjoint");
         if (ok && log_f) {

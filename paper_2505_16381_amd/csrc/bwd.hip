@@ -12,7 +12,7 @@
 //        dS = scale * P o (dO V_j^T - delta),   P = exp(scale * Xs Kb_j^T - lse)
 //        g(i,j) = dS Kb_j + g(i,j-1) (I - dP_j)^T          (g(i,-1) = 0)
 //      g(i,i-1) is the gradient of the boundary-adjusted queries Qb_i.
-//   4. bwd_near / bwd_far (bwd_keys.hip; fp32 operands: bwd_keyside2 / bwd_ddp): per key chunk j, over query chunks i > j (no atomics):
+//   4. bwd_far (bwd_keys.hip) and the near sums of chunk_fused (chunk_adj.hip; fp32 operands: bwd_keyside2 / bwd_ddp): per key chunk j, over query chunks i > j (no atomics):
 //        dV_j += P^T dO_i,  dKb_j += dS^T Xs(i,j),  ddP_j -= Xs(i,j)^T g(i,j-1).
 //   5. adjoint of the second level (dKb2, ddP2 -> dKb, ddP) and of the chunk transform
 //      (Qb, Kb, dP, Sd -> q, k, w, beta): fused kernels (chunk_adj.hip); fp32 operands: short sequences of
@@ -1106,14 +1106,12 @@ static hipError_t launch_scan_t(const BwdParams& p, int stages, hipStream_t st) 
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    if (stages & BWD_STAGE_KEYS_NEAR) {
-        if constexpr (F32) {
+    if constexpr (F32) {       // (16-bit operands: the chunk-transform adjoint takes the near sums)
+        if (stages & BWD_STAGE_KEYS_NEAR) {
             const size_t key_bytes = Key2Cfg<TIO, D>::smem_bytes;
             if ((e = set_smem<&bwd_keyside2_kernel<TIO, D, false, FOX>>(key_bytes)) != hipSuccess) return e;
             hipLaunchKernelGGL((bwd_keyside2_kernel<TIO, D, false, FOX>), dim3(rounds * nsb * SBC), dim3(256), key_bytes, st, p);
             if ((e = hipGetLastError()) != hipSuccess) return e;
-        } else {
-            if ((e = launch_bwd_near(p, D, st)) != hipSuccess) return e;
         }
     }
     if (has_far && (stages & BWD_STAGE_KEYS_FAR)) {

@@ -124,8 +124,10 @@ struct ChunkFusedArgs {
     const float* sd;                             // raw diagonal logits as the sweep reads them (accumulator order)
     const void *fm, *gktm, *nm, *aim, *ytm;      // operand type, [BH][NC][64][64]
     const void* utm;                             // operand type, [BH][NC][d][64]
-    const float *dqb, *dkb, *dvp;                // [BH][Lp][d]
-    const float* ddp;                            // [BH][NC][d][d]: its near part
+    // near key-side sums: chunk-level keys, values, dO tiles; states and adjoint states of the pairs; row constants
+    const void *kt, *vk, *doq, *xs, *gs;
+    const float* lse2p;                          // [BH][Lp]
+    const float *dqb, *dvp;                      // [BH][Lp][d]: dQb; dV over the far queries (not of the last super-block's keys)
     const void *rm, *dr;                         // second level: tiles of R_c and of the gradient of R_{c-1} (NULL: one super-block)
     const float* dk2;                            // [BH][Lp][d]: gradient of the second-level keys
     void *dq, *dk, *dv, *dw, *dbeta;             // I/O type
@@ -137,11 +139,10 @@ struct ChunkFusedArgs {
 hipError_t launch_chunk_fused(const ChunkFusedArgs& a, int BH, int d, hipStream_t st);
 
 // Stages of the backward after the transforms, as bits (the public PATH_BWD_STAGE_* values of the header):
-// dO tiles + adjoint scan | near key-side | far key-side | far (fp32: and near) ddP | second-level chain and
-// chunk-transform adjoint.  launch_bwd_scan runs the first four as asked, in this order.
+// dO tiles + adjoint scan | near key-side (fp32) | far key-side | ddP (fp32) | second-level chain and chunk-transform
+// adjoint (16-bit operands: with the near key-side sums).  launch_bwd_scan runs the first four as asked, in this order.
 enum { BWD_STAGE_SCAN = 1, BWD_STAGE_KEYS_NEAR = 2, BWD_STAGE_KEYS_FAR = 4, BWD_STAGE_DDP = 8, BWD_STAGE_CHUNK = 16, BWD_STAGE_ALL = 31 };
 hipError_t launch_bwd_scan(const BwdParams& p, int d, int is_bf16, int stages, hipStream_t st);
-hipError_t launch_bwd_near(const BwdParams& p, int d, hipStream_t st);                   // 2-byte operand types only
 hipError_t launch_bwd_adjoint(const BwdParams& p, hipStream_t st);                       // 2-byte operand types, d = 128
 hipError_t launch_bwd_far(const BwdParams& p, int d, hipStream_t st);                    // 2-byte operand types only
 hipError_t launch_batched_gemm(const GemmArgs& a, int BH, hipStream_t st);                          // fp32 operands only

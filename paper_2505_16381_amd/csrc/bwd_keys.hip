@@ -176,9 +176,9 @@ __global__ __launch_bounds__(512, 2) void bwd_far_kernel(BwdParams p) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) element_wise(st, 1, S1, P1, k);
         lds_barrier();
-        if (FOX) {           // the two half-waves hold different query rows of the same keys; added to the near part
+        if (FOX) {           // the two half-waves hold different query rows of the same keys
             dcol += __shfl_xor(dcol, 32);
-            if (h == 0) p.dcol[(size_t)bh * Lp + key_tok] += dcol;
+            if (h == 0) p.dcol[(size_t)bh * Lp + key_tok] = dcol;
         }
         return;
     }
@@ -303,12 +303,10 @@ __global__ __launch_bounds__(512, 2) void bwd_far_kernel(BwdParams p) {
             for (int b = 0; b < DB; ++b)
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
-                    float* dst = (KEYS ? p.dk2 : p.dvp) + row + (size_t)(32 * k) * D + 32 * b + 8 * g;
-                    f32x4 v4 = {0.f, 0.f, 0.f, 0.f};
-                    if (!KEYS) v4 = *reinterpret_cast<const f32x4*>(dst);      // dV: added to the near part
+                    f32x4 v4;
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) v4[r] = KEYS ? p.scale * acc[b][k][4 * g + r] : v4[r] + acc[b][k][4 * g + r];
-                    *reinterpret_cast<f32x4*>(dst) = v4;
+                    for (int r = 0; r < 4; ++r) v4[r] = KEYS ? p.scale * acc[b][k][4 * g + r] : acc[b][k][4 * g + r];
+                    *reinterpret_cast<f32x4*>((KEYS ? p.dk2 : p.dvp) + row + (size_t)(32 * k) * D + 32 * b + 8 * g) = v4;
                 }
         if (KEYS && Blocks::writes(pos, ck)) {
             // the gradient of P_superblock starts the second level's chain (nothing lies left of super-block 0)
@@ -326,235 +324,6 @@ __global__ __launch_bounds__(512, 2) void bwd_far_kernel(BwdParams p) {
     else sums(std::true_type{});
 }
 
-// ---------------------------------------------------------------------------------------
-// Key-side sums over the NEAR query chunks (those right of the key's chunk inside its own super-block), 16-bit
-// operands: one key chunk j per workgroup, chunk-level keys Kb, and the chunk's own product,
-//
-//     S = Xs Kb_j^T,  dP = dO V_j^T,  ...       dV^T += dO^T P      dKb^T += Xs^T dS      ddP_j -= Xs^T g
-//
-// Split by kind as above, one barrier per pair (64 queries):
-//   waves 0..3  (key half w & 1) x (query half w >> 1): logits, dP, element-wise part of the pair;
-//   waves 4..7  a quarter of each sum: ddP_j of this pair, dV^T and dKb^T of the pair before (its transposed fragments
-//               stay in registers, so that two stages of tiles do).
-// All eight request the next pair's tiles.
-// What bounds it: memory.  At B=4, H=16, L=8192, d=128 it reads 2.0 GB of states and adjoint states, each pair's once,
-// and writes 1.07 GB of sums (0.61 ms at the 5.1 TB/s of a large copy); 0.98 -> 0.75 ms with this split against one
-// wave per SIMD doing all of it in turn.  B=8, H=16, L=4096, d=64: 1.4 GB = 0.28 ms; 0.35 -> 0.34.
-template <typename TIO, int D> struct NearCfg {
-    typedef typename Compute<TIO>::type T;
-    static constexpr int KVF = CHUNK * D / Tr<T>::FE;                 // fragments of a tile
-    static constexpr int STF = 3 * KVF + 32;                          // a stage: xs | doq | gT | lse2, delta
-    static constexpr int PDF = 2 * 2 * 4 * 64;                        // a hand-over buffer: (P | dS) x 2 key halves x 4 slabs
-    // d = 64: one hand-over buffer (and a second barrier per pair), so that two workgroups share a CU: a pair has half
-    // the products of d = 128 but the same element-wise part, and one workgroup alone leaves the matrix pipes idle.  (Two of
-    // the 128 registers that this leaves lie in scratch.)
-    static constexpr int WGS_PER_CU = D == 64 ? 2 : 1, HB = D == 64 ? 1 : 2;
-    static constexpr size_t smem_bytes = (size_t)(2 * STF + HB * PDF) * 16;
-    static_assert(WGS_PER_CU * smem_bytes <= 160 * 1024, "LDS budget");
-};
-
-template <typename TIO, int D, bool FOX>
-__global__ __launch_bounds__(512, 2 * (NearCfg<TIO, D>::WGS_PER_CU)) void bwd_near_kernel(BwdParams p) {
-    using C = NearCfg<TIO, D>;
-    using T = typename C::T;
-    using Frag = typename Tr<T>::Frag;
-    using FragV = typename Tr<TIO>::Frag;
-    constexpr int KW = Tr<T>::KW, SPB = 32 / KW, DB = D / 32, DS = D / KW, QS = CHUNK / KW;
-    constexpr int KVF = C::KVF, STF = C::STF, PDF = C::PDF, HB = C::HB;
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    Frag* const stages = reinterpret_cast<Frag*>(smem);
-    Frag* const hand = stages + 2 * STF;
-
-    // numbering as above; inside a super-block the key chunks with the most queries first
-    const int NC = p.NC, nsb = (NC + SBC - 1) / SBC;
-    const int xcd = blockIdx.x & 7, kk = blockIdx.x >> 3;
-    const int j = __builtin_amdgcn_readfirstlane(kk / SBC % nsb * SBC + kk % SBC);
-    const int bh = __builtin_amdgcn_readfirstlane(kk / (SBC * nsb) * 8 + xcd);
-    if (bh >= p.B * p.H) return;
-    const int NCo = (seq_len(p.ul, bh, p.L) + CHUNK - 1) / CHUNK;      // this head's own chunks
-    if (j >= NCo) return;
-    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), h = lane >> 5, l32 = lane & 31;
-    const size_t Lp = (size_t)NC * CHUNK, nslots = num_block_slots(NC);
-    const int i0 = j + 1, i1 = (j / SBC + 1) * SBC < NCo ? (j / SBC + 1) * SBC : NCo;
-
-    auto issue = [&](int i) {                             // into stage i & 1, by all eight waves
-        Frag* buf = stages + (i & 1) * STF;
-        const size_t slot = ((size_t)bh * nslots + block_slot(i, j, NC)) * (size_t)CHUNK * D;
-        async_copy_tile<512, KVF>(reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(p.xs) + slot), buf, tid, wv);
-        async_copy_tile<512, KVF>(reinterpret_cast<const Frag*>(reinterpret_cast<const TIO*>(p.doq) + ((size_t)bh * NC + i) * CHUNK * D), buf + KVF, tid, wv);
-        async_copy_tile<512, KVF>(reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(p.gs) + slot), buf + 2 * KVF, tid, wv);
-        if (tid < 32) {         // 64 floats of lse2 (lanes 0-15) and of delta (lanes 16-31): 16 bytes per lane
-            const float* src = (tid < 16 ? p.lse2p : p.delta) + (size_t)bh * Lp + (size_t)i * CHUNK + 4 * (tid & 15);
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
-                                             (__attribute__((address_space(3))) void*)(buf + 3 * KVF), 16, 0, 0);
-        }
-    };
-    if (i0 < i1) issue(i0);
-
-    if (wv < 4) {
-        // ---- logits and the element-wise part -----------------------------------------------------------------
-        const float sl2 = p.scale * 1.44269504088896340736f;
-        const int kh = wv & 1, qh = wv >> 1;
-        Frag Kb[DS];
-        FragV Vb[DS];
-        {
-            const Frag* kg = reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(p.kt) + ((size_t)bh * NC + j) * CHUNK * D);
-            const FragV* vg = reinterpret_cast<const FragV*>(reinterpret_cast<const TIO*>(p.vk) + ((size_t)bh * NC + j) * CHUNK * D);
-#pragma unroll
-            for (int s = 0; s < DS; ++s) { Kb[s] = kg[((size_t)kh * DS + s) * 64 + tile_lane<T>(lane, s)]; Vb[s] = vg[((size_t)kh * DS + s) * 64 + lane]; }
-        }
-        const int key_tok = j * CHUNK + 32 * kh + l32;
-        const float ckj = FOX ? p.cum[(size_t)bh * Lp + key_tok] : 0.f;
-        float dcol = 0.f;
-        for (int i = i0; i < i1; ++i) {
-            copies_landed();
-            lds_barrier();                                // pair i has landed; pair i - 1 has been read
-            const Frag* sX = stages + (i & 1) * STF;
-            const FragV* sDQ = reinterpret_cast<const FragV*>(sX + KVF);
-            Frag xa[DS];
-            FragV da[DS];
-#pragma unroll
-            for (int u = 0; u < DS; ++u) { xa[u] = sX[(qh * DS + u) * 64 + tile_lane<T>(lane, u)]; da[u] = sDQ[(qh * DS + u) * 64 + tile_lane<T>(lane, u)]; }
-            __builtin_amdgcn_sched_barrier(0);
-            if (i + 1 < i1) issue(i + 1);
-            __builtin_amdgcn_sched_barrier(0);
-            f32x16 S = zero16(), dP = zero16();           // rows q, lane s
-#pragma unroll
-            for (int u = 0; u < DS; ++u) {
-                S = Tr<T>::mma(xa[u], Kb[u], S);
-                dP = Tr<TIO>::mma(da[u], Vb[u], dP);
-            }
-            const float* lse2 = reinterpret_cast<const float*>(sX + 3 * KVF) + 32 * qh + 4 * h;
-            Frag* out = hand + (i & (HB - 1)) * PDF + (kh * QS + qh * SPB) * 64;
-            FragV Pb[SPB];
-            Frag dSb[SPB];
-#pragma unroll
-            for (int u = 0; u < SPB; ++u) {
-#pragma unroll
-                for (int g = 2 * u; g < 2 * u + 2; ++g) {
-                    const f32x4 ls = *reinterpret_cast<const f32x4*>(lse2 + 8 * g), dls = *reinterpret_cast<const f32x4*>(lse2 + CHUNK + 8 * g);
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        // Rows past L need no mask: their padded lse2p is huge, so P = exp2(-huge) = 0.
-                        float arg = __builtin_fmaf(S[4 * g + r], sl2, -ls[r]);
-                        if (FOX) arg -= ckj;
-                        const float P = __builtin_amdgcn_exp2f(arg);
-                        const float dz = P * (dP[4 * g + r] - dls[r]);      // the factor scale is applied to the finished sums
-                        if (FOX) dcol += dz;
-                        Pb[u][(4 * g + r) % 8] = (TIO)P;
-                        dSb[u][(4 * g + r) % 8] = (T)dz;
-                    }
-                }
-            }
-            if (HB == 1) lds_barrier();                   // the pair before has been read
-#pragma unroll
-            for (int u = 0; u < SPB; ++u) {
-                reinterpret_cast<FragV*>(out)[u * 64 + lane] = Pb[u];
-                out[(2 * QS + u) * 64 + lane] = dSb[u];
-            }
-        }
-        lds_barrier();
-        if (FOX) {           // summed over the half-waves here and over the two query halves through LDS
-            dcol += __shfl_xor(dcol, 32);
-            float* red = reinterpret_cast<float*>(stages);          // (nobody reads tiles any more)
-            if (qh == 1 && h == 0) red[32 * kh + l32] = dcol;
-            lds_barrier();
-            if (qh == 0 && h == 0) p.dcol[(size_t)bh * Lp + key_tok] = dcol + red[32 * kh + l32];
-        }
-        return;
-    }
-
-    // ---- the sums: row blocks NA rb .. of dV^T and dKb^T for key half kb, blocks (NA rb .., NA kb ..) of ddP ---------
-    constexpr int NA = DB / 2;
-    const int rb = (wv - 4) >> 1, kb = wv & 1;
-    f32x16 dV[NA], dK[NA], dd[NA][NA];
-#pragma unroll
-    for (int a = 0; a < NA; ++a) {
-        dV[a] = zero16(); dK[a] = zero16();
-#pragma unroll
-        for (int b = 0; b < NA; ++b) dd[a][b] = zero16();
-    }
-    Frag xt[NA * QS];
-    FragV dt[NA * QS];
-    auto pair_sums = [&](int i) {                         // dV^T, dKb^T of pair i
-        const Frag* in = hand + (i & (HB - 1)) * PDF + kb * QS * 64;
-        FragV pf[QS];
-        Frag sf[QS];
-#pragma unroll
-        for (int s = 0; s < QS; ++s) { pf[s] = reinterpret_cast<const FragV*>(in)[s * 64 + lane]; sf[s] = in[(2 * QS + s) * 64 + lane]; }
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int s = 0; s < QS; ++s)
-#pragma unroll
-            for (int a = 0; a < NA; ++a) {
-                dV[a] = Tr<TIO>::mma(dt[a * QS + s], pf[s], dV[a]);
-                dK[a] = Tr<T>::mma(xt[a * QS + s], sf[s], dK[a]);
-            }
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    auto pair_tile = [&](int i) {                         // ddP of pair i; its transposed fragments
-        const Frag* sX = stages + (i & 1) * STF;
-        Frag gf[NA * QS];
-#pragma unroll
-        for (int a = 0; a < NA; ++a)
-#pragma unroll
-            for (int s = 0; s < QS; ++s) {
-                xt[a * QS + s] = ld_tile_frag_tr<T, DS>(reinterpret_cast<const T*>(sX), s, NA * rb + a, l32, h);
-                gf[a * QS + s] = sX[2 * KVF + ((NA * kb + a) * QS + s) * 64 + lane];
-            }
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int s = 0; s < QS; ++s)
-#pragma unroll
-            for (int a = 0; a < NA; ++a)
-#pragma unroll
-                for (int b = 0; b < NA; ++b) dd[a][b] = Tr<T>::mma(xt[a * QS + s], gf[b * QS + s], dd[a][b]);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int a = 0; a < NA; ++a)
-#pragma unroll
-            for (int s = 0; s < QS; ++s) dt[a * QS + s] = ld_tile_frag_tr<TIO, DS>(reinterpret_cast<const TIO*>(sX + KVF), s, NA * rb + a, l32, h);
-    };
-    if (i0 < i1) {
-        copies_landed();
-        lds_barrier();
-        if (i0 + 1 < i1) issue(i0 + 1);
-        pair_tile(i0);
-        if (HB == 1) lds_barrier();
-        for (int i = i0 + 1; i < i1; ++i) {
-            copies_landed();
-            lds_barrier();
-            if (i + 1 < i1) issue(i + 1);
-            pair_sums(i - 1);
-            pair_tile(i);
-            if (HB == 1) lds_barrier();
-        }
-    }
-    lds_barrier();
-    if (i0 < i1) pair_sums(i1 - 1);
-    if (FOX) lds_barrier();
-
-    const size_t row = ((size_t)bh * Lp + j * CHUNK + 32 * kb + l32) * D + 4 * h;
-#pragma unroll
-    for (int a = 0; a < NA; ++a)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            f32x4 v4, k4;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) { v4[r] = dV[a][4 * g + r]; k4[r] = p.scale * dK[a][4 * g + r]; }
-            *reinterpret_cast<f32x4*>(p.dvp + row + 32 * (NA * rb + a) + 8 * g) = v4;
-            *reinterpret_cast<f32x4*>(p.dkb + row + 32 * (NA * rb + a) + 8 * g) = k4;
-        }
-    float* const ddp = p.ddp + ((size_t)bh * NC + j) * D * D;
-#pragma unroll
-    for (int a = 0; a < NA; ++a)
-#pragma unroll
-        for (int b = 0; b < NA; ++b)
-#pragma unroll
-            for (int jj = 0; jj < 16; ++jj)               // (chunk 0 has no transform to the left of it)
-                __builtin_nontemporal_store(j >= 1 ? -dd[a][b][jj] : 0.f, &ddp[(size_t)(32 * (NA * rb + a) + acc_row(jj, h)) * D + 32 * (NA * kb + b) + l32]);
-}
-
 template <typename TIO, int D, bool FOX>
 static hipError_t launch_far_f(const BwdParams& p, hipStream_t st) {
     using C = FarCfg<TIO, D>;
@@ -568,21 +337,6 @@ static hipError_t launch_far_f(const BwdParams& p, hipStream_t st) {
 hipError_t launch_bwd_far(const BwdParams& p, int d, hipStream_t st) {
     if (d == 64) return p.cum ? launch_far_f<bf16_t, 64, true>(p, st) : launch_far_f<bf16_t, 64, false>(p, st);
     return p.cum ? launch_far_f<bf16_t, 128, true>(p, st) : launch_far_f<bf16_t, 128, false>(p, st);
-}
-
-template <typename TIO, int D, bool FOX>
-static hipError_t launch_near_f(const BwdParams& p, hipStream_t st) {
-    using C = NearCfg<TIO, D>;
-    static const hipError_t attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&bwd_near_kernel<TIO, D, FOX>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::smem_bytes);
-    if (attr_err != hipSuccess) return attr_err;
-    const int nsb = (p.NC + SBC - 1) / SBC;
-    hipLaunchKernelGGL((bwd_near_kernel<TIO, D, FOX>), dim3((unsigned)(8 * ((p.B * p.H + 7) / 8) * nsb * SBC)), dim3(512), C::smem_bytes, st, p);
-    return hipGetLastError();
-}
-hipError_t launch_bwd_near(const BwdParams& p, int d, hipStream_t st) {
-    if (d == 64) return p.cum ? launch_near_f<bf16_t, 64, true>(p, st) : launch_near_f<bf16_t, 64, false>(p, st);
-    return p.cum ? launch_near_f<bf16_t, 128, true>(p, st) : launch_near_f<bf16_t, 128, false>(p, st);
 }
 
 }  // namespace path

@@ -1,4 +1,4 @@
-// Adjoint of the chunk transform (the UT transform of Sec. 3.2 and the diagonal block of
+// Near key-side sums and adjoint of the chunk transform (the UT transform of Sec. 3.2 and the diagonal block of
 // Sec. 3.3), fused: one workgroup per (chunk, head) for 2-byte operand types.  The paper gives
 // no backward; with the chunk's matrices (rows = the 64 tokens of the chunk)
 //
@@ -12,7 +12,7 @@
 //   dV  = dV' + P^T dO
 //   dF  = tril(-dSd Y^T - dQb U^T)            dY = -F^T dSd - W dKb^T
 //   dU  = -F^T dQb + W ddP                     dN = dY Gk^T + dU W^T
-//   (ddP, dKb: what the key-side kernels left plus the second level's share, see sb_chain_kernel below)
+//   (ddP, dKb: the near sums, which this kernel takes first, plus the second level's share, see sb_chain_kernel below)
 //   dGk = sl(N^T dY)     R = A^-T dN     M = sl(-R N^T)     dGs = diag(beta) M + (diag(beta) M)^T
 //   dbeta_a = R_aa + sum_s M_as G_as
 //   dQ  = dQb + dSd K + dF W
@@ -23,8 +23,15 @@
 // memory (converted to the operand type); a product whose contraction runs along the rows of a
 // stored matrix takes its 16-byte fragments with two transposing LDS reads instead of keeping a
 // transposed copy.  dK and dW accumulate in registers across the whole kernel; the 64 x 64
-// intermediates never leave LDS.  Per chunk the kernel reads about 0.46 MB and writes the four
-// gradients, against about 1.5 MB for the same steps run as separate staged products.
+// intermediates never leave LDS.
+//
+// What bounds it: latency -- chains of short dependent phases between barriers, at d = 128 with one workgroup per CU -- and
+// then memory: at d = 128 the states and adjoint states of 7.5 pairs on average (0.24 MB), 0.3 MB of the chunk's matrices and
+// the four gradients (0.06 MB) per chunk.  The near sums as a kernel of its own left dV, dKb and ddP in memory, 128 KB
+// written and read again per chunk: 743 + 1027 -> 1450 us at B=4, H=16, L=8192, d=128, 357 + 417 -> 671 at B=8, H=16, L=4096,
+// d=64, packed batch of 64 sequences of 256 .. 2048 tokens (8 heads, d = 128) 700 + 1267 -> 1460.  (Near sums alone 681 us, the
+// rest alone 892, at the first of these shapes.  With a third stage of states for the pairs the near sums take as long, and at
+// d = 64 longer.)
 #include "path_common.h"
 #include "bwd_decl.h"
 
@@ -32,6 +39,20 @@ namespace path {
 namespace {
 
 constexpr int CA_NT = 512;       // threads per workgroup (8 waves)
+
+// Near key-side sums (the first part of the kernel): stages of tiles and hand-over buffers, in fragments.
+template <typename TIO, int D> struct NearCfg {
+    typedef typename Compute<TIO>::type T;
+    static constexpr int KVF = CHUNK * D / Tr<T>::FE;                 // fragments of a tile
+    static constexpr int STF = 3 * KVF + 32;                          // a stage: xs | doq | gT | lse2, delta
+    static constexpr int PDF = 2 * 2 * 4 * 64;                        // a hand-over buffer: (P | dS) x 2 key halves x 4 slabs
+    // d = 64: one hand-over buffer (and a second barrier per pair), so that two workgroups share a CU.  (Of the 128 registers
+    // that this leaves 6 lie in scratch, with gates up to 26, none of them inside the loop over pairs.)
+    static constexpr int HB = D == 64 ? 1 : 2;
+    static constexpr int smem_bytes = (2 * STF + HB * PDF) * 16;
+    // dV | dKb on their way to the waves that go on with them, fp32 [key][D + 4]
+    static constexpr int LDX = D + 4, XV = 0, XK = CHUNK * LDX, xch_bytes = 2 * CHUNK * LDX * 4;
+};
 
 template <typename TIO, int D> struct CaCfg {
     typedef typename Compute<TIO>::type T;
@@ -43,11 +64,14 @@ template <typename TIO, int D> struct CaCfg {
     static constexpr int LDM = 65;             // pitch of the fp32 copy of M
     // byte offsets.  d = 128: W | X0 X3 (adjacent: ddP spans both, later the fp32 M) | X1 | X2 | Y0 Y1 Y2 | N | misc.
     // d = 64, where all tiles have one size: W | X0 Y0 (adjacent: the fp32 M) | X1 | X2 | X3 = N | Y1 | Y2 | misc: 74 KB, two
-    // workgroups per CU (with ten tiles, 92 KB and one workgroup it took 0.63 ms at B=8, H=16, L=4096).  With gates 1 to 6 of
-    // its 128 registers lie in scratch.
+    // workgroups per CU (with ten tiles, 92 KB and one workgroup what follows the near sums took 0.63 ms at B=8, H=16, L=4096, not
+    // 0.42).
     static constexpr int XW = 0, X0 = BIG, X3 = D == 64 ? 5 * BIG : 2 * BIG, X1 = 3 * BIG, X2 = 4 * BIG;
     static constexpr int Y0 = D == 64 ? 2 * BIG : 5 * BIG, Y1 = D == 64 ? 6 * BIG : Y0 + SMALL, Y2 = Y1 + SMALL, YN = D == 64 ? X3 : Y2 + SMALL;
-    static constexpr int MISC = D == 64 ? Y2 + SMALL : YN + SMALL;
+    static constexpr int TILES = D == 64 ? Y2 + SMALL : YN + SMALL, NEAR = NearCfg<TIO, D>::smem_bytes;
+    // between the near sums and the chunk's tiles: R | D of the second level | dV, dKb | dKb2
+    static constexpr int SR = 0, SD = D * D * 2, XCH = 2 * SD, SK2 = XCH + NearCfg<TIO, D>::xch_bytes, MID = SK2 + 64 * LDD * 2;
+    static constexpr int MISC = MID > NEAR ? (MID > TILES ? MID : TILES) : (NEAR > TILES ? NEAR : TILES);
     static constexpr int TOTAL = MISC + 2048;
     static constexpr int WGS_PER_CU = D == 64 ? 2 : 1;
     static_assert(D == 64 ? BIG == SMALL : D * LDD * 2 <= 2 * BIG, "ddP tile must fit X0 (d = 64) or X0 and X3");
@@ -92,8 +116,182 @@ __device__ __forceinline__ void st_block(T* dst, int ld, int r0, int c0, const f
     for (int jj = 0; jj < 16; ++jj) dst[(r0 + acc_row(jj, h)) * ld + c0 + l32] = (T)acc[jj];
 }
 
+// Near key-side sums, over the query chunks i right of the key's chunk j inside its own super-block, with the
+// chunk-level keys Kb and the chunk's own product,
+//
+//     S = Xs Kb_j^T,  dP = dO V_j^T,  ...       dV^T += dO^T P      dKb^T += Xs^T dS      ddP_j -= Xs^T g
+//
+// split by kind of work as for the far keys (bwd_keys.hip), one barrier per pair (64 queries):
+//   waves 0..3  (key half w & 1) x (query half w >> 1): logits, dP, element-wise part of the pair;
+//   waves 4..7  a quarter of each sum: ddP_j of this pair, dV^T and dKb^T of the pair before (its transposed fragments
+//               stay in registers, so that two stages of tiles do).
+// The former request the next pair's tiles.  The sums stay in the registers of waves 4..7 (dV^T, dKb^T row blocks NA rb + a
+// of key half kb, -ddP blocks (NA rb + a, NA kb + b); rb = (wave - 4) / 2, kb = wave % 2), the keys' part of the gate
+// gradient, one query half each, in dcol of waves 0..3.  tiles_read(): run by all waves when the tiles have been read for
+// the last time; the hand-over buffer of the last pair is read after that.
+template <typename TIO, int D, bool FOX, typename F>
+__device__ __forceinline__ void near_sums(const ChunkFusedArgs& a, unsigned char* smem, int j, int bh, int NCown, F tiles_read,
+                                          f32x16 (&dV)[D / 64], f32x16 (&dK)[D / 64], f32x16 (&dd)[D / 64][D / 64], float& dcol) {
+    using C = NearCfg<TIO, D>;
+    using T = typename C::T;
+    using Frag = typename Tr<T>::Frag;
+    using FragV = typename Tr<TIO>::Frag;
+    constexpr int KW = Tr<T>::KW, SPB = 32 / KW, DB = D / 32, DS = D / KW, QS = CHUNK / KW;
+    constexpr int KVF = C::KVF, STF = C::STF, PDF = C::PDF, HB = C::HB;
+    Frag* const stages = reinterpret_cast<Frag*>(smem);
+    Frag* const hand = stages + 2 * STF;
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), h = lane >> 5, l32 = lane & 31;
+    const int NC = a.NC;
+    const size_t Lp = (size_t)NC * CHUNK, nslots = num_block_slots(NC);
+    const int i0 = j + 1, i1 = (j / SBC + 1) * SBC < NCown ? (j / SBC + 1) * SBC : NCown;
+    constexpr int NA = DB / 2;
+#pragma unroll
+    for (int a2 = 0; a2 < NA; ++a2) {
+        dV[a2] = zero16(); dK[a2] = zero16();
+#pragma unroll
+        for (int b = 0; b < NA; ++b) dd[a2][b] = zero16();
+    }
+    dcol = 0.f;
+    if (i0 >= i1) { tiles_read(); return; }               // the super-block's last chunk: no such queries
+    auto issue = [&](int i) {                             // into stage i & 1, by waves 0..3: a transposing read, as the others make, waits for
+                                                          // every copy its own wave has in flight (by all eight waves: 1630 us, d = 64 945)
+        Frag* buf = stages + (i & 1) * STF;
+        const size_t slot = ((size_t)bh * nslots + block_slot(i, j, NC)) * (size_t)CHUNK * D;
+        async_copy_tile<256, KVF>(reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(a.xs) + slot), buf, tid, wv);
+        async_copy_tile<256, KVF>(reinterpret_cast<const Frag*>(reinterpret_cast<const TIO*>(a.doq) + ((size_t)bh * NC + i) * CHUNK * D), buf + KVF, tid, wv);
+        async_copy_tile<256, KVF>(reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(a.gs) + slot), buf + 2 * KVF, tid, wv);
+        if (tid < 32) {         // 64 floats of lse2 (lanes 0-15) and of delta (lanes 16-31): 16 bytes per lane
+            const float* src = (tid < 16 ? a.lse2p : a.delta) + (size_t)bh * Lp + (size_t)i * CHUNK + 4 * (tid & 15);
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                             (__attribute__((address_space(3))) void*)(buf + 3 * KVF), 16, 0, 0);
+        }
+    };
+    if (wv < 4) {
+        issue(i0);
+        // ---- logits and the element-wise part -----------------------------------------------------------------
+        const float sl2 = a.scale * 1.44269504088896340736f;
+        const int kh = wv & 1, qh = wv >> 1;
+        Frag Kb[DS];
+        FragV Vb[DS];
+        {
+            const Frag* kg = reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(a.kt) + ((size_t)bh * NC + j) * CHUNK * D);
+            const FragV* vg = reinterpret_cast<const FragV*>(reinterpret_cast<const TIO*>(a.vk) + ((size_t)bh * NC + j) * CHUNK * D);
+#pragma unroll
+            for (int s = 0; s < DS; ++s) { Kb[s] = kg[((size_t)kh * DS + s) * 64 + tile_lane<T>(lane, s)]; Vb[s] = vg[((size_t)kh * DS + s) * 64 + lane]; }
+        }
+        const int key_tok = j * CHUNK + 32 * kh + l32;
+        const float ckj = FOX ? a.cum[(size_t)bh * Lp + key_tok] : 0.f;
+        for (int i = i0; i < i1; ++i) {
+            copies_landed();
+            lds_barrier();                                // pair i has landed; pair i - 1 has been read
+            const Frag* sX = stages + (i & 1) * STF;
+            const FragV* sDQ = reinterpret_cast<const FragV*>(sX + KVF);
+            Frag xa[DS];
+            FragV da[DS];
+#pragma unroll
+            for (int u = 0; u < DS; ++u) { xa[u] = sX[(qh * DS + u) * 64 + tile_lane<T>(lane, u)]; da[u] = sDQ[(qh * DS + u) * 64 + tile_lane<T>(lane, u)]; }
+            __builtin_amdgcn_sched_barrier(0);
+            if (i + 1 < i1) issue(i + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            f32x16 S = zero16(), dP = zero16();           // rows q, lane s
+#pragma unroll
+            for (int u = 0; u < DS; ++u) {
+                S = Tr<T>::mma(xa[u], Kb[u], S);
+                dP = Tr<TIO>::mma(da[u], Vb[u], dP);
+            }
+            const float* lse2 = reinterpret_cast<const float*>(sX + 3 * KVF) + 32 * qh + 4 * h;
+            Frag* out = hand + (i & (HB - 1)) * PDF + (kh * QS + qh * SPB) * 64;
+            FragV Pb[SPB];
+            Frag dSb[SPB];
+#pragma unroll
+            for (int u = 0; u < SPB; ++u) {
+#pragma unroll
+                for (int g = 2 * u; g < 2 * u + 2; ++g) {
+                    const f32x4 ls = *reinterpret_cast<const f32x4*>(lse2 + 8 * g), dls = *reinterpret_cast<const f32x4*>(lse2 + CHUNK + 8 * g);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        // Rows past L need no mask: their padded lse2p is huge, so P = exp2(-huge) = 0.
+                        float arg = __builtin_fmaf(S[4 * g + r], sl2, -ls[r]);
+                        if (FOX) arg -= ckj;
+                        const float P = __builtin_amdgcn_exp2f(arg);
+                        const float dz = P * (dP[4 * g + r] - dls[r]);      // the factor scale is applied to the finished sums
+                        if (FOX) dcol += dz;
+                        Pb[u][(4 * g + r) % 8] = (TIO)P;
+                        dSb[u][(4 * g + r) % 8] = (T)dz;
+                    }
+                }
+            }
+            if (HB == 1) lds_barrier();                   // the pair before has been read
+#pragma unroll
+            for (int u = 0; u < SPB; ++u) {
+                reinterpret_cast<FragV*>(out)[u * 64 + lane] = Pb[u];
+                out[(2 * QS + u) * 64 + lane] = dSb[u];
+            }
+        }
+        lds_barrier();
+        tiles_read();
+        return;
+    }
+
+    // ---- the sums: row blocks NA rb .. of dV^T and dKb^T for key half kb, blocks (NA rb .., NA kb ..) of ddP ---------
+    const int rb = (wv - 4) >> 1, kb = wv & 1;
+    Frag xt[NA * QS];
+    FragV dt[NA * QS];
+    auto pair_sums = [&](int i) {                         // dV^T, dKb^T of pair i
+        const Frag* in = hand + (i & (HB - 1)) * PDF + kb * QS * 64;
+        FragV pf[QS];
+        Frag sf[QS];
+#pragma unroll
+        for (int s = 0; s < QS; ++s) { pf[s] = reinterpret_cast<const FragV*>(in)[s * 64 + lane]; sf[s] = in[(2 * QS + s) * 64 + lane]; }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int s = 0; s < QS; ++s)
+#pragma unroll
+            for (int a = 0; a < NA; ++a) {
+                dV[a] = Tr<TIO>::mma(dt[a * QS + s], pf[s], dV[a]);
+                dK[a] = Tr<T>::mma(xt[a * QS + s], sf[s], dK[a]);
+            }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto pair_tile = [&](int i) {                         // ddP of pair i; its transposed fragments
+        const Frag* sX = stages + (i & 1) * STF;
+        Frag gf[NA * QS];
+#pragma unroll
+        for (int a = 0; a < NA; ++a)
+#pragma unroll
+            for (int s = 0; s < QS; ++s) {
+                xt[a * QS + s] = ld_tile_frag_tr<T, DS>(reinterpret_cast<const T*>(sX), s, NA * rb + a, l32, h);
+                gf[a * QS + s] = sX[2 * KVF + ((NA * kb + a) * QS + s) * 64 + lane];
+            }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int s = 0; s < QS; ++s)
+#pragma unroll
+            for (int a = 0; a < NA; ++a)
+#pragma unroll
+                for (int b = 0; b < NA; ++b) dd[a][b] = Tr<T>::mma(xt[a * QS + s], gf[b * QS + s], dd[a][b]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int a = 0; a < NA; ++a)
+#pragma unroll
+            for (int s = 0; s < QS; ++s) dt[a * QS + s] = ld_tile_frag_tr<TIO, DS>(reinterpret_cast<const TIO*>(sX + KVF), s, NA * rb + a, l32, h);
+    };
+    lds_barrier();
+    pair_tile(i0);
+    if (HB == 1) lds_barrier();
+    for (int i = i0 + 1; i < i1; ++i) {
+        lds_barrier();
+        pair_sums(i - 1);
+        pair_tile(i);
+        if (HB == 1) lds_barrier();
+    }
+    lds_barrier();
+    tiles_read();
+    pair_sums(i1 - 1);
+}
+
 template <typename TIO, int D, bool FOX, bool STRIDED>
-__global__ __launch_bounds__(CA_NT, 2 * (CaCfg<TIO, D>::WGS_PER_CU)) void chunk_fused_kernel(ChunkFusedArgs a) {
+__global__ __launch_bounds__(CA_NT, 2 * (CaCfg<TIO, D>::WGS_PER_CU)) void chunk_fused_kernel(ChunkFusedArgs args) {
     using C = CaCfg<TIO, D>;
     typedef typename C::T T;
     constexpr int LDD = C::LDD, LDC = C::LDC, LDM = C::LDM;
@@ -109,13 +307,43 @@ __global__ __launch_bounds__(CA_NT, 2 * (CaCfg<TIO, D>::WGS_PER_CU)) void chunk_
     T* YN = reinterpret_cast<T*>(smem + C::YN);
     float* Mf = reinterpret_cast<float*>(smem + C::X0);      // fp32 M, after ddP is dead
     float* misc = reinterpret_cast<float*>(smem + C::MISC);
-    float *beta_s = misc, *rdiag = misc + 64, *rowsum = misc + 128, *colsum = misc + 256;
+    float *beta_s = misc, *rdiag = misc + 64, *rowsum = misc + 128, *colsum = misc + 256, *nearcol = misc + 384;
 
     int chunk, bh;
-    chunk_and_head(a.ul, a.NC, a.BH, chunk, bh);
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, h = lane >> 5, l32 = lane & 31;
-    const int L = seq_len(a.ul, bh, a.L), NC = a.NC;      // this head's own length; NC: chunks per head in the workspace arrays
+    super_block_and_head(args.ul, args.NC, args.BH, chunk, bh);
+    if (bh >= args.BH) return;
+    const int L = seq_len(args.ul, bh, args.L), NC = args.NC;      // this head's own length; NC: chunks per head in the workspace arrays
     if (chunk * CHUNK >= L) return;                        // (packed batch: a shorter sequence has fewer chunks)
+    const int NCown = (L + CHUNK - 1) / CHUNK;
+
+    const bool right = !is_last_sb(chunk / SBC, NCown);          // there are queries right of the super-block
+
+    // ---- near key-side sums: dV, dKb, ddP over the query chunks right of this one in its super-block -----------
+    // (behind them, the second level's tiles of the chunk: R_c and the gradient of R_{c-1})
+    constexpr int NA = D / 64;
+    f32x16 nV[NA], nK[NA], dd[NA][NA];
+    float ncol;
+    near_sums<TIO, D, FOX>(args, smem, chunk, bh, NCown, [&]() {
+        if (!right) return;
+        typedef typename Tr<T>::Frag Frag;
+        constexpr int DPF = D * D / 8;
+        const size_t o = ((size_t)bh * NC + chunk) * D * D;
+        const int t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t >> 6);
+        async_copy_tile<CA_NT, DPF>(reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(args.rm) + o), reinterpret_cast<Frag*>(smem + C::SR), t, w);
+        async_copy_tile<CA_NT, DPF>(reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(args.dr) + o), reinterpret_cast<Frag*>(smem + C::SD), t, w);
+    }, nV, nK, dd, ncol);
+
+    // (from here on nothing is shared with the above, or the compiler would keep addresses and arguments in registers
+    // across both)
+    typedef const __attribute__((address_space(4))) void* KernArg;
+    KernArg ka = (KernArg)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(ka));
+    const ChunkFusedArgs& a = *(const ChunkFusedArgs*)ka;
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid), "+v"(bh), "+v"(chunk));
+    bh = __builtin_amdgcn_readfirstlane(bh);
+    chunk = __builtin_amdgcn_readfirstlane(chunk);
+    const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), h = lane >> 5, l32 = lane & 31;
     const int ntok = (L - chunk * CHUNK < CHUNK) ? L - chunk * CHUNK : CHUNK;
     const size_t Lp = (size_t)NC * CHUNK;
     const long long ubase = user_vec(a.ul, bh, (long long)chunk * CHUNK);    // the caller's tensors: row of the chunk's first token
@@ -130,7 +358,6 @@ __global__ __launch_bounds__(CA_NT, 2 * (CaCfg<TIO, D>::WGS_PER_CU)) void chunk_
     const TIO* wg = reinterpret_cast<const TIO*>(a.w) + ubase;
     const TIO* dog = reinterpret_cast<const TIO*>(a.d_o) + ubase;
     const T* utmg = reinterpret_cast<const T*>(a.utm) + ((size_t)bh * NC + chunk) * D * CHUNK;
-    const float* ddpg = a.ddp + ((size_t)bh * NC + chunk) * D * D;
 
     // wave -> 32x32 block of a 64 x D result (all 8 waves for D = 128; waves 0..3 for D = 64) and of a 64 x 64 result
     // (waves 0..3; waves 4..7 for D = 64)
@@ -151,76 +378,108 @@ __global__ __launch_bounds__(CA_NT, 2 * (CaCfg<TIO, D>::WGS_PER_CU)) void chunk_
         }
     };
 
-    // ---- the second level's share: ddP -= R^T D, dKb += dKb2 R (D = gradient of R_{c-1}) -------------------
-    // blocks of ddP: wave -> wv, wv + 8 (d = 128), one on waves 4..7 (d = 64)
-    constexpr int NDD = D == 128 ? 2 : 1;
-    const bool actP = D == 128 || wv >= 4;
-    const int blk0 = D == 128 ? wv : wv & 3;
-    f32x16 accV, accQ, accK = zero16();
-    // (d = 64: waves 0..3 and 4..7 hold different things, and two workgroups per CU leave 128 registers: one place
-    // each for dV / ddP, dK / its near part, dQ / dY)
-    f32x16 dd_own[NDD], ddn_own[NDD], y_own;
-    auto dd = [&](int o) -> f32x16& { if constexpr (D == 64) return accV; else return dd_own[o]; };
-    auto ddn = [&](int o) -> f32x16& { if constexpr (D == 64) return accK; else return ddn_own[o]; };
+    // blocks of ddP: NA x NA on each of the waves 4..7, as the near sums left them
+    const bool actP = wv >= 4;
+    const int rb = (wv >> 1) & 1, kb = wv & 1;
+    f32x16 accV = zero16(), accQ, accK = zero16();
+    // (d = 64: waves 0..3 and 4..7 hold different things, and two workgroups per CU leave 128 registers: one place for dQ / dY)
+    f32x16 y_own;
     f32x16& accY = D == 64 ? accQ : y_own;
-#pragma unroll
-    for (int o = 0; o < NDD; ++o) dd(o) = zero16();
+
+    // ---- the second level's share: ddP -= R^T D, dKb += dKb2 R (D = gradient of R_{c-1}); dV, dKb change hands ----
     GTile<TIO, 64, D> tW, tdO, tV;
-    if (a.rm && !is_last_sb(chunk / SBC, (L + CHUNK - 1) / CHUNK)) {
-        constexpr int DPF = D * D / 8, DS = D / 16;
+    {
+        constexpr int DS = D / 16;
         typedef typename Tr<T>::Frag Frag;
-        const size_t bhc = (size_t)bh * NC + chunk;
-        T* sR = X0;                                  // R | D in X0 .. X2 (d = 64: in X0, Y0), dKb2 in Y0 (d = 64: X1)
-        T* sD = sR + D * D;
-        T* sK2 = D == 64 ? X1 : Y0;
+        using N = NearCfg<TIO, D>;
+        const T *sR = reinterpret_cast<const T*>(smem + C::SR), *sD = reinterpret_cast<const T*>(smem + C::SD);
+        T* sK2 = reinterpret_cast<T*>(smem + C::SK2);
+        float* x = reinterpret_cast<float*>(smem + C::XCH);
         GTile<float, 64, D> tK2;
-        tK2.load(a.dk2 + bhc * CHUNK * D, D, 64, tid);
-        async_copy_tile<CA_NT, DPF>(reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(a.rm) + bhc * D * D), reinterpret_cast<Frag*>(sR), tid, wv);
-        async_copy_tile<CA_NT, DPF>(reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(a.dr) + bhc * D * D), reinterpret_cast<Frag*>(sD), tid, wv);
+        f32x16 far = zero16();
+        if (right) {
+            tK2.load(a.dk2 + ((size_t)bh * NC + chunk) * CHUNK * D, D, 64, tid);
+            if (actD) cin(a.dvp + pbase, far);
+        }
         tW.load(wg, TS, ntok, tid);
         tdO.load(dog, TS, ntok, tid);
         tV.load(vg, TS, ntok, tid);
-        tK2.template store<T, false>(sK2, LDD, tid);
-        wait_async_and_sync();
+        if (FOX) {           // summed over the half-waves here and over the two query halves through LDS
+            ncol += __shfl_xor(ncol, 32);
+            if (wv < 4 && (wv >> 1) == 1 && h == 0) nearcol[32 * (wv & 1) + l32] = ncol;
+        }
+        lds_barrier();                                    // the last hand-over buffer has been read
+        if (FOX && wv < 2 && h == 0) nearcol[32 * wv + l32] += ncol;
+        if (actP) {
 #pragma unroll
-        for (int o = 0; o < NDD; ++o) {
-            const int blk = blk0 + 8 * o, xb = blk / NBD, bb = blk % NBD;
+            for (int i = 0; i < NA; ++i)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    f32x4 v4, k4;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) { v4[r] = nV[i][4 * g + r]; k4[r] = a.scale * nK[i][4 * g + r]; }
+                    float* y = x + (32 * kb + l32) * N::LDX + 32 * (NA * rb + i) + 8 * g + 4 * h;
+                    *reinterpret_cast<f32x4*>(y + N::XV) = v4;
+                    *reinterpret_cast<f32x4*>(y + N::XK) = k4;
+                }
+#pragma unroll
+            for (int i = 0; i < NA; ++i)
+#pragma unroll
+                for (int b = 0; b < NA; ++b)
+#pragma unroll
+                    for (int jj = 0; jj < 16; ++jj) dd[i][b][jj] = chunk >= 1 ? -dd[i][b][jj] : 0.f;      // (chunk 0 has no transform to the left of it)
+        }
+        if (right) tK2.template store<T, false>(sK2, LDD, tid);
+        wait_async_and_sync();
+        if (actD) {
+#pragma unroll
+            for (int jj = 0; jj < 16; ++jj) {
+                const int r = (32 * mbD + acc_row(jj, h)) * N::LDX + 32 * cbD + l32;
+                accV[jj] = x[N::XV + r] + far[jj];
+                accK[jj] = x[N::XK + r];
+            }
+        }
+        if (right) {
             if (actP) {
+#pragma unroll
+                for (int i = 0; i < NA; ++i)
+#pragma unroll
+                    for (int b = 0; b < NA; ++b) {
+                        f32x16 acc = zero16();
+#pragma unroll
+                        for (int s0 = 0; s0 < DS; s0 += 4) {
+                            Frag fa[4], fb[4];
+#pragma unroll
+                            for (int s = 0; s < 4; ++s) { fa[s] = ld_tile_frag_tr<T, DS>(sR, s0 + s, NA * rb + i, l32, h); fb[s] = ld_tile_frag_tr<T, DS>(sD, s0 + s, NA * kb + b, l32, h); }
+#pragma unroll
+                            for (int s = 0; s < 4; ++s) acc = Tr<T>::mma(fa[s], fb[s], acc);
+                        }
+#pragma unroll
+                        for (int jj = 0; jj < 16; ++jj) dd[i][b][jj] -= acc[jj];
+                    }
+            }
+            if (actD) {
+                typedef typename Tr<T>::Vec4 TVec4;
                 f32x16 acc = zero16();
 #pragma unroll
                 for (int s0 = 0; s0 < DS; s0 += 4) {
                     Frag fa[4], fb[4];
 #pragma unroll
-                    for (int s = 0; s < 4; ++s) { fa[s] = ld_tile_frag_tr<T, DS>(sR, s0 + s, xb, l32, h); fb[s] = ld_tile_frag_tr<T, DS>(sD, s0 + s, bb, l32, h); }
+                    for (int s = 0; s < 4; ++s) {
+                        const T* kp = sK2 + (32 * mbD + l32) * LDD + 16 * (s0 + s) + 4 * h;        // contraction index in accumulator order
+                        const TVec4 lo = *reinterpret_cast<const TVec4*>(kp), hi = *reinterpret_cast<const TVec4*>(kp + 8);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) { fa[s][e] = lo[e]; fa[s][4 + e] = hi[e]; }
+                        fb[s] = ld_tile_frag_tr<T, DS>(sR, s0 + s, cbD, l32, h);
+                    }
 #pragma unroll
                     for (int s = 0; s < 4; ++s) acc = Tr<T>::mma(fa[s], fb[s], acc);
                 }
 #pragma unroll
-                for (int jj = 0; jj < 16; ++jj) dd(o)[jj] = -acc[jj];
-            }
-        }
-        if (actD) {
-            typedef typename Tr<T>::Vec4 TVec4;
-#pragma unroll
-            for (int s0 = 0; s0 < DS; s0 += 4) {
-                Frag fa[4], fb[4];
-#pragma unroll
-                for (int s = 0; s < 4; ++s) {
-                    const T* kp = sK2 + (32 * mbD + l32) * LDD + 16 * (s0 + s) + 4 * h;        // contraction index in accumulator order
-                    const TVec4 lo = *reinterpret_cast<const TVec4*>(kp), hi = *reinterpret_cast<const TVec4*>(kp + 8);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) { fa[s][e] = lo[e]; fa[s][4 + e] = hi[e]; }
-                    fb[s] = ld_tile_frag_tr<T, DS>(sR, s0 + s, cbD, l32, h);
-                }
-#pragma unroll
-                for (int s = 0; s < 4; ++s) accK = Tr<T>::mma(fa[s], fb[s], accK);
+                for (int jj = 0; jj < 16; ++jj) accK[jj] += acc[jj];
             }
         }
         __syncthreads();
-    } else {
-        tW.load(wg, TS, ntok, tid);
-        tdO.load(dog, TS, ntok, tid);
-        tV.load(vg, TS, ntok, tid);
     }
 
     // ---- stage W, dO, V; per-token scalars ---------------------------------------------------
@@ -243,7 +502,6 @@ __global__ __launch_bounds__(CA_NT, 2 * (CaCfg<TIO, D>::WGS_PER_CU)) void chunk_
     tdO.template store<T, false>(X0, LDD, tid);
     tV.template store<T, false>(X1, LDD, tid);
     f32x16 accW = zero16();
-    if (actD) cin(a.dvp + pbase, accV);
     GTile<TIO, 64, D> tQ;
     tQ.load(qg, TS, ntok, tid);
     GTile<T, 64, 64> tY;
@@ -287,7 +545,7 @@ __global__ __launch_bounds__(CA_NT, 2 * (CaCfg<TIO, D>::WGS_PER_CU)) void chunk_
     if (actD) cin(a.dqb + pbase, accQ);
     __syncthreads();
     if (FOX && tid < CHUNK) {        // the diagonal block's column and row sums of the logit gradient
-        a.dcol[tpad + tid] += colsum[tid];
+        a.dcol[tpad + tid] = (nearcol[tid] + (right ? a.dcol[tpad + tid] : 0.f)) + colsum[tid];
         a.drow[tpad + tid] += colsum[CHUNK + tid];
     }
 
@@ -295,10 +553,6 @@ __global__ __launch_bounds__(CA_NT, 2 * (CaCfg<TIO, D>::WGS_PER_CU)) void chunk_
     if (actD) {
         mm<T, 64, true, true>(accV, Y0, LDC, 32 * mbD, X0, LDD, 32 * cbD, l32, h);
         out_user(a.dv, accV);
-        f32x16 kin;
-        cin(a.dkb + pbase, kin);
-#pragma unroll
-        for (int jj = 0; jj < 16; ++jj) accK[jj] += kin[jj];
     }
     __syncthreads();                 // dO (X0), V (X1), P (Y0) are free
     tQ.template store<T, false>(X0, LDD, tid);
@@ -327,14 +581,6 @@ __global__ __launch_bounds__(CA_NT, 2 * (CaCfg<TIO, D>::WGS_PER_CU)) void chunk_
         for (int jj = 0; jj < 16; ++jj)
             if (32 * cb6 + l32 > 32 * mb6 + acc_row(jj, h)) acc[jj] = 0.f;
         st_block<T>(Y2, LDC, 32 * mb6, 32 * cb6, acc, l32, h);
-    }
-    if (actP) {                      // the near part of ddP, in flight until it is stored
-#pragma unroll
-        for (int o = 0; o < NDD; ++o) {
-            const int blk = blk0 + 8 * o, xb = blk / NBD, bb = blk % NBD;
-#pragma unroll
-            for (int jj = 0; jj < 16; ++jj) ddn(o)[jj] = ddpg[(size_t)(32 * xb + acc_row(jj, h)) * D + 32 * bb + l32];
-        }
     }
     __syncthreads();
 
@@ -371,12 +617,9 @@ __global__ __launch_bounds__(CA_NT, 2 * (CaCfg<TIO, D>::WGS_PER_CU)) void chunk_
     if (act6) st_block<T>(Y2, LDC, 32 * mb6, 32 * cb6, accY, l32, h);     // dY
     if (actP) {                      // ddP [a][b] (d = 128: spans X0 and X3)
 #pragma unroll
-        for (int o = 0; o < NDD; ++o) {
-            const int blk = blk0 + 8 * o, xb = blk / NBD, bb = blk % NBD;
+        for (int i = 0; i < NA; ++i)
 #pragma unroll
-            for (int jj = 0; jj < 16; ++jj) ddn(o)[jj] += dd(o)[jj];
-            st_block<T>(X0, LDD, 32 * xb, 32 * bb, ddn(o), l32, h);
-        }
+            for (int b = 0; b < NA; ++b) st_block<T>(X0, LDD, 32 * (NA * rb + i), 32 * (NA * kb + b), dd[i][b], l32, h);
     }
     tN.template store<T, false>(YN, LDC, tid);
     tG.template store<T, false>(Y1, LDC, tid);
@@ -483,7 +726,7 @@ hipError_t launch_s(const ChunkFusedArgs& a, int BH, hipStream_t st) {
     static const hipError_t attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&chunk_fused_kernel<TIO, D, FOX, STRIDED>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::TOTAL);
     if (attr_err != hipSuccess) return attr_err;
-    hipLaunchKernelGGL((chunk_fused_kernel<TIO, D, FOX, STRIDED>), dim3((unsigned)(a.NC * BH)), dim3(CA_NT), (size_t)C::TOTAL, st, a);
+    hipLaunchKernelGGL((chunk_fused_kernel<TIO, D, FOX, STRIDED>), dim3(super_block_grid(a.NC, BH)), dim3(CA_NT), (size_t)C::TOTAL, st, a);
     return hipGetLastError();
 }
 template <typename TIO, int D, bool FOX>

@@ -363,7 +363,7 @@ __device__ __forceinline__ long long user_scl(const UserLayout& u, int bh, long 
 // 4 x 3000 tokens 5 % of the chunk transform).  Packed batch: heads first, chunk by chunk -- workgroup n runs on XCD
 // n % 8, and with chunks first an XCD would take the same chunk numbers of every sequence, of which the late ones
 // exist in the long sequences only.  64 sequences of 256 .. 2048 tokens, 8 heads, d = 128: chunk transform 799 ->
-// 584 us, with the backward's outputs 1042 -> 796, its adjoint 1610 -> 1128.
+// 584 us, with the backward's outputs 1042 -> 796.
 // Where a sequence has no multiple of eight heads, they are turned by one per chunk: else, with a multiple of eight in all,
 // the chunks of a head go to one XCD and to half of its CUs, and sequences of different lengths do not balance each other.
 // Not if an XCD has a CU for each of its chunks anyway: then a head's chunks had better lie in the L2 of the XCD that its
@@ -380,6 +380,29 @@ __device__ __forceinline__ void chunk_and_head(const UserLayout& u, int NC, int 
         bh += __builtin_amdgcn_readfirstlane(hi % m);
         if (bh >= m) bh -= m;
     }
+}
+// The same for a kernel whose workgroups of one (super-block, head) read the same tiles: its SBC workgroups run on one XCD,
+// first chunk first, and the (super-block, head) pairs are dealt to the XCDs in the order, and with the turn, of above.  Launched
+// with super_block_grid() workgroups; those past the last pair get bh >= BH.
+__device__ __forceinline__ void super_block_and_head(const UserLayout& u, int NC, int BH, int& chunk, int& bh) {
+    const int nsb = (NC + SBC - 1) / SBC, kk = blockIdx.x >> 3;
+    const int n = kk / SBC * 8 + (blockIdx.x & 7), m = u.cu ? BH : nsb;
+    const int hi = __builtin_amdgcn_readfirstlane(n / m), lo = n - hi * m;
+    int sb = lo;
+    bh = hi;
+    if (u.cu) {
+        sb = hi;
+        bh = lo;
+        if ((u.H & 7) && NC * ((BH + 7) >> 3) > 32) {
+            bh += __builtin_amdgcn_readfirstlane(hi % m);
+            if (bh >= m) bh -= m;
+        }
+        if (sb >= nsb) bh = BH;
+    }
+    chunk = sb * SBC + kk % SBC;
+}
+__host__ __forceinline__ unsigned super_block_grid(int NC, int BH) {
+    return (unsigned)(((long long)((NC + SBC - 1) / SBC) * BH + 7) / 8 * 8 * SBC);
 }
 // length of head bh's sequence: the launch's L, or the head's own in a packed batch
 __device__ __forceinline__ int seq_len(const UserLayout& u, int bh, int L) {
