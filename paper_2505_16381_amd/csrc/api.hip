@@ -642,7 +642,7 @@ static path_status_t bwd_run(BwdMode mode, int stages, const UserLayout& ul, con
 
 extern "C" size_t path_decode_workspace_bytes(int B, int H, int d) {
     if (B < 1 || H < 1 || (d != 64 && d != 128)) return 0;
-    return align256((size_t)B * H * DECODE_MAX_SPLITS * (d + 2) * 4);
+    return align256((size_t)B * H * DECODE_SPLIT_ROOM * (d + 2) * 4);
 }
 
 extern "C" path_status_t path_key_prefill(const void* v, int B, int H, int L, int d, path_dtype_t dt,
@@ -684,7 +684,7 @@ extern "C" path_status_t path_decode_step(const void* q, const void* k, const vo
     const void* al[] = {q, k, v, w, kcache, vcache, o};
     for (const void* ptr : al) if (misaligned(ptr)) return PATH_ERR_ALIGN;
     clear_inherited_error();
-    DecodeArgs a{q, k, v, w, beta, kcache, vcache, o, lse, static_cast<float*>(workspace), n, Lmax, scale, nullptr, nullptr};
+    DecodeArgs a{q, k, v, w, beta, kcache, vcache, o, lse, static_cast<float*>(workspace), n, Lmax, scale, nullptr, nullptr, 0};
     if (!hip_ok(launch_decode_step(a, B * H, d, dt == PATH_BF16, static_cast<hipStream_t>(stream)), "decode step"))
         return PATH_ERR_HIP;
     return PATH_OK;
@@ -717,7 +717,7 @@ extern "C" path_status_t path_decode_step_fox(const void* q, const void* k, cons
     const void* al[] = {q, k, v, w, kcache, vcache, o};
     for (const void* ptr : al) if (misaligned(ptr)) return PATH_ERR_ALIGN;
     clear_inherited_error();
-    DecodeArgs a{q, k, v, w, beta, kcache, vcache, o, lse, static_cast<float*>(workspace), n, Lmax, scale, log_f, ccache};
+    DecodeArgs a{q, k, v, w, beta, kcache, vcache, o, lse, static_cast<float*>(workspace), n, Lmax, scale, log_f, ccache, 0};
     if (!hip_ok(launch_decode_step(a, B * H, d, dt == PATH_BF16, static_cast<hipStream_t>(stream)), "gated decode step"))
         return PATH_ERR_HIP;
     return PATH_OK;
@@ -771,8 +771,8 @@ extern "C" path_status_t path_decode_step_static(const void* q, const void* k, c
     clear_inherited_error();
     void* ws = scratch_on_current_device();
     if (!ws) return PATH_ERR_HIP;
-    // (nothing in the array has to start at zero: every split writes its whole record before the merge reads it)
-    DecodeArgs a{q, k, v, w, beta, kcache, vcache, o, lse, static_cast<float*>(ws), n, Lmax, scale, nullptr, nullptr};
+    // (nothing in the array has to start at zero: a record counts once its flag has this call's value)
+    DecodeArgs a{q, k, v, w, beta, kcache, vcache, o, lse, static_cast<float*>(ws), n, Lmax, scale, nullptr, nullptr, 0};
     if (!hip_ok(launch_decode_step(a, B * H, d, dt == PATH_BF16, static_cast<hipStream_t>(stream)), "decode step (static scratch)"))
         return PATH_ERR_HIP;
     return PATH_OK;

@@ -18,12 +18,13 @@
 //    refreshed in place, k_i <- k_i - beta_t (w_t . k_i) w_t, and attention of q_t over the
 //    refreshed cache is ordinary softmax attention.  Both happen in ONE pass over the key cache
 //    (read k, write k, read v: 3 n d elements per head -- HBM-bound), split over the cached
-//    positions; a second small kernel merges the splits, adds the arriving token's own key and
-//    value, and appends them to the caches.  Short caches are not split: one kernel does it all.
+//    positions; the split that ends last merges them, adds the arriving token's own key and
+//    value, and appends them to the caches.  Short caches are not split.
 //
 //  * PaTH-FoX at decode time (Sec. 2.2 extension): with the running sums c_i of the log gates kept beside the
 //    caches, key i's logit gets c_t - c_i, c_t = c_{t-1} + log f_t; the arriving token's own logit gets nothing
-//    and its sum is appended (GATES instantiations of the two kernels).
+//    and its sum is appended (GATES instantiations).
+#include <atomic>
 #include <type_traits>
 
 #include "path_common.h"
@@ -175,7 +176,8 @@ struct DecodeTail {
 };
 
 // One pass over the cached keys of a split: refresh, logit, online softmax, P V.  DIRECT: the split is the whole head
-// and the workgroup ends the step itself; else partial results (m, l, o[D]) per split go to the workspace.
+// and the workgroup ends the step itself; else every split leaves its partial results in the
+// workspace, and the last one merges them.
 // A key is handled by LPK = D/8 consecutive lanes (8 elements each); a wave takes 64/LPK keys at a time and UN such
 // rounds per step, whose rows it has requested a step ahead.  The sums over a key's lanes are DPP moves (a shuffle
 // through LDS costs its latency eight times per key).
@@ -194,6 +196,22 @@ template <int LPK> __device__ __forceinline__ float group_sum(float x) {      //
     if (LPK == 16) add(std::integral_constant<int, 0x140>{});     // row_mirror: the other eight
     return x;
 }
+
+template <typename T> __device__ __forceinline__ void agent_store(T* p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+template <typename T> __device__ __forceinline__ T agent_load(const T* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+// Merge of the splits inside the same launch, without a counter that would have to start at zero: every split leaves its
+// record and then its flag, and then looks at all flags of the head; a split that finds them all set merges.  The last one
+// to set its flag does; so may others that look at that moment, which write the same bits.  Nobody waits for another.  A
+// merge clears the flags behind it, by when every split has set its own, so that the next step finds none; a workspace that
+// has been anything else holds the call's 64-bit pattern with probability 2^-64 (a pattern per call, so that flags of a call
+// that raced with another on its workspace mean nothing later).  All inputs of the token are in registers before a flag is
+// set (o may be one of them).  It takes as long as a second launch on the GPU, and 2.8 us less on the host.  (A tag
+// beside every value instead of the flag, one trip to memory less: 1024 keys, 64 heads, d = 128 16.3 us against 14.2.)
+struct DecodeRecord {            // of one split and 64 components
+    float o[64], m, l;
+    unsigned long long flag;
+};
 
 template <typename TIO, int D, bool GATES, int NT, bool DIRECT>
 __global__ __launch_bounds__(NT) void decode_partial_kernel(DecodeArgs a) {
@@ -226,7 +244,7 @@ __global__ __launch_bounds__(NT) void decode_partial_kernel(DecodeArgs a) {
     int i0 = i_begin + wv * (UN * KPW);
     if (i0 < i_end) request(i0);
     DecodeTail<TIO, D, GATES> tail;
-    if (DIRECT && tid < D) tail.load(a, bh, tid);
+    if (tid < D) tail.load(a, bh, tid);
 
     float q8[8], w8[8];
     {
@@ -317,7 +335,10 @@ __global__ __launch_bounds__(NT) void decode_partial_kernel(DecodeArgs a) {
             for (int e = 0; e < 8; ++e) red_o[wv][8 * sub + e] = acc[e];
         }
     }
-    if (DIRECT && wv < D / 64) tail.logit(a.scale);
+    if (wv < D / 64) {
+        tail.logit(a.scale);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // all that this wave reads of the token's inputs is in registers
+    }
     __syncthreads();
     if (tid >= D) return;
     float M = -INFINITY;
@@ -331,51 +352,45 @@ __global__ __launch_bounds__(NT) void decode_partial_kernel(DecodeArgs a) {
         O += red_o[g][tid] * sc;
     }
     if (DIRECT) { tail.finish(a, bh, tid, M, Ls, O); return; }
-    float* part = a.partial + ((size_t)bh * nsplit + split) * (D + 2);
-    part[2 + tid] = O;
-    if (tid == 0) { part[0] = M; part[1] = Ls; }
-}
-
-// Merge the splits (at most 64: lane s holds the maximum and the row sum of split s), then the step's last part.
-template <typename TIO, int D, bool GATES>
-__global__ __launch_bounds__(D) void decode_combine_kernel(DecodeArgs a, int nsplit) {
+    // The record of this wave's 64 components, past the L2s (agent scope); once it is there, the flag.
     static_assert(DECODE_MAX_SPLITS <= 64, "one split per lane");
+    DecodeRecord* const rec = reinterpret_cast<DecodeRecord*>(a.partial) + (size_t)(bh * (D / 64) + wv) * nsplit;
+    DecodeRecord* const own = rec + split;
+    agent_store(&own->o[lane], O);
+    if (lane == 0) { agent_store(&own->m, M); agent_store(&own->l, Ls); }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (lane == 0) agent_store(&own->flag, a.flag);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    const unsigned long long flag = lane < nsplit ? agent_load(&rec[lane].flag) : a.flag;
+    if (__builtin_amdgcn_ballot_w64(flag != a.flag) != 0) return;      // another split will find them all set
+    asm volatile("" ::: "memory");
     constexpr int NB = 16;                            // outputs of so many splits requested at once
-    const int bh = blockIdx.x, c = threadIdx.x, lane = c & 63;
-    const float* part = a.partial + (size_t)bh * nsplit * (D + 2);
     float on[NB];
-    auto request = [&](int s0) {                      // (splits past the last one repeat it, and count as zero)
+    auto request_o = [&](int s0) {                    // (splits past the last one repeat it, and count as zero)
 #pragma unroll
-        for (int r = 0; r < NB; ++r) on[r] = part[(size_t)(s0 + r < nsplit ? s0 + r : nsplit - 1) * (D + 2) + 2 + c];
+        for (int r = 0; r < NB; ++r) on[r] = agent_load(&rec[s0 + r < nsplit ? s0 + r : nsplit - 1].o[lane]);
     };
-    const float ms = lane < nsplit ? part[(size_t)lane * (D + 2)] : -INFINITY;
-    float Ls = lane < nsplit ? part[(size_t)lane * (D + 2) + 1] : 0.f;
-    request(0);
-    DecodeTail<TIO, D, GATES> tail;
-    tail.load(a, bh, c);
-    tail.logit(a.scale);
-    if (D > 64) __syncthreads();
-    float M = ms;
+    const float ms = lane < nsplit ? agent_load(&rec[lane].m) : -INFINITY;
+    Ls = lane < nsplit ? agent_load(&rec[lane].l) : 0.f;
+    request_o(0);
+    M = ms;
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) M = fmaxf(M, __shfl_xor(M, off));
     const float wt = ms == -INFINITY ? 0.f : __expf(ms - M);
     Ls *= wt;
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) Ls += __shfl_xor(Ls, off);
-    float O = 0.f;
+    O = 0.f;
     for (int s0 = 0; s0 < nsplit; s0 += NB) {
         float oc[NB];
 #pragma unroll
-        for (int r = 0; r < NB; ++r) oc[r] = on[r];
-        if (s0 + NB < nsplit) request(s0 + NB);
-        if (s0 + NB > nsplit) {
-#pragma unroll
-            for (int r = 0; r < NB; ++r) oc[r] = s0 + r < nsplit ? oc[r] : 0.f;
-        }
+        for (int r = 0; r < NB; ++r) oc[r] = s0 + r < nsplit ? on[r] : 0.f;
+        if (s0 + NB < nsplit) request_o(s0 + NB);
 #pragma unroll
         for (int r = 0; r < NB; ++r) O += oc[r] * __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wt), s0 + r));
     }
-    tail.finish(a, bh, c, M, Ls, O);
+    if (lane < nsplit) agent_store(&rec[lane].flag, 0ull);
+    tail.finish(a, bh, tid, M, Ls, O);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -393,44 +408,52 @@ hipError_t launch_key_prefill(const PrefillArgs& a, int BH, int d, int is_bf16, 
     return d == 64 ? launch_prefill_t<float, 64>(a, BH, st) : launch_prefill_t<float, 128>(a, BH, st);
 }
 
-// Splits of the cached positions.  About four workgroups per CU: three rows per 16 lanes in flight in each of their
-// 16 waves cover the latency of HBM (two per CU: 3 % slower at B=4, H=16, n=8192, eight: the same).  At least 64 keys
-// each: with 32 a single sequence of 16 heads takes 13.1 us for 2000 keys against 12.0, with 128 10.7 against 9.6 for
-// 1000 (d = 128).
-int decode_num_splits(int BH, int n) {
+// Splits of the cached positions.  About four workgroups of four waves per CU: three rows per 16 lanes in flight in each of
+// their 16 waves cover the latency of HBM (two per CU: 3 % slower at B=4, H=16, n=8192, eight: the same).  At least 64 keys
+// each.  From 17 splits on half as many of eight waves: there is less to merge (replayed from a graph, d = 128: 16 heads of
+// 1100 keys 10.1 -> 9.1 us, 2000 11.6 -> 10.2, 3000 14.9 -> 13.7; one head of 2000 7.6 -> 7.1; 16 splits or less do not
+// gain).  A few long heads take as many as there is room for: one head of 32000 keys 23.5 us with 32 of eight waves, 18.0 with 60.
+struct DecodeSplits { int n, waves; };
+static DecodeSplits decode_splits(int BH, int n) {
     int s = (1024 + BH - 1) / BH;
-    if (s > DECODE_MAX_SPLITS) s = DECODE_MAX_SPLITS;
+    if (s > 64) s = 64;
     const int by_len = (n + 63) / 64;
     if (s > by_len) s = by_len;
-    return s < 1 ? 1 : s;
+    if (s == 64 && s * BH < 512) return {DECODE_MAX_SPLITS, 8};
+    if (s > 16) return {(s + 1) / 2, 8};
+    return {s < 1 ? 1 : s, 4};
 }
 
-// Heads of up to 128 KB of keys are not split: one workgroup, one launch.  The choice favours steps that are launched one by
-// one, where a second launch costs the host about 3 us and a step that short is bound by it: 16 heads, d = 128, 12.9 us whatever
-// their length, against 15.9 split and merged.  On the GPU alone -- a step replayed from a graph -- one workgroup is ahead up to
-// 70 KB for up to 64 heads (200 keys 5.9 us against 6.6) and behind above (320: 7.1 / 6.8, 450: 8.6 / 6.8, 512: 9.1 / 6.9), for 256
-// heads and more always ahead (512 keys 16.8 / 21.0).  One rule for all callers: a replayed step, the step with static scratch
-// and the eager one give the same bits.  Up to 128 keys four waves do: 512 heads of 100 keys, d = 64, 7.9 us against 10.7 with
-// sixteen.
+// Short heads are not split: one workgroup of sixteen waves (up to 128 keys four: 512 heads of 100 keys, d = 64, 7.9 us against
+// 10.7), which has nothing to merge -- 2.4 us of a step -- but one CU for a head.  That is ahead up to 64 KB of keys for 16
+// heads, 80 for 64, 112 for 96 and 128 for 128 heads; above 128 KB it never is.  Replayed from a graph, us, one workgroup against
+// splits, d = 128: 16 heads 256 keys 7.6 / 7.7, 320 8.4 / 7.8, 512 10.9 / 8.1; 64 heads 320 9.4 / 9.5, 400 10.8 / 10.0; 96 heads
+// 400 11.6 / 11.5, 512 13.6 / 12.3; 128 heads 400 12.3 / 13.2, 512 14.4 / 14.0; 256 heads 512 18.4 / 21.4.
+static bool decode_one_workgroup(int BH, size_t key_bytes) {
+    const int kb = BH + 16 < 64 ? 64 : BH + 16 > 128 ? 128 : BH + 16;
+    return key_bytes <= (size_t)kb * 1024;
+}
+
 template <typename TIO, int D, bool GATES>
 static hipError_t launch_decode_g(const DecodeArgs& a, int BH, hipStream_t st) {
-    if ((size_t)a.n * D * sizeof(TIO) <= 131072) {
+    if (decode_one_workgroup(BH, (size_t)a.n * D * sizeof(TIO))) {
         if (a.n <= 128) hipLaunchKernelGGL((decode_partial_kernel<TIO, D, GATES, 256, true>), dim3(1, BH), dim3(256), 0, st, a);
         else hipLaunchKernelGGL((decode_partial_kernel<TIO, D, GATES, 1024, true>), dim3(1, BH), dim3(1024), 0, st, a);
         return hipGetLastError();
     }
-    const int nsplit = decode_num_splits(BH, a.n);
-    hipLaunchKernelGGL((decode_partial_kernel<TIO, D, GATES, 256, false>), dim3(nsplit, BH), dim3(256), 0, st, a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((decode_combine_kernel<TIO, D, GATES>), dim3(BH), dim3(D), 0, st, a, nsplit);
+    static_assert(DECODE_MAX_SPLITS * (D / 64) * sizeof(DecodeRecord) <= DECODE_SPLIT_ROOM * (D + 2) * 4, "the workspace holds the records");
+    const DecodeSplits s = decode_splits(BH, a.n);
+    if (s.waves == 4) hipLaunchKernelGGL((decode_partial_kernel<TIO, D, GATES, 256, false>), dim3(s.n, BH), dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((decode_partial_kernel<TIO, D, GATES, 512, false>), dim3(s.n, BH), dim3(512), 0, st, a);
     return hipGetLastError();
 }
 template <typename TIO, int D>
 static hipError_t launch_decode_t(const DecodeArgs& a, int BH, hipStream_t st) {
     return a.ccache ? launch_decode_g<TIO, D, true>(a, BH, st) : launch_decode_g<TIO, D, false>(a, BH, st);
 }
-hipError_t launch_decode_step(const DecodeArgs& a, int BH, int d, int is_bf16, hipStream_t st) {
+hipError_t launch_decode_step(DecodeArgs a, int BH, int d, int is_bf16, hipStream_t st) {
+    static std::atomic<unsigned long long> calls{0};
+    a.flag = (calls.fetch_add(1, std::memory_order_relaxed) + 1) * 0x9e3779b97f4a7c15ull;      // (odd factor: 2^64 calls before one recurs; never 0 before)
     if (is_bf16) return d == 64 ? launch_decode_t<bf16_t, 64>(a, BH, st) : launch_decode_t<bf16_t, 128>(a, BH, st);
     return d == 64 ? launch_decode_t<float, 64>(a, BH, st) : launch_decode_t<float, 128>(a, BH, st);
 }

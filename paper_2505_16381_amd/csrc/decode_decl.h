@@ -4,7 +4,8 @@
 
 namespace path {
 
-constexpr int DECODE_MAX_SPLITS = 64;
+constexpr int DECODE_MAX_SPLITS = 60;
+constexpr int DECODE_SPLIT_ROOM = 64;    // the workspace has room for so many records of d + 2 floats per head
 
 struct PrefillArgs {
     const void *kt2, *dp2;   // second-level tiles of the forward workspace
@@ -33,17 +34,17 @@ struct DecodeArgs {
     void *kcache, *vcache;              // [BH][Lmax][d]
     void* o;                            // [BH][d]
     float* lse;                         // [BH]
-    float* partial;                     // [BH][splits][d + 2]: m, l, o
+    float* partial;                     // the workspace: records of the splits
     int n, Lmax;                        // cached tokens before the step
     float scale;
     // PaTH-FoX (NULL for plain PaTH): the arriving token's log gate [BH] (I/O type) and the running sums
     // c_i = sum_{s<=i} log f_s of the cached tokens, fp32 [BH][Lmax], natural logarithm; the step appends c_n
     const void* log_f;
     float* ccache;
+    unsigned long long flag;            // this call's "record is there", set by the launcher
 };
 
 hipError_t launch_key_prefill(const PrefillArgs& a, int BH, int d, int is_bf16, hipStream_t st);
-hipError_t launch_decode_step(const DecodeArgs& a, int BH, int d, int is_bf16, hipStream_t st);
-int decode_num_splits(int BH, int n);
+hipError_t launch_decode_step(DecodeArgs a, int BH, int d, int is_bf16, hipStream_t st);
 
 }  // namespace path
