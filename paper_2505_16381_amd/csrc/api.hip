@@ -659,7 +659,12 @@ extern "C" path_status_t path_key_prefill(const void* v, int B, int H, int L, in
     hipStream_t st = static_cast<hipStream_t>(stream);
     clear_inherited_error();
     const int NC = (L + CHUNK - 1) / CHUNK;
-    if (NC <= SBC) {      // one super-block: its second-level keys are the prompt's (the forward has not formed them)
+    const bool one = NC <= SBC;
+    if (dt == PATH_BF16 && carry_pays(B * H, NC, one ? NC : (NC + SBC - 1) / SBC, d)) {
+        const CarryArgs a{base + (one ? ws.kt : ws.kt2), base + (one ? ws.dp : ws.dp2), v, kcache, vcache, B * H, L, NC, Lmax, one ? 1 : SBC};
+        return hip_ok(launch_key_carry(a, d, st), "key prefill") ? PATH_OK : PATH_ERR_HIP;
+    }
+    if (one) {      // one super-block: its second-level keys are the prompt's (the forward has not formed them)
         FwdParams p = {};
         const path_status_t ps = fwd_setup(p, layout_of(PATH_LAYOUT_BHLD, H, L, d), B, H, L, d, dt, const_cast<void*>(fws), fws_bytes);
         if (ps != PATH_OK) return ps;

@@ -12,7 +12,8 @@
 //    workgroup of the head, hence the same E) and carries only its own super-block's keys.
 //    Results go row-major into the key cache, in the cache's storage type.  (A prompt of one super-block
 //    has nothing to carry beyond it: its keys take the second level's own step straight to the cache,
-//    see prep2_fwd.hip.)  Further workgroups copy the values.
+//    see prep2_fwd.hip.  16-bit operands, few heads or short prompts: every chunk by itself, see key_carry.hip.)
+//    Further workgroups copy the values.
 //
 //  * Decode step (the section's first equation): when token t arrives every cached key is
 //    refreshed in place, k_i <- k_i - beta_t (w_t . k_i) w_t, and attention of q_t over the

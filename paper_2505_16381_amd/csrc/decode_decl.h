@@ -17,7 +17,7 @@ struct PrefillArgs {
 // The values of a prompt go to their cache unchanged, VROWS rows of a head per workgroup (of the launch that fills the
 // key cache: a copy of its own takes 5 us of the stream's time).
 constexpr int VROWS = 128;
-inline int value_row_pieces(int L) { return (L + VROWS - 1) / VROWS; }
+__host__ __device__ inline int value_row_pieces(int L) { return (L + VROWS - 1) / VROWS; }
 template <typename TIO, int D, int NT>
 __device__ __forceinline__ void copy_value_rows(const void* v, void* vcache, int L, int Lmax, int bh, int piece, int tid) {
     typedef TIO Vec __attribute__((ext_vector_type(16 / sizeof(TIO))));
@@ -43,6 +43,22 @@ struct DecodeArgs {
     float* ccache;
     unsigned long long flag;            // this call's "record is there", set by the launcher
 };
+
+// The same chunk by chunk (16-bit operands): key tiles of the prompt, products of the blocks of cpb chunks.
+struct CarryArgs {
+    const void *kt, *dp;     // [BH][NC] key tiles at their block's right edge; [BH][ceil(NC/cpb)] tiles of -dP
+    const void* v;           // [BH][L][d]
+    void *kcache, *vcache;   // [BH][Lmax][d], cache storage type
+    int BH, L, NC, Lmax, cpb;
+};
+// Chunk by chunk for few heads or short prompts: it does every product of a chunk's way for that chunk alone, in a chain of
+// light steps on many CUs, where the other kernels run one chain of heavy steps per super-block or head and share the
+// products.  The line, in products plus two per workgroup for its start, lies where both take as long; us, chunk by chunk
+// against the others: d = 128, 16 heads of 1000 tokens (2432) 15.1 / 37.4, of 4000 (3528) 21.8 / 36.1, 32 of 1000 (4864)
+// 28.5 / 40.7, 64 of 2048 (5120) 33.5 / 34.4, 32 of 4096 (7168) 40.0 / 37.8, 64 of 1000 (9728) 47.0 / 44.8; d = 64, 64 of
+// 1000 (9728) 16.3 / 19.6, 128 of 1000 (19456) 26.5 / 23.9, 32 of 8192 (22528) 32.0 / 27.7.
+inline bool carry_pays(int BH, int NC, int blocks, int d) { return (long long)BH * NC * (blocks + 3) / 2 <= (d == 64 ? 14000 : 6000); }
+hipError_t launch_key_carry(const CarryArgs& a, int d, hipStream_t st);
 
 hipError_t launch_key_prefill(const PrefillArgs& a, int BH, int d, int is_bf16, hipStream_t st);
 hipError_t launch_decode_step(DecodeArgs a, int BH, int d, int is_bf16, hipStream_t st);
