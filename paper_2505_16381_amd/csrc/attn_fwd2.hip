@@ -37,6 +37,7 @@ template <typename TIO, int D> struct Fwd2Cfg {
     static constexpr int HALF_FRAGS = 32 * D / FE;      // fragments of 32 keys of a key tile / V^T tile
     static constexpr int DP_FRAGS = D * D / FE;         // fragments per -dP tile
     static constexpr size_t smem_bytes = (size_t)(4 * HALF_FRAGS + DP_FRAGS) * 16 + 256;   // 2 stages x (K|V) + dP + 2 x 32 gate sums
+    static constexpr size_t smem_bytes_few = (size_t)(8 * HALF_FRAGS + 2 * DP_FRAGS) * 16 + 512;      // FEW: 4 stages, 2 x dP
 };
 
 __device__ __forceinline__ void wait_tiles_and_sync() {
@@ -58,8 +59,14 @@ __device__ __forceinline__ void wait_tiles_and_sync() {
 // edge, ready for the keys of the segment before) and stores its registers instead of writing o and lse.
 // 2 = one hop: the registers are loaded, all chunks of an earlier segment are swept as "far" blocks (second-level
 // keys, one product per super-block, the first one's included), and the registers are stored again.
-template <typename TIO, int D, bool FOX, bool EMIT, int RING = 0>
-__global__ __launch_bounds__(FWD2_THREADS, 512 / FWD2_THREADS) void attn_fwd2_kernel(FwdParams p) {
+//
+// FEW (no more workgroups than CUs, 16-bit operands): four more waves make the tile copies, three stages ahead, where
+// otherwise every wave makes them one stage ahead, 70 cycles a copy, and waits: a stage is then as long as the latency of a
+// copy, with nothing else on the SIMD.  The sweep of 16 heads of 1000 tokens, d = 128: 46 -> 36 us; forward of 8 heads of 4000
+// tokens 183 -> 160.  With a second workgroup for every CU the other form is ahead (its LDS leaves room for two at d = 128:
+// one head of 16384 tokens, 128 workgroups on the 32 CUs of one XCD, 602 / 679 us).
+template <typename TIO, int D, bool FOX, bool EMIT, int RING = 0, bool FEW = false>
+__global__ __launch_bounds__((FEW ? 2 * FWD2_THREADS : FWD2_THREADS), (512 / FWD2_THREADS)) void attn_fwd2_kernel(FwdParams p) {
     using C = Fwd2Cfg<TIO, D>;
     using T = typename C::T;
     using Frag = typename Tr<T>::Frag;
@@ -71,20 +78,18 @@ __global__ __launch_bounds__(FWD2_THREADS, 512 / FWD2_THREADS) void attn_fwd2_ke
     constexpr bool HAS_MASTER = sizeof(T) == 2;      // fp32 operands are their own master copy
 
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    Frag* sKV = reinterpret_cast<Frag*>(smem);                  // [2 stages][K half | V half]
-    Frag* sP = sKV + 4 * HF;                                    // -dP tile
-    float* sC = reinterpret_cast<float*>(sP + DPF);             // FOX: [2 stages][32] gate sums of the stage's keys
+    constexpr int NST = FEW ? 4 : 2, NP = FEW ? 2 : 1;
+    Frag* sKV = reinterpret_cast<Frag*>(smem);                  // [NST stages][K half | V half]
+    Frag* sP = sKV + 2 * NST * HF;                              // [NP] -dP tile
+    float* sC = reinterpret_cast<float*>(sP + NP * DPF);        // FOX: [NST stages][32] gate sums of the stage's keys
 
     const int BH = p.B * p.H, NC = p.NC;            // NC: chunks per head in the workspace arrays and in the grid's numbering
     const int NCq = RING == 2 ? p.NCq : NC;         // chunks of the query side (a hop's keys belong to another segment)
     const int ntiles = (NCq + FWD2_CPT - 1) / FWD2_CPT;
-    // XCD-aware numbering: workgroup b runs on XCD b % 8; that XCD takes heads xcd, xcd+8, ...
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    // (the division runs on the vector unit; its result, uniform over the workgroup, goes back to scalar
-    // registers, so that everything derived from it -- loop bounds, tile addresses -- is scalar arithmetic)
-    const int bh = __builtin_amdgcn_readfirstlane((slot / ntiles) * 8 + xcd);
-    const int tile = __builtin_amdgcn_readfirstlane(ntiles - 1 - slot % ntiles);
-    if (bh >= BH) return;
+    int bh, rank;
+    if (!xcd_deal(slot, xcd, ntiles, BH, bh, rank)) return;
+    const int tile = ntiles - 1 - rank;                // heaviest first
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), h = lane >> 5, l32 = lane & 31;
 
     const int L = seq_len(p.ul, bh, p.L);
@@ -92,7 +97,7 @@ __global__ __launch_bounds__(FWD2_THREADS, 512 / FWD2_THREADS) void attn_fwd2_ke
     if (tile * FWD2_CPT >= NCown) return;
     const int cq = tile * FWD2_CPT + (wv >> 1);     // this wave's chunk
     const int qb = wv & 1;                          // ... and which 32-query half of it
-    const bool active = cq < NCown;
+    const bool active = cq < NCown && (!FEW || wv < 4);
     // (a hop sweeps every chunk of the other segment, all of them as far blocks)
     const int jtop = RING == 2 ? NC - 1 : ((tile * FWD2_CPT + FWD2_CPT - 1 < NCown) ? tile * FWD2_CPT + FWD2_CPT - 1 : NCown - 1);
     static_assert(SBC % FWD2_CPT == 0, "a tile must lie in one super-block");
@@ -147,32 +152,74 @@ __global__ __launch_bounds__(FWD2_THREADS, 512 / FWD2_THREADS) void attn_fwd2_ke
 
     // Stage u = 0, 1, ...: chunk j = jtop - u/2, key half kb = u % 2, LDS buffer u % 2.
     const int nstage = 2 * (jtop + 1);
+    const int ctid = FEW ? tid - FWD2_THREADS : tid, cwv = FEW ? wv - FWD2_THREADS / 64 : wv;      // among the threads that copy
     auto issue_kv = [&](int u) {
         const int j = jtop - (u >> 1), kb = u & 1;
-        Frag* buf = sKV + (size_t)(u & 1) * 2 * HF;
+        Frag* buf = sKV + (size_t)(u & (NST - 1)) * 2 * HF;
         const T* kg = (j >= jsb ? ktg : kt2g) + (size_t)j * CHUNK * D;
-        async_copy_tile<FWD2_THREADS, HF>(reinterpret_cast<const Frag*>(kg) + kb * HF, buf, tid, wv);
-        async_copy_tile<FWD2_THREADS, HF>(reinterpret_cast<const Frag*>(vtg + (size_t)j * CHUNK * D) + kb * HF, buf + HF, tid, wv);
-        if (FOX && tid < 8)      // 32 floats, 16 bytes per lane
+        async_copy_tile<FWD2_THREADS, HF>(reinterpret_cast<const Frag*>(kg) + kb * HF, buf, ctid, cwv);
+        async_copy_tile<FWD2_THREADS, HF>(reinterpret_cast<const Frag*>(vtg + (size_t)j * CHUNK * D) + kb * HF, buf + HF, ctid, cwv);
+        if (FOX && FEW) {        // 8 floats per wave: every wave makes as many copies
+            if (lane < 2)
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(p.cum + (size_t)bh * NC * CHUNK + (size_t)j * CHUNK + 32 * kb + 8 * cwv + 4 * lane),
+                                                 (__attribute__((address_space(3))) void*)(sC + (u & (NST - 1)) * 32 + 8 * cwv), 16, 0, 0);
+        } else if (FOX && ctid < 8)      // 32 floats, 16 bytes per lane
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(p.cum + (size_t)bh * NC * CHUNK + (size_t)j * CHUNK + 32 * kb + 4 * tid),
                                              (__attribute__((address_space(3))) void*)(sC + (u & 1) * 32), 16, 0, 0);
     };
     // the product applied after chunk j (if any): loaded while the chunk's first half is
     // processed (sP is free then: the previous update ended before this stage's barrier)
     auto issue_dp = [&](int j) {
+        Frag* dst = FEW ? sP + ((jtop - j) & 1) * DPF : sP;
         if (j >= jsb) {
-            if (j < jtop && (j > 0 || RING)) async_copy_tile<FWD2_THREADS, DPF>(reinterpret_cast<const Frag*>(dpg + (size_t)j * D * D), sP, tid, wv);
+            if (j < jtop && (j > 0 || RING)) async_copy_tile<FWD2_THREADS, DPF>(reinterpret_cast<const Frag*>(dpg + (size_t)j * D * D), dst, ctid, cwv);
         } else if (j % SBC == 0 && (j > 0 || RING)) {
-            async_copy_tile<FWD2_THREADS, DPF>(reinterpret_cast<const Frag*>(dp2g + (size_t)(j / SBC) * D * D), sP, tid, wv);
+            async_copy_tile<FWD2_THREADS, DPF>(reinterpret_cast<const Frag*>(dp2g + (size_t)(j / SBC) * D * D), dst, ctid, cwv);
         }
     };
+    if constexpr (FEW) {
+        if (wv >= FWD2_THREADS / 64) {
+            // The copies, three stages ahead; a chunk's product with its second half: its place is free by then.
+            constexpr int CS = 2 * HF / FWD2_THREADS + (FOX ? 1 : 0), CP = DPF / FWD2_THREADS;      // a wave's copies per stage, per product
+            static_assert(HF % FWD2_THREADS == 0 && DPF % FWD2_THREADS == 0, "every wave makes as many copies");
+            auto issue = [&](int u) {
+                if (u >= nstage) return;
+                issue_kv(u);
+                if (u & 1) issue_dp(jtop - (u >> 1));
+            };
+            auto has_dp = [&](int j) { return (j > 0 || RING) && (j >= jsb ? j < jtop : j % SBC == 0); };
+            auto copies = [&](int u) { return u < nstage ? CS + ((u & 1) && has_dp(jtop - (u >> 1)) ? CP : 0) : 0; };
+            for (int u = 0; u < NST - 1; ++u) issue(u);
+            for (int u = 0; u < nstage; ++u) {
+                // stage u has landed: what may be on its way is the two behind it
+                const int n = copies(u + 1) + copies(u + 2);
+                if (n >= 2 * CS + CP) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * CS + CP) : "memory");
+                else if (n >= 2 * CS) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * CS) : "memory");
+                else if (n >= CS) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(CS) : "memory");
+                else copies_landed();
+                lds_barrier();               // ... for everybody, and stage u - 1 has been read
+                issue(u + NST - 1);
+            }
+            return;
+        }
+    }
+    // FEW: the raw logits of the own chunk, which a wave would otherwise wait for when it gets there
+    f32x4 diag_pre[FEW ? 2 : 1][4];
+    if (FEW && active) {
+#pragma unroll
+        for (int kb = 0; kb < (FEW ? 2 : 1); ++kb)
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+                diag_pre[kb][g] = *reinterpret_cast<const f32x4*>(p.sd + ((size_t)bh * NC + cq) * 4096 + ((size_t)qb * 2 + kb) * 1024 + g * 256 + lane * 4);
+    }
 
     // One stage of an active wave (chunk j <= cq).  DIAG: the wave's own chunk (precomputed logits, causal mask,
-    // no state update after it); otherwise a chunk further left.
-    auto stage = [&](int u, auto diag_tag) {
-        constexpr bool DIAG = decltype(diag_tag)::value;
-        const int j = jtop - (u >> 1), kb = u & 1;
-        const Frag* sK = sKV + (size_t)(u & 1) * 2 * HF;
+    // no state update after it), first or second half (tag 0, 1) or either (tag 2); otherwise
+    // (tag 3) a chunk further left.
+    auto stage = [&](int u, auto tag) {
+        constexpr bool DIAG = decltype(tag)::value < 3;
+        const int j = jtop - (u >> 1), kb = decltype(tag)::value < 2 ? decltype(tag)::value : u & 1;
+        const Frag* sK = sKV + (size_t)(u & (NST - 1)) * 2 * HF;
         const FragV* sV = reinterpret_cast<const FragV*>(sK + HF);
         if (!DIAG) {
             if (EMIT && kb == 0 && (j >= jsb || (j % SBC) == SBC - 1)) {
@@ -203,7 +250,9 @@ __global__ __launch_bounds__(FWD2_THREADS, 512 / FWD2_THREADS) void attn_fwd2_ke
             const float* diag = p.sd + ((size_t)bh * NC + j) * 4096 + ((size_t)qb * 2 + kb) * 1024;
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
-                const f32x4 v4 = *reinterpret_cast<const f32x4*>(diag + g * 256 + lane * 4);
+                f32x4 v4;
+                if constexpr (FEW) v4 = diag_pre[decltype(tag)::value & 1][g];
+                else v4 = *reinterpret_cast<const f32x4*>(diag + g * 256 + lane * 4);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const int sk = 32 * kb + 8 * g + 4 * h + r, tq = 32 * qb + l32;
@@ -237,7 +286,7 @@ __global__ __launch_bounds__(FWD2_THREADS, 512 / FWD2_THREADS) void attn_fwd2_ke
             f32x16 E;
             float rs = 0.f;
             if (FOX) {            // T = logit in base-2 units minus the key's gate sum; then as below with scale 1
-                const float* ck = sC + (u & 1) * 32 + 4 * h;
+                const float* ck = sC + (u & (NST - 1)) * 32 + 4 * h;
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
                     const f32x4 c4 = *reinterpret_cast<const f32x4*>(ck + 8 * g);
@@ -292,6 +341,7 @@ __global__ __launch_bounds__(FWD2_THREADS, 512 / FWD2_THREADS) void attn_fwd2_ke
             // ---- X <- X (I - dP) after the chunk (phase A) / after the super-block (phase B) -------
             const bool upd = kb == 1 && (j > 0 || RING) && (j >= jsb || (j % SBC) == 0);
             if (upd) {
+                const Frag* sPu = sP + (FEW ? (u >> 1) & 1 : 0) * DPF;
                 f32x16 Xn[DB];
 #pragma unroll
                 for (int b = 0; b < DB; ++b) {
@@ -303,7 +353,7 @@ __global__ __launch_bounds__(FWD2_THREADS, 512 / FWD2_THREADS) void attn_fwd2_ke
 #pragma unroll
                 for (int b = 0; b < DB; ++b)
 #pragma unroll
-                    for (int s = 0; s < DS; ++s) Xn[b] = Tr<T>::mma(sP[(b * DS + s) * 64 + tile_lane<T>(lane, s)], Xh[s], Xn[b]);
+                    for (int s = 0; s < DS; ++s) Xn[b] = Tr<T>::mma(sPu[(b * DS + s) * 64 + tile_lane<T>(lane, s)], Xh[s], Xn[b]);
 #pragma unroll
                 for (int b = 0; b < DB; ++b) {
                     if (HAS_MASTER) Xm[b] = Xn[b];
@@ -315,22 +365,23 @@ __global__ __launch_bounds__(FWD2_THREADS, 512 / FWD2_THREADS) void attn_fwd2_ke
     // Every wave passes the same nstage barriers: as a bystander (stages right of its own chunk: it only helps
     // with the tile copies), through its own chunk (two stages), then the steady state.
     auto top_of_stage = [&](int u) {
+        if (FEW) { lds_barrier(); return; }
         wait_tiles_and_sync();            // stage u has landed; everyone is done with stage u-1
         if (u + 1 < nstage) issue_kv(u + 1);
         if ((u & 1) == 0) issue_dp(jtop - (u >> 1));
     };
     const int u0 = RING == 2 ? (active ? 0 : nstage) : (active ? 2 * (jtop - cq) : nstage);      // this wave's first stage
-    issue_kv(0);
+    if (!FEW) issue_kv(0);
     int u = 0;
     for (; u < u0; ++u) top_of_stage(u);
     if (active) {
         if (RING != 2) {
-            top_of_stage(u); stage(u, std::true_type{}); ++u;
-            top_of_stage(u); stage(u, std::true_type{}); ++u;
+            top_of_stage(u); stage(u, std::integral_constant<int, FEW ? 0 : 2>{}); ++u;
+            top_of_stage(u); stage(u, std::integral_constant<int, FEW ? 1 : 2>{}); ++u;
         }
         for (; u < nstage; ++u) {
             top_of_stage(u);
-            stage(u, std::false_type{});
+            stage(u, std::integral_constant<int, 3>{});
         }
     }
     if (RING) {
@@ -377,18 +428,23 @@ __global__ __launch_bounds__(FWD2_THREADS, 512 / FWD2_THREADS) void attn_fwd2_ke
     }
 }
 
-template <typename TIO, int D, bool FOX, bool EMIT, int RING = 0>
+template <typename TIO, int D, bool FOX, bool EMIT, int RING = 0, bool FEW = false>
 hipError_t launch_attn_fwd2_f(const FwdParams& p, hipStream_t stream) {
     using C = Fwd2Cfg<TIO, D>;
+    constexpr size_t bytes = FEW ? C::smem_bytes_few : C::smem_bytes;
+    static_assert(bytes <= 160 * 1024, "LDS budget");
     // set once per process; a function-local static is initialised under the language's own lock
-    static const hipError_t attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_fwd2_kernel<TIO, D, FOX, EMIT, RING>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::smem_bytes);
+    static const hipError_t attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_fwd2_kernel<TIO, D, FOX, EMIT, RING, FEW>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
     if (attr_err != hipSuccess) return attr_err;
     const int ntiles = ((RING == 2 ? p.NCq : p.NC) + FWD2_CPT - 1) / FWD2_CPT;
     const int BH = p.B * p.H;
-    dim3 grid((unsigned)(((BH + 7) / 8) * 8 * ntiles));
-    const size_t bytes = C::smem_bytes;
-    hipLaunchKernelGGL((attn_fwd2_kernel<TIO, D, FOX, EMIT, RING>), grid, dim3(FWD2_THREADS), bytes, stream, p);
+    dim3 grid(xcd_deal_grid(ntiles, BH));
+    if constexpr (RING == 0 && !FEW && sizeof(TIO) == 2) {
+        // one workgroup or none for each of the 32 CUs of an XCD
+        if (grid.x <= 256) return launch_attn_fwd2_f<TIO, D, FOX, EMIT, RING, true>(p, stream);
+    }
+    hipLaunchKernelGGL((attn_fwd2_kernel<TIO, D, FOX, EMIT, RING, FEW>), grid, dim3(FEW ? 2 * FWD2_THREADS : FWD2_THREADS), bytes, stream, p);
     return hipGetLastError();
 }
 template <typename TIO, int D>

@@ -133,13 +133,12 @@ __global__ __launch_bounds__(256) void bwd_adjoint2_kernel(BwdParams p) {
 
     const int BH = p.B * p.H, NC = p.NC;
     const int ntiles = (NC + 1) / 2;
-    // XCD-aware numbering: workgroup n runs on XCD n % 8; that XCD takes heads xcd, xcd+8, ... one
-    // after the other, all tiles of a head together (heaviest first).  They walk the key chunks
+    // XCD-aware numbering (xcd_deal.h): all tiles of a head together, heaviest first.  They walk the key chunks
     // from 0 upwards at the same pace, so each tile is fetched once per head into that XCD's L2.
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    const int bh = __builtin_amdgcn_readfirstlane((slot / ntiles) * 8 + xcd);        // (divisions run on the vector unit:
-    const int tile = __builtin_amdgcn_readfirstlane(ntiles - 1 - slot % ntiles);     // back to scalar registers)
-    if (bh >= BH) return;
+    int bh, rank;
+    if (!xcd_deal(slot, xcd, ntiles, BH, bh, rank)) return;
+    const int tile = ntiles - 1 - rank;
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), h = lane >> 5, l32 = lane & 31;
     const int NCo = (seq_len(p.ul, bh, p.L) + CHUNK - 1) / CHUNK;          // this head's own chunks (NC: per head in the workspace arrays)
     if (tile * 2 >= NCo) return;
@@ -338,9 +337,9 @@ __global__ __launch_bounds__(256, 2) void bwd_adjoint2_lite_kernel(BwdParams p) 
     const int BH = p.B * p.H, NC = p.NC;
     const int ntiles = (NC + 1) / 2;
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;        // numbering as in bwd_adjoint2_kernel
-    const int bh = __builtin_amdgcn_readfirstlane((slot / ntiles) * 8 + xcd);        // (divisions run on the vector unit:
-    const int tile = __builtin_amdgcn_readfirstlane(ntiles - 1 - slot % ntiles);     // back to scalar registers)
-    if (bh >= BH) return;
+    int bh, rank;
+    if (!xcd_deal(slot, xcd, ntiles, BH, bh, rank)) return;
+    const int tile = ntiles - 1 - rank;
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), h = lane >> 5, l32 = lane & 31;
     const int NCo = (seq_len(p.ul, bh, p.L) + CHUNK - 1) / CHUNK;          // this head's own chunks (NC: per head in the workspace arrays)
     if (tile * 2 >= NCo) return;
@@ -1084,7 +1083,7 @@ static hipError_t launch_scan_t(const BwdParams& p, int stages, hipStream_t st) 
     const unsigned rounds = 8 * (unsigned)((BH + 7) / 8);
     hipError_t e = hipSuccess;
     if (stages & BWD_STAGE_SCAN) {
-        const dim3 grid((unsigned)(p.NC * BH)), grid_adj(rounds * ntiles);
+        const dim3 grid((unsigned)(p.NC * BH)), grid_adj(xcd_deal_grid(ntiles, BH));
         if (p.ul.vt != D) hipLaunchKernelGGL((bwd_dotile_kernel<TIO, D, true>), grid, dim3(256), 0, st, p);
         else hipLaunchKernelGGL((bwd_dotile_kernel<TIO, D, false>), grid, dim3(256), 0, st, p);
         if ((e = hipGetLastError()) != hipSuccess) return e;

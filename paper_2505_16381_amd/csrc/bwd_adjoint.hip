@@ -54,14 +54,13 @@ __global__ __launch_bounds__(512, 2) void bwd_adjoint_kernel(BwdParams p) {
     Frag* const sDP = stages + 2 * STF;
     Frag* const hand = sDP + DPF;
 
-    // XCD-aware numbering: workgroup n runs on XCD n % 8; that XCD takes heads xcd, xcd+8, ... one after the other, all
-    // tiles of a head together (heaviest first).  They walk the key chunks at the same pace, so a chunk's tiles are
-    // fetched once per head into that XCD's L2.
+    // XCD-aware numbering (xcd_deal.h): all tiles of a head together, heaviest first.  They walk the key chunks at the same
+    // pace, so a chunk's tiles are fetched once per head into that XCD's L2.
     const int BH = p.B * p.H, NC = p.NC, ntiles = (NC + ADJ_CPT - 1) / ADJ_CPT;
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    const int bh = __builtin_amdgcn_readfirstlane((slot / ntiles) * 8 + xcd);        // (divisions run on the vector unit:
-    const int tile = __builtin_amdgcn_readfirstlane(ntiles - 1 - slot % ntiles);     // back to scalar registers)
-    if (bh >= BH) return;
+    int bh, rank;
+    if (!xcd_deal(slot, xcd, ntiles, BH, bh, rank)) return;
+    const int tile = ntiles - 1 - rank;                                    // heaviest first
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), h = lane >> 5, l32 = lane & 31;
     const int NCo = (seq_len(p.ul, bh, p.L) + CHUNK - 1) / CHUNK;          // this head's own chunks (NC: per head in the workspace arrays)
     if (tile * ADJ_CPT >= NCo) return;
@@ -325,7 +324,7 @@ static hipError_t launch_adjoint_f(const BwdParams& p, hipStream_t st) {
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::smem_bytes);
     if (attr_err != hipSuccess) return attr_err;
     const unsigned ntiles = (unsigned)((p.NC + ADJ_CPT - 1) / ADJ_CPT);
-    hipLaunchKernelGGL((bwd_adjoint_kernel<TIO, D, FOX>), dim3(8 * (unsigned)((p.B * p.H + 7) / 8) * ntiles), dim3(512), C::smem_bytes, st, p);
+    hipLaunchKernelGGL((bwd_adjoint_kernel<TIO, D, FOX>), dim3(xcd_deal_grid((int)ntiles, p.B * p.H)), dim3(512), C::smem_bytes, st, p);
     return hipGetLastError();
 }
 hipError_t launch_bwd_adjoint(const BwdParams& p, hipStream_t st) {

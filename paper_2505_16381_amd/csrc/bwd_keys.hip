@@ -56,14 +56,13 @@ __global__ __launch_bounds__(512, 2) void bwd_far_kernel(BwdParams p) {
     Frag* const stages = reinterpret_cast<Frag*>(smem);
     Frag* const hand = stages + 3 * STF;
 
-    // XCD x takes the heads bh = x (mod 8); the workgroups of a super-block get consecutive numbers on it (they
-    // stream the same states and dO tiles at the same time, out of that XCD's L2), the left-most super-block first.
+    // Numbering as in xcd_deal.h, super-block by super-block, the left-most first; the workgroups of a super-block get
+    // consecutive numbers on its XCD (they stream the same states and dO tiles at the same time, out of that XCD's L2).
     constexpr int NPOS = Blocks::NPOS;
     const int NC = p.NC, nsb = (NC + SBC - 1) / SBC;
     const int xcd = blockIdx.x & 7, kk = blockIdx.x >> 3, pos = kk % NPOS;
-    const int J = __builtin_amdgcn_readfirstlane(kk / NPOS % (nsb - 1));
-    const int bh = __builtin_amdgcn_readfirstlane(kk / (NPOS * (nsb - 1)) * 8 + xcd);
-    if (bh >= p.B * p.H) return;
+    int J, bh;
+    if (!xcd_deal(kk / NPOS, xcd, nsb - 1, p.B * p.H, bh, J)) return;
     const int NCo = (seq_len(p.ul, bh, p.L) + CHUNK - 1) / CHUNK;      // this head's own chunks
     if (is_last_sb(J, NCo)) return;                                    // no queries to the right
     const int j = J * SBC + 2 * pos;
@@ -331,7 +330,7 @@ static hipError_t launch_far_f(const BwdParams& p, hipStream_t st) {
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::smem_bytes);
     if (attr_err != hipSuccess) return attr_err;
     const int nsb = (p.NC + SBC - 1) / SBC;
-    hipLaunchKernelGGL((bwd_far_kernel<TIO, D, FOX>), dim3((unsigned)(8 * ((p.B * p.H + 7) / 8) * (nsb - 1) * (SBC / 2))), dim3(512), C::smem_bytes, st, p);
+    hipLaunchKernelGGL((bwd_far_kernel<TIO, D, FOX>), dim3(xcd_deal_grid(nsb - 1, p.B * p.H) * (SBC / 2)), dim3(512), C::smem_bytes, st, p);
     return hipGetLastError();
 }
 hipError_t launch_bwd_far(const BwdParams& p, int d, hipStream_t st) {

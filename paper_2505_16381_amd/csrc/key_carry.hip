@@ -35,10 +35,9 @@ __global__ __launch_bounds__((CarryCfg<TIO, D>::NT)) void key_carry_kernel(Carry
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     Frag* const tiles = reinterpret_cast<Frag*>(smem);
 
-    // a head's workgroups run on one XCD, longest chains first, then the pieces of its values
-    const int n = a.NC + value_row_pieces(a.L);
-    const int slot = blockIdx.x >> 3, bh = slot / n * 8 + (blockIdx.x & 7), c = slot % n;
-    if (bh >= a.BH) return;
+    // longest chains first, then the pieces of the values
+    int bh, c;
+    if (!xcd_deal(blockIdx.x >> 3, blockIdx.x & 7, a.NC + value_row_pieces(a.L), a.BH, bh, c)) return;
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), h = lane >> 5, l32 = lane & 31;
     if (c >= a.NC) { copy_value_rows<TIO, D, C::NT>(a.v, a.vcache, a.L, a.Lmax, bh, c - a.NC, tid); return; }
     const int nblk = (a.NC + a.cpb - 1) / a.cpb, j0 = c / a.cpb + 1;      // chunks per block; the first block to pass
@@ -113,8 +112,7 @@ static hipError_t launch_carry_t(const CarryArgs& a, hipStream_t st) {
     static const hipError_t attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&key_carry_kernel<bf16_t, D>),
                                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::smem_bytes);
     if (attr_err != hipSuccess) return attr_err;
-    const unsigned grid = 8u * (unsigned)((a.BH + 7) / 8) * (unsigned)(a.NC + value_row_pieces(a.L));
-    hipLaunchKernelGGL((key_carry_kernel<bf16_t, D>), dim3(grid), dim3(C::NT), C::smem_bytes, st, a);
+    hipLaunchKernelGGL((key_carry_kernel<bf16_t, D>), dim3(xcd_deal_grid(a.NC + value_row_pieces(a.L), a.BH)), dim3(C::NT), C::smem_bytes, st, a);
     return hipGetLastError();
 }
 hipError_t launch_key_carry(const CarryArgs& a, int d, hipStream_t st) { return d == 64 ? launch_carry_t<64>(a, st) : launch_carry_t<128>(a, st); }

@@ -30,6 +30,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "xcd_deal.h"
+
 namespace path {
 
 typedef __bf16 bf16_t;
@@ -381,8 +383,19 @@ __device__ __forceinline__ void chunk_and_head(const UserLayout& u, int NC, int 
         if (bh >= m) bh -= m;
     }
 }
-// The same for a kernel whose workgroups of one (super-block, head) read the same tiles: its SBC workgroups run on one XCD,
-// first chunk first, and the (super-block, head) pairs are dealt to the XCDs in the order, and with the turn, of above.  Launched
+// The workgroup's head and its place among the head's N, see xcd_deal.h (the division runs on the vector unit; its result,
+// uniform over the workgroup, goes back to scalar registers, so that everything derived from it -- loop bounds, tile
+// addresses -- is scalar arithmetic).
+__device__ __forceinline__ bool xcd_deal(int slot, int xcd, int N, int BH, int& bh, int& r) {
+    const int np = xcd_per_part(N, BH), round = __builtin_amdgcn_readfirstlane(slot / np);
+    const XcdPlace p = xcd_place(round, slot - round * np, xcd, BH);
+    bh = __builtin_amdgcn_readfirstlane(p.bh);
+    r = __builtin_amdgcn_readfirstlane(p.r);
+    return bh < BH && r < N;
+}
+// For a kernel whose workgroups of one (super-block, head) read the same tiles: its SBC workgroups run on one XCD,
+// first chunk first, and the (super-block, head) pairs are dealt to the XCDs in the order, and with the turn, of
+// chunk_and_head.  Launched
 // with super_block_grid() workgroups; those past the last pair get bh >= BH.
 __device__ __forceinline__ void super_block_and_head(const UserLayout& u, int NC, int BH, int& chunk, int& bh) {
     const int nsb = (NC + SBC - 1) / SBC, kk = blockIdx.x >> 3;

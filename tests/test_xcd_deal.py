@@ -1,0 +1,42 @@
+"""How the kernels that keep a head's workgroups together deal them out to the eight XCDs (CPU; the header is plain C++): every
+workgroup of every head exactly once, and equal shares where few heads are no multiple of eight."""
+import os
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2505_16381_amd", "csrc")
+SOURCE = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "xcd_deal.h"
+int main(int, char** v) {
+    const int N = atoi(v[1]), BH = atoi(v[2]), np = path::xcd_per_part(N, BH);
+    for (unsigned b = 0; b < path::xcd_deal_grid(N, BH); ++b) {
+        const path::XcdPlace p = path::xcd_place((int)(b >> 3) / np, (int)(b >> 3) % np, b & 7, BH);
+        if (p.bh < BH && p.r < N) printf("%u %d %d\n", b & 7, p.bh, p.r);
+    }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def deal(tmp_path_factory):
+    d = tmp_path_factory.mktemp("deal")
+    (d / "deal.cpp").write_text(SOURCE)
+    subprocess.run(["g++", "-std=c++17", f"-I{CSRC}", str(d / "deal.cpp"), "-o", str(d / "deal")], check=True)
+    return lambda N, BH: [tuple(map(int, l.split())) for l in subprocess.run([str(d / "deal"), str(N), str(BH)], capture_output=True, text=True, check=True).stdout.splitlines()]
+
+
+@pytest.mark.parametrize("N", [1, 2, 7, 8, 9, 64, 127])
+@pytest.mark.parametrize("BH", [1, 2, 3, 4, 6, 7, 8, 9, 12, 16, 20, 31, 32, 33, 64, 100])
+def test_every_workgroup_once(deal, N, BH):
+    got = deal(N, BH)
+    assert sorted((bh, r) for _, bh, r in got) == [(bh, r) for bh in range(BH) for r in range(N)]
+    if BH < 8:
+        share = [sum(x == i for x, _, _ in got) for i in range(8)]
+        parts = next(p for p in (1, 2, 4, 8) if BH * p % 8 == 0)
+        assert max(share) <= -(-N // parts) * BH * parts // 8
+    for x in range(8):                      # a head's workgroups in their order on each XCD
+        mine = [(bh, r) for y, bh, r in got if y == x]
+        assert all(a[1] < b[1] for a, b in zip(mine, mine[1:]) if a[0] == b[0])
