@@ -76,10 +76,10 @@ static BwdWorkspace bwd_workspace(int B, int H, int L, int d, size_t es) {
     take(w.dr, (es == 2 ? 1 : 0) * BH * NC * d * d * es);
     take(w.dk2, BH * Lp * d * 4);
     take(w.dchain, BH * (es == 4 ? NC + 1 : NSB) * d * d * 4);
-    // (regions only the fp32-operand path uses -- the second level's chain and the chunk-transform adjoint as
-    //  staged products -- have size zero for 2-byte operands, whose fused kernels keep these in LDS)
-    const size_t staged = es == 4 ? 1 : 0;
-    take(w.t1, staged * BH * NC * d * CHUNK * 4);
+    // (regions only products staged one by one use -- fp32 operands: the second level's chain, and at d = 128 the
+    //  chunk-transform adjoint -- have size zero elsewhere: the fused kernels keep these in LDS)
+    const size_t staged = es == 4 && d == 128 ? 1 : 0;
+    take(w.t1, (es == 4 ? 1 : 0) * BH * NC * d * CHUNK * 4);
     take(w.dcol, BH * Lp * 4);
     take(w.drow, BH * Lp * 4);
     for (size_t* f : {&w.fm, &w.gktm, &w.nm, &w.aim, &w.ytm}) take(*f, BH * NC * 4096 * es);
@@ -89,8 +89,8 @@ static BwdWorkspace bwd_workspace(int B, int H, int L, int d, size_t es) {
     take(w.delta, BH * Lp * 4);
     take(w.lse2p, BH * Lp * 4);
     for (size_t* f : {&w.dqb, &w.dvp}) take(*f, BH * Lp * d * 4);
-    take(w.dkb, staged * BH * Lp * d * 4);
-    take(w.ddp, staged * BH * NC * d * d * 4);
+    take(w.dkb, (es == 4 ? 1 : 0) * BH * Lp * d * 4);
+    take(w.ddp, (es == 4 ? 1 : 0) * BH * NC * d * d * 4);
     for (size_t* f : {&w.dpd, &w.pd, &w.dsd, &w.df, &w.dy, &w.dn, &w.dgk, &w.rr, &w.mm, &w.dgs}) take(*f, staged * BH * NC * 4096 * 4);
     for (size_t* f : {&w.du, &w.dqf, &w.dkf, &w.dwf}) take(*f, staged * BH * Lp * d * 4);
     take(w.dbf, staged * BH * Lp * 4);
@@ -460,7 +460,7 @@ static path_status_t bwd_run(BwdMode mode, int stages, const UserLayout& ul, con
     fp.B = B; fp.H = H; fp.L = L; fp.NC = NC; fp.scale = scale; fp.ul = ul;
     fp.ktT = base + ws.ktT; fp.vk = base + ws.vk; fp.dpt = base + ws.dpt; fp.xs = base + ws.xs; fp.xsT = base + ws.xsT;
     fp.fm = base + ws.fm; fp.gktm = base + ws.gktm; fp.nm = base + ws.nm; fp.aim = base + ws.aim;
-    fp.ytm = base + ws.ytm; fp.utm = base + ws.utm; fp.gm = bf ? nullptr : F(ws.gm); fp.sdm = bf ? nullptr : F(ws.sdm);
+    fp.ytm = base + ws.ytm; fp.utm = base + ws.utm; fp.gm = bf || d == 64 ? nullptr : F(ws.gm); fp.sdm = bf || d == 64 ? nullptr : F(ws.sdm);
     float* cum = log_f ? F(ws.f.cum) : nullptr;
     if (mode != BWD_RESUME && mode != BWD_FWD_SWEEP) {
         if (log_f && !hip_ok(launch_gate_sums(log_f, ul, cum, B, H, L, dt, st), "gate sums (backward)")) return PATH_ERR_HIP;
@@ -567,14 +567,14 @@ static path_status_t bwd_run(BwdMode mode, int stages, const UserLayout& ul, con
     // 5b. adjoint of the chunk transform: one fused kernel runs this list per (chunk, head).
     // Chains of products that add into the same result are consecutive.
     if (!ok) return PATH_ERR_HIP;
-    if (bf) {      // 2-byte operand types: the hand-fused kernel
+    if (bf || d == 64) {      // 2-byte operand types, fp32 at d = 64: the hand-fused kernel
         ChunkFusedArgs ca{ul, q, k, v, w, beta, d_o, lse, bp.delta, fp.sd, fp.fm, fp.gktm, fp.nm, fp.aim, fp.ytm,
-                          base + ws.utm, fp.kt, fp.vk, bp.doq, fp.xs, bp.gs, bp.lse2p, bp.dqb, bp.dvp, base + ws.rm, base + ws.dr, F(ws.dk2), dq, dk, dv, dw, dbeta, bp.cum, bp.dcol, bp.drow,
+                          base + ws.utm, fp.kt, fp.vk, bp.doq, fp.xs, bp.gs, bp.lse2p, bp.dqb, bp.dvp, bp.dkb, F(ws.ddp), base + ws.rm, base + ws.dr, F(ws.dk2), dq, dk, dv, dw, dbeta, bp.cum, bp.dcol, bp.drow,
                           L, NC, BH, scale};
-        ok = hip_ok(launch_chunk_fused(ca, BH, d, st), "chunk-transform adjoint");
+        ok = hip_ok(launch_chunk_fused(ca, BH, d, bf, st), "chunk-transform adjoint");
         if (ok && log_f) {
             ScanArgs sa{bp.dcol, bp.drow, dlog_f, (int)Lp, L, L, L, 0, 1.f, 0, 1, ul};
-            ok = hip_ok(launch_fox_scan(sa, BH, 0, 1, st), "gate gradient");
+            ok = hip_ok(launch_fox_scan(sa, BH, 0, bf, st), "gate gradient");
         }
         return ok ? PATH_OK : PATH_ERR_HIP;
     }

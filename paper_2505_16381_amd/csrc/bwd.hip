@@ -994,7 +994,7 @@ __device__ __forceinline__ void chunk_store(const OutArgs& a, const UserLayout& 
         reinterpret_cast<TIO*>(a.dbeta)[user_scl(ul, bh, chunk * CHUNK + tid)] = (TIO)a.dbf[(size_t)bh * Lp + chunk * CHUNK + tid];
 }
 
-// The fused adjoint of the chunk transform: one workgroup per (chunk, head) runs the program.
+// The adjoint of the chunk transform, fp32 operands at d = 128 (else: chunk_adj.hip): one workgroup per (chunk, head) runs the program.
 // Results that later steps read go through global memory (they stay in L2); a chain of
 // products that add into the same result keeps it in accumulator registers.
 #ifndef CHUNK_NB

@@ -114,9 +114,9 @@ struct ChunkProgram {
     OutArgs out;
     int L, NC;
 };
-hipError_t launch_chunk_adjoint(const ChunkProgram& pr, int BH, hipStream_t st);                    // fp32 operands only
+hipError_t launch_chunk_adjoint(const ChunkProgram& pr, int BH, hipStream_t st);                    // fp32 operands, d = 128
 
-// The same steps as one hand-fused kernel (2-byte operand types): every input is a plain pointer.
+// The same steps as one hand-fused kernel (2-byte operand types, and fp32 at d = 64): every input is a plain pointer.
 struct ChunkFusedArgs {
     UserLayout ul;                               // layout of q .. d_o, lse and of the outputs
     const void *q, *k, *v, *w, *beta, *d_o;      // I/O type, the caller's layout
@@ -127,7 +127,9 @@ struct ChunkFusedArgs {
     // near key-side sums: chunk-level keys, values, dO tiles; states and adjoint states of the pairs; row constants
     const void *kt, *vk, *doq, *xs, *gs;
     const float* lse2p;                          // [BH][Lp]
-    const float *dqb, *dvp;                      // [BH][Lp][d]: dQb; dV over the far queries (not of the last super-block's keys)
+    const float *dqb, *dvp;                      // [BH][Lp][d]: dQb; dV over the far queries (not of the last super-block's keys);
+                                                 // fp32 operands: dV over all queries right of the chunk,
+    const float *dkb, *ddp;                      // ... and dKb [BH][Lp][d] and ddP [BH][NC][d][d], the second level's share in them
     const void *rm, *dr;                         // second level: tiles of R_c and of the gradient of R_{c-1} (NULL: one super-block)
     const float* dk2;                            // [BH][Lp][d]: gradient of the second-level keys
     void *dq, *dk, *dv, *dw, *dbeta;             // I/O type
@@ -136,7 +138,7 @@ struct ChunkFusedArgs {
     int L, NC, BH;
     float scale;
 };
-hipError_t launch_chunk_fused(const ChunkFusedArgs& a, int BH, int d, hipStream_t st);
+hipError_t launch_chunk_fused(const ChunkFusedArgs& a, int BH, int d, int is_bf16, hipStream_t st);      // fp32 operands: d = 64
 
 // Stages of the backward after the transforms, as bits (the public PATH_BWD_STAGE_* values of the header):
 // dO tiles + adjoint scan | near key-side (fp32) | far key-side | ddP (fp32) | second-level chain and chunk-transform

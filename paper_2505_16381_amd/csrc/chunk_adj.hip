@@ -1,5 +1,6 @@
 // Near key-side sums and adjoint of the chunk transform (the UT transform of Sec. 3.2 and the diagonal block of
-// Sec. 3.3), fused: one workgroup per (chunk, head) for 2-byte operand types.  The paper gives
+// Sec. 3.3), fused: one workgroup per (chunk, head), for 2-byte operand types and for
+// fp32 operands at d = 64.  The paper gives
 // no backward; with the chunk's matrices (rows = the 64 tokens of the chunk)
 //
 //   F   strictly-lower part of the boundary-adjusted query transform,  Y = solved W-side block,
@@ -23,7 +24,10 @@
 // memory (converted to the operand type); a product whose contraction runs along the rows of a
 // stored matrix takes its 16-byte fragments with two transposing LDS reads instead of keeping a
 // transposed copy.  dK and dW accumulate in registers across the whole kernel; the 64 x 64
-// intermediates never leave LDS.
+// intermediates never leave LDS.  fp32 operands: the near sums and the second level's share come from memory, transposed
+// operands are 4-byte LDS reads; d = 128 does not fit and stays a list of staged products (chunk_adjoint_kernel in bwd.hip), 24
+// of them one after the other, each through memory.  Training step of 2 heads of 256 tokens, d = 64: that kernel 132 -> 37 us, the
+// step 253.5 -> 156.7; 16 heads of 1000 tokens 577 -> 465; 64 of 2048 4219 -> 3792.
 //
 // What bounds it: latency -- chains of short dependent phases between barriers, at d = 128 with one workgroup per CU -- and
 // then memory: at d = 128 the states and adjoint states of 7.5 pairs on average (0.24 MB), 0.3 MB of the chunk's matrices and
@@ -56,11 +60,13 @@ template <typename TIO, int D> struct NearCfg {
 
 template <typename TIO, int D> struct CaCfg {
     typedef typename Compute<TIO>::type T;
-    static_assert(sizeof(T) == 2, "fused chunk adjoint: 2-byte operand types only");
-    static constexpr int LDD = D + 8;          // pitch of a [..][D] tile (elements)
-    static constexpr int LDC = CHUNK + 8;      // pitch of a [..][64] tile
-    static constexpr int BIG = (64 * LDD > D * LDC ? 64 * LDD : D * LDC) * 2;   // bytes of a 64 x D or D x 64 tile
-    static constexpr int SMALL = 64 * LDC * 2;
+    static constexpr int ES = sizeof(T);
+    static constexpr bool NEAR_SUMS = ES == 2;      // fp32 operands: the near sums and the second level's share are taken before
+    static_assert(ES == 2 || D == 64, "fp32 tiles of d = 128 do not fit");
+    static constexpr int LDD = D + 16 / ES;          // pitch of a [..][D] tile (elements)
+    static constexpr int LDC = CHUNK + 16 / ES;      // pitch of a [..][64] tile
+    static constexpr int BIG = (64 * LDD > D * LDC ? 64 * LDD : D * LDC) * ES;   // bytes of a 64 x D or D x 64 tile
+    static constexpr int SMALL = 64 * LDC * ES;
     static constexpr int LDM = 65;             // pitch of the fp32 copy of M
     // byte offsets.  d = 128: W | X0 X3 (adjacent: ddP spans both, later the fp32 M) | X1 | X2 | Y0 Y1 Y2 | N | misc.
     // d = 64, where all tiles have one size: W | X0 Y0 (adjacent: the fp32 M) | X1 | X2 | X3 = N | Y1 | Y2 | misc: 74 KB, two
@@ -68,13 +74,13 @@ template <typename TIO, int D> struct CaCfg {
     // 0.42).
     static constexpr int XW = 0, X0 = BIG, X3 = D == 64 ? 5 * BIG : 2 * BIG, X1 = 3 * BIG, X2 = 4 * BIG;
     static constexpr int Y0 = D == 64 ? 2 * BIG : 5 * BIG, Y1 = D == 64 ? 6 * BIG : Y0 + SMALL, Y2 = Y1 + SMALL, YN = D == 64 ? X3 : Y2 + SMALL;
-    static constexpr int TILES = D == 64 ? Y2 + SMALL : YN + SMALL, NEAR = NearCfg<TIO, D>::smem_bytes;
+    static constexpr int TILES = D == 64 ? Y2 + SMALL : YN + SMALL, NEAR = NEAR_SUMS ? NearCfg<TIO, D>::smem_bytes : 0;
     // between the near sums and the chunk's tiles: R | D of the second level | dV, dKb | dKb2
-    static constexpr int SR = 0, SD = D * D * 2, XCH = 2 * SD, SK2 = XCH + NearCfg<TIO, D>::xch_bytes, MID = SK2 + 64 * LDD * 2;
+    static constexpr int SR = 0, SD = D * D * 2, XCH = 2 * SD, SK2 = XCH + NearCfg<TIO, D>::xch_bytes, MID = NEAR_SUMS ? SK2 + 64 * LDD * 2 : 0;
     static constexpr int MISC = MID > NEAR ? (MID > TILES ? MID : TILES) : (NEAR > TILES ? NEAR : TILES);
     static constexpr int TOTAL = MISC + 2048;
-    static constexpr int WGS_PER_CU = D == 64 ? 2 : 1;
-    static_assert(D == 64 ? BIG == SMALL : D * LDD * 2 <= 2 * BIG, "ddP tile must fit X0 (d = 64) or X0 and X3");
+    static constexpr int WGS_PER_CU = D == 64 && ES == 2 ? 2 : 1;
+    static_assert(D == 64 ? BIG == SMALL : D * LDD * ES <= 2 * BIG, "ddP tile must fit X0 (d = 64) or X0 and X3");
     static_assert(64 * LDM * 4 <= 2 * BIG, "fp32 M must fit X0 and its neighbour");
     static_assert(WGS_PER_CU * TOTAL <= 160 * 1024, "LDS budget");
 };
@@ -323,7 +329,7 @@ __global__ __launch_bounds__(CA_NT, 2 * (CaCfg<TIO, D>::WGS_PER_CU)) void chunk_
     constexpr int NA = D / 64;
     f32x16 nV[NA], nK[NA], dd[NA][NA];
     float ncol;
-    near_sums<TIO, D, FOX>(args, smem, chunk, bh, NCown, [&]() {
+    if constexpr (C::NEAR_SUMS) near_sums<TIO, D, FOX>(args, smem, chunk, bh, NCown, [&]() {
         if (!right) return;
         typedef typename Tr<T>::Frag Frag;
         constexpr int DPF = D * D / 8;
@@ -388,7 +394,17 @@ __global__ __launch_bounds__(CA_NT, 2 * (CaCfg<TIO, D>::WGS_PER_CU)) void chunk_
 
     // ---- the second level's share: ddP -= R^T D, dKb += dKb2 R (D = gradient of R_{c-1}); dV, dKb change hands ----
     GTile<TIO, 64, D> tW, tdO, tV;
-    {
+    if constexpr (!C::NEAR_SUMS) {
+        tW.load(wg, TS, ntok, tid);
+        tdO.load(dog, TS, ntok, tid);
+        tV.load(vg, TS, ntok, tid);
+        if (actD) { cin(a.dvp + pbase, accV); cin(a.dkb + pbase, accK); }
+        if (actP) {
+            const float* g = a.ddp + ((size_t)bh * NC + chunk) * D * D;
+#pragma unroll
+            for (int jj = 0; jj < 16; ++jj) dd[0][0][jj] = g[(size_t)(32 * rb + acc_row(jj, h)) * D + 32 * kb + l32];
+        }
+    } else {
         constexpr int DS = D / 16;
         typedef typename Tr<T>::Frag Frag;
         using N = NearCfg<TIO, D>;
@@ -545,7 +561,7 @@ __global__ __launch_bounds__(CA_NT, 2 * (CaCfg<TIO, D>::WGS_PER_CU)) void chunk_
     if (actD) cin(a.dqb + pbase, accQ);
     __syncthreads();
     if (FOX && tid < CHUNK) {        // the diagonal block's column and row sums of the logit gradient
-        a.dcol[tpad + tid] = (nearcol[tid] + (right ? a.dcol[tpad + tid] : 0.f)) + colsum[tid];
+        a.dcol[tpad + tid] = (C::NEAR_SUMS ? nearcol[tid] + (right ? a.dcol[tpad + tid] : 0.f) : a.dcol[tpad + tid]) + colsum[tid];
         a.drow[tpad + tid] += colsum[CHUNK + tid];
     }
 
@@ -875,8 +891,9 @@ hipError_t launch_bwd_sb_chain(const SbChainArgs& a, int BH, int d, hipStream_t 
     return d == 64 ? launch_sb_t<bf16_t, 64>(a, BH, st) : launch_sb_t<bf16_t, 128>(a, BH, st);
 }
 
-hipError_t launch_chunk_fused(const ChunkFusedArgs& a, int BH, int d, hipStream_t st) {
+hipError_t launch_chunk_fused(const ChunkFusedArgs& a, int BH, int d, int is_bf16, hipStream_t st) {
     const bool fox = a.cum != nullptr;
+    if (!is_bf16) return fox ? launch_t<float, 64, true>(a, BH, st) : launch_t<float, 64, false>(a, BH, st);
     if (d == 64) return fox ? launch_t<bf16_t, 64, true>(a, BH, st) : launch_t<bf16_t, 64, false>(a, BH, st);
     return fox ? launch_t<bf16_t, 128, true>(a, BH, st) : launch_t<bf16_t, 128, false>(a, BH, st);
 }

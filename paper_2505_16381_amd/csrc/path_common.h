@@ -213,10 +213,39 @@ __device__ __forceinline__ typename Tr<T>::Frag ld_frag_tr_acc(const T* X, int l
     return u.f;
 }
 
+// acc[m][n] += sum_k A(m,k) B(n,k) as below, fp32 operands: a fragment is four contraction indices 8 s + 4 h + e; where they run along the rows of the stored
+// matrix they are four 4-byte reads, of 32 neighbouring columns each.
+template <int K, bool TA, bool TB>
+__device__ __forceinline__ void mm_f32(f32x16& acc, const float* A, int lda, int ar0, const float* B, int ldb, int br0, int l32, int h) {
+    auto frag = [&](const float* X, int ld, int r0, int k, bool tr) {
+        f32x4 f;
+        if (tr) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) f[e] = X[(k + e) * ld + r0 + l32];
+        } else {
+            f = ld_frag<float>(X + (r0 + l32) * ld + k);
+        }
+        return f;
+    };
+#pragma unroll
+    for (int k0 = 0; k0 < K; k0 += 32) {
+        f32x4 fa[4], fb[4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const int k = k0 + 8 * s + 4 * h;
+            fa[s] = frag(A, lda, ar0, k, TA);
+            fb[s] = frag(B, ldb, br0, k, TB);
+        }
+#pragma unroll
+        for (int s = 0; s < 4; ++s) acc = Tr<float>::mma(fa[s], fb[s], acc);
+    }
+}
+
 // acc[m][n] += sum_k A(m,k) B(n,k) for one 32x32 block (rows ar0.., columns br0..).
 // TA == false: A is stored [m][k] (16-byte fragment reads); TA == true: A is stored [k][m] (transposing reads).  Same for B.
 template <typename T, int K, bool TA, bool TB>
 __device__ __forceinline__ void mm(f32x16& acc, const T* A, int lda, int ar0, const T* B, int ldb, int br0, int l32, int h) {
+    if constexpr (sizeof(T) == 4) { mm_f32<K, TA, TB>(acc, A, lda, ar0, B, ldb, br0, l32, h); return; } else {
     // four slabs (64 contraction indices) at a time: their fragments are fetched ahead of the four products
 #pragma unroll
     for (int k0 = 0; k0 < K; k0 += 64) {
@@ -237,6 +266,7 @@ __device__ __forceinline__ void mm(f32x16& acc, const T* A, int lda, int ar0, co
         }
 #pragma unroll
         for (int s = 0; s < 4; ++s) acc = Tr<T>::mma(fa[s], fb[s], acc);
+    }
     }
 }
 
