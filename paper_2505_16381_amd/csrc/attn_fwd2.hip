@@ -456,36 +456,52 @@ hipError_t launch_attn_fwd2_t(const FwdParams& p, hipStream_t stream) {
 }
 
 // Sequence-parallel forward, last step: o = O / l and lse = m + log l from the stored registers (the sweep's own
-// epilogue, on what the last hop left).  One wave per (head, chunk, 32-query half).
+// epilogue, on what the last hop left).  One wave per (head, chunk, 32-query half).  Bound by memory (O in fp32, o out):
+// the rows go through LDS, so that they are stored whole -- as the registers have them, sixteen stores of 32 pieces of 16 bytes
+// each, 32 heads of 4096 tokens, d = 128, took 34 us, so 18.
 template <typename TIO, int D>
-__global__ __launch_bounds__(64) void ring_finish_kernel(FwdParams p) {
+__global__ __launch_bounds__(256) void ring_finish_kernel(FwdParams p) {
     using Vec4 = typename Tr<TIO>::Vec4;
-    constexpr int DB = D / 32;
-    const int lane = threadIdx.x, h = lane >> 5, l32 = lane & 31;
-    const int cq = blockIdx.x >> 1, qb = blockIdx.x & 1, bh = blockIdx.y;
+    typedef TIO RowVec __attribute__((ext_vector_type(16 / sizeof(TIO))));
+    constexpr int DB = D / 32, NW = sizeof(TIO) == 2 ? 4 : 2, VE = 16 / (int)sizeof(TIO), VPR = D / VE, LD = D + VE;
+    __shared__ __attribute__((aligned(16))) TIO rows[NW][32 * LD];
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), h = lane >> 5, l32 = lane & 31;
+    const int half = blockIdx.x * NW + wv, cq = half >> 1, qb = half & 1, bh = blockIdx.y;
+    if (cq >= p.NC) return;
     const float* rec = p.ring_state + (((size_t)bh * p.NC + cq) * 2 + qb) * ring_rec_floats(D);
+    f32x4 O[DB][4];
+#pragma unroll
+    for (int b = 0; b < DB; ++b)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) O[b][g] = *reinterpret_cast<const f32x4*>(rec + (size_t)(DB + b) * 1024 + g * 256 + lane * 4);
     const float m_run = rec[2 * DB * 1024 + lane], l_run = rec[2 * DB * 1024 + 64 + lane];
     const float l_tot = l_run + __shfl_xor(l_run, 32);
     const float inv = 1.f / l_tot;
-    const int tq = cq * CHUNK + 32 * qb + l32;
-    if (tq >= p.L) return;
-    TIO* orow = reinterpret_cast<TIO*>(p.o) + user_vec(p.ul, bh, tq) + 4 * h;
+    const int t0 = cq * CHUNK + 32 * qb, tq = t0 + l32;
+    TIO* mine = rows[wv];
 #pragma unroll
     for (int b = 0; b < DB; ++b)
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-            const f32x4 o4 = *reinterpret_cast<const f32x4*>(rec + (size_t)(DB + b) * 1024 + g * 256 + lane * 4);
             Vec4 v4;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) v4[r] = (TIO)(o4[r] * inv);
-            *reinterpret_cast<Vec4*>(orow + 32 * b + 8 * g) = v4;
+            for (int r = 0; r < 4; ++r) v4[r] = (TIO)(O[b][g][r] * inv);
+            *reinterpret_cast<Vec4*>(mine + l32 * LD + 32 * b + 8 * g + 4 * h) = v4;
         }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // (the wave's own rows)
+#pragma unroll
+    for (int i = 0; i < 32 * VPR / 64; ++i) {
+        const int r = (i * 64 + lane) / VPR, c = (lane % VPR) * VE;
+        if (t0 + r < p.L) *reinterpret_cast<RowVec*>(reinterpret_cast<TIO*>(p.o) + user_vec(p.ul, bh, t0 + r) + c) = *reinterpret_cast<const RowVec*>(mine + r * LD + c);
+    }
+    if (tq >= p.L) return;
     const float ci = p.cum ? p.cum[(size_t)bh * p.NC * CHUNK + tq] : 0.f;      // PaTH-FoX: the query's own gate sum, inside its segment
     if (h == 0) p.lse[user_scl(p.ul, bh, tq)] = (m_run + __builtin_amdgcn_logf(l_tot) + ci) * 0.69314718055994530942f;
 }
 template <typename TIO, int D>
 static hipError_t launch_ring_finish_t(const FwdParams& p, hipStream_t stream) {
-    hipLaunchKernelGGL((ring_finish_kernel<TIO, D>), dim3(2 * p.NC, p.B * p.H), dim3(64), 0, stream, p);
+    constexpr int NW = sizeof(TIO) == 2 ? 4 : 2;
+    hipLaunchKernelGGL((ring_finish_kernel<TIO, D>), dim3((2 * p.NC + NW - 1) / NW, p.B * p.H), dim3(64 * NW), 0, stream, p);
     return hipGetLastError();
 }
 hipError_t launch_ring_finish(const FwdParams& p, int d, int is_bf16, hipStream_t stream) {
