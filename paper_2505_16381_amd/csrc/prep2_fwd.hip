@@ -21,7 +21,8 @@
 //
 // What bounds it: memory where there are many super-blocks (64 KB per chunk at d = 128, 96 with the backward's
 // outputs), the chain of 16 chunks where there are few.  Hence two shapes: more than one workgroup per CU, one stage of
-// tiles each, and a single workgroup per CU with the next chunk's tiles on their way during the current one's products.
+// tiles each, and a single workgroup per CU with the next two chunks' tiles on their way during the current one's products,
+// brought by waves of their own (a copy takes the wave that makes it 70 cycles).
 // At d = 128: 64 heads of 7 super-blocks with the backward's outputs 160 us (4.3 TB/s), 512 heads of 2 without them
 // 154 us, one super-block per head into the cache 38 us.  (Waves that each took all of E's blocks from LDS, two
 // fragments per product: 171, 226 and, with the rows turned and copied afterwards, 84 us.)  With the backward's outputs and
@@ -42,11 +43,13 @@ template <typename TIO, int D, int NBUF> struct Prep2Cfg {
     static constexpr int NT = 64 * (D / 32) * SPLIT;
     static constexpr int XCH_FRAGS = SPLIT == 1 ? 0 : DP_FRAGS;          // E as operand fragments
     static constexpr size_t smem_bytes = ((size_t)NBUF * (KV_FRAGS + DP_FRAGS) + XCH_FRAGS) * 16;      // stages of (key tile | -dP tile)
-    static constexpr int WAVES_PER_SIMD = sizeof(T) == 2 && NBUF == 1 ? (D == 64 ? 3 : 2) : 1;
+    static constexpr bool COPIERS = NBUF == 3;                           // as many waves again make the copies, two stages ahead
+    static constexpr int THREADS = COPIERS ? 2 * NT : NT;
+    static constexpr int WAVES_PER_SIMD = COPIERS ? 2 : sizeof(T) == 2 && NBUF == 1 ? (D == 64 ? 3 : 2) : 1;
 };
 
 template <typename TIO, int D, int MODE, int NBUF>
-__global__ __launch_bounds__((Prep2Cfg<TIO, D, NBUF>::NT), (Prep2Cfg<TIO, D, NBUF>::WAVES_PER_SIMD)) void prep2_fwd_kernel(FwdParams p) {
+__global__ __launch_bounds__((Prep2Cfg<TIO, D, NBUF>::THREADS), (Prep2Cfg<TIO, D, NBUF>::WAVES_PER_SIMD)) void prep2_fwd_kernel(FwdParams p) {
     using C = Prep2Cfg<TIO, D, NBUF>;
     using T = typename C::T;
     using Frag = typename Tr<T>::Frag;
@@ -82,21 +85,38 @@ __global__ __launch_bounds__((Prep2Cfg<TIO, D, NBUF>::NT), (Prep2Cfg<TIO, D, NBU
 #pragma unroll
     for (int o = 0; o < NB; ++o) Fm[o] = zero16();
 
-    auto issue = [&](int c) {
+    auto place = [&](int c) { return stage + (size_t)(NBUF == 3 ? (clast - c) % 3 : c & (NBUF - 1)) * (KVF + DPF); };
+    auto issue = [&](int c, int ctid, int cwv) {
         const size_t bhc = (size_t)bh * NC + c;
-        Frag* buf = stage + (size_t)(c & (NBUF - 1)) * (KVF + DPF);
-        async_copy_tile<NT, KVF>(reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(p.kt) + bhc * (size_t)CHUNK * D), buf, tid, wv);
-        async_copy_tile<NT, DPF>(reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(p.dp) + bhc * (size_t)D * D), buf + KVF, tid, wv);
+        Frag* buf = place(c);
+        async_copy_tile<NT, KVF>(reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(p.kt) + bhc * (size_t)CHUNK * D), buf, ctid, cwv);
+        async_copy_tile<NT, DPF>(reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(p.dp) + bhc * (size_t)D * D), buf + KVF, ctid, cwv);
     };
-    if (NBUF == 2) issue(clast);
+    if constexpr (C::COPIERS) {
+        if (wv >= NT / 64) {
+            const int ctid = tid - NT, cwv = wv - NT / 64;
+            issue(clast, ctid, cwv);
+            if (clast > c0) issue(clast - 1, ctid, cwv);
+            for (int c = clast; c >= c0; --c) {
+                if (c > c0) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((KVF + DPF) / NT) : "memory");      // chunk c has landed, the next one may be on its way
+                else copies_landed();
+                lds_barrier();                 // ... for everybody, and chunk c + 1 has been read
+                if (c - 2 >= c0) issue(c - 2, ctid, cwv);
+            }
+            return;
+        }
+    }
+    if (NBUF == 2) issue(clast, tid, wv);
     for (int c = clast; c >= c0; --c) {
         const size_t bhc = (size_t)bh * NC + c;
-        if (NBUF == 2) {
+        if (C::COPIERS) {
+            lds_barrier();
+        } else if (NBUF == 2) {
             wait_async_and_sync();             // chunk c has landed; everyone is done with chunk c+1
-            if (c > c0) issue(c - 1);
+            if (c > c0) issue(c - 1, tid, wv);
         } else {
             __syncthreads();
-            issue(c);
+            issue(c, tid, wv);
             if (SPLIT > 1) {
 #pragma unroll
                 for (int o = 0; o < NB; ++o) {
@@ -108,7 +128,7 @@ __global__ __launch_bounds__((Prep2Cfg<TIO, D, NBUF>::NT), (Prep2Cfg<TIO, D, NBU
             }
             wait_async_and_sync();
         }
-        const Frag* k1 = stage + (size_t)(c & (NBUF - 1)) * (KVF + DPF);
+        const Frag* k1 = place(c);
         const Frag* dpn = k1 + KVF;                                                                                  // (rows b, contr a) = -dP[a][b]
         if constexpr (SPLIT == 1) {
 #pragma unroll
@@ -256,7 +276,7 @@ hipError_t launch_prep2_b(const FwdParams& p, dim3 grid, hipStream_t stream) {
     static const hipError_t attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&prep2_fwd_kernel<TIO, D, MODE, NBUF>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::smem_bytes);
     if (attr_err != hipSuccess) return attr_err;
-    hipLaunchKernelGGL((prep2_fwd_kernel<TIO, D, MODE, NBUF>), grid, dim3(C::NT), C::smem_bytes, stream, p);
+    hipLaunchKernelGGL((prep2_fwd_kernel<TIO, D, MODE, NBUF>), grid, dim3(C::THREADS), C::smem_bytes, stream, p);
     return hipGetLastError();
 }
 template <typename TIO, int D, int MODE>
@@ -271,8 +291,10 @@ hipError_t launch_prep2_m(const FwdParams& p, hipStream_t stream) {
         // (fp32 operands: two stages of tiles do not fit)
         if constexpr (sizeof(TIO) == 2) {
             // one workgroup for every CU or less; above that the second workgroup hides more than the second stage does
-            // (one stage against two, us: d = 128, 128 workgroups 59 / 52, 192 59 / 50, 512 106 / 127; d = 64, 256 30 / 24, 384 47 / 50)
-            if ((long long)nsb * BH <= 256) return launch_prep2_b<TIO, D, MODE, 2>(p, grid, stream);
+            // (one stage against two, us: d = 128, 128 workgroups 59 / 52, 192 59 / 50, 512 106 / 127; d = 64, 256 30 / 24, 384 47 / 50).
+            // With copying waves and three stages another 4 to 9 us less (128 workgroups, d = 128: both transforms 144 -> 135, 32
+            // workgroups 66.9 -> 59.7; d = 64, 6 workgroups 32.2 -> 28.3)
+            if ((long long)nsb * BH <= 256) return launch_prep2_b<TIO, D, MODE, 3>(p, grid, stream);
         }
         return launch_prep2_b<TIO, D, MODE, 1>(p, grid, stream);
     }
