@@ -310,16 +310,26 @@ __global__ __launch_bounds__(256) void bwd_adjoint2_kernel(BwdParams p) {
 // ---------------------------------------------------------------------------------------
 // The adjoint scan for 16-bit operands, d = 64 and short sequences (d = 128, more than eight chunks: bwd_adjoint.hip, to
 // the same bits), with TWO workgroups per CU: the same arithmetic as
-// bwd_adjoint2_kernel, arranged to fit 256 registers per wave and one 80 KB stage per workgroup, so that
+// bwd_adjoint2_kernel, arranged to fit 256 registers per wave and half a CU's LDS per workgroup, so that
 // the second workgroup's waves fill the gaps of the first (tile requests, LDS latencies, the dependent
-// chain logits -> exponentials -> update) instead of hand-interleaved halves of one wave.  Per step: one
-// request for the chunk's four tiles, no prefetch; the state fragments of a new block are fetched while
-// those tiles are on their way; the operand copy of g exists only while a block boundary needs it.
+// chain logits -> exponentials -> update) instead of hand-interleaved halves of one wave.  The operand copy of g
+// exists only while a block boundary needs it.
 // The fragments of Kb^T for g^T += Kb^T dS^T are read out of the key tile itself with transposing LDS reads
 // (three tiles per step instead of four: the transposed key tiles are neither written nor copied; as a fourth
 // tile they cost 4 % of this kernel), and likewise the fragments of -dP in the arrangement (rows a, contraction b)
-// out of the forward's tile (rows b, contraction a): p.dpt / p.dpt2 point at the FORWARD's tiles here.  No copy is in
-// flight while a step computes, so those reads wait for nothing.
+// out of the forward's tile (rows b, contraction a): p.dpt / p.dpt2 point at the FORWARD's tiles here.
+// d = 128: one stage; per step one request for the chunk's tiles, the state fragments of a new block fetched while those
+// are on their way.  No copy is in flight while a step computes, so the transposing reads wait for nothing.
+// d = 64 (AHEAD): a step has half the products to wait for as many requests, and two stages still
+// leave room for three workgroups, as many as the registers allow.  The next chunk's tiles are requested at a step's
+// start, the next block's state after the last product with the current one, and the transposing reads are written so
+// that they do not wait for those.  Training step, one stage -> two: B=1, H=4, L=16384 1240 -> 1179 us; one head, L=8192
+// 540 -> 498; H=64, L=1000 gated 274 -> 262; B=8, H=16, L=4096 2701 -> 2680, gated 2929 -> 2864.
+template <typename TIO, int D> struct LiteCfg {
+    static constexpr bool AHEAD = D == 64;
+    static constexpr int STF = 2 * Adj2Cfg<TIO, D>::KV_FRAGS + Adj2Cfg<TIO, D>::DP_FRAGS + 16;
+    static constexpr size_t smem_bytes = (size_t)(AHEAD ? 2 : 1) * STF * 16;
+};
 template <typename TIO, int D, bool FOX>
 __global__ __launch_bounds__(256, 2) void bwd_adjoint2_lite_kernel(BwdParams p) {
     using C = Adj2Cfg<TIO, D>;
@@ -329,10 +339,10 @@ __global__ __launch_bounds__(256, 2) void bwd_adjoint2_lite_kernel(BwdParams p) 
     static_assert(sizeof(T) == 2, "16-bit operands");
     constexpr int KW = Tr<T>::KW, SPB = 32 / KW, DB = D / 32, DS = D / KW, QS = CHUNK / KW;
     constexpr int KVF = C::KV_FRAGS, DPF = C::DP_FRAGS;
+    constexpr bool AHEAD = LiteCfg<TIO, D>::AHEAD;
+    constexpr int STF = LiteCfg<TIO, D>::STF;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    Frag* sK = reinterpret_cast<Frag*>(smem);
-    const FragV* sV = reinterpret_cast<const FragV*>(sK + KVF);
-    const Frag* sDP = sK + 2 * KVF;
+    Frag* const stages = reinterpret_cast<Frag*>(smem);                    // keys | values | -dP | gate sums
 
     const int BH = p.B * p.H, NC = p.NC;
     const int ntiles = (NC + 1) / 2;
@@ -369,28 +379,51 @@ __global__ __launch_bounds__(256, 2) void bwd_adjoint2_lite_kernel(BwdParams p) 
     for (int s = 0; s < DS; ++s) Xb[s] = Tr<T>::zero();
     auto block_start = [&](int j) { return j >= jsb || j % SBC == 0; };
 
-    for (int j = 0; j <= jmax; ++j) {
+    auto issue = [&](int j) {
+        const size_t bhc = (size_t)bh * NC + j;
         const bool far = j < jsb;
+        Frag* sK = stages + (AHEAD ? j & 1 : 0) * STF;
+        async_copy_tile<256, KVF>(reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(far ? p.kt2 : p.kt) + bhc * CHUNK * D), sK, tid, wv);
+        async_copy_tile<256, KVF>(reinterpret_cast<const Frag*>(reinterpret_cast<const TIO*>(p.vk) + bhc * CHUNK * D), sK + KVF, tid, wv);
+        if (j > 0 && block_start(j)) {
+            const T* src = far ? reinterpret_cast<const T*>(p.dpt2) + ((size_t)bh * nsb + j / SBC) * (size_t)D * D
+                               : reinterpret_cast<const T*>(p.dpt) + bhc * (size_t)D * D;
+            async_copy_tile<256, DPF>(reinterpret_cast<const Frag*>(src), sK + 2 * KVF, tid, wv);
+        }
+        if (FOX && tid < 16)      // 64 floats, 16 bytes per lane
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(p.cum + (size_t)bh * Lp + (size_t)j * CHUNK + 4 * tid),
+                                             (__attribute__((address_space(3))) void*)(sK + 2 * KVF + DPF), 16, 0, 0);
+    };
+    auto read_state = [&](int j) {                 // the state of the block that starts at chunk j
+        const size_t xslot = ((size_t)bh * nslots + block_slot(cq, j, NC)) * (size_t)CHUNK * D;
+        const Frag* xg = reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(p.xs) + xslot);
+#pragma unroll
+        for (int s = 0; s < DS; ++s) Xb[s] = __builtin_nontemporal_load(&xg[((size_t)qb * DS + s) * 64 + tile_lane<TIO>(lane, s)]);
+    };
+    if (AHEAD) {
+        if (jmax >= 0) issue(0);
+        if (active && cq > 0) read_state(0);
+    }
+
+    for (int j = 0; j <= jmax; ++j) {
         const bool mine = active && j < cq;
         const bool first = block_start(j);
-        __syncthreads();                           // everyone is done with the previous chunk's tiles
-        {
-            const size_t bhc = (size_t)bh * NC + j;
-            async_copy_tile<256, KVF>(reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(far ? p.kt2 : p.kt) + bhc * CHUNK * D), sK, tid, wv);
-            async_copy_tile<256, KVF>(reinterpret_cast<const Frag*>(reinterpret_cast<const TIO*>(p.vk) + bhc * CHUNK * D), sK + KVF, tid, wv);
-            if (j > 0 && first) {
-                const T* src = far ? reinterpret_cast<const T*>(p.dpt2) + ((size_t)bh * nsb + j / SBC) * (size_t)D * D
-                                   : reinterpret_cast<const T*>(p.dpt) + bhc * (size_t)D * D;
-                async_copy_tile<256, DPF>(reinterpret_cast<const Frag*>(src), sK + 2 * KVF, tid, wv);
-            }
-        }
-        if (mine && first) {                       // the state of the block that starts here
-            const size_t xslot = ((size_t)bh * nslots + block_slot(cq, j, NC)) * (size_t)CHUNK * D;
-            const Frag* xg = reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(p.xs) + xslot);
+        if (AHEAD) {
 #pragma unroll
-            for (int s = 0; s < DS; ++s) Xb[s] = __builtin_nontemporal_load(&xg[((size_t)qb * DS + s) * 64 + tile_lane<TIO>(lane, s)]);
+            for (int s = 0; s < DS; ++s) asm volatile("" : "+v"(Xb[s]));   // (waited for here, not behind the next copies)
+            copies_landed();
+            lds_barrier();                         // chunk j has landed; chunk j - 1 has been read
+            if (j < jmax) issue(j + 1);
+        } else {
+            __syncthreads();                       // everyone is done with the previous chunk's tiles
+            issue(j);
+            if (mine && first) read_state(j);
+            wait_async_and_sync();
         }
-        wait_async_and_sync();
+        const Frag* sK = stages + (AHEAD ? j & 1 : 0) * STF;
+        const FragV* sV = reinterpret_cast<const FragV*>(sK + KVF);
+        const Frag* sDP = sK + 2 * KVF;
+        const TileTr kt = tile_tr<T>(reinterpret_cast<const T*>(sK), l32, h), pt = tile_tr<T>(reinterpret_cast<const T*>(sDP), l32, h);   // (AHEAD)
         if (!mine) continue;
 
         if (j > 0 && first) {                      // g <- g (I - dP_blk)^T: the product with the state before this step
@@ -402,8 +435,13 @@ __global__ __launch_bounds__(256, 2) void bwd_adjoint2_lite_kernel(BwdParams p) 
 #pragma unroll
                 for (int s0 = 0; s0 < DS; s0 += 4) {
                     Frag pa[4];
+                    if constexpr (AHEAD) {
+                        const unsigned o = (unsigned)((s0 >> 1) * DS + 2 * b) * 1024;      // (bytes of two slabs' rows, of a block of columns)
+                        ld_tile_frags_tr<T, DS, 0, 0, 1, 0, 2, 0, 3, 0>({pt.even + o, pt.odd + o}, pa);
+                    } else {
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) pa[u] = ld_tile_frag_tr<T, DS>(reinterpret_cast<const T*>(sDP), s0 + u, b, l32, h);
+                        for (int u = 0; u < 4; ++u) pa[u] = ld_tile_frag_tr<T, DS>(reinterpret_cast<const T*>(sDP), s0 + u, b, l32, h);
+                    }
 #pragma unroll
                     for (int u = 0; u < 4; ++u) Gm[b] = Tr<T>::mma(pa[u], Gb[s0 + u], Gm[b]);
                 }
@@ -425,7 +463,7 @@ __global__ __launch_bounds__(256, 2) void bwd_adjoint2_lite_kernel(BwdParams p) 
             }
             f32x4 ck4[4];
             if (FOX) {      // gate sums of the 16 keys this lane holds (rows 8g + 4h + r of the 32-key block)
-                const float* ck = p.cum + (size_t)bh * Lp + (size_t)j * CHUNK + 32 * kb + 4 * h;
+                const float* ck = reinterpret_cast<const float*>(sDP + DPF) + 32 * kb + 4 * h;
 #pragma unroll
                 for (int g = 0; g < 4; ++g) ck4[g] = *reinterpret_cast<const f32x4*>(ck + 8 * g);
             }
@@ -440,13 +478,22 @@ __global__ __launch_bounds__(256, 2) void bwd_adjoint2_lite_kernel(BwdParams p) 
             pack_block<T>(S, dSh);
             // g^T += Kb^T dS^T, the 32 keys of this half
 #pragma unroll
-            for (int b = 0; b < DB; ++b) {
-                Frag ta[SPB];
+            for (int b = 0; b < DB; b += 2) {
+                Frag ta[4];
+                if constexpr (AHEAD) {
+                    const unsigned o = (unsigned)(kb * DS + 2 * b) * 1024;
+                    ld_tile_frags_tr<T, DS, 0, 0, 1, 0, 0, 1, 1, 1>({kt.even + o, kt.odd + o}, ta);
+                } else {
 #pragma unroll
-                for (int u = 0; u < SPB; ++u) ta[u] = ld_tile_frag_tr<T, DS>(reinterpret_cast<const T*>(sK), kb * SPB + u, b, l32, h);
+                    for (int u = 0; u < 4; ++u) ta[u] = ld_tile_frag_tr<T, DS>(reinterpret_cast<const T*>(sK), kb * SPB + (u & 1), b + (u >> 1), l32, h);
+                }
 #pragma unroll
-                for (int u = 0; u < SPB; ++u) Gm[b] = Tr<T>::mma(ta[u], dSh[u], Gm[b]);
+                for (int u = 0; u < SPB; ++u) {
+                    Gm[b] = Tr<T>::mma(ta[u], dSh[u], Gm[b]);
+                    Gm[b + 1] = Tr<T>::mma(ta[2 + u], dSh[u], Gm[b + 1]);
+                }
             }
+            if (AHEAD && kb == 1 && j + 1 < cq && block_start(j + 1)) read_state(j + 1);
         }
         if (j + 1 < cq && block_start(j + 1)) {    // g after this block: tile gT (rows b, contraction q) of the pair (cq, next block)
             Frag idf[SPB];
@@ -1098,7 +1145,7 @@ static hipError_t launch_scan_t(const BwdParams& p, int stages, hipStream_t st) 
             if (D == 128 && p.NC > 8) {
                 if ((e = launch_bwd_adjoint(p, st)) != hipSuccess) return e;
             } else {
-                const size_t bytes = (size_t)(2 * Adj2Cfg<TIO, D>::KV_FRAGS + Adj2Cfg<TIO, D>::DP_FRAGS) * 16;      // kt | vk | dpt
+                const size_t bytes = LiteCfg<TIO, D>::smem_bytes;
                 if ((e = set_smem<&bwd_adjoint2_lite_kernel<TIO, D, FOX>>(bytes)) != hipSuccess) return e;
                 hipLaunchKernelGGL((bwd_adjoint2_lite_kernel<TIO, D, FOX>), grid_adj, dim3(256), bytes, st, p);
             }

@@ -21,7 +21,7 @@
 // fragment from LDS per product, which keeps the LDS port busy for as long as the matrix pipes (3072 cycles per chunk and
 // two waves each); with 64 queries per wave every fragment serves two products, two thirds of that.  d = 64 has half the
 // products for the same element-wise part and four of the smaller workgroups on a CU: it stays with those
-// (bwd_adjoint2_lite_kernel in bwd.hip; B=8, H=16, L=4096 takes 2.89 ms a step with this split, 2.80 without).
+// (bwd_adjoint2_lite_kernel in bwd.hip; B=8, H=16, L=4096 took 2.89 ms a step with this split, 2.80 without).
 // Measured at d = 128: B=4, H=16, L=8192 2.09 -> 1.86 ms, training step 8.22 -> 7.99; L=32768, H=32 42.8 -> 41.5.
 #include <type_traits>
 

@@ -297,6 +297,34 @@ __device__ __forceinline__ typename Tr<E>::Frag ld_tile_frag_tr(const E* tile, i
     return u.f;
 }
 
+// Four fragments of the transpose of a tile, (QS0, B0) .. (QS3, B3), as ld_tile_frag_tr gives them, for a wave that has copies
+// to LDS in flight: the compiler has a transposing read (the builtin) wait for all of them.  The block waits for its own reads.
+struct TileTr { unsigned even, odd; };      // LDS byte addresses of the lane's two reads of fragment (0, 0)
+template <typename E>
+__device__ __forceinline__ TileTr tile_tr(const E* tile, int l32, int h) {
+    const int i = l32 & 15, sl = l32 >> 4, hh = i & 1;
+    const int row = (4 * h + (i >> 2)) ^ (4 * hh), odd = 8 * sl;
+    const unsigned p = (unsigned)(uintptr_t)(__attribute__((address_space(3))) const void*)tile + (unsigned)(((sl * 64 + hh * 32 + row) * 8 + 4 * ((i >> 1) & 1)) * 2);
+    return {p + odd * 16, p + (8 - odd) * 16};
+}
+template <typename E, int DS, int QS0, int B0, int QS1, int B1, int QS2, int B2, int QS3, int B3>
+__device__ __forceinline__ void ld_tile_frags_tr(const TileTr& a, typename Tr<E>::Frag (&f)[4]) {
+    static_assert(sizeof(E) == 2, "16-bit transposing reads");
+    union U { unsigned long long v[2]; typename Tr<E>::Frag f; } u[4];
+#define TILE_TR_OFF(qs, b) ((((qs) >> 1) * DS + 2 * (b)) * 64 + 16 * ((qs) & 1)) * 16
+    asm volatile("ds_read_b64_tr_b16 %0, %8 offset:%10\n\tds_read_b64_tr_b16 %1, %9 offset:%10\n\t"
+                 "ds_read_b64_tr_b16 %2, %8 offset:%11\n\tds_read_b64_tr_b16 %3, %9 offset:%11\n\t"
+                 "ds_read_b64_tr_b16 %4, %8 offset:%12\n\tds_read_b64_tr_b16 %5, %9 offset:%12\n\t"
+                 "ds_read_b64_tr_b16 %6, %8 offset:%13\n\tds_read_b64_tr_b16 %7, %9 offset:%13\n\t"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&v"(u[0].v[0]), "=&v"(u[0].v[1]), "=&v"(u[1].v[0]), "=&v"(u[1].v[1]), "=&v"(u[2].v[0]), "=&v"(u[2].v[1]), "=&v"(u[3].v[0]), "=&v"(u[3].v[1])
+                 : "v"(a.even), "v"(a.odd), "n"(TILE_TR_OFF(QS0, B0)), "n"(TILE_TR_OFF(QS1, B1)), "n"(TILE_TR_OFF(QS2, B2)), "n"(TILE_TR_OFF(QS3, B3))
+                 : "memory");
+#undef TILE_TR_OFF
+#pragma unroll
+    for (int k = 0; k < 4; ++k) f[k] = u[k].f;
+}
+
 // Linear copy of NFRAG 16-byte fragments global -> LDS, asynchronous (direct-to-LDS), by a workgroup of
 // NT threads.  One instruction moves 64 consecutive fragments (lane = fragment); wave wv takes the
 // groups wv*NPT .. wv*NPT + NPT-1 (NPT = NFRAG / NT), which are 1 KB apart, so that one
