@@ -176,7 +176,7 @@ def bench_decode(args, torch, pa, si, dev):
         "data": "synthetic",
         "config": {"workload": f"decode step over a cache of L={L} tokens, B={B} H={H} d={d}"},
         "key_prefill_ms": prefill_ms,
-        "roofline": {"kernel": "decode_partial_kernel + decode_combine_kernel", "bound": "hbm", "achieved": bytes_alg / (ms * 1e-3) / 1e9,
+        "roofline": {"kernel": "decode_partial_kernel (with the merge of its splits)", "bound": "hbm", "achieved": bytes_alg / (ms * 1e-3) / 1e9,
                      "peak": 8000.0, "unit": "GB/s", "frac": bytes_alg / (ms * 1e-3) / 1e9 / 8000.0, "traffic": None,
                      "note": "algorithmic bytes = read K + write K + read V = 3*L*d*2 per head; HIP-event time of one step"},
     }
