@@ -416,8 +416,9 @@ path_status_t path_probe_mfma_operands(void* sink, int waves_per_simd, int iters
  *   Limit: path_decode_workspace_bytes(B, H, d) <= PATH_DECODE_STATIC_BYTES, i.e. B*H <= 252 at d = 128 and
  *   B*H <= 496 at d = 64; beyond it PATH_ERR_WORKSPACE (the reason is in path_attn_last_error()).
  *   All calls on one GPU share the one array, which keeps the previous call's contents (nothing in it has to
- *   start at zero: a split's record counts once it carries the call's own mark).  Calls that may overlap on one GPU -- different
- *   streams without an ordering between them, or several host threads -- RACE on it: order them.
+ *   start at zero: a split's record counts once it carries the call's own mark, or, of a captured call, in the second
+ *   launch that merges them).  Calls that may overlap on one GPU -- different streams without an ordering between
+ *   them, or several host threads -- RACE on it: order them.  (A race spoils the calls that overlap, not later ones.)
  * path_decode_static_scratch_bytes returns PATH_DECODE_STATIC_BYTES.
  */
 #define PATH_DECODE_STATIC_BYTES (8u * 1024u * 1024u)

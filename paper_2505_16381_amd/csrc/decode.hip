@@ -151,7 +151,7 @@ struct DecodeTail {
         vt = reinterpret_cast<const TIO*>(a.v)[(size_t)bh * D + c];
         qk = 0.f;
 #pragma unroll
-        for (int b = 0; b < D; b += 64) qk += (float)q[b + (c & 63)] * (float)k[b + (c & 63)];
+        for (int b = 0; b < D; b += 64) qk = __builtin_fmaf((float)q[b + (c & 63)], (float)k[b + (c & 63)], qk);
         // the token's running gate sum, which joins the cache (its own logit carries no gate)
         gate = GATES ? (a.n > 0 ? a.ccache[(size_t)bh * a.Lmax + a.n - 1] : 0.f) + (float)reinterpret_cast<const TIO*>(a.log_f)[bh] : 0.f;
     }
@@ -163,11 +163,12 @@ struct DecodeTail {
         qk *= scale;
     }
     __device__ __forceinline__ void finish(const DecodeArgs& a, int bh, int c, float M, float Ls, float O) const {
+#pragma clang fp contract(off)
         const float s_new = qk;
         const float Mn = fmaxf(M, s_new);
         const float old = M == -INFINITY ? 0.f : __expf(M - Mn), own = __expf(s_new - Mn);
-        Ls = Ls * old + own;
-        O = O * old + own * (float)vt;
+        Ls = __builtin_fmaf(Ls, old, own);
+        O = __builtin_fmaf(O, old, own * (float)vt);
         reinterpret_cast<TIO*>(a.o)[(size_t)bh * D + c] = (TIO)(O / Ls);
         if (c == 0) a.lse[bh] = Mn + __logf(Ls);
         reinterpret_cast<TIO*>(a.kcache)[((size_t)bh * a.Lmax + a.n) * D + c] = kt;
@@ -178,7 +179,7 @@ struct DecodeTail {
 
 // One pass over the cached keys of a split: refresh, logit, online softmax, P V.  DIRECT: the split is the whole head
 // and the workgroup ends the step itself; else every split leaves its partial results in the
-// workspace, and the last one merges them.
+// workspace, and the last one (MERGED) or decode_merge_kernel (RECORDS) merges them.
 // A key is handled by LPK = D/8 consecutive lanes (8 elements each); a wave takes 64/LPK keys at a time and UN such
 // rounds per step, whose rows it has requested a step ahead.  The sums over a key's lanes are DPP moves (a shuffle
 // through LDS costs its latency eight times per key).
@@ -209,13 +210,55 @@ template <typename T> __device__ __forceinline__ T agent_load(const T* p) { retu
 // that raced with another on its workspace mean nothing later).  All inputs of the token are in registers before a flag is
 // set (o may be one of them).  It takes as long as a second launch on the GPU, and 2.8 us less on the host.  (A tag
 // beside every value instead of the flag, one trip to memory less: 1024 keys, 64 heads, d = 128 16.3 us against 14.2.)
+// A captured step would carry one pattern through all its replays, and flags that a replay left standing would be taken for
+// the next one's: its splits leave records only, and a second launch merges them, whatever the workspace held.  (Both forms
+// give the same bits: what may be rounded once is written as __builtin_fmaf, and the compiler fuses nothing by itself.)
+enum DecodeMode { DECODE_DIRECT, DECODE_MERGED, DECODE_RECORDS };
 struct DecodeRecord {            // of one split and 64 components
     float o[64], m, l;
     unsigned long long flag;
 };
 
-template <typename TIO, int D, bool GATES, int NT, bool DIRECT>
+// One wave: the records of its 64 components (at most 64 splits: lane s holds the maximum and the row sum of split s), then the
+// step's last part, component c of D per lane.
+template <typename TIO, int D, bool GATES, bool AGENT, typename F>
+__device__ __forceinline__ void decode_merge(const DecodeArgs& a, const DecodeRecord* rec, int nsplit, const DecodeTail<TIO, D, GATES>& tail, int bh, int c, F meanwhile) {
+#pragma clang fp contract(off)
+    static_assert(DECODE_MAX_SPLITS <= 64, "one split per lane");
+    const int lane = c & 63;
+    auto get = [](const float* p) { return AGENT ? agent_load(p) : *p; };
+    constexpr int NB = 16;                            // outputs of so many splits requested at once
+    float on[NB];
+    auto request_o = [&](int s0) {                    // (splits past the last one repeat it, and count as zero)
+#pragma unroll
+        for (int r = 0; r < NB; ++r) on[r] = get(&rec[s0 + r < nsplit ? s0 + r : nsplit - 1].o[lane]);
+    };
+    const float ms = lane < nsplit ? get(&rec[lane].m) : -INFINITY;
+    float Ls = lane < nsplit ? get(&rec[lane].l) : 0.f;
+    request_o(0);
+    meanwhile();
+    float M = ms;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) M = fmaxf(M, __shfl_xor(M, off));
+    const float wt = ms == -INFINITY ? 0.f : __expf(ms - M);
+    Ls *= wt;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) Ls += __shfl_xor(Ls, off);
+    float O = 0.f;
+    for (int s0 = 0; s0 < nsplit; s0 += NB) {
+        float oc[NB];
+#pragma unroll
+        for (int r = 0; r < NB; ++r) oc[r] = s0 + r < nsplit ? on[r] : 0.f;
+        if (s0 + NB < nsplit) request_o(s0 + NB);
+#pragma unroll
+        for (int r = 0; r < NB; ++r) O = __builtin_fmaf(oc[r], __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wt), s0 + r)), O);
+    }
+    tail.finish(a, bh, c, M, Ls, O);
+}
+
+template <typename TIO, int D, bool GATES, int NT, DecodeMode MODE>
 __global__ __launch_bounds__(NT) void decode_partial_kernel(DecodeArgs a) {
+#pragma clang fp contract(off)
     constexpr int LPK = D / 8, KPW = 64 / LPK, NW = NT / 64, UN = 4 / (int)sizeof(TIO), STEP = NW * UN * KPW;
     typedef TIO Vec8 __attribute__((ext_vector_type(8)));
     __shared__ float red_m[NW], red_l[NW];
@@ -245,7 +288,7 @@ __global__ __launch_bounds__(NT) void decode_partial_kernel(DecodeArgs a) {
     int i0 = i_begin + wv * (UN * KPW);
     if (i0 < i_end) request(i0);
     DecodeTail<TIO, D, GATES> tail;
-    if (tid < D) tail.load(a, bh, tid);
+    if (MODE != DECODE_RECORDS && tid < D) tail.load(a, bh, tid);
 
     float q8[8], w8[8];
     {
@@ -271,7 +314,7 @@ __global__ __launch_bounds__(NT) void decode_partial_kernel(DecodeArgs a) {
         for (int r = 0; r < UN; ++r) {
             wk[r] = 0.f;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) wk[r] += w8[e] * (float)kv[r][e];
+            for (int e = 0; e < 8; ++e) wk[r] = __builtin_fmaf(w8[e], (float)kv[r][e], wk[r]);
         }
 #pragma unroll
         for (int r = 0; r < UN; ++r) wk[r] = group_sum<LPK>(wk[r]);
@@ -283,16 +326,15 @@ __global__ __launch_bounds__(NT) void decode_partial_kernel(DecodeArgs a) {
             s[r] = 0.f;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                kv[r][e] = (TIO)((float)kv[r][e] - beta * wk[r] * w8[e]);
-                s[r] += q8[e] * (float)kv[r][e];
+                kv[r][e] = (TIO)__builtin_fmaf(-beta * wk[r], w8[e], (float)kv[r][e]);
+                s[r] = __builtin_fmaf(q8[e], (float)kv[r][e], s[r]);
             }
             if (i < i_end) __builtin_nontemporal_store(kv[r], reinterpret_cast<Vec8*>(kc + (size_t)i * D));
         }
         float mn = m;
 #pragma unroll
         for (int r = 0; r < UN; ++r) {
-            s[r] = a.scale * group_sum<LPK>(s[r]);
-            if (GATES) s[r] += c_t - ci[r];
+            s[r] = GATES ? __builtin_fmaf(a.scale, group_sum<LPK>(s[r]), c_t - ci[r]) : a.scale * group_sum<LPK>(s[r]);
         }
         if (i0 + UN * KPW > i_end) {                      // past the end: weight zero, and a zero to weigh (the repeated row may hold infinities)
 #pragma unroll
@@ -304,15 +346,14 @@ __global__ __launch_bounds__(NT) void decode_partial_kernel(DecodeArgs a) {
         const float ref = mn == -INFINITY ? 0.f : mn;             // nothing yet: every weight below is exp(-inf)
         const float alpha = __expf(m - ref);
         m = mn;
-        l *= alpha;
 #pragma unroll
         for (int e = 0; e < 8; ++e) acc[e] *= alpha;
 #pragma unroll
         for (int r = 0; r < UN; ++r) {
             const float pr = __expf(s[r] - ref);
-            l += pr;
+            l = r == 0 ? __builtin_fmaf(l, alpha, pr) : l + pr;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) acc[e] += pr * (float)vv[r][e];
+            for (int e = 0; e < 8; ++e) acc[e] = __builtin_fmaf(pr, (float)vv[r][e], acc[e]);
         }
     }
     // merge the keys of the wave's lanes, then the waves
@@ -336,7 +377,7 @@ __global__ __launch_bounds__(NT) void decode_partial_kernel(DecodeArgs a) {
             for (int e = 0; e < 8; ++e) red_o[wv][8 * sub + e] = acc[e];
         }
     }
-    if (wv < D / 64) {
+    if (MODE != DECODE_RECORDS && wv < D / 64) {
         tail.logit(a.scale);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // all that this wave reads of the token's inputs is in registers
     }
@@ -349,14 +390,18 @@ __global__ __launch_bounds__(NT) void decode_partial_kernel(DecodeArgs a) {
 #pragma unroll
     for (int g = 0; g < NW; ++g) {
         const float sc = red_m[g] == -INFINITY ? 0.f : __expf(red_m[g] - M);
-        Ls += red_l[g] * sc;
-        O += red_o[g][tid] * sc;
+        Ls = __builtin_fmaf(red_l[g], sc, Ls);
+        O = __builtin_fmaf(red_o[g][tid], sc, O);
     }
-    if (DIRECT) { tail.finish(a, bh, tid, M, Ls, O); return; }
+    if constexpr (MODE == DECODE_DIRECT) { tail.finish(a, bh, tid, M, Ls, O); return; }
     // The record of this wave's 64 components, past the L2s (agent scope); once it is there, the flag.
-    static_assert(DECODE_MAX_SPLITS <= 64, "one split per lane");
     DecodeRecord* const rec = reinterpret_cast<DecodeRecord*>(a.partial) + (size_t)(bh * (D / 64) + wv) * nsplit;
     DecodeRecord* const own = rec + split;
+    if constexpr (MODE == DECODE_RECORDS) {
+        own->o[lane] = O;
+        if (lane == 0) { own->m = M; own->l = Ls; }
+        return;
+    }
     agent_store(&own->o[lane], O);
     if (lane == 0) { agent_store(&own->m, M); agent_store(&own->l, Ls); }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -365,33 +410,20 @@ __global__ __launch_bounds__(NT) void decode_partial_kernel(DecodeArgs a) {
     const unsigned long long flag = lane < nsplit ? agent_load(&rec[lane].flag) : a.flag;
     if (__builtin_amdgcn_ballot_w64(flag != a.flag) != 0) return;      // another split will find them all set
     asm volatile("" ::: "memory");
-    constexpr int NB = 16;                            // outputs of so many splits requested at once
-    float on[NB];
-    auto request_o = [&](int s0) {                    // (splits past the last one repeat it, and count as zero)
-#pragma unroll
-        for (int r = 0; r < NB; ++r) on[r] = agent_load(&rec[s0 + r < nsplit ? s0 + r : nsplit - 1].o[lane]);
-    };
-    const float ms = lane < nsplit ? agent_load(&rec[lane].m) : -INFINITY;
-    Ls = lane < nsplit ? agent_load(&rec[lane].l) : 0.f;
-    request_o(0);
-    M = ms;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) M = fmaxf(M, __shfl_xor(M, off));
-    const float wt = ms == -INFINITY ? 0.f : __expf(ms - M);
-    Ls *= wt;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) Ls += __shfl_xor(Ls, off);
-    O = 0.f;
-    for (int s0 = 0; s0 < nsplit; s0 += NB) {
-        float oc[NB];
-#pragma unroll
-        for (int r = 0; r < NB; ++r) oc[r] = s0 + r < nsplit ? on[r] : 0.f;
-        if (s0 + NB < nsplit) request_o(s0 + NB);
-#pragma unroll
-        for (int r = 0; r < NB; ++r) O += oc[r] * __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wt), s0 + r));
-    }
+    decode_merge<TIO, D, GATES, true>(a, rec, nsplit, tail, bh, tid, []() {});
     if (lane < nsplit) agent_store(&rec[lane].flag, 0ull);
-    tail.finish(a, bh, tid, M, Ls, O);
+}
+
+template <typename TIO, int D, bool GATES>
+__global__ __launch_bounds__(D) void decode_merge_kernel(DecodeArgs a, int nsplit) {
+    const int bh = blockIdx.x, c = threadIdx.x;
+    const DecodeRecord* rec = reinterpret_cast<const DecodeRecord*>(a.partial) + (size_t)(bh * (D / 64) + (c >> 6)) * nsplit;
+    DecodeTail<TIO, D, GATES> tail;
+    decode_merge<TIO, D, GATES, false>(a, rec, nsplit, tail, bh, c, [&]() {
+        tail.load(a, bh, c);
+        tail.logit(a.scale);
+        if (D > 64) __syncthreads();
+    });
 }
 
 // ---------------------------------------------------------------------------------------
@@ -438,14 +470,22 @@ static bool decode_one_workgroup(int BH, size_t key_bytes) {
 template <typename TIO, int D, bool GATES>
 static hipError_t launch_decode_g(const DecodeArgs& a, int BH, hipStream_t st) {
     if (decode_one_workgroup(BH, (size_t)a.n * D * sizeof(TIO))) {
-        if (a.n <= 128) hipLaunchKernelGGL((decode_partial_kernel<TIO, D, GATES, 256, true>), dim3(1, BH), dim3(256), 0, st, a);
-        else hipLaunchKernelGGL((decode_partial_kernel<TIO, D, GATES, 1024, true>), dim3(1, BH), dim3(1024), 0, st, a);
+        if (a.n <= 128) hipLaunchKernelGGL((decode_partial_kernel<TIO, D, GATES, 256, DECODE_DIRECT>), dim3(1, BH), dim3(256), 0, st, a);
+        else hipLaunchKernelGGL((decode_partial_kernel<TIO, D, GATES, 1024, DECODE_DIRECT>), dim3(1, BH), dim3(1024), 0, st, a);
         return hipGetLastError();
     }
     static_assert(DECODE_MAX_SPLITS * (D / 64) * sizeof(DecodeRecord) <= DECODE_SPLIT_ROOM * (D + 2) * 4, "the workspace holds the records");
     const DecodeSplits s = decode_splits(BH, a.n);
-    if (s.waves == 4) hipLaunchKernelGGL((decode_partial_kernel<TIO, D, GATES, 256, false>), dim3(s.n, BH), dim3(256), 0, st, a);
-    else hipLaunchKernelGGL((decode_partial_kernel<TIO, D, GATES, 512, false>), dim3(s.n, BH), dim3(512), 0, st, a);
+    if (a.flag != 0) {
+        if (s.waves == 4) hipLaunchKernelGGL((decode_partial_kernel<TIO, D, GATES, 256, DECODE_MERGED>), dim3(s.n, BH), dim3(256), 0, st, a);
+        else hipLaunchKernelGGL((decode_partial_kernel<TIO, D, GATES, 512, DECODE_MERGED>), dim3(s.n, BH), dim3(512), 0, st, a);
+        return hipGetLastError();
+    }
+    if (s.waves == 4) hipLaunchKernelGGL((decode_partial_kernel<TIO, D, GATES, 256, DECODE_RECORDS>), dim3(s.n, BH), dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((decode_partial_kernel<TIO, D, GATES, 512, DECODE_RECORDS>), dim3(s.n, BH), dim3(512), 0, st, a);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((decode_merge_kernel<TIO, D, GATES>), dim3(BH), dim3(D), 0, st, a, s.n);
     return hipGetLastError();
 }
 template <typename TIO, int D>
@@ -454,7 +494,10 @@ static hipError_t launch_decode_t(const DecodeArgs& a, int BH, hipStream_t st) {
 }
 hipError_t launch_decode_step(DecodeArgs a, int BH, int d, int is_bf16, hipStream_t st) {
     static std::atomic<unsigned long long> calls{0};
-    a.flag = (calls.fetch_add(1, std::memory_order_relaxed) + 1) * 0x9e3779b97f4a7c15ull;      // (odd factor: 2^64 calls before one recurs; never 0 before)
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    const bool known = hipStreamIsCapturing(st, &cs) == hipSuccess;
+    if (!known) (void)hipGetLastError();              // (the null stream while another one is captured; the launch says whether that is allowed)
+    a.flag = !known || cs != hipStreamCaptureStatusNone ? 0 : (calls.fetch_add(1, std::memory_order_relaxed) + 1) * 0x9e3779b97f4a7c15ull;      // (odd factor: 2^64 calls before one recurs; never 0 before)
     if (is_bf16) return d == 64 ? launch_decode_t<bf16_t, 64>(a, BH, st) : launch_decode_t<bf16_t, 128>(a, BH, st);
     return d == 64 ? launch_decode_t<float, 64>(a, BH, st) : launch_decode_t<float, 128>(a, BH, st);
 }

@@ -41,7 +41,7 @@ struct DecodeArgs {
     // c_i = sum_{s<=i} log f_s of the cached tokens, fp32 [BH][Lmax], natural logarithm; the step appends c_n
     const void* log_f;
     float* ccache;
-    unsigned long long flag;            // this call's "record is there", set by the launcher
+    unsigned long long flag;            // this call's "record is there", set by the launcher; 0: a second launch merges (captured steps)
 };
 
 // The same chunk by chunk (16-bit operands): key tiles of the prompt, products of the blocks of cpb chunks.
