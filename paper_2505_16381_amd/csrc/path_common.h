@@ -445,8 +445,9 @@ __device__ __forceinline__ void chunk_and_head(const UserLayout& u, int NC, int 
 // uniform over the workgroup, goes back to scalar registers, so that everything derived from it -- loop bounds, tile
 // addresses -- is scalar arithmetic).
 __device__ __forceinline__ bool xcd_deal(int slot, int xcd, int N, int BH, int& bh, int& r) {
-    const int np = xcd_per_part(N, BH), round = __builtin_amdgcn_readfirstlane(slot / np);
-    const XcdPlace p = xcd_place(round, slot - round * np, xcd, BH);
+    const XcdDivision v = xcd_division(slot, xcd, N, BH);
+    const int q = __builtin_amdgcn_readfirstlane(v.num / v.den);
+    const XcdPlace p = xcd_place(q, v.num - q * v.den, xcd, BH);
     bh = __builtin_amdgcn_readfirstlane(p.bh);
     r = __builtin_amdgcn_readfirstlane(p.r);
     return bh < BH && r < N;

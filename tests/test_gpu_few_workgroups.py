@@ -19,7 +19,7 @@ def test_heads_by_themselves_and_among_many(d, L, few, many, gates):
     log_f = torch.nn.functional.logsigmoid(rn(1, many, L) + 2).bfloat16() if gates else None
     do = rn(1, many, L, d).bfloat16()
     tiles = -(-L // 128)
-    assert few < 8 and many * tiles > 256 >= few * (tiles + 7)          # both forms (fewer than eight heads are dealt in up to eight parts)
+    assert few < 8 and many * tiles > 256 >= few * (tiles + 7)          # both forms (fewer than eight heads are dealt out to all XCDs)
 
     def run(sel):
         a, f, g = [t[:, sel].contiguous() for t in x], None if log_f is None else log_f[:, sel].contiguous(), do[:, sel].contiguous()

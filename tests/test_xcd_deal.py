@@ -1,5 +1,5 @@
 """How the kernels that keep a head's workgroups together deal them out to the eight XCDs (CPU; the header is plain C++): every
-workgroup of every head exactly once, and equal shares where few heads are no multiple of eight."""
+workgroup of every head exactly once, and of fewer than eight heads equal shares, the first of all heads before the second."""
 import os
 import subprocess
 
@@ -11,9 +11,10 @@ SOURCE = r"""
 #include <cstdlib>
 #include "xcd_deal.h"
 int main(int, char** v) {
-    const int N = atoi(v[1]), BH = atoi(v[2]), np = path::xcd_per_part(N, BH);
+    const int N = atoi(v[1]), BH = atoi(v[2]);
     for (unsigned b = 0; b < path::xcd_deal_grid(N, BH); ++b) {
-        const path::XcdPlace p = path::xcd_place((int)(b >> 3) / np, (int)(b >> 3) % np, b & 7, BH);
+        const path::XcdDivision q = path::xcd_division((int)(b >> 3), b & 7, N, BH);
+        const path::XcdPlace p = path::xcd_place(q.num / q.den, q.num % q.den, b & 7, BH);
         if (p.bh < BH && p.r < N) printf("%u %d %d\n", b & 7, p.bh, p.r);
     }
 }
@@ -35,8 +36,10 @@ def test_every_workgroup_once(deal, N, BH):
     assert sorted((bh, r) for _, bh, r in got) == [(bh, r) for bh in range(BH) for r in range(N)]
     if BH < 8:
         share = [sum(x == i for x, _, _ in got) for i in range(8)]
-        parts = next(p for p in (1, 2, 4, 8) if BH * p % 8 == 0)
-        assert max(share) <= -(-N // parts) * BH * parts // 8
+        assert max(share) - min(share) <= 1
+        for i in range(8):
+            ranks = [r for x, _, r in got if x == i]
+            assert ranks == sorted(ranks)
     for x in range(8):                      # a head's workgroups in their order on each XCD
         mine = [(bh, r) for y, bh, r in got if y == x]
         assert all(a[1] < b[1] for a, b in zip(mine, mine[1:]) if a[0] == b[0])
