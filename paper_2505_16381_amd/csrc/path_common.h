@@ -452,30 +452,14 @@ __device__ __forceinline__ bool xcd_deal(int slot, int xcd, int N, int BH, int& 
     r = __builtin_amdgcn_readfirstlane(p.r);
     return bh < BH && r < N;
 }
-// For a kernel whose workgroups of one (super-block, head) read the same tiles: its SBC workgroups run on one XCD,
-// first chunk first, and the (super-block, head) pairs are dealt to the XCDs in the order, and with the turn, of
-// chunk_and_head.  Launched
-// with super_block_grid() workgroups; those past the last pair get bh >= BH.
+// The workgroup's chunk and head as numbered by sb_place in xcd_deal.h, launched with super_block_grid() workgroups; those past
+// the last pair get bh >= BH.
 __device__ __forceinline__ void super_block_and_head(const UserLayout& u, int NC, int BH, int& chunk, int& bh) {
-    const int nsb = (NC + SBC - 1) / SBC, kk = blockIdx.x >> 3;
-    const int n = kk / SBC * 8 + (blockIdx.x & 7), m = u.cu ? BH : nsb;
-    const int hi = __builtin_amdgcn_readfirstlane(n / m), lo = n - hi * m;
-    int sb = lo;
-    bh = hi;
-    if (u.cu) {
-        sb = hi;
-        bh = lo;
-        if ((u.H & 7) && NC * ((BH + 7) >> 3) > 32) {
-            bh += __builtin_amdgcn_readfirstlane(hi % m);
-            if (bh >= m) bh -= m;
-        }
-        if (sb >= nsb) bh = BH;
-    }
-    chunk = sb * SBC + kk % SBC;
+    const SbPlace p = sb_place(blockIdx.x >> 3, blockIdx.x & 7, NC, SBC, BH, u.cu != nullptr, (u.H & 7) && NC * ((BH + 7) >> 3) > 32);
+    chunk = __builtin_amdgcn_readfirstlane(p.chunk);
+    bh = __builtin_amdgcn_readfirstlane(p.bh);
 }
-__host__ __forceinline__ unsigned super_block_grid(int NC, int BH) {
-    return (unsigned)(((long long)((NC + SBC - 1) / SBC) * BH + 7) / 8 * 8 * SBC);
-}
+__host__ __forceinline__ unsigned super_block_grid(int NC, int BH) { return sb_grid(NC, SBC, BH); }
 // length of head bh's sequence: the launch's L, or the head's own in a packed batch
 __device__ __forceinline__ int seq_len(const UserLayout& u, int bh, int L) {
     if (!u.cu) return L;

@@ -28,4 +28,38 @@ XCD_FN XcdDivision xcd_division(int slot, int xcd, int N, int BH) { return xcd_s
 struct XcdPlace { int bh, r; };
 XCD_FN XcdPlace xcd_place(int quotient, int rest, int xcd, int BH) { return xcd_spread(BH) ? XcdPlace{rest, quotient} : XcdPlace{quotient * 8 + xcd, rest}; }
 
+// Numbering of the chunk workgroups of the chunk-transform adjoint: those of a (super-block, head) pair run on one XCD, first
+// chunk -- the one with the most queries to its right -- first, and the pairs are dealt to the XCDs in order: head after head, or, in
+// a packed batch, super-block after super-block, where the late ones exist in the long sequences only (`turn`: the heads turned by
+// one per super-block, see chunk_and_head).  The last, partial super-blocks come behind the whole ones, with as many workgroups as
+// they have chunks: an idle workgroup here waits for a CU's LDS like any other.  With sixteen for every pair a training step of
+// 144 heads of 63 tokens, d = 128, took 101 us, so 64; 99 heads of 1320, gated, 1302 / 1111; d = 64, 96 heads of 1046, gated, 579 / 456.
+// (All chunks dealt out without regard to pairs: 128 heads of 4096, d = 64, 2760 us, so 2650; 64 of 8192, d = 128, 8030 / 7720.)
+// Chunk workgroup kk of XCD xcd; sbc chunks per super-block; bh >= BH: nothing to do.
+struct SbPlace { int bh, chunk; };
+XCD_FN SbPlace sb_place(int kk, int xcd, int NC, int sbc, int BH, bool packed, bool turn) {
+    const int full = NC / sbc, rem = NC - full * sbc, P = full * BH;      // whole super-blocks of a head, chunks of the partial one; whole pairs
+    const int F = P > xcd ? (P - xcd + 7) >> 3 : 0;                       // ... of this XCD
+    const bool tail = kk >= F * sbc;
+    if (tail && !rem) return {BH, 0};
+    const int n = tail ? rem : sbc, k = tail ? kk - F * sbc : kk, q = k / n;
+    const int p = (tail ? F + q : q) * 8 + xcd - (tail ? P : 0);
+    if (tail && p >= BH) return {BH, 0};
+    const int m = packed ? BH : tail ? 1 : full, hi = p / m, lo = p - hi * m;
+    const int sb = tail ? full : packed ? hi : lo;
+    int bh = packed ? lo : hi;
+    if (packed && turn) bh = (bh + sb) % BH;
+    return {bh, sb * sbc + k - q * n};
+}
+XCD_FN unsigned sb_grid(int NC, int sbc, int BH) {
+    const int full = NC / sbc, rem = NC - full * sbc, P = full * BH, A = P + (rem ? BH : 0);
+    unsigned most = 0;
+    for (int x = 0; x < 8; ++x) {
+        const int F = P > x ? (P - x + 7) / 8 : 0, n = A > x ? (A - x + 7) / 8 : 0;
+        const unsigned w = (unsigned)(F * sbc + (n - F) * rem);
+        if (w > most) most = w;
+    }
+    return 8 * most;
+}
+
 }  // namespace path
