@@ -441,42 +441,62 @@ hipError_t launch_key_prefill(const PrefillArgs& a, int BH, int d, int is_bf16, 
     return d == 64 ? launch_prefill_t<float, 64>(a, BH, st) : launch_prefill_t<float, 128>(a, BH, st);
 }
 
-// Splits of the cached positions.  About four workgroups of four waves per CU: three rows per 16 lanes in flight in each of
-// their 16 waves cover the latency of HBM (two per CU: 3 % slower at B=4, H=16, n=8192, eight: the same).  At least 64 keys
-// each.  From 17 splits on half as many of eight waves: there is less to merge (replayed from a graph, d = 128: 16 heads of
-// 1100 keys 10.1 -> 9.1 us, 2000 11.6 -> 10.2, 3000 14.9 -> 13.7; one head of 2000 7.6 -> 7.1; 16 splits or less do not
-// gain).  A few long heads take as many as there is room for: one head of 32000 keys 23.5 us with 32 of eight waves, 18.0 with 60.
-struct DecodeSplits { int n, waves; };
-static DecodeSplits decode_splits(int BH, int n) {
-    int s = (1024 + BH - 1) / BH;
-    if (s > 64) s = 64;
-    const int by_len = (n + 63) / 64;
-    if (s > by_len) s = by_len;
-    if (s == 64 && s * BH < 512) return {DECODE_MAX_SPLITS, 8};
-    if (s > 16) return {(s + 1) / 2, 8};
-    return {s < 1 ? 1 : s, 4};
+// Splits of the cached positions.  Bound by HBM, a step takes as long as the fullest CU: what counts is the share of a head's
+// keys that its workgroups have, ceil(splits * heads / 256) / splits.  Eight waves, one or two workgroups per CU (registers
+// leave room for sixteen waves): 34 heads of 12825 keys, d = 128, 15 splits (510 workgroups) 55.5 us, 16 (544) 64.1; 62 of 2152
+// 8 (496) 20.8, 9 (558) 25.2; fp32, 10 of 6441 25 (250) 22.9, 32 (320) 29.2.  Two only up to 16 splits -- one batch of the
+// merge: 16 heads of 8192 keys 16 20.8, 32 21.2 -- and otherwise if they are the better ones.  Four waves, up to four
+// workgroups, where that divides better from 96 heads on: gated, 140 of 1827 7 (980) 36.3, eight waves 3 (420) 37.1; 200 of 2000 5
+// (1000) 52.8, 2 (400) 54.8.
+// A split has a step of its waves to do, 16 KB of keys, and no more of them are taken than pay for their merge: one head,
+// replayed, 350 KB of keys 15 splits 7.0 us, 32 7.2; fp32 1400 KB 32 8.1, 44 8.2; 8 MB 60 12.9, 32 15.8.  Short and few heads: splits of
+// four waves and 64 keys, which start on more CUs (one head of 577 keys, d = 64, 10 of four waves 6.5 us, 5 of eight 6.9), unless they
+// fill them less evenly.
+// More than 256 heads: a step takes 50 us and more of the GPU, a second launch costs none of it, and without the merge the
+// kernel has 91 registers and not 99, five waves per SIMD: 300 heads of 1500 keys 59.0 us, merged in the launch 63.8.
+struct DecodeSplits { int n, waves; bool merged; };
+static DecodeSplits decode_splits(int BH, int n, size_t key_bytes) {
+    const int len4 = (n + 63) / 64, steps = (int)((key_bytes + 16383) / 16384);
+    if (BH > 256) { const int s = (1024 + BH - 1) / BH; return {s < 1 ? 1 : s < len4 ? s : len4, 4, false}; }
+    const int most = key_bytes < 400 * 1024 ? 16 : key_bytes < 2560 * 1024 ? 32 : DECODE_MAX_SPLITS, lim = most < steps ? most : steps;
+    auto load = [&](int s) { return (s * BH + 255) / 256; };                   // workgroups of the fullest CU
+    int s8 = 256 / BH < lim ? 256 / BH : lim;
+    if (len4 <= 16 && len4 * BH <= 512) return load(len4) * s8 <= load(s8) * len4 ? DecodeSplits{len4, 4, true} : DecodeSplits{s8, 8, true};
+    const int two = 512 / BH < lim ? 512 / BH : lim;
+    if (two <= 16 && load(two) * s8 <= load(s8) * two) s8 = two;
+    if (BH >= 96) {
+        int s4 = 1;
+        for (int j = 1; j <= 4; ++j) {
+            const int s = 256 * j / BH < len4 ? 256 * j / BH : len4;
+            if (load(s) * s4 < load(s4) * s) s4 = s;
+        }
+        if (10 * load(s4) * s8 <= 9 * load(s8) * s4) return {s4, 4, true};
+    }
+    return {s8, 8, true};
 }
 
 // Short heads are not split: one workgroup of sixteen waves (up to 128 keys four: 512 heads of 100 keys, d = 64, 7.9 us against
-// 10.7), which has nothing to merge -- 2.4 us of a step -- but one CU for a head.  That is ahead up to 64 KB of keys for 16
-// heads, 80 for 64, 112 for 96 and 128 for 128 heads; above 128 KB it never is.  Replayed from a graph, us, one workgroup against
-// splits, d = 128: 16 heads 256 keys 7.6 / 7.7, 320 8.4 / 7.8, 512 10.9 / 8.1; 64 heads 320 9.4 / 9.5, 400 10.8 / 10.0; 96 heads
-// 400 11.6 / 11.5, 512 13.6 / 12.3; 128 heads 400 12.3 / 13.2, 512 14.4 / 14.0; 256 heads 512 18.4 / 21.4.
-static bool decode_one_workgroup(int BH, size_t key_bytes) {
-    const int kb = BH + 16 < 64 ? 64 : BH + 16 > 128 ? 128 : BH + 16;
-    return key_bytes <= (size_t)kb * 1024;
+// 10.7), which has nothing to merge but one CU for a head.  The line holds for steps replayed from a graph (eager ones are bound by
+// their one launch, 9.3 us, on either side): bf16 64 KB of keys up to 40 heads, 88 for 64, 120 for 96, 128 from 104 on; fp32, whose
+// keys a wave is done with sooner, 88 KB up to 40 heads, 112 for 64, 128 from 80 on.  Above 128 KB it never is ahead.  us, one
+// workgroup against splits, bf16: 16 heads, d = 128, 56 KB 6.7 / 7.1, 72 7.3 / 7.0, 120 9.4 / 7.1; 48 heads, d = 64, 72 KB 7.6 / 7.9, 88 8.4 / 8.2;
+// 96 heads, d = 64, 72 KB 8.0 / 9.1, 104 9.7 / 10.1, 120 11.0 / 10.5; 200 heads, d = 64, 104 KB 12.8 / 15.0.  fp32: 4 heads, d = 128, 72 KB 6.4 /
+// 6.9, 88 7.0 / 7.1; 48 heads, d = 128, 72 KB 6.9 / 7.8, 88 7.7 / 7.9, 104 8.3 / 7.8; d = 64, 88 KB 7.6 / 8.0.
+static bool decode_one_workgroup(int BH, size_t key_bytes, bool f32) {
+    const int least = f32 ? 88 : 64, kb = BH + (f32 ? 48 : 24);
+    return key_bytes <= (size_t)(kb < least ? least : kb > 128 ? 128 : kb) * 1024;
 }
 
 template <typename TIO, int D, bool GATES>
 static hipError_t launch_decode_g(const DecodeArgs& a, int BH, hipStream_t st) {
-    if (decode_one_workgroup(BH, (size_t)a.n * D * sizeof(TIO))) {
+    if (decode_one_workgroup(BH, (size_t)a.n * D * sizeof(TIO), sizeof(TIO) == 4)) {
         if (a.n <= 128) hipLaunchKernelGGL((decode_partial_kernel<TIO, D, GATES, 256, DECODE_DIRECT>), dim3(1, BH), dim3(256), 0, st, a);
         else hipLaunchKernelGGL((decode_partial_kernel<TIO, D, GATES, 1024, DECODE_DIRECT>), dim3(1, BH), dim3(1024), 0, st, a);
         return hipGetLastError();
     }
     static_assert(DECODE_MAX_SPLITS * (D / 64) * sizeof(DecodeRecord) <= DECODE_SPLIT_ROOM * (D + 2) * 4, "the workspace holds the records");
-    const DecodeSplits s = decode_splits(BH, a.n);
-    if (a.flag != 0) {
+    const DecodeSplits s = decode_splits(BH, a.n, (size_t)a.n * D * sizeof(TIO));
+    if (s.merged && a.flag != 0) {
         if (s.waves == 4) hipLaunchKernelGGL((decode_partial_kernel<TIO, D, GATES, 256, DECODE_MERGED>), dim3(s.n, BH), dim3(256), 0, st, a);
         else hipLaunchKernelGGL((decode_partial_kernel<TIO, D, GATES, 512, DECODE_MERGED>), dim3(s.n, BH), dim3(512), 0, st, a);
         return hipGetLastError();

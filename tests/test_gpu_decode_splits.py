@@ -1,6 +1,8 @@
 """GPU parity of one decoding step at the edges of its launch rules (run with -m gpu): cache lengths around a step of
-four and of sixteen waves, around the largest head that one workgroup takes, around a multiple of the split length and
-with the largest number of splits, from caches of random content, plain and gated, against the decode oracle."""
+four and of sixteen waves, around the largest head that one workgroup takes -- 64 KB of keys for few heads, 88 KB of fp32 ones, 88 KB
+of bf16 ones for 64 heads, 128 KB for many --, around a multiple of the split length, with the largest number of splits, with
+splits of four waves for many heads and with records that a second launch merges, from caches of random content, plain and
+gated, against the decode oracle."""
 import numpy as np
 import pytest
 
@@ -12,7 +14,13 @@ pytestmark = pytest.mark.gpu
     ("bf16", 128, 1, 3, 0), ("bf16", 64, 1, 2, 1), ("bf16", 128, 2, 2, 33), ("bf16", 64, 1, 3, 128), ("bf16", 64, 1, 3, 129),
     ("bf16", 128, 1, 2, 512), ("bf16", 128, 1, 2, 513), ("bf16", 64, 2, 2, 1024), ("bf16", 64, 2, 2, 1025), ("bf16", 128, 1, 2, 1089),
     ("bf16", 128, 1, 1, 8200), ("bf16", 64, 16, 65, 1100), ("fp32", 128, 1, 2, 129), ("fp32", 128, 1, 2, 256),
-    ("fp32", 128, 1, 2, 257), ("fp32", 64, 1, 2, 513), ("fp32", 64, 1, 1, 5000), ("fp32", 128, 1, 1, 4100), ("fp32", 128, 1, 2, 8200)])
+    ("fp32", 128, 1, 2, 257), ("fp32", 64, 1, 2, 513), ("fp32", 64, 1, 1, 5000), ("fp32", 128, 1, 1, 4100), ("fp32", 128, 1, 2, 8200),
+    # one workgroup and the first length that is split
+    ("bf16", 128, 1, 2, 129), ("bf16", 128, 1, 2, 256), ("bf16", 128, 1, 2, 257), ("bf16", 64, 1, 3, 512), ("bf16", 64, 1, 3, 513),
+    ("bf16", 128, 4, 16, 352), ("bf16", 128, 4, 16, 353), ("bf16", 128, 7, 16, 512), ("bf16", 128, 7, 16, 513),
+    ("fp32", 128, 1, 2, 176), ("fp32", 128, 1, 2, 177), ("fp32", 64, 1, 2, 352), ("fp32", 64, 1, 2, 353), ("fp32", 128, 7, 16, 256), ("fp32", 128, 7, 16, 257),
+    # sixty splits; seven of four waves; a second launch's merge
+    ("bf16", 128, 1, 1, 10300), ("bf16", 128, 3, 43, 600), ("bf16", 64, 3, 100, 1030)])
 def test_one_step_from_random_caches(dtype, d, B, H, n, gates):
     import torch
     import paper_2505_16381_amd as pa
