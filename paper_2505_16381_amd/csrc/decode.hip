@@ -448,6 +448,9 @@ hipError_t launch_key_prefill(const PrefillArgs& a, int BH, int d, int is_bf16, 
 // merge: 16 heads of 8192 keys 16 20.8, 32 21.2 -- and otherwise if they are the better ones.  Four waves, up to four
 // workgroups, where that divides better from 96 heads on: gated, 140 of 1827 7 (980) 36.3, eight waves 3 (420) 37.1; 200 of 2000 5
 // (1000) 52.8, 2 (400) 54.8.
+// Where keys and values are as large as the Infinity Cache, four workgroups per CU in two rounds: in one round some lengths bring
+// the workgroups' addresses into step, 64 heads of 8192 keys in caches of 8256 87.7 us, of 8000 in 8256 86.8, in two 84.0, 83.6.  (Else
+// they are level: 8192 in 8200 84.6 / 82.9, in 9192 85.2 / 85.3, 7000 in 7064 70.5 / 71.8; 64 heads of 4096 36.1 / 38.)
 // A split has a step of its waves to do, 16 KB of keys, and no more of them are taken than pay for their merge: one head,
 // replayed, 350 KB of keys 15 splits 7.0 us, 32 7.2; fp32 1400 KB 32 8.1, 44 8.2; 8 MB 60 12.9, 32 15.8.  Short and few heads: splits of
 // four waves and 64 keys, which start on more CUs (one head of 577 keys, d = 64, 10 of four waves 6.5 us, 5 of eight 6.9), unless they
@@ -459,6 +462,7 @@ static DecodeSplits decode_splits(int BH, int n, size_t key_bytes) {
     const int len4 = (n + 63) / 64, steps = (int)((key_bytes + 16383) / 16384);
     if (BH > 256) { const int s = (1024 + BH - 1) / BH; return {s < 1 ? 1 : s < len4 ? s : len4, 4, false}; }
     const int most = key_bytes < 400 * 1024 ? 16 : key_bytes < 2560 * 1024 ? 32 : DECODE_MAX_SPLITS, lim = most < steps ? most : steps;
+    if (BH >= 64 && BH * key_bytes >= (size_t)120 << 20) return {1024 / BH, 8, true};
     auto load = [&](int s) { return (s * BH + 255) / 256; };                   // workgroups of the fullest CU
     int s8 = 256 / BH < lim ? 256 / BH : lim;
     if (len4 <= 16 && len4 * BH <= 512) return load(len4) * s8 <= load(s8) * len4 ? DecodeSplits{len4, 4, true} : DecodeSplits{s8, 8, true};

@@ -19,8 +19,8 @@ pytestmark = pytest.mark.gpu
     ("bf16", 128, 1, 2, 129), ("bf16", 128, 1, 2, 256), ("bf16", 128, 1, 2, 257), ("bf16", 64, 1, 3, 512), ("bf16", 64, 1, 3, 513),
     ("bf16", 128, 4, 16, 352), ("bf16", 128, 4, 16, 353), ("bf16", 128, 7, 16, 512), ("bf16", 128, 7, 16, 513),
     ("fp32", 128, 1, 2, 176), ("fp32", 128, 1, 2, 177), ("fp32", 64, 1, 2, 352), ("fp32", 64, 1, 2, 353), ("fp32", 128, 7, 16, 256), ("fp32", 128, 7, 16, 257),
-    # sixty splits; seven of four waves; a second launch's merge
-    ("bf16", 128, 1, 1, 10300), ("bf16", 128, 3, 43, 600), ("bf16", 64, 3, 100, 1030)])
+    # sixty splits; seven of four waves; caches as large as the Infinity Cache; a second launch's merge
+    ("bf16", 128, 1, 1, 10300), ("bf16", 128, 3, 43, 600), ("fp32", 128, 4, 16, 3841), ("bf16", 64, 3, 100, 1030)])
 def test_one_step_from_random_caches(dtype, d, B, H, n, gates):
     import torch
     import paper_2505_16381_amd as pa
