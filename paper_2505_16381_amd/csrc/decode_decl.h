@@ -54,10 +54,17 @@ struct CarryArgs {
 // Chunk by chunk for few heads or short prompts: it does every product of a chunk's way for that chunk alone, in a chain of
 // light steps on many CUs, where the other kernels run one chain of heavy steps per super-block or head and share the
 // products.  The line, in products plus two per workgroup for its start, lies where both take as long; us, chunk by chunk
-// against the others: d = 128, 16 heads of 1000 tokens (2432) 15.1 / 37.4, of 4000 (3528) 21.8 / 36.1, 32 of 1000 (4864)
-// 28.5 / 40.7, 64 of 2048 (5120) 33.5 / 34.4, 32 of 4096 (7168) 40.0 / 37.8, 64 of 1000 (9728) 47.0 / 44.8; d = 64, 64 of
-// 1000 (9728) 16.3 / 19.6, 128 of 1000 (19456) 26.5 / 23.9, 32 of 8192 (22528) 32.0 / 27.7.
-inline bool carry_pays(int BH, int NC, int blocks, int d) { return (long long)BH * NC * (blocks + 3) / 2 <= (d == 64 ? 14000 : 6000); }
+// against the others: d = 128, 16 heads of 1000 tokens (2432) 14.6 / 37.1, 135 of 500 (5940) 30.2 / 30.0, 132 of 1100 (5940) 33.4 /
+// 34.8, 74 of 2048 (5920) 32.4 / 34.9, 14 of 6000 (5922) 29.3 / 40.9; d = 64, 163 of 1500 (9780) 22.7 / 25.3, 198 (11880) 26.6 / 26.7, 79 of
+// 3143 (13825) 26.6 / 25.0.  One super-block at d = 64: up to 230 heads the others take as long as their one chain of chunks, 159 of
+// 500 (6996) 13.5 / 12.1, 132 of 715 (11880) 17.5 / 16.1, 91 of 1000 (13832) 19.4 / 20.0; above, with a second round of workgroups, 315 of
+// 500 (13860) 22.3 / 24.7, 693 of 300 (13860) 25.4 / 46.9.
+inline bool carry_pays(int BH, int NC, int blocks, int d) {
+    const long long work = (long long)BH * NC * (blocks + 3) / 2;
+    if (d == 128) return work <= 6000;
+    if (blocks < NC) return work <= 12000;
+    return work <= (BH <= 230 && NC > 3 ? 900 * NC - 600 : 14000);
+}
 hipError_t launch_key_carry(const CarryArgs& a, int d, hipStream_t st);
 
 hipError_t launch_key_prefill(const PrefillArgs& a, int BH, int d, int is_bf16, hipStream_t st);

@@ -6,11 +6,12 @@
 // longer one (second-level keys, super-block products).  One workgroup per (chunk, head): two waves of 32 keys each keep
 // them transposed in registers (fp32, lane = key) with the packed copy as the operand, as the forward sweep keeps its
 // queries; -dP_j is wanted with rows a and contraction b and is read out of the sweep's tile (rows b, contraction a) with
-// transposing LDS reads.  Four more waves bring the tiles, up to three ahead: a transposing read waits for every copy that
+// transposing LDS reads.  Four more waves bring the tiles, one (d = 64: three) ahead: a transposing read waits for every copy that
 // its own wave has in flight.
 //
 // What bounds it: the chain of products, 0.8 us each at d = 128 (32 products of one wave are 0.5), and the products' way
-// through L2 when there are many heads.  The prefill of a prompt of 16 heads and 1000 tokens, d = 128: 37.4 -> 15.1 us (one chain
+// through L2 when there are many heads.  At d = 128 two places for tiles, so that a second workgroup shares the CU, are ahead of four
+// throughout: 132 heads of 1100 tokens 33.4 / 40.5 us, 300 of 200 23.1 / 27.0, 19 of 1000 19.2 / 20.2.  The prefill of a prompt of 16 heads and 1000 tokens, d = 128: 37.4 -> 15.1 us (one chain
 // of 16 chunks per head before), of 2000 tokens 27.9 -> 9.6.  It rounds once per block the keys where the chains round the
 // product of the blocks: against the recurrence in 64 bits 1.727e-3 of the keys' norm instead of 1.807e-3 (1000 tokens; the
 // rounding to bf16 alone is 1.652e-3), d = 64 1.737e-3 / 1.916e-3, 2100 tokens 1.815e-3 / 1.831e-3.
@@ -22,7 +23,7 @@ namespace path {
 template <typename TIO, int D> struct CarryCfg {
     typedef typename Compute<TIO>::type T;
     static_assert(sizeof(T) == 2, "transposing reads");
-    static constexpr int DPF = D * D / Tr<T>::FE, NBUF = 4, NT = 384;
+    static constexpr int DPF = D * D / Tr<T>::FE, NBUF = D == 128 ? 2 : 4, NT = 384;      // (d = 128: two workgroups per CU)
     static constexpr size_t smem_bytes = (size_t)NBUF * DPF * 16;
 };
 
@@ -50,8 +51,8 @@ __global__ __launch_bounds__((CarryCfg<TIO, D>::NT)) void key_carry_kernel(Carry
         for (int j = j0; j < nblk && j < j0 + NBUF - 1; ++j) issue(j);
         for (int j = j0; j < nblk; ++j) {
             const int ahead = nblk - 1 - j;                      // tile j has landed: so many may be on their way behind it
-            if (ahead >= 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * PER) : "memory");
-            else if (ahead == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PER) : "memory");
+            if (NBUF > 3 && ahead >= 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * PER) : "memory");
+            else if (NBUF > 2 && ahead >= 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PER) : "memory");
             else copies_landed();
             lds_barrier();                                       // ... for everybody, and tile j - 1 has been read
             if (j + NBUF - 1 < nblk) issue(j + NBUF - 1);
