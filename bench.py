@@ -52,17 +52,9 @@ def path_extra_flops(B, H, L, d):
     return (prep + prep2 + 2.0 * CHUNK * d * d * upd) * B * H
 
 
-def pair_counts(L):
-    """(near, far) query-key pairs per head of the backward's key-side kernels: near = keys in the query's own
-    super-block but left of its chunk; far = keys in super-blocks left of the query's."""
-    nc = -(-L // CHUNK)
-    near = far = 0
-    for c in range(nc):
-        nq = min(CHUNK, L - c * CHUNK)
-        jsb = (c // SBC) * SBC
-        near += nq * (c - jsb) * CHUNK
-        far += nq * jsb * CHUNK
-    return near, far
+def far_pair_count(L):
+    """Query-key pairs per head of the backward's far key-side kernel: keys in super-blocks left of the query's."""
+    return sum(min(CHUNK, L - c * CHUNK) * (c // SBC) * SBC * CHUNK for c in range(-(-L // CHUNK)))
 
 
 def measured_mfma_peak(torch, pa, dev, random_operands=False):
@@ -358,8 +350,11 @@ def main():
 
     # One training step = the training pair: forward and backward share the backward-sized workspace, so the
     # chunk transform runs once per step (forward-only runs use the plain forward and its smaller workspace).
-    BWD_STAGES = (("scan", pa.PATH_BWD_STAGE_SCAN), ("keys_near", pa.PATH_BWD_STAGE_KEYS_NEAR), ("keys_far", pa.PATH_BWD_STAGE_KEYS_FAR),
-                  ("ddp", pa.PATH_BWD_STAGE_DDP), ("chunk", pa.PATH_BWD_STAGE_CHUNK))
+    # (bf16: the near key-side sums run inside the last stage, and there is no launch for the products' gradients)
+    near, ddp, chunk = pa.PATH_BWD_STAGE_KEYS_NEAR, pa.PATH_BWD_STAGE_DDP, pa.PATH_BWD_STAGE_CHUNK
+    BWD_STAGES = ((("scan", pa.PATH_BWD_STAGE_SCAN), ("keys_far", pa.PATH_BWD_STAGE_KEYS_FAR), ("keys_near_and_chunk", near | ddp | chunk))
+                  if cfg["dtype"] == "bf16" else
+                  (("scan", pa.PATH_BWD_STAGE_SCAN), ("keys_near", near), ("keys_far", pa.PATH_BWD_STAGE_KEYS_FAR), ("ddp", ddp), ("chunk", chunk)))
     grads = [torch.empty_like(t["q"]) for _ in range(4)] + [torch.empty_like(t["beta"])] if do_bwd else None
 
     def step(record):
@@ -422,7 +417,7 @@ def main():
     # Roofline of the dominant kernel of the timed step.  The stages that are ONE kernel launch each are the sweep
     # and the far key-side pass; their algorithmic flops: sweep 4d per (query, key <= query) pair; key-side 8d
     # per pair of its range (logit and dP recomputed, dV and dK accumulated: four d-long dot products).
-    _, far_pairs = pair_counts(L)
+    far_pairs = far_pair_count(L)
     single = {"attn_fwd2_kernel (forward sweep" + ("; in the training pair it also writes the backward's query states)" if do_bwd else ")"):
               (sweep_ms, fl_f, "4*d flops per (query, key <= query) pair")}
     if do_bwd:
