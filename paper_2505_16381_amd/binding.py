@@ -177,7 +177,10 @@ def _dt_of(t):
 def _stream_handle(stream):
     if stream is None:      # the current stream of the current device (torch.cuda.current_stream() makes an object of it: 2.7 us of a call)
         import torch
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        try:
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        except AttributeError:      # (names that torch does not promise)
+            stream = torch.cuda.current_stream()
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
