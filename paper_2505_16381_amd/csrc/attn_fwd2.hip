@@ -63,8 +63,10 @@ __device__ __forceinline__ void wait_tiles_and_sync() {
 // FEW (no more workgroups than CUs, 16-bit operands): four more waves make the tile copies, three stages ahead, where
 // otherwise every wave makes them one stage ahead, 70 cycles a copy, and waits: a stage is then as long as the latency of a
 // copy, with nothing else on the SIMD.  The sweep of 16 heads of 1000 tokens, d = 128: 46 -> 36 us; forward of 8 heads of 4000
-// tokens 183 -> 160.  With a second workgroup for every CU the other form is ahead (its LDS leaves room for two at d = 128:
-// one head of 16384 tokens, 128 workgroups on the 32 CUs of one XCD, 602 / 679 us).
+// tokens 183 -> 160.  Not with more workgroups than CUs: at d = 128 its LDS leaves room for one on a CU, and for two of the other
+// form.  (One head's 128 workgroups on the 32 CUs of one XCD, while one XCD had all of a head: 16384 tokens 679 us, 602 in the other
+// form.)  A ring's own segment and hop still take the other form.  They would gain alike: own segment of 8 heads of 2048 tokens, d = 128,
+// 119 / 106 us, its hop 51 / 44; of one head of 8192, d = 64, 163 / 134 and 131 / 103.
 template <typename TIO, int D, bool FOX, bool EMIT, int RING = 0, bool FEW = false>
 __global__ __launch_bounds__((FEW ? 2 * FWD2_THREADS : FWD2_THREADS), (512 / FWD2_THREADS)) void attn_fwd2_kernel(FwdParams p) {
     using C = Fwd2Cfg<TIO, D>;
@@ -150,7 +152,7 @@ __global__ __launch_bounds__((FEW ? 2 * FWD2_THREADS : FWD2_THREADS), (512 / FWD
     const T* dpg = reinterpret_cast<const T*>(p.dp) + (size_t)bh * NC * D * D;
     const T* dp2g = reinterpret_cast<const T*>(p.dp2) + (size_t)bh * nsb * D * D;
 
-    // Stage u = 0, 1, ...: chunk j = jtop - u/2, key half kb = u % 2, LDS buffer u % 2.
+    // Stage u = 0, 1, ...: chunk j = jtop - u/2, key half kb = u % 2, LDS buffer u % NST.
     const int nstage = 2 * (jtop + 1);
     const int ctid = FEW ? tid - FWD2_THREADS : tid, cwv = FEW ? wv - FWD2_THREADS / 64 : wv;      // among the threads that copy
     auto issue_kv = [&](int u) {
@@ -414,7 +416,7 @@ __global__ __launch_bounds__((FEW ? 2 * FWD2_THREADS : FWD2_THREADS), (512 / FWD
     const int tq = cq * CHUNK + 32 * qb + l32;
     // A lane holds pieces of four components, 4h of every eight; with 16-bit results the two halves of the wave exchange
     // every other one, so that each stores eight at a time (16 bytes: half as many stores.  Whole forward, 512 heads of 300
-    // tokens, d = 128 211.4 -> 207.7 us; 128 heads of 2048, d = 64 276 -> 272; 16 heads of 1000, d = 128 55.9 -> 55.4).
+    // tokens, d = 128 211.4 -> 207.7 us; 128 heads of 2048, d = 64 273.0 -> 270.1, within what two runs differ by).
     typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
     union { Vec4 v4[4]; u32x4 v8[2]; unsigned w[8]; } out[DB];
 #pragma unroll

@@ -15,8 +15,9 @@
 //   4. bwd_far (bwd_keys.hip) and the near sums of chunk_fused (chunk_adj.hip; fp32 operands: bwd_keyside2 / bwd_ddp): per key chunk j, over query chunks i > j (no atomics):
 //        dV_j += P^T dO_i,  dKb_j += dS^T Xs(i,j),  ddP_j -= Xs(i,j)^T g(i,j-1).
 //   5. adjoint of the second level (dKb2, ddP2 -> dKb, ddP) and of the chunk transform
-//      (Qb, Kb, dP, Sd -> q, k, w, beta): fused kernels (chunk_adj.hip); fp32 operands: short sequences of
-//      batched products (batched_gemm) and elementwise steps, driven from the host code.
+//      (Qb, Kb, dP, Sd -> q, k, w, beta): fused kernels (chunk_adj.hip).  fp32 operands: the second level as a
+//      sequence of batched products (batched_gemm) driven from the host code, and at d = 128 the chunk transform as a
+//      list of products and elementwise steps (chunk_adjoint_kernel).
 //
 // Steps 3 and 4 follow the forward's scheme: activations stay in registers in
 // transposed form, streamed operands are fragment-order tiles (written by prep, the

@@ -449,8 +449,9 @@ hipError_t launch_key_prefill(const PrefillArgs& a, int BH, int d, int is_bf16, 
 // workgroups, where that divides better from 96 heads on: gated, 140 of 1827 7 (980) 36.3, eight waves 3 (420) 37.1; 200 of 2000 5
 // (1000) 52.8, 2 (400) 54.8.
 // Where keys and values are as large as the Infinity Cache, four workgroups per CU in two rounds: in one round some lengths bring
-// the workgroups' addresses into step, 64 heads of 8192 keys in caches of 8256 87.7 us, of 8000 in 8256 86.8, in two 84.0, 83.6.  (Else
-// they are level: 8192 in 8200 84.6 / 82.9, in 9192 85.2 / 85.3, 7000 in 7064 70.5 / 71.8; 64 heads of 4096 36.1 / 38.)
+// the workgroups' addresses into step: three caches in turn, 64 heads of 8192 keys in caches of 8256 88 us, of 8000 in 8256 88, in two
+// 84 both; else they are level (8192 in 8200 84.6 / 83.1, in 9192 85.5 / 85.0; of 7000 keys 70.6 / 72.1).  One cache step after step, part of
+// which stays in the Infinity Cache, is ahead in one round (66 / 68.4), and so is everything smaller (64 heads of 4096 36 / 41).
 // A split has a step of its waves to do, 16 KB of keys, and no more of them are taken than pay for their merge: one head,
 // replayed, 350 KB of keys 15 splits 7.0 us, 32 7.2; fp32 1400 KB 32 8.1, 44 8.2; 8 MB 60 12.9, 32 15.8.  Short and few heads: splits of
 // four waves and 64 keys, which start on more CUs (one head of 577 keys, d = 64, 10 of four waves 6.5 us, 5 of eight 6.9), unless they
