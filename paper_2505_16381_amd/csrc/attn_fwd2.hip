@@ -60,13 +60,13 @@ __device__ __forceinline__ void wait_tiles_and_sync() {
 // 2 = one hop: the registers are loaded, all chunks of an earlier segment are swept as "far" blocks (second-level
 // keys, one product per super-block, the first one's included), and the registers are stored again.
 //
-// FEW (no more workgroups than CUs, 16-bit operands): four more waves make the tile copies, three stages ahead, where
+// FEW (no more workgroups than CUs, 16-bit operands, ring or not): four more waves make the tile copies, three stages ahead, where
 // otherwise every wave makes them one stage ahead, 70 cycles a copy, and waits: a stage is then as long as the latency of a
 // copy, with nothing else on the SIMD.  The sweep of 16 heads of 1000 tokens, d = 128: 46 -> 36 us; forward of 8 heads of 4000
 // tokens 183 -> 160.  Not with more workgroups than CUs: at d = 128 its LDS leaves room for one on a CU, and for two of the other
 // form.  (One head's 128 workgroups on the 32 CUs of one XCD, while one XCD had all of a head: 16384 tokens 679 us, 602 in the other
-// form.)  A ring's own segment and hop still take the other form.  They would gain alike: own segment of 8 heads of 2048 tokens, d = 128,
-// 119 / 106 us, its hop 51 / 44; of one head of 8192, d = 64, 163 / 134 and 131 / 103.
+// form.)  A ring's own segment and hop gain alike: transforms and own segment of 8 heads of 2048 tokens, d = 128, 119.4 -> 105.1, its
+// hop 50.8 -> 43.4; of one head of 8192, d = 64, 163 -> 133 and 130 -> 102; 32 of 1024, d = 128, 112 -> 103 and 34.1 -> 30.8.
 template <typename TIO, int D, bool FOX, bool EMIT, int RING = 0, bool FEW = false>
 __global__ __launch_bounds__((FEW ? 2 * FWD2_THREADS : FWD2_THREADS), (512 / FWD2_THREADS)) void attn_fwd2_kernel(FwdParams p) {
     using C = Fwd2Cfg<TIO, D>;
@@ -206,10 +206,10 @@ __global__ __launch_bounds__((FEW ? 2 * FWD2_THREADS : FWD2_THREADS), (512 / FWD
         }
     }
     // FEW: the raw logits of the own chunk, which a wave would otherwise wait for when it gets there
-    f32x4 diag_pre[FEW ? 2 : 1][4];
-    if (FEW && active) {
+    f32x4 diag_pre[FEW && RING != 2 ? 2 : 1][4];
+    if (FEW && RING != 2 && active) {
 #pragma unroll
-        for (int kb = 0; kb < (FEW ? 2 : 1); ++kb)
+        for (int kb = 0; kb < (FEW && RING != 2 ? 2 : 1); ++kb)
 #pragma unroll
             for (int g = 0; g < 4; ++g)
                 diag_pre[kb][g] = *reinterpret_cast<const f32x4*>(p.sd + ((size_t)bh * NC + cq) * 4096 + ((size_t)qb * 2 + kb) * 1024 + g * 256 + lane * 4);
@@ -253,7 +253,7 @@ __global__ __launch_bounds__((FEW ? 2 * FWD2_THREADS : FWD2_THREADS), (512 / FWD
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
                 f32x4 v4;
-                if constexpr (FEW) v4 = diag_pre[decltype(tag)::value & 1][g];
+                if constexpr (FEW && RING != 2) v4 = diag_pre[decltype(tag)::value & 1][g];
                 else v4 = *reinterpret_cast<const f32x4*>(diag + g * 256 + lane * 4);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
@@ -466,7 +466,7 @@ hipError_t launch_attn_fwd2_f(const FwdParams& p, hipStream_t stream) {
     const int ntiles = ((RING == 2 ? p.NCq : p.NC) + FWD2_CPT - 1) / FWD2_CPT;
     const int BH = p.B * p.H;
     dim3 grid(xcd_deal_grid(ntiles, BH));
-    if constexpr (RING == 0 && !FEW && sizeof(TIO) == 2) {
+    if constexpr (!FEW && sizeof(TIO) == 2) {
         // one workgroup or none for each of the 32 CUs of an XCD
         if (grid.x <= 256) return launch_attn_fwd2_f<TIO, D, FOX, EMIT, RING, true>(p, stream);
     }

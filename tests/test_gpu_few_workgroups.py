@@ -33,3 +33,38 @@ def test_heads_by_themselves_and_among_many(d, L, few, many, gates):
 
     for p, q in zip(run(slice(many - few, many)), run(slice(0, many))):
         assert torch.isfinite(p).all() and torch.equal(p, q[:, many - few:])
+
+
+@pytest.mark.parametrize("gates", [False, True])
+@pytest.mark.parametrize("d,L,few,many", [(128, 64, 1, 260), (64, 192, 3, 136), (128, 1088, 2, 32), (64, 2112, 4, 24)])
+def test_ring_of_heads_by_themselves_and_among_many(d, L, few, many, gates):
+    """Own segment and one hop (over a segment of another length), likewise."""
+    import torch
+    import paper_2505_16381_amd as pa
+    gen = torch.Generator(device="cuda").manual_seed(7 * L + d)
+    rn = lambda *s: torch.randn(*s, device="cuda", generator=gen)
+    Lk = L + 64
+
+    def segment(n):
+        return [rn(1, many, n, d).bfloat16() for _ in range(3)] + [torch.nn.functional.normalize(rn(1, many, n, d), dim=-1).bfloat16(),
+                (2 * torch.sigmoid(rn(1, many, n))).bfloat16(), torch.nn.functional.logsigmoid(rn(1, many, n) + 2).bfloat16()]
+
+    own, earlier = segment(L), segment(Lk)
+    tiles = -(-L // 128)
+    assert few < 8 and many * tiles > 256 >= few * (tiles + 7)
+
+    def run(sel):
+        H = len(range(many)[sel])
+        nan = lambda n: torch.full((n,), 255, dtype=torch.uint8, device="cuda")
+        ws = [nan(pa.path_attn_workspace_bytes(1, H, n, d, pa.PATH_BF16, False)) for n in (L, Lk)]
+        st = [nan(pa.path_attn_ring_state_bytes(1, H, n, d)) for n in (L, Lk)]
+        for i, seg in enumerate((own, earlier)):
+            a = [t[:, sel].contiguous() for t in seg]
+            pa.path_attn_ring_local(*a[:5], st[i], ws[i], log_f=a[5] if gates else None, scale=d ** -0.5)
+        pa.path_attn_ring_hop(st[0], 1, H, L, ws[1], Lk, d, pa.PATH_BF16, with_gates=gates, scale=d ** -0.5)
+        o, lse = torch.empty(1, H, L, d, dtype=torch.bfloat16, device="cuda"), torch.empty(1, H, L, device="cuda")
+        pa.path_attn_ring_finish(st[0], o, lse, gates_workspace=ws[0] if gates else None)
+        return o, lse
+
+    for p, q in zip(run(slice(many - few, many)), run(slice(0, many))):
+        assert torch.isfinite(p).all() and torch.equal(p, q[:, many - few:])
