@@ -461,6 +461,7 @@ static path_status_t bwd_run(BwdMode mode, int stages, const UserLayout& ul, con
     fp.ktT = base + ws.ktT; fp.vk = base + ws.vk; fp.dpt = base + ws.dpt; fp.xs = base + ws.xs; fp.xsT = base + ws.xsT;
     fp.fm = base + ws.fm; fp.gktm = base + ws.gktm; fp.nm = base + ws.nm; fp.aim = base + ws.aim;
     fp.ytm = base + ws.ytm; fp.utm = base + ws.utm; fp.gm = bf || d == 64 ? nullptr : F(ws.gm); fp.sdm = bf || d == 64 ? nullptr : F(ws.sdm);
+    if (mode == BWD_FULL && bf) fp.vt = nullptr;      // (the sweep's values: a backward by itself has no reader for them)
     float* cum = log_f ? F(ws.f.cum) : nullptr;
     if (mode != BWD_RESUME && mode != BWD_FWD_SWEEP) {
         if (log_f && !hip_ok(launch_gate_sums(log_f, ul, cum, B, H, L, dt, st), "gate sums (backward)")) return PATH_ERR_HIP;

@@ -13,6 +13,7 @@
 //
 // The triangular system is solved by forward substitution in fp32 (never
 // through 1/beta, so beta = 0 is regular); everything else is MFMA.
+// This file: fp32 operands (16-bit operands: prep16_fwd.hip).
 // Outputs go to the workspace in the layouts the sweep kernel consumes
 // without any shuffling: K-tile, V^T-tile and -dP-tile in fragment order,
 // Qb and Sd in accumulator order (fp32).  Rows past L are treated as
@@ -21,63 +22,40 @@
 
 namespace path {
 
-// TIO: storage type of the inputs; T = Compute<TIO>::type: operand type of the transform.
-template <typename TIO, int D> struct PrepCfg {
-    typedef typename Compute<TIO>::type T;
+template <int D> struct PrepCfg {
+    typedef float T;
     static constexpr int FE = Tr<T>::FE;
     static constexpr int KW = Tr<T>::KW;
     static constexpr int LDD = D + FE;                 // padded length-D rows
     static constexpr int LDC = CHUNK + FE;             // padded length-64 rows
-    static constexpr int LDA = CHUNK + 4;              // fp32 solve matrix
-    static constexpr int LDH = 32 + 4;                 // fp32 32x32 helpers of the blocked inverse
+    static constexpr int LDA = CHUNK + 4;              // solve matrix
+    static constexpr int LDH = 32 + 4;                 // 32x32 helpers of the blocked inverse
     // Q and K are not staged: their operand fragments come straight from global memory (the chunk's rows are
-    // read a few times, out of L2), converted to the operand type on the way.
-    //
-    // 2-byte operands use a compact map (50 KB at d = 64: THREE workgroups per CU; 67 KB at d = 128: two), so that the
-    // barriers and the half-empty phases of one overlap the work of the others -- the kernel is a chain of short dependent
-    // phases, not a stream.  W | Gk | U^T | Y^T | N | helper of the inverse, and in turn: the fp32 matrix A and its
-    // inverse, their three 32x32 blocks, lie where U^T, Y^T and N come to lie when they are done with (N passes
-    // through registers); F, needed only by the output phase, is computed there in place of Gk.  (With the
-    // inverse beside the rest, 79 KB and two workgroups per CU at d = 64: forward at B=8, H=16, L=2048 305 us against 281,
-    // training step at L=4096 2.92 ms against 2.87; the same at d = 128.)
-    // fp32 operands keep separate blocks (N overwrites A^{-1} in place; one workgroup per CU).
-    static constexpr bool COMPACT = sizeof(T) == 2;
-    static constexpr int LDB = COMPACT ? LDH : LDA;    // pitch of the 32x32 blocks of A and A^{-1}
-    static constexpr int BLK21 = COMPACT ? 32 * LDH : 32 * LDA, BLK22 = COMPACT ? 2 * 32 * LDH : 32 * LDA + 32;     // their places
-    static constexpr int WSUT = COMPACT ? CHUNK * LDD : ((CHUNK * LDD > D * LDC) ? CHUNK * LDD : D * LDC);   // fp32: U^T re-uses W's rows
-    // element offsets (in T) -- every block is a multiple of 16 bytes
-    static constexpr size_t off_ws = 0;                               // W rows (fp32: later U^T)
-    static constexpr size_t off_gk = COMPACT ? off_ws + WSUT : off_ws + WSUT + (size_t)D * LDC + (size_t)CHUNK * LDC;     // (strictLower(W K^T))^T
-    static constexpr size_t off_wt = COMPACT ? off_gk + (size_t)CHUNK * LDC : off_ws + WSUT;    // fp32: W^T; 2-byte: U^T
-    static constexpr size_t off_f = COMPACT ? off_gk : off_wt + (size_t)D * LDC;                // F (2-byte: in Gk's place, from phase 4 on)
-    static constexpr size_t off_yt = COMPACT ? off_wt + (size_t)D * LDC : off_gk + (size_t)CHUNK * LDC;    // Y^T
-    static constexpr size_t off_nt = off_yt + (size_t)CHUNK * LDC;    // N (operand precision)
-    static constexpr bool NT_IN_XF = sizeof(T) == 4;                  // fp32: N overwrites A^{-1} in place (same shape)
-    static constexpr size_t t_elems = off_nt + (NT_IN_XF ? 0 : (size_t)CHUNK * LDC);
-    static constexpr size_t t_bytes = ((t_elems * sizeof(T) + 15) / 16) * 16;
-    static constexpr size_t a_bytes = COMPACT ? 3 * 32 * LDH * 4 : (size_t)CHUNK * LDA * 4;
-    static constexpr size_t off_af_bytes = COMPACT ? off_wt * sizeof(T) : t_bytes;                // fp32 A / solve
-    static constexpr size_t off_beta_bytes = COMPACT ? t_bytes + (size_t)32 * LDH * 4 : off_af_bytes + a_bytes;
-    static constexpr size_t off_xf_bytes = COMPACT ? off_af_bytes + a_bytes : off_beta_bytes + CHUNK * 4;   // A^{-1}, fp32
-    // the two 32x32 fp32 helpers: (A^{-1})_11^T and (A_21 (A^{-1})_11)^T; 2-byte operands: one place, the second takes
-    // the first's, fp32: in Y^T's space (Y^T is written only after the inverse is done)
-    static constexpr size_t off_xt1_bytes = COMPACT ? t_bytes : off_yt * sizeof(T);
-    static constexpr size_t off_tt_bytes = COMPACT ? off_xt1_bytes : off_xt1_bytes + (size_t)32 * LDH * 4;
-    static_assert(COMPACT || 2 * 32 * LDH * 4 <= CHUNK * LDC * sizeof(T), "helpers must fit in Y^T");
-    static_assert(!COMPACT || off_xf_bytes + a_bytes <= t_bytes, "A and its inverse lie in U^T, Y^T and N");
-    static constexpr size_t smem_bytes = COMPACT ? off_beta_bytes + CHUNK * 4 : off_xf_bytes + a_bytes;
-    static constexpr int WGS_PER_CU = COMPACT ? (D == 64 ? 3 : 2) : 1;
-    static_assert(!COMPACT || WGS_PER_CU * smem_bytes <= 160 * 1024, "LDS budget");
+    // read a few times, out of L2).  One workgroup per CU.
+    static constexpr int WSUT = (CHUNK * LDD > D * LDC) ? CHUNK * LDD : D * LDC;   // U^T re-uses W's rows
+    // element offsets -- every block is a multiple of 16 bytes
+    static constexpr size_t off_ws = 0;                               // W rows, later U^T
+    static constexpr size_t off_wt = off_ws + WSUT;                   // W^T
+    static constexpr size_t off_f = off_wt + (size_t)D * LDC;         // F
+    static constexpr size_t off_gk = off_f + (size_t)CHUNK * LDC;     // (strictLower(W K^T))^T
+    static constexpr size_t off_yt = off_gk + (size_t)CHUNK * LDC;    // Y^T
+    static constexpr size_t off_af = off_yt + (size_t)CHUNK * LDC;    // A / solve
+    static constexpr size_t off_beta = off_af + (size_t)CHUNK * LDA;
+    static constexpr size_t off_xf = off_beta + CHUNK;                // A^{-1}, overwritten by N (same shape)
+    static constexpr size_t smem_bytes = (off_xf + (size_t)CHUNK * LDA) * 4;
+    // the two 32x32 helpers, (A^{-1})_11^T and (A_21 (A^{-1})_11)^T, lie in Y^T's space (Y^T is written only after the inverse is done)
+    static constexpr size_t off_xt1 = off_yt, off_tt = off_xt1 + (size_t)32 * LDH;
+    static_assert(2 * 32 * LDH <= CHUNK * LDC, "helpers must fit in Y^T");
+    static_assert(LDC == LDA, "in-place N needs equal row pitch");
 };
 
 // BWD: also write the backward-only outputs (all of them; their pointers are set).  A compile-time
 // switch, so that the forward's instantiation carries none of that code.
-template <typename TIO, int D, bool BWD, bool STRIDED>
-__global__ __launch_bounds__(256, (PrepCfg<TIO, D>::WGS_PER_CU)) void prep_fwd_kernel(FwdParams p) {
-    using C = PrepCfg<TIO, D>;
+template <int D, bool BWD, bool STRIDED>
+__global__ __launch_bounds__(256, 1) void prep_fwd_kernel(FwdParams p) {
+    using C = PrepCfg<D>;
     using T = typename C::T;
     using Frag = typename Tr<T>::Frag;
-    using FragV = typename Tr<TIO>::Frag;
     using Vec4 = typename Tr<T>::Vec4;
     constexpr int FE = C::FE, KW = C::KW, LDD = C::LDD, LDC = C::LDC, LDA = C::LDA;
     constexpr int SPB = 32 / KW;   // slabs per 32-index block
@@ -85,24 +63,19 @@ __global__ __launch_bounds__(256, (PrepCfg<TIO, D>::WGS_PER_CU)) void prep_fwd_k
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     T* sT = reinterpret_cast<T*>(smem);
     T* Ws = sT + C::off_ws;
-    // 16-bit operands: products with W^T take their fragments from the rows of W with transposing LDS reads, and
-    // U^T has the space a transposed copy of W would need.  fp32 operands (no such read): W^T is written out,
-    // element by element, while the chunk is staged, and U^T re-uses W's rows once phase 1 is over.
-    constexpr bool WTR = sizeof(T) == 2;
+    // W^T is written out, element by element, while the chunk is staged, and U^T re-uses W's rows once phase 1 is over.
     T* Wt = sT + C::off_wt;
-    T* Ut = WTR ? Wt : Ws;
+    T* Ut = Ws;
     T* Fs = sT + C::off_f;
     T* Gk = sT + C::off_gk;
     T* Yt = sT + C::off_yt;
-    T* Nt = C::NT_IN_XF ? reinterpret_cast<T*>(smem + C::off_xf_bytes) : sT + C::off_nt;
-    static_assert(!C::NT_IN_XF || C::LDC == C::LDA, "in-place N needs equal row pitch");
-    float* Af = reinterpret_cast<float*>(smem + C::off_af_bytes);
-    float* bs = reinterpret_cast<float*>(smem + C::off_beta_bytes);
-    float* Xf = reinterpret_cast<float*>(smem + C::off_xf_bytes);
-    float* XT1 = reinterpret_cast<float*>(smem + C::off_xt1_bytes);
-    float* TT = reinterpret_cast<float*>(smem + C::off_tt_bytes);
-    constexpr int LDH = C::LDH, LDB = C::LDB, BLK21 = C::BLK21, BLK22 = C::BLK22;
-    constexpr bool COMPACT = C::COMPACT;
+    float* Af = sT + C::off_af;
+    float* bs = sT + C::off_beta;
+    float* Xf = sT + C::off_xf;
+    T* Nt = Xf;
+    float* XT1 = sT + C::off_xt1;
+    float* TT = sT + C::off_tt;
+    constexpr int LDH = C::LDH;
 
     int chunk, bh;
     chunk_and_head(p.ul, p.NC, p.B * p.H, chunk, bh);
@@ -115,18 +88,17 @@ __global__ __launch_bounds__(256, (PrepCfg<TIO, D>::WGS_PER_CU)) void prep_fwd_k
     // token stride of the caller's tensors; a compile-time constant unless the layout interleaves heads
     // (then every row address costs vector arithmetic instead of an immediate offset)
     const int TS = STRIDED ? (int)p.ul.vt : D;
-    const TIO* Qg = reinterpret_cast<const TIO*>(p.q) + rowbase;
-    const TIO* Kg = reinterpret_cast<const TIO*>(p.k) + rowbase;
-    const TIO* Vg = reinterpret_cast<const TIO*>(p.v) + rowbase;
-    const TIO* Wg = reinterpret_cast<const TIO*>(p.w) + rowbase;
-    const TIO* Bg = reinterpret_cast<const TIO*>(p.beta) + user_scl(p.ul, bh, t0);
+    const T* Qg = reinterpret_cast<const T*>(p.q) + rowbase;
+    const T* Kg = reinterpret_cast<const T*>(p.k) + rowbase;
+    const T* Vg = reinterpret_cast<const T*>(p.v) + rowbase;
+    const T* Wg = reinterpret_cast<const T*>(p.w) + rowbase;
+    const T* Bg = reinterpret_cast<const T*>(p.beta) + user_scl(p.ul, bh, t0);
 
     // V is only re-arranged (tiles V^T and, for the backward, V): the wave's elements of both, fetched at the
     // start and held in registers until the output phase.
     constexpr int NBV = (D / 32) * 2 / 4;           // 32x32 blocks of a 64 x d tile per wave
-    typedef typename Tr<TIO>::Vec4 VecIO4;
-    TIO vt_r[NBV][16];                              // V^T blocks: registers rows s, lane c
-    VecIO4 vk_r[BWD ? NBV : 1][4];                  // V blocks: registers rows c (4 consecutive per load), lane s
+    T vt_r[NBV][16];                              // V^T blocks: registers rows s, lane c
+    Vec4 vk_r[BWD ? NBV : 1][4];                  // V blocks: registers rows c (4 consecutive per load), lane s
     auto load_v = [&]() {
 #pragma unroll
         for (int i = 0; i < NBV; ++i) {
@@ -135,15 +107,15 @@ __global__ __launch_bounds__(256, (PrepCfg<TIO, D>::WGS_PER_CU)) void prep_fwd_k
 #pragma unroll
             for (int j = 0; j < 16; ++j) {
                 const int s = 32 * sb + acc_row(j, h);
-                vt_r[i][j] = (s < nvalid) ? Vg[s * TS + 32 * cb + l32] : (TIO)0.f;
+                vt_r[i][j] = (s < nvalid) ? Vg[s * TS + 32 * cb + l32] : (T)0.f;
             }
             if (BWD && p.ktT) {
                 const int s = 32 * sb + l32;
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) vk_r[i][g][r] = (TIO)0.f;
-                    if (s < nvalid) vk_r[i][g] = *reinterpret_cast<const VecIO4*>(Vg + s * TS + 32 * cb + 8 * g + 4 * h);
+                    for (int r = 0; r < 4; ++r) vk_r[i][g][r] = (T)0.f;
+                    if (s < nvalid) vk_r[i][g] = *reinterpret_cast<const Vec4*>(Vg + s * TS + 32 * cb + 8 * g + 4 * h);
                 }
             }
         }
@@ -152,24 +124,22 @@ __global__ __launch_bounds__(256, (PrepCfg<TIO, D>::WGS_PER_CU)) void prep_fwd_k
     // ---- phase 0: stage the chunk (zero rows past L) ---------------------------
     // All of a thread's loads are issued before the first conversion, so their latencies overlap.
     {
-        typedef typename Tr<TIO>::Frag FragIO;
         constexpr int NIT = CHUNK * (D / FE) / 256;
-        FragIO wr[NIT];
+        Frag wr[NIT];
 #pragma unroll
         for (int it = 0; it < NIT; ++it) {
             const int idx = tid + it * 256, row = idx / (D / FE), cf = idx % (D / FE);
-            if (row < nvalid) wr[it] = ld_frag<TIO>(Wg + row * TS + cf * FE);
+            if (row < nvalid) wr[it] = ld_frag<T>(Wg + row * TS + cf * FE);
         }
         load_v();                     // needed only at the very end: in flight during everything in between
 #pragma unroll
         for (int it = 0; it < NIT; ++it) {
             const int idx = tid + it * 256, row = idx / (D / FE), cf = idx % (D / FE);
             Frag wv_ = Tr<T>::zero();
-            if (row < nvalid) wv_ = cvt_frag<T, TIO>(wr[it]);
+            if (row < nvalid) wv_ = wr[it];
             *reinterpret_cast<Frag*>(Ws + row * LDD + cf * FE) = wv_;
-            if (!WTR)
 #pragma unroll
-                for (int e = 0; e < FE; ++e) Wt[(cf * FE + e) * LDC + row] = wv_[e];
+            for (int e = 0; e < FE; ++e) Wt[(cf * FE + e) * LDC + row] = wv_[e];
         }
     }
     if (tid < CHUNK) bs[tid] = (tid < nvalid) ? (float)Bg[tid * (int)p.ul.st] : 0.f;
@@ -185,7 +155,7 @@ __global__ __launch_bounds__(256, (PrepCfg<TIO, D>::WGS_PER_CU)) void prep_fwd_k
     auto qk_row = [&](int r) { return r < nvalid ? r : 0; };
     auto qk_ok = [&](int r) { return r < nvalid; };
     // operand fragment of row r of Q or K: the FE elements from column k on
-    auto qk_frag = [&](const TIO* base, int r, int k) { return cvt_frag<T, TIO>(ld_frag<TIO>(base + (size_t)qk_row(r) * TS + k)); };
+    auto qk_frag = [&](const T* base, int r, int k) { return ld_frag<T>(base + (size_t)qk_row(r) * TS + k); };
     // F block: rows t (Q), cols t' (W); keep t' <= t.
     auto f_block = [&]() {
         const int ar = 32 * (wv >> 1) + l32, bjj = wv & 1;
@@ -202,24 +172,8 @@ __global__ __launch_bounds__(256, (PrepCfg<TIO, D>::WGS_PER_CU)) void prep_fwd_k
     };
 
     // (W^T block cb) x (rows xr0.. of X)^T and (rows xr0.. of X) x (W^T block cb)^T, contraction over the chunk's tokens
-    auto wt_times = [&](int cb, const T* X, int xr0) {
-        if constexpr (WTR) {
-            f32x16 acc = zero16();
-            mm<T, CHUNK, true, false>(acc, Ws, LDD, 32 * cb, X, LDC, xr0, l32, h);
-            return acc;
-        } else {
-            return gemm32<T, CHUNK>(Wt, LDC, 32 * cb, X, LDC, xr0, l32, h, zero16());
-        }
-    };
-    auto times_wt = [&](const T* X, int xr0, int cb) {
-        if constexpr (WTR) {
-            f32x16 acc = zero16();
-            mm<T, CHUNK, false, true>(acc, X, LDC, xr0, Ws, LDD, 32 * cb, l32, h);
-            return acc;
-        } else {
-            return gemm32<T, CHUNK>(X, LDC, xr0, Wt, LDC, 32 * cb, l32, h, zero16());
-        }
-    };
+    auto wt_times = [&](int cb, const T* X, int xr0) { return gemm32<T, CHUNK>(Wt, LDC, 32 * cb, X, LDC, xr0, l32, h, zero16()); };
+    auto times_wt = [&](const T* X, int xr0, int cb) { return gemm32<T, CHUNK>(X, LDC, xr0, Wt, LDC, 32 * cb, l32, h, zero16()); };
 
     // ---- phase 1: products of the inputs ----------------------------------------
     // G block -> Af[t][s] = beta_t G[t][s] for s < t, else 0.
@@ -229,12 +183,11 @@ __global__ __launch_bounds__(256, (PrepCfg<TIO, D>::WGS_PER_CU)) void prep_fwd_k
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
             const int t = 32 * bi + acc_row(j, h);
-            if (!COMPACT) Af[t * LDA + s] = (s < t) ? bs[t] * acc[j] : 0.f;
-            else if (bi >= bj) Af[(bi + bj) * BLK21 + (t & 31) * LDB + l32] = (s < t) ? bs[t] * acc[j] : 0.f;
+            Af[t * LDA + s] = (s < t) ? bs[t] * acc[j] : 0.f;
             if (BWD && p.gm) p.gm[bhc * 4096 + t * 64 + s] = acc[j];
         }
     }
-    if (!COMPACT) f_block();          // (2-byte operands: at the start of phase 4, in A's place)
+    f_block();
     // Gk block: rows t' (W), cols s (K); stored transposed Gk[s][t'], keep t' > s.
     {
         f32x16 acc = zero16();
@@ -269,7 +222,7 @@ __global__ __launch_bounds__(256, (PrepCfg<TIO, D>::WGS_PER_CU)) void prep_fwd_k
     // block X_21 = -X_22 (A_21 X_11) by two fp32 MFMA products.
     if (wv < 2) {
         if (lane < 32) {
-            const int c = lane, r0 = wv ? BLK22 : 0;       // the wave's diagonal block
+            const int c = lane, r0 = wv ? 32 * LDA + 32 : 0;       // the wave's diagonal block
             float n[32];
 #pragma unroll
             for (int t = 0; t < 32; ++t) n[t] = 0.f;
@@ -278,7 +231,7 @@ __global__ __launch_bounds__(256, (PrepCfg<TIO, D>::WGS_PER_CU)) void prep_fwd_k
                 float a0 = (t == c) ? 1.f : 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
 #pragma unroll
                 for (int s4 = 0; s4 < (t + 3) / 4; ++s4) {
-                    const f32x4 a4 = *reinterpret_cast<const f32x4*>(Af + r0 + t * LDB + 4 * s4);   // zeros for s >= t
+                    const f32x4 a4 = *reinterpret_cast<const f32x4*>(Af + r0 + t * LDA + 4 * s4);   // zeros for s >= t
                     a0 -= a4[0] * n[4 * s4 + 0];
                     a1 -= a4[1] * n[4 * s4 + 1];
                     a2 -= a4[2] * n[4 * s4 + 2];
@@ -286,16 +239,16 @@ __global__ __launch_bounds__(256, (PrepCfg<TIO, D>::WGS_PER_CU)) void prep_fwd_k
                 }
                 const float acc = (a0 + a1) + (a2 + a3);
                 n[t] = acc;
-                Xf[r0 + t * LDB + c] = acc;
+                Xf[r0 + t * LDA + c] = acc;
                 if (wv == 0) XT1[c * LDH + t] = acc;
             }
         }
-    } else if (!COMPACT && wv == 2) {
+    } else if (wv == 2) {
         for (int idx = lane; idx < 32 * 32; idx += 64) Xf[(idx >> 5) * LDA + 32 + (idx & 31)] = 0.f;   // upper-right block
     }
     __syncthreads();
     if (wv == 0) {      // T = A_21 X_11, stored transposed
-        f32x16 acc = gemm32<float, 32>(Af + BLK21, LDB, 0, XT1, LDH, 0, l32, h, zero16());
+        f32x16 acc = gemm32<float, 32>(Af + 32 * LDA, LDA, 0, XT1, LDH, 0, l32, h, zero16());
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
             f32x4 v4;
@@ -306,9 +259,9 @@ __global__ __launch_bounds__(256, (PrepCfg<TIO, D>::WGS_PER_CU)) void prep_fwd_k
     }
     __syncthreads();
     if (wv == 0) {      // X_21 = -X_22 T
-        f32x16 acc = gemm32<float, 32>(Xf + BLK22, LDB, 0, TT, LDH, 0, l32, h, zero16());
+        f32x16 acc = gemm32<float, 32>(Xf + 32 * LDA + 32, LDA, 0, TT, LDH, 0, l32, h, zero16());
 #pragma unroll
-        for (int j = 0; j < 16; ++j) Xf[BLK21 + acc_row(j, h) * LDB + l32] = -acc[j];
+        for (int j = 0; j < 16; ++j) Xf[32 * LDA + acc_row(j, h) * LDA + l32] = -acc[j];
     }
     __syncthreads();
     {
@@ -317,11 +270,9 @@ __global__ __launch_bounds__(256, (PrepCfg<TIO, D>::WGS_PER_CU)) void prep_fwd_k
         const int c = tid & 63;
 #pragma unroll
         for (int it = 0; it < NX; ++it) {
-            const int t = (tid >> 6) + 4 * it, tb = it / (NX / 2), cb = c >> 5;
-            if (!COMPACT) x[it] = Xf[t * LDA + c];
-            else x[it] = tb >= cb ? Xf[(tb + cb) * BLK21 + (t & 31) * LDB + (c & 31)] : 0.f;
+            const int t = (tid >> 6) + 4 * it;
+            x[it] = Xf[t * LDA + c];
         }
-        if (COMPACT) __syncthreads();                    // (N takes the inverse's place)
 #pragma unroll
         for (int it = 0; it < NX; ++it) {
             const int t = (tid >> 6) + 4 * it;
@@ -344,7 +295,7 @@ __global__ __launch_bounds__(256, (PrepCfg<TIO, D>::WGS_PER_CU)) void prep_fwd_k
             *reinterpret_cast<Vec4*>(Yt + s * LDC + 32 * bi + 8 * g + 4 * h) = v4;
         }
     }
-    // U^T blocks: rows c (W^T), cols t (N rows).  (fp32 operands: Ut aliases Ws, all reads of Ws are done.)
+    // U^T blocks: rows c (W^T), cols t (N rows).  (Ut aliases Ws, all reads of Ws are done.)
     {
         f32x16 accU[D / 64];
 #pragma unroll
@@ -375,11 +326,6 @@ __global__ __launch_bounds__(256, (PrepCfg<TIO, D>::WGS_PER_CU)) void prep_fwd_k
             const int r = idx / VPR, c = (idx % VPR) * VE;
             __builtin_nontemporal_store(*reinterpret_cast<const RowVec*>(Gk + r * LDC + c), reinterpret_cast<RowVec*>(gk + r * 64 + c));
         }
-        if (COMPACT) __syncthreads();
-    }
-    if (COMPACT) {       // F, in Gk's place
-        f_block();
-        __syncthreads();
     }
     if (BWD && p.fm) {   // backward: keep the chunk's matrices (row-major, operand type)
         T* fm = reinterpret_cast<T*>(p.fm) + bhc * 4096;
@@ -438,11 +384,11 @@ __global__ __launch_bounds__(256, (PrepCfg<TIO, D>::WGS_PER_CU)) void prep_fwd_k
             const int cb = blk >> 1, sb = blk & 1;
             f32x16 acc = wt_times(cb, Yt, 32 * sb);
             const int s = 32 * sb + l32;
-            const TIO* krow = Kg + (size_t)qk_row(s) * TS + 32 * cb + 4 * h;
+            const T* krow = Kg + (size_t)qk_row(s) * TS + 32 * cb + 4 * h;
             const bool ok = qk_ok(s);
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
-                const VecIO4 k4 = *reinterpret_cast<const VecIO4*>(krow + 8 * g);
+                const Vec4 k4 = *reinterpret_cast<const Vec4*>(krow + 8 * g);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) acc[4 * g + r] = (ok ? (float)k4[r] : 0.f) - acc[4 * g + r];
             }
@@ -450,15 +396,14 @@ __global__ __launch_bounds__(256, (PrepCfg<TIO, D>::WGS_PER_CU)) void prep_fwd_k
             pack_block<T>(acc, fr);
 #pragma unroll
             for (int s2 = 0; s2 < SPB; ++s2) __builtin_nontemporal_store(fr[s2], &kdst[((size_t)sb * (D / KW) + cb * SPB + s2) * 64 + tile_lane<T>(lane, s2)]);
-            if (BWD && sizeof(T) == 4) {       // backward with fp32 operands only: the same keys row-major [token][c]
-                typedef typename Tr<T>::Vec4 TVec4;
+            if (BWD) {       // the same keys row-major [token][c]
                 T* kb = reinterpret_cast<T*>(p.kbm) + (bhc * CHUNK + s) * (size_t)D + 32 * cb + 4 * h;
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
-                    TVec4 o4;
+                    Vec4 o4;
 #pragma unroll
                     for (int r = 0; r < 4; ++r) o4[r] = (T)acc[4 * g + r];
-                    *reinterpret_cast<TVec4*>(kb + 8 * g) = o4;
+                    *reinterpret_cast<Vec4*>(kb + 8 * g) = o4;
                 }
             }
         }
@@ -468,13 +413,13 @@ __global__ __launch_bounds__(256, (PrepCfg<TIO, D>::WGS_PER_CU)) void prep_fwd_k
             const int cb = blk >> 1, tb = blk & 1;
             f32x16 acc = gemm32<T, CHUNK>(Ut, LDC, 32 * cb, Fs, LDC, 32 * tb, l32, h, zero16());
             const int t = 32 * tb + l32;
-            const TIO* qrow = Qg + (size_t)qk_row(t) * TS + 32 * cb + 4 * h;
+            const T* qrow = Qg + (size_t)qk_row(t) * TS + 32 * cb + 4 * h;
             const bool ok = qk_ok(t);
             // xinit: [bh][query block of 32][d block][g][lane][4]
             float* xdst = p.xinit + ((((size_t)bh * NC + chunk) * 2 + tb) * (D / 32) + cb) * 1024;
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
-                const VecIO4 q4 = *reinterpret_cast<const VecIO4*>(qrow + 8 * g);
+                const Vec4 q4 = *reinterpret_cast<const Vec4*>(qrow + 8 * g);
                 f32x4 v4;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) v4[r] = (ok ? (float)q4[r] : 0.f) - acc[4 * g + r];
@@ -482,7 +427,7 @@ __global__ __launch_bounds__(256, (PrepCfg<TIO, D>::WGS_PER_CU)) void prep_fwd_k
             }
         }
         // (e) V^T tile (rows = c, contraction = key s): plain re-layout of V.
-        FragV* vdst = reinterpret_cast<FragV*>(reinterpret_cast<TIO*>(p.vt) + bhc * (size_t)CHUNK * D);
+        Frag* vdst = reinterpret_cast<Frag*>(reinterpret_cast<T*>(p.vt) + bhc * (size_t)CHUNK * D);
 #pragma unroll
         for (int i = 0; i < NB / 4; ++i) {
             const int blk = wv + 4 * i;
@@ -490,14 +435,14 @@ __global__ __launch_bounds__(256, (PrepCfg<TIO, D>::WGS_PER_CU)) void prep_fwd_k
             f32x16 acc;
 #pragma unroll
             for (int j = 0; j < 16; ++j) acc[j] = (float)vt_r[i][j];
-            FragV fr[SPB];
-            pack_block<TIO>(acc, fr);
+            Frag fr[SPB];
+            pack_block<T>(acc, fr);
 #pragma unroll
             for (int s2 = 0; s2 < SPB; ++s2) __builtin_nontemporal_store(fr[s2], &vdst[(((size_t)sb * (D / 32) + cb) * SPB + s2) * 64 + lane]);   // [key half][d block][slab]
         }
-        if (BWD && p.dpt && sizeof(T) == 4) {
+        if (BWD && p.dpt) {
             // -dP in the transposed arrangement (rows c, contraction b) = -dP[c][b]: accumulate with rows b,
-            // lane c.  Read by the backward's adjoint scan for fp32 operands (the 16-bit one transposes in LDS).
+            // lane c.  Read by the backward's adjoint scan.
             Frag* pdst = reinterpret_cast<Frag*>(reinterpret_cast<T*>(p.dpt) + bhc * (size_t)D * D);
             constexpr int NBP = (D / 32) * (D / 32);
 #pragma unroll
@@ -516,11 +461,10 @@ __global__ __launch_bounds__(256, (PrepCfg<TIO, D>::WGS_PER_CU)) void prep_fwd_k
         if (BWD && p.ktT) {
             // ---- backward-only tiles ------------------------------------------------------------
             constexpr int QS = CHUNK / KW;
-            // ktT (rows c, contraction s) = Kb[s][c]: accumulate with rows s, lane c.  fp32 operands only: the 16-bit
-            // adjoint scan reads these fragments out of the key tile with transposing LDS reads.
+            // ktT (rows c, contraction s) = Kb[s][c]: accumulate with rows s, lane c.
             Frag* tdst = reinterpret_cast<Frag*>(reinterpret_cast<T*>(p.ktT) + bhc * (size_t)CHUNK * D);
 #pragma unroll
-            for (int i = 0; i < (sizeof(T) == 4 ? NB / 4 : 0); ++i) {
+            for (int i = 0; i < NB / 4; ++i) {
                 const int blk = wv + 4 * i;
                 const int cb = blk >> 1, sb = blk & 1;
                 f32x16 acc = times_wt(Yt, 32 * sb, cb);
@@ -537,7 +481,7 @@ __global__ __launch_bounds__(256, (PrepCfg<TIO, D>::WGS_PER_CU)) void prep_fwd_k
                 for (int s2 = 0; s2 < SPB; ++s2) __builtin_nontemporal_store(fr[s2], &tdst[((size_t)cb * QS + sb * SPB + s2) * 64 + lane]);
             }
             // vk (rows s, contraction c) = V[s][c] (I/O type): registers rows c, lane s
-            FragV* vkd = reinterpret_cast<FragV*>(reinterpret_cast<TIO*>(p.vk) + bhc * (size_t)CHUNK * D);
+            Frag* vkd = reinterpret_cast<Frag*>(reinterpret_cast<T*>(p.vk) + bhc * (size_t)CHUNK * D);
 #pragma unroll
             for (int i = 0; i < NB / 4; ++i) {
                 const int blk = wv + 4 * i;
@@ -545,8 +489,8 @@ __global__ __launch_bounds__(256, (PrepCfg<TIO, D>::WGS_PER_CU)) void prep_fwd_k
                 f32x16 acc;
 #pragma unroll
                 for (int j = 0; j < 16; ++j) acc[j] = (float)vk_r[i][j >> 2][j & 3];
-                FragV fr[SPB];
-                pack_block<TIO>(acc, fr);
+                Frag fr[SPB];
+                pack_block<T>(acc, fr);
 #pragma unroll
                 for (int s2 = 0; s2 < SPB; ++s2) __builtin_nontemporal_store(fr[s2], &vkd[((size_t)sb * (D / KW) + cb * SPB + s2) * 64 + lane]);
             }
@@ -554,30 +498,30 @@ __global__ __launch_bounds__(256, (PrepCfg<TIO, D>::WGS_PER_CU)) void prep_fwd_k
     }
 }
 
-template <typename T, int D, bool BWD, bool STRIDED>
+template <int D, bool BWD, bool STRIDED>
 hipError_t launch_prep_fwd_s(const FwdParams& p, hipStream_t stream) {
-    using C = PrepCfg<T, D>;
-    static_assert(sizeof(typename C::T) == sizeof(T), "tile sizes assume equal operand and I/O width");
+    using C = PrepCfg<D>;
     // set once per process; a function-local static is initialised under the language's own lock
-    static const hipError_t attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&prep_fwd_kernel<T, D, BWD, STRIDED>),
+    static const hipError_t attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&prep_fwd_kernel<D, BWD, STRIDED>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)C::smem_bytes);
     if (attr_err != hipSuccess) return attr_err;
     dim3 grid((unsigned)(p.NC * p.B * p.H));
-    hipLaunchKernelGGL((prep_fwd_kernel<T, D, BWD, STRIDED>), grid, dim3(256), C::smem_bytes, stream, p);
+    hipLaunchKernelGGL((prep_fwd_kernel<D, BWD, STRIDED>), grid, dim3(256), C::smem_bytes, stream, p);
     return hipGetLastError();
 }
-template <typename T, int D, bool BWD>
+template <int D, bool BWD>
 hipError_t launch_prep_fwd_b(const FwdParams& p, hipStream_t stream) {
-    return p.ul.vt != D ? launch_prep_fwd_s<T, D, BWD, true>(p, stream) : launch_prep_fwd_s<T, D, BWD, false>(p, stream);
+    return p.ul.vt != D ? launch_prep_fwd_s<D, BWD, true>(p, stream) : launch_prep_fwd_s<D, BWD, false>(p, stream);
 }
-template <typename T, int D>
+template <int D>
 hipError_t launch_prep_fwd_t(const FwdParams& p, hipStream_t stream) {
-    return p.fm ? launch_prep_fwd_b<T, D, true>(p, stream) : launch_prep_fwd_b<T, D, false>(p, stream);
+    return p.fm ? launch_prep_fwd_b<D, true>(p, stream) : launch_prep_fwd_b<D, false>(p, stream);
 }
 
+hipError_t launch_prep16_fwd(const FwdParams& p, int d, hipStream_t stream);      // 16-bit operands
 hipError_t launch_prep_fwd(const FwdParams& p, int d, int is_bf16, hipStream_t stream) {
-    if (is_bf16) return d == 64 ? launch_prep_fwd_t<bf16_t, 64>(p, stream) : launch_prep_fwd_t<bf16_t, 128>(p, stream);
-    return d == 64 ? launch_prep_fwd_t<float, 64>(p, stream) : launch_prep_fwd_t<float, 128>(p, stream);
+    if (is_bf16) return launch_prep16_fwd(p, d, stream);
+    return d == 64 ? launch_prep_fwd_t<64>(p, stream) : launch_prep_fwd_t<128>(p, stream);
 }
 
 }  // namespace path
