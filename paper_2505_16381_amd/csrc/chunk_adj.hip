@@ -35,9 +35,17 @@
 // written and read again per chunk: 743 + 1027 -> 1450 us at B=4, H=16, L=8192, d=128, 357 + 417 -> 671 at B=8, H=16, L=4096,
 // d=64, packed batch of 64 sequences of 256 .. 2048 tokens (8 heads, d = 128) 700 + 1267 -> 1460.  (Near sums alone 681 us, the
 // rest alone 892, at the first of these shapes.  With a third stage of states for the pairs the near sums take as long, and at
-// d = 64 longer.)
+// d = 64 longer.)  Of what follows the near sums most is vector instructions, in a chain: addresses, conversions, LDS stores of two
+// bytes.  With tiles turned instead of padded (lds_tile.h; no bank conflicts), addresses that leave one exclusive or per access,
+// 64 x 64 results multiplied out transposed, so that they are stored four at a time, dGs formed where M is and whole chunks stored without
+// checks of the row, the chunk stage (with sb_chain_kernel) went, us, at d = 128 from 1594 to 1499 (64 heads of 8192 tokens), 1288 to 1163
+// (512 of 1024), 42.2 to 38.2 (8 of 1000), at d = 64 from 711 to 675 (128 of 4096).  The turned tiles alone, with addresses left to the compiler,
+// gave nothing: what they saved in conflicts they cost in vector instructions.
+#include <type_traits>
+
 #include "path_common.h"
 #include "bwd_decl.h"
+#include "lds_tile.h"
 
 namespace path {
 namespace {
@@ -58,18 +66,36 @@ template <typename TIO, int D> struct NearCfg {
     static constexpr int LDX = D + 4, XV = 0, XK = CHUNK * LDX, xch_bytes = 2 * CHUNK * LDX * 4;
 };
 
+// A tile of rows of W elements in LDS: 16-bit types as in lds_tile.h, 32-bit types padded.
+template <typename T, int W> struct Tile {
+    static constexpr int PITCH = sizeof(T) == 2 ? W : W + 4;
+    static __device__ __forceinline__ int at(int row, int col) { return sizeof(T) == 4 ? row * PITCH + col : TurnedTile<W>::at(row, col); }
+};
+struct TileLanes {      // a lane's share of addresses in tiles of both widths
+    int l32, h;
+    TurnedLane<64> w64;
+    TurnedLane<128> w128;
+    __device__ __forceinline__ TileLanes(int tid) : l32(tid & 31), h((tid >> 5) & 1), w64(tid), w128(tid) {}
+    template <int W> __device__ __forceinline__ const TurnedLane<W>& of() const {
+        if constexpr (W == 64) return w64; else return w128;
+    }
+};
+typedef __attribute__((address_space(3))) unsigned char LdsByte;
+template <typename V> __device__ __forceinline__ V lds_read(unsigned a) { return *(__attribute__((address_space(3))) const V*)(LdsByte*)(uintptr_t)a; }
+template <typename V> __device__ __forceinline__ void lds_write(unsigned a, V v) { *(__attribute__((address_space(3))) V*)(LdsByte*)(uintptr_t)a = v; }
+template <typename T> __device__ __forceinline__ unsigned lds_addr(const T* p) { return (unsigned)(uintptr_t)(__attribute__((address_space(3))) const void*)p; }
+
 template <typename TIO, int D> struct CaCfg {
     typedef typename Compute<TIO>::type T;
     static constexpr int ES = sizeof(T);
     static constexpr bool NEAR_SUMS = ES == 2;      // fp32 operands: the near sums and the second level's share are taken before
     static_assert(ES == 2 || D == 64, "fp32 tiles of d = 128 do not fit");
-    static constexpr int LDD = D + 16 / ES;          // pitch of a [..][D] tile (elements)
-    static constexpr int LDC = CHUNK + 16 / ES;      // pitch of a [..][64] tile
-    static constexpr int BIG = (64 * LDD > D * LDC ? 64 * LDD : D * LDC) * ES;   // bytes of a 64 x D or D x 64 tile
-    static constexpr int SMALL = 64 * LDC * ES;
-    static constexpr int LDM = 65;             // pitch of the fp32 copy of M
-    // byte offsets.  d = 128: W | X0 X3 (adjacent: ddP spans both, later the fp32 M) | X1 | X2 | Y0 Y1 Y2 | N | misc.
-    // d = 64, where all tiles have one size: W | X0 Y0 (adjacent: the fp32 M) | X1 | X2 | X3 = N | Y1 | Y2 | misc: 74 KB, two
+    typedef Tile<T, D> TileD;
+    typedef Tile<T, CHUNK> TileC;
+    static constexpr int LDD = D + 16 / ES;          // pitch of the second level's dKb2 rows (elements)
+    static constexpr int SMALL = 64 * TileC::PITCH * ES, BIG_ = 64 * TileD::PITCH * ES, BIG = BIG_ > D * TileC::PITCH * ES ? BIG_ : D * TileC::PITCH * ES;   // bytes of a 64 x 64, of a 64 x D or D x 64 tile
+    // byte offsets.  d = 128: W | X0 X3 (adjacent: ddP spans both) | X1 | X2 | Y0 Y1 Y2 | N | misc.
+    // d = 64, where all tiles have one size: W | X0 | Y0 | X1 | X2 | X3 = N | Y1 | Y2 | misc: two
     // workgroups per CU (with ten tiles, 92 KB and one workgroup what follows the near sums took 0.63 ms at B=8, H=16, L=4096, not
     // 0.42).
     static constexpr int XW = 0, X0 = BIG, X3 = D == 64 ? 5 * BIG : 2 * BIG, X1 = 3 * BIG, X2 = 4 * BIG;
@@ -80,8 +106,7 @@ template <typename TIO, int D> struct CaCfg {
     static constexpr int MISC = MID > NEAR ? (MID > TILES ? MID : TILES) : (NEAR > TILES ? NEAR : TILES);
     static constexpr int TOTAL = MISC + 2048;
     static constexpr int WGS_PER_CU = D == 64 && ES == 2 ? 2 : 1;
-    static_assert(D == 64 ? BIG == SMALL : D * LDD * ES <= 2 * BIG, "ddP tile must fit X0 (d = 64) or X0 and X3");
-    static_assert(64 * LDM * 4 <= 2 * BIG, "fp32 M must fit X0 and its neighbour");
+    static_assert(D == 64 ? BIG == SMALL : D * TileD::PITCH * ES <= 2 * BIG, "ddP tile must fit X0 (d = 64) or X0 and X3");
     static_assert(WGS_PER_CU * TOTAL <= 160 * 1024, "LDS budget");
 };
 
@@ -102,24 +127,89 @@ template <typename S, int ROWS, int COLS, int NT = CA_NT> struct GTile {
                 for (int e = 0; e < 8; ++e) v[u][e] = (S)0.f;
         }
     }
-    template <typename T, bool NEG> __device__ __forceinline__ void store(T* dst, int ld, int tid) const {
+    template <typename T, bool NEG> __device__ __forceinline__ auto converted(int u) const {
         typedef T TVec8 __attribute__((ext_vector_type(8)));
+        TVec8 o;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[e] = (T)(NEG ? -(float)v[u][e] : (float)v[u][e]);
+        return o;
+    }
+    template <typename T, bool NEG> __device__ __forceinline__ void store(T* dst, int ld, int tid) const {      // padded rows
 #pragma unroll
         for (int u = 0; u < NV; ++u) {
             const int idx = tid + u * NT, r = idx / (COLS / 8), c = (idx % (COLS / 8)) * 8;
-            TVec8 o;
+            const auto o = converted<T, NEG>(u);
+            *reinterpret_cast<decltype(converted<T, NEG>(0))*>(dst + r * ld + c) = o;
+        }
+    }
+    template <typename T, bool NEG> __device__ __forceinline__ void store(T* dst, int tid, const TileLanes& t) const {      // a Tile
+        if constexpr (sizeof(T) == 4) { store<T, NEG>(dst, Tile<T, COLS>::PITCH, tid); return; } else {
+        static_assert(NT == 512, "copy_at's threads");
 #pragma unroll
-            for (int e = 0; e < 8; ++e) o[e] = (T)(NEG ? -(float)v[u][e] : (float)v[u][e]);
-            *reinterpret_cast<TVec8*>(dst + r * ld + c) = o;
+        for (int u = 0; u < NV; ++u) lds_write(lds_addr(dst) + t.of<COLS>().copy_at(u), converted<T, NEG>(u));
         }
     }
 };
 
-// One 32x32 accumulator block -> LDS, stored [m][n] in the operand type.
-template <typename T>
-__device__ __forceinline__ void st_block(T* dst, int ld, int r0, int c0, const f32x16& acc, int l32, int h) {
+// One 32x32 accumulator block (rows m, lane n) -> rows r0 .., columns c0 .. of a tile [m][n], in the operand type.
+template <typename T, int W>
+__device__ __forceinline__ void st_block(T* dst, int r0, int c0, const f32x16& acc, const TileLanes& t) {
+    if constexpr (sizeof(T) == 4) {
 #pragma unroll
-    for (int jj = 0; jj < 16; ++jj) dst[(r0 + acc_row(jj, h)) * ld + c0 + l32] = (T)acc[jj];
+        for (int jj = 0; jj < 16; ++jj) dst[Tile<T, W>::at(r0 + acc_row(jj, t.h), c0 + t.l32)] = (T)acc[jj];
+    } else {
+        const unsigned a = lds_addr(dst) + t.of<W>().elem_at(r0, c0);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) lds_write(TurnedLane<W>::elem_step(a, q, r), (T)acc[4 * q + r]);
+    }
+}
+// The same of a block with rows n, lane m (the product with its operands exchanged): a quarter of the stores.
+template <typename T, int W>
+__device__ __forceinline__ void st_block_t(T* dst, int r0, int c0, const f32x16& acc, const TileLanes& t) {
+    typedef typename Tr<T>::Vec4 TVec4;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        TVec4 v4;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v4[r] = (T)acc[4 * g + r];
+        if constexpr (sizeof(T) == 4) *reinterpret_cast<TVec4*>(dst + Tile<T, W>::at(r0 + t.l32, c0 + 8 * g + 4 * t.h)) = v4;
+        else lds_write(lds_addr(dst) + t.of<W>().vec_at(r0, c0 + 8 * g), v4);
+    }
+}
+
+// The four fragments of 64 contraction indices from k0 on, of rows (TR: columns) r0 + l32 of a tile.
+template <typename T, int W, bool TR>
+__device__ __forceinline__ void tile_frags(typename Tr<T>::Frag (&f)[4], const T* X, int r0, int k0, const TileLanes& t) {
+    if constexpr (!TR) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) f[s] = lds_read<typename Tr<T>::Frag>(lds_addr(X) + t.of<W>().nat_at(r0, k0 + 16 * s));
+    } else {
+        typedef short v4s __attribute__((ext_vector_type(4)));
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            union { v4s v[2]; typename Tr<T>::Frag f; } u;
+            u.v[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)(LdsByte*)(uintptr_t)(lds_addr(X) + t.of<W>().tr_at(k0 + 16 * s, r0, 0)));
+            u.v[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s*)(LdsByte*)(uintptr_t)(lds_addr(X) + t.of<W>().tr_at(k0 + 16 * s, r0, 1)));
+            f[s] = u.f;
+        }
+    }
+}
+// acc[m][n] += sum_k A(m,k) B(n,k) as mm() in path_common.h, for operands in tiles of WA and WB columns.
+template <typename T, int K, bool TA, int WA, bool TB, int WB>
+__device__ __forceinline__ void mmt(f32x16& acc, const T* A, int ar0, const T* B, int br0, const TileLanes& t) {
+    if constexpr (sizeof(T) == 4) { mm_f32<K, TA, TB>(acc, A, Tile<T, WA>::PITCH, ar0, B, Tile<T, WB>::PITCH, br0, t.l32, t.h); return; } else {
+    // four slabs (64 contraction indices) at a time: their fragments are fetched ahead of the four products
+#pragma unroll
+    for (int k0 = 0; k0 < K; k0 += 64) {
+        typename Tr<T>::Frag fa[4], fb[4];
+        tile_frags<T, WA, TA>(fa, A, ar0, k0, t);
+        tile_frags<T, WB, TB>(fb, B, br0, k0, t);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) acc = Tr<T>::mma(fa[s], fb[s], acc);
+    }
+    }
 }
 
 // Near key-side sums, over the query chunks i right of the key's chunk j inside its own super-block, with the
@@ -132,7 +222,7 @@ __device__ __forceinline__ void st_block(T* dst, int ld, int r0, int c0, const f
 //   waves 4..7  a quarter of each sum: ddP_j of this pair, dV^T and dKb^T of the pair before (its transposed fragments
 //               stay in registers, so that two stages of tiles do).
 // The former request the next pair's tiles.  The sums stay in the registers of waves 4..7 (dV^T, dKb^T row blocks NA rb + a
-// of key half kb, -ddP blocks (NA rb + a, NA kb + b); rb = (wave - 4) / 2, kb = wave % 2), the keys' part of the gate
+// of key half kb, -ddP blocks (NA rb + a, NA kb + b), rows = second index; rb = (wave - 4) / 2, kb = wave % 2), the keys' part of the gate
 // gradient, one query half each, in dcol of waves 0..3.  tiles_read(): run by all waves when the tiles have been read for
 // the last time; the hand-over buffer of the last pair is read after that.
 template <typename TIO, int D, bool FOX, typename F>
@@ -275,7 +365,7 @@ __device__ __forceinline__ void near_sums(const ChunkFusedArgs& a, unsigned char
 #pragma unroll
             for (int a = 0; a < NA; ++a)
 #pragma unroll
-                for (int b = 0; b < NA; ++b) dd[a][b] = Tr<T>::mma(xt[a * QS + s], gf[b * QS + s], dd[a][b]);
+                for (int b = 0; b < NA; ++b) dd[a][b] = Tr<T>::mma(gf[b * QS + s], xt[a * QS + s], dd[a][b]);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int a = 0; a < NA; ++a)
@@ -300,8 +390,8 @@ template <typename TIO, int D, bool FOX, bool STRIDED>
 __global__ __launch_bounds__(CA_NT, 2 * (CaCfg<TIO, D>::WGS_PER_CU)) void chunk_fused_kernel(ChunkFusedArgs args) {
     using C = CaCfg<TIO, D>;
     typedef typename C::T T;
-    constexpr int LDD = C::LDD, LDC = C::LDC, LDM = C::LDM;
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    constexpr int LDD = C::LDD;
+    extern __shared__ __attribute__((aligned(256))) unsigned char smem[];
     T* XW = reinterpret_cast<T*>(smem + C::XW);
     T* X0 = reinterpret_cast<T*>(smem + C::X0);
     T* X1 = reinterpret_cast<T*>(smem + C::X1);
@@ -311,7 +401,6 @@ __global__ __launch_bounds__(CA_NT, 2 * (CaCfg<TIO, D>::WGS_PER_CU)) void chunk_
     T* Y1 = reinterpret_cast<T*>(smem + C::Y1);
     T* Y2 = reinterpret_cast<T*>(smem + C::Y2);
     T* YN = reinterpret_cast<T*>(smem + C::YN);
-    float* Mf = reinterpret_cast<float*>(smem + C::X0);      // fp32 M, after ddP is dead
     float* misc = reinterpret_cast<float*>(smem + C::MISC);
     float *beta_s = misc, *rdiag = misc + 64, *rowsum = misc + 128, *colsum = misc + 256, *nearcol = misc + 384;
 
@@ -371,16 +460,21 @@ __global__ __launch_bounds__(CA_NT, 2 * (CaCfg<TIO, D>::WGS_PER_CU)) void chunk_
     const bool actD = wv < 2 * NBD, act6 = D == 64 ? wv >= 4 : wv < 4;
     const int mbD = wv / NBD, cbD = wv % NBD, mb6 = (wv >> 1) & 1, cb6 = wv & 1;
 
+    // (the lane's part of an address apart, as an unsigned offset: the rest stays in scalar registers)
+    const unsigned lane_in = 4 * h * D + l32, lane_out = 4 * h * TS + l32;
     auto cin = [&](const float* g, f32x16& acc) {       // accumulator block (mbD, cbD) from a padded fp32 [64][D] tensor
 #pragma unroll
-        for (int jj = 0; jj < 16; ++jj) acc[jj] = g[(size_t)(32 * mbD + acc_row(jj, h)) * D + 32 * cbD + l32];
+        for (int jj = 0; jj < 16; ++jj) acc[jj] = (g + (32 * mbD + acc_row(jj, 0)) * D + 32 * cbD)[lane_in];
     };
     auto out_user = [&](void* base, const f32x16& acc) {   // ... to a user gradient, rows of existing tokens only
-        TIO* g = reinterpret_cast<TIO*>(base) + ubase;
+        TIO* g = reinterpret_cast<TIO*>(base) + ubase + 32 * mbD * TS + 32 * cbD;
+        if (ntok == CHUNK) {
 #pragma unroll
-        for (int jj = 0; jj < 16; ++jj) {
-            const int t = 32 * mbD + acc_row(jj, h);
-            if (t < ntok) g[t * TS + 32 * cbD + l32] = (TIO)acc[jj];
+            for (int jj = 0; jj < 16; ++jj) (g + acc_row(jj, 0) * TS)[lane_out] = (TIO)acc[jj];
+        } else {
+#pragma unroll
+            for (int jj = 0; jj < 16; ++jj)
+                if (32 * mbD + acc_row(jj, h) < ntok) (g + acc_row(jj, 0) * TS)[lane_out] = (TIO)acc[jj];
         }
     };
 
@@ -402,7 +496,11 @@ __global__ __launch_bounds__(CA_NT, 2 * (CaCfg<TIO, D>::WGS_PER_CU)) void chunk_
         if (actP) {
             const float* g = a.ddp + ((size_t)bh * NC + chunk) * D * D;
 #pragma unroll
-            for (int jj = 0; jj < 16; ++jj) dd[0][0][jj] = g[(size_t)(32 * rb + acc_row(jj, h)) * D + 32 * kb + l32];
+            for (int gg = 0; gg < 4; ++gg) {
+                const f32x4 v4 = *reinterpret_cast<const f32x4*>(g + (size_t)(32 * rb + l32) * D + 32 * kb + 8 * gg + 4 * h);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) dd[0][0][4 * gg + r] = v4[r];
+            }
         }
     } else {
         constexpr int DS = D / 16;
@@ -468,7 +566,7 @@ __global__ __launch_bounds__(CA_NT, 2 * (CaCfg<TIO, D>::WGS_PER_CU)) void chunk_
 #pragma unroll
                             for (int s = 0; s < 4; ++s) { fa[s] = ld_tile_frag_tr<T, DS>(sR, s0 + s, NA * rb + i, l32, h); fb[s] = ld_tile_frag_tr<T, DS>(sD, s0 + s, NA * kb + b, l32, h); }
 #pragma unroll
-                            for (int s = 0; s < 4; ++s) acc = Tr<T>::mma(fa[s], fb[s], acc);
+                            for (int s = 0; s < 4; ++s) acc = Tr<T>::mma(fb[s], fa[s], acc);
                         }
 #pragma unroll
                         for (int jj = 0; jj < 16; ++jj) dd[i][b][jj] -= acc[jj];
@@ -498,6 +596,8 @@ __global__ __launch_bounds__(CA_NT, 2 * (CaCfg<TIO, D>::WGS_PER_CU)) void chunk_
         __syncthreads();
     }
 
+    const TileLanes tl(tid);
+
     // ---- stage W, dO, V; per-token scalars ---------------------------------------------------
     if (tid < CHUNK) {
         beta_s[tid] = tid < ntok ? (float)reinterpret_cast<const TIO*>(a.beta)[user_scl(a.ul, bh, chunk * CHUNK + tid)] : 0.f;
@@ -514,9 +614,9 @@ __global__ __launch_bounds__(CA_NT, 2 * (CaCfg<TIO, D>::WGS_PER_CU)) void chunk_
         if (tq < ntok) lse_t = a.lse[user_scl(a.ul, bh, chunk * CHUNK + tq)];
         delta_t = a.delta[tpad + tq];
     }
-    tW.template store<T, false>(XW, LDD, tid);
-    tdO.template store<T, false>(X0, LDD, tid);
-    tV.template store<T, false>(X1, LDD, tid);
+    tW.template store<T, false>(XW, tid, tl);
+    tdO.template store<T, false>(X0, tid, tl);
+    tV.template store<T, false>(X1, tid, tl);
     f32x16 accW = zero16();
     GTile<TIO, 64, D> tQ;
     tQ.load(qg, TS, ntok, tid);
@@ -529,7 +629,7 @@ __global__ __launch_bounds__(CA_NT, 2 * (CaCfg<TIO, D>::WGS_PER_CU)) void chunk_
     // ---- dPd = dO V^T; P, dSd (diagonal block) -> Y0 = P, Y1 = dSd, both [query][key] ----------
     if (act6) {
         f32x16 acc = zero16();
-        mm<T, D, false, false>(acc, X1, LDD, 32 * mb6, X0, LDD, 32 * cb6, l32, h);
+        mmt<T, D, false, D, false, D>(acc, X1, 32 * mb6, X0, 32 * cb6, tl);
         const float cum_t = FOX ? a.cum[tpad + tq] : 0.f;
         float rsum = 0.f;
         typedef typename Tr<T>::Vec4 TVec4;
@@ -553,8 +653,8 @@ __global__ __launch_bounds__(CA_NT, 2 * (CaCfg<TIO, D>::WGS_PER_CU)) void chunk_
                 p4[r] = (T)P;
                 d4[r] = (T)ds;
             }
-            *reinterpret_cast<TVec4*>(Y0 + tq * LDC + s0) = p4;
-            *reinterpret_cast<TVec4*>(Y1 + tq * LDC + s0) = d4;
+            *reinterpret_cast<TVec4*>(Y0 + C::TileC::at(tq, s0)) = p4;
+            *reinterpret_cast<TVec4*>(Y1 + C::TileC::at(tq, s0)) = d4;
         }
         if (FOX) atomicAdd(colsum + CHUNK + tq, rsum);
     }
@@ -567,20 +667,20 @@ __global__ __launch_bounds__(CA_NT, 2 * (CaCfg<TIO, D>::WGS_PER_CU)) void chunk_
 
     // ---- dV = dV' + P^T dO ---------------------------------------------------------------------
     if (actD) {
-        mm<T, 64, true, true>(accV, Y0, LDC, 32 * mbD, X0, LDD, 32 * cbD, l32, h);
+        mmt<T, 64, true, 64, true, D>(accV, Y0, 32 * mbD, X0, 32 * cbD, tl);
         out_user(a.dv, accV);
     }
     __syncthreads();                 // dO (X0), V (X1), P (Y0) are free
-    tQ.template store<T, false>(X0, LDD, tid);
-    tY.template store<T, true>(Y0, LDC, tid);          // -Y^T as stored ([r][s])
+    tQ.template store<T, false>(X0, tid, tl);
+    tY.template store<T, true>(Y0, tid, tl);          // -Y^T as stored ([r][s])
     if (actD) {
         f32x16 neg;
 #pragma unroll
         for (int jj = 0; jj < 16; ++jj) neg[jj] = -accQ[jj];
-        st_block<T>(X1, LDD, 32 * mbD, 32 * cbD, neg, l32, h);                // -dQb
-        st_block<T>(X3, LDD, 32 * mbD, 32 * cbD, accK, l32, h);               // dKb
+        st_block<T, D>(X1, 32 * mbD, 32 * cbD, neg, tl);                // -dQb
+        st_block<T, D>(X3, 32 * mbD, 32 * cbD, accK, tl);               // dKb
     }
-    tU.template store<T, false>(X2, LDC, tid);         // U as stored: [feature][token]
+    tU.template store<T, false>(X2, tid, tl);         // U as stored: [feature][token]
     GTile<TIO, 64, D> tK;
     tK.load(kg, TS, ntok, tid);
     GTile<T, 64, 64> tF;
@@ -588,26 +688,26 @@ __global__ __launch_bounds__(CA_NT, 2 * (CaCfg<TIO, D>::WGS_PER_CU)) void chunk_
     __syncthreads();
 
     // ---- dK = dKb + dSd^T Q (kept open);  dF = tril(-dSd Y^T - dQb U^T) -> Y2 --------------------
-    if (actD) mm<T, 64, true, true>(accK, Y1, LDC, 32 * mbD, X0, LDD, 32 * cbD, l32, h);
+    if (actD) mmt<T, 64, true, 64, true, D>(accK, Y1, 32 * mbD, X0, 32 * cbD, tl);
     if (act6) {
         f32x16 acc = zero16();
-        mm<T, 64, false, true>(acc, Y1, LDC, 32 * mb6, Y0, LDC, 32 * cb6, l32, h);
-        mm<T, D, false, true>(acc, X1, LDD, 32 * mb6, X2, LDC, 32 * cb6, l32, h);
+        mmt<T, 64, true, 64, false, 64>(acc, Y0, 32 * cb6, Y1, 32 * mb6, tl);
+        mmt<T, D, true, 64, false, D>(acc, X2, 32 * cb6, X1, 32 * mb6, tl);
 #pragma unroll
         for (int jj = 0; jj < 16; ++jj)
-            if (32 * cb6 + l32 > 32 * mb6 + acc_row(jj, h)) acc[jj] = 0.f;
-        st_block<T>(Y2, LDC, 32 * mb6, 32 * cb6, acc, l32, h);
+            if (32 * cb6 + acc_row(jj, h) > 32 * mb6 + l32) acc[jj] = 0.f;
+        st_block_t<T, 64>(Y2, 32 * mb6, 32 * cb6, acc, tl);
     }
     __syncthreads();
 
     // ---- dW = dF^T Q - Y dKb (kept open) ----------------------------------------------------------
     if (actD) {
-        mm<T, 64, true, true>(accW, Y2, LDC, 32 * mbD, X0, LDD, 32 * cbD, l32, h);
-        mm<T, 64, true, true>(accW, Y0, LDC, 32 * mbD, X3, LDD, 32 * cbD, l32, h);
+        mmt<T, 64, true, 64, true, D>(accW, Y2, 32 * mbD, X0, 32 * cbD, tl);
+        mmt<T, 64, true, 64, true, D>(accW, Y0, 32 * mbD, X3, 32 * cbD, tl);
     }
     __syncthreads();                 // Q (X0) and Y (Y0) are free
-    tK.template store<T, false>(X0, LDD, tid);
-    tF.template store<T, false>(Y0, LDC, tid);
+    tK.template store<T, false>(X0, tid, tl);
+    tF.template store<T, false>(Y0, tid, tl);
     GTile<T, 64, 64> tN, tG;
     tN.load(reinterpret_cast<const T*>(a.nm) + cbase, 64, 64, tid);
     tG.load(reinterpret_cast<const T*>(a.gktm) + cbase, 64, 64, tid);
@@ -615,14 +715,14 @@ __global__ __launch_bounds__(CA_NT, 2 * (CaCfg<TIO, D>::WGS_PER_CU)) void chunk_
 
     // ---- dQ = dQb + dSd K + dF W;  dY = -(F^T dSd + W dKb^T) ----------------------------------------
     if (actD) {
-        mm<T, 64, false, true>(accQ, Y1, LDC, 32 * mbD, X0, LDD, 32 * cbD, l32, h);
-        mm<T, 64, false, true>(accQ, Y2, LDC, 32 * mbD, XW, LDD, 32 * cbD, l32, h);
+        mmt<T, 64, false, 64, true, D>(accQ, Y1, 32 * mbD, X0, 32 * cbD, tl);
+        mmt<T, 64, false, 64, true, D>(accQ, Y2, 32 * mbD, XW, 32 * cbD, tl);
         out_user(a.dq, accQ);
     }
     if (act6) {
         accY = zero16();
-        mm<T, 64, true, true>(accY, Y0, LDC, 32 * mb6, Y1, LDC, 32 * cb6, l32, h);
-        mm<T, D, false, false>(accY, XW, LDD, 32 * mb6, X3, LDD, 32 * cb6, l32, h);
+        mmt<T, 64, true, 64, true, 64>(accY, Y1, 32 * cb6, Y0, 32 * mb6, tl);
+        mmt<T, D, false, D, false, D>(accY, X3, 32 * cb6, XW, 32 * mb6, tl);
 #pragma unroll
         for (int jj = 0; jj < 16; ++jj) accY[jj] = -accY[jj];
     }
@@ -630,57 +730,57 @@ __global__ __launch_bounds__(CA_NT, 2 * (CaCfg<TIO, D>::WGS_PER_CU)) void chunk_
     tA.load(reinterpret_cast<const T*>(a.aim) + cbase, 64, 64, tid);
     tK.load(kg, TS, ntok, tid);       // K once more, for dGk K at the end
     __syncthreads();                 // K (X0), dKb (X3), dSd (Y1), dF (Y2) are free
-    if (act6) st_block<T>(Y2, LDC, 32 * mb6, 32 * cb6, accY, l32, h);     // dY
+    if (act6) st_block_t<T, 64>(Y2, 32 * mb6, 32 * cb6, accY, tl);     // dY
     if (actP) {                      // ddP [a][b] (d = 128: spans X0 and X3)
 #pragma unroll
         for (int i = 0; i < NA; ++i)
 #pragma unroll
-            for (int b = 0; b < NA; ++b) st_block<T>(X0, LDD, 32 * (NA * rb + i), 32 * (NA * kb + b), dd[i][b], l32, h);
+            for (int b = 0; b < NA; ++b) st_block_t<T, D>(X0, 32 * (NA * rb + i), 32 * (NA * kb + b), dd[i][b], tl);
     }
-    tN.template store<T, false>(YN, LDC, tid);
-    tG.template store<T, false>(Y1, LDC, tid);
+    tN.template store<T, false>(YN, tid, tl);
+    tG.template store<T, false>(Y1, tid, tl);
     __syncthreads();
 
     // ---- dU = -F^T dQb + W ddP;  dW += U ddP^T ---------------------------------------------------
     f32x16 accU = zero16();
     if (actD) {
-        mm<T, 64, true, true>(accU, Y0, LDC, 32 * mbD, X1, LDD, 32 * cbD, l32, h);
-        mm<T, D, false, true>(accU, XW, LDD, 32 * mbD, X0, LDD, 32 * cbD, l32, h);
-        mm<T, D, true, false>(accW, X2, LDC, 32 * mbD, X0, LDD, 32 * cbD, l32, h);
+        mmt<T, 64, true, D, true, 64>(accU, X1, 32 * cbD, Y0, 32 * mbD, tl);
+        mmt<T, D, true, D, false, D>(accU, X0, 32 * cbD, XW, 32 * mbD, tl);
+        mmt<T, D, true, 64, false, D>(accW, X2, 32 * mbD, X0, 32 * cbD, tl);
     }
     __syncthreads();                 // every wave is done with dQb (X1), U (X2)
-    if (actD) st_block<T>(X1, LDD, 32 * mbD, 32 * cbD, accU, l32, h);       // dU [token][feature]
-    tK.template store<T, false>(X2, LDD, tid);
+    if (actD) st_block_t<T, D>(X1, 32 * mbD, 32 * cbD, accU, tl);       // dU [token][feature]
+    tK.template store<T, false>(X2, tid, tl);
     __syncthreads();
 
     // ---- dW += N^T dU;  dN = dY Gk^T + dU W^T -> Y0 ------------------------------------------------
-    if (actD) mm<T, 64, true, true>(accW, YN, LDC, 32 * mbD, X1, LDD, 32 * cbD, l32, h);
+    if (actD) mmt<T, 64, true, 64, true, D>(accW, YN, 32 * mbD, X1, 32 * cbD, tl);
     if (act6) {
         f32x16 acc = zero16();
-        mm<T, 64, false, true>(acc, Y2, LDC, 32 * mb6, Y1, LDC, 32 * cb6, l32, h);
-        mm<T, D, false, false>(acc, X1, LDD, 32 * mb6, XW, LDD, 32 * cb6, l32, h);
-        st_block<T>(Y0, LDC, 32 * mb6, 32 * cb6, acc, l32, h);
+        mmt<T, 64, true, 64, false, 64>(acc, Y1, 32 * cb6, Y2, 32 * mb6, tl);
+        mmt<T, D, false, D, false, D>(acc, XW, 32 * cb6, X1, 32 * mb6, tl);
+        st_block_t<T, 64>(Y0, 32 * mb6, 32 * cb6, acc, tl);
     }
     __syncthreads();                 // dN visible; Gk (Y1) is free
 
     // ---- dGk = sl(N^T dY) -> Y1 ----------------------------------------------------------------------
     if (act6) {
         f32x16 acc = zero16();
-        mm<T, 64, true, true>(acc, YN, LDC, 32 * mb6, Y2, LDC, 32 * cb6, l32, h);
+        mmt<T, 64, true, 64, true, 64>(acc, Y2, 32 * cb6, YN, 32 * mb6, tl);
 #pragma unroll
         for (int jj = 0; jj < 16; ++jj)
-            if (32 * cb6 + l32 >= 32 * mb6 + acc_row(jj, h)) acc[jj] = 0.f;
-        st_block<T>(Y1, LDC, 32 * mb6, 32 * cb6, acc, l32, h);
+            if (32 * cb6 + acc_row(jj, h) >= 32 * mb6 + l32) acc[jj] = 0.f;
+        st_block_t<T, 64>(Y1, 32 * mb6, 32 * cb6, acc, tl);
     }
     __syncthreads();                 // dY (Y2) is free
-    tA.template store<T, false>(Y2, LDC, tid);
+    tA.template store<T, false>(Y2, tid, tl);
     __syncthreads();
 
     // ---- R = A^-T dN -> X1 (operand) and its diagonal (fp32) ----------------------------------------
     if (act6) {
         f32x16 acc = zero16();
-        mm<T, 64, true, true>(acc, Y2, LDC, 32 * mb6, Y0, LDC, 32 * cb6, l32, h);
-        st_block<T>(X1, LDC, 32 * mb6, 32 * cb6, acc, l32, h);
+        mmt<T, 64, true, 64, true, 64>(acc, Y0, 32 * cb6, Y2, 32 * mb6, tl);
+        st_block_t<T, 64>(X1, 32 * mb6, 32 * cb6, acc, tl);
         if (mb6 == cb6) {
 #pragma unroll
             for (int jj = 0; jj < 16; ++jj)
@@ -689,48 +789,41 @@ __global__ __launch_bounds__(CA_NT, 2 * (CaCfg<TIO, D>::WGS_PER_CU)) void chunk_
     }
     __syncthreads();
 
-    // ---- M = sl(-R N^T) -> fp32 in LDS; row sums of M o G for dbeta ----------------------------------
-    if (act6) {
-        f32x16 acc = zero16(), gacc = zero16();
-        mm<T, 64, false, false>(acc, X1, LDC, 32 * mb6, YN, LDC, 32 * cb6, l32, h);
-        mm<T, D, false, false>(gacc, XW, LDD, 32 * mb6, XW, LDD, 32 * cb6, l32, h);       // G = W W^T, as the transform forms it
+    // ---- M = sl(-R N^T);  dGs = diag(beta) M + (diag(beta) M)^T -> Y2;  row sums of M o G for dbeta ----------------
+    if (act6 && mb6 >= cb6) {
+        f32x16 acc = zero16(), gacc = zero16();           // rows n, lane m
+        mmt<T, 64, false, 64, false, 64>(acc, YN, 32 * cb6, X1, 32 * mb6, tl);
+        mmt<T, D, false, D, false, D>(gacc, XW, 32 * cb6, XW, 32 * mb6, tl);          // G = W W^T, as the transform forms it
+        const int m = 32 * mb6 + l32;
+        const float bm = beta_s[m];
+        float sum = 0.f;
 #pragma unroll
         for (int jj = 0; jj < 16; ++jj) {
-            const int m = 32 * mb6 + acc_row(jj, h), n = 32 * cb6 + l32;
-            const float mv = (n >= m) ? 0.f : -acc[jj];
-            Mf[m * LDM + n] = mv;
-            gacc[jj] *= mv;
+            const float mv = (32 * cb6 + acc_row(jj, h) >= m) ? 0.f : -acc[jj];
+            sum += gacc[jj] * mv;
+            acc[jj] = bm * mv;
         }
-        // sums over the 32 columns: in four rounds a lane passes on half of its rows, one round adds the last pair up
-        float v8[8], v4[4], v2[2];
-        const bool b4 = l32 & 16, b3 = l32 & 8, b2 = l32 & 4, b1 = l32 & 2;
+        sum += __shfl_xor(sum, 32);
+        if (h == 0) rowsum[cb6 * CHUNK + m] = sum;
+        st_block_t<T, 64>(Y2, 32 * mb6, 32 * cb6, acc, tl);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) v8[i] = (b4 ? gacc[i + 8] : gacc[i]) + __shfl_xor(b4 ? gacc[i] : gacc[i + 8], 16);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) v4[i] = (b3 ? v8[i + 4] : v8[i]) + __shfl_xor(b3 ? v8[i] : v8[i + 4], 8);
-#pragma unroll
-        for (int i = 0; i < 2; ++i) v2[i] = (b2 ? v4[i + 2] : v4[i]) + __shfl_xor(b2 ? v4[i] : v4[i + 2], 4);
-        float v = (b1 ? v2[1] : v2[0]) + __shfl_xor(b1 ? v2[0] : v2[1], 2);
-        v += __shfl_xor(v, 1);
-        if (!(l32 & 1)) rowsum[cb6 * CHUNK + 32 * mb6 + acc_row(8 * b4 + 4 * b3 + 2 * b2 + b1, h)] = v;
+        for (int jj = 0; jj < 16; ++jj) {                 // ... and its mirror image, right of the diagonal
+            const int n = 32 * cb6 + acc_row(jj, h);
+            if (n < m) Y2[C::TileC::at(n, m)] = (T)acc[jj];
+        }
     }
     __syncthreads();
 
-    // ---- dGs = diag(beta) M + (diag(beta) M)^T -> Y2;  dbeta ------------------------------------------
-    for (int idx = tid; idx < 4096; idx += CA_NT) {
-        const int r = idx >> 6, c = idx & 63;
-        Y2[r * LDC + c] = (T)(beta_s[r] * Mf[r * LDM + c] + beta_s[c] * Mf[c * LDM + r]);
-    }
+    // ---- dbeta -----------------------------------------------------------------------------------------------------
     if (tid < ntok)
-        reinterpret_cast<TIO*>(a.dbeta)[user_scl(a.ul, bh, chunk * CHUNK + tid)] = (TIO)(rowsum[tid] + rowsum[CHUNK + tid] + rdiag[tid]);
-    __syncthreads();
+        reinterpret_cast<TIO*>(a.dbeta)[user_scl(a.ul, bh, chunk * CHUNK + tid)] = (TIO)(rowsum[tid] + (tid >= 32 ? rowsum[CHUNK + tid] : 0.f) + rdiag[tid]);
 
     // ---- dK += dGk^T W;  dW += dGs W + dGk K ------------------------------------------------------------
     if (actD) {
-        mm<T, 64, true, true>(accK, Y1, LDC, 32 * mbD, XW, LDD, 32 * cbD, l32, h);
+        mmt<T, 64, true, 64, true, D>(accK, Y1, 32 * mbD, XW, 32 * cbD, tl);
         out_user(a.dk, accK);
-        mm<T, 64, false, true>(accW, Y2, LDC, 32 * mbD, XW, LDD, 32 * cbD, l32, h);
-        mm<T, 64, false, true>(accW, Y1, LDC, 32 * mbD, X2, LDD, 32 * cbD, l32, h);
+        mmt<T, 64, false, 64, true, D>(accW, Y2, 32 * mbD, XW, 32 * cbD, tl);
+        mmt<T, 64, false, 64, true, D>(accW, Y1, 32 * mbD, X2, 32 * cbD, tl);
         out_user(a.dw, accW);
     }
 }
