@@ -318,7 +318,9 @@ __global__ __launch_bounds__(256) void bwd_adjoint2_kernel(BwdParams p) {
 // The fragments of Kb^T for g^T += Kb^T dS^T are read out of the key tile itself with transposing LDS reads
 // (three tiles per step instead of four: the transposed key tiles are neither written nor copied; as a fourth
 // tile they cost 4 % of this kernel), and likewise the fragments of -dP in the arrangement (rows a, contraction b)
-// out of the forward's tile (rows b, contraction a): p.dpt / p.dpt2 point at the FORWARD's tiles here.
+// out of the forward's tile (rows b, contraction a): p.dpt / p.dpt2 point at the FORWARD's tiles here.  g is left after a block as
+// it stands, a tile with rows q, which its readers transpose (turned through the matrix unit first, as for fp32 operands: backward of
+// 128 heads of 2048 tokens, d = 64, gated 736 us, so 721).
 // d = 128: one stage; per step one request for the chunk's tiles, the state fragments of a new block fetched while those
 // are on their way.  No copy is in flight while a step computes, so the transposing reads wait for nothing.
 // d = 64 (AHEAD): a step has half the products to wait for as many requests, and two stages still
@@ -496,20 +498,15 @@ __global__ __launch_bounds__(256, 2) void bwd_adjoint2_lite_kernel(BwdParams p) 
             }
             if (AHEAD && kb == 1 && j + 1 < cq && block_start(j + 1)) read_state(j + 1);
         }
-        if (j + 1 < cq && block_start(j + 1)) {    // g after this block: tile gT (rows b, contraction q) of the pair (cq, next block)
-            Frag idf[SPB];
-            identity_frags<T>(idf, l32, h);
+        if (j + 1 < cq && block_start(j + 1)) {    // g after this block: tile (rows q, contraction b) of the pair (cq, next block)
             const size_t slot2 = ((size_t)bh * nslots + block_slot(cq, j + 1, NC)) * (size_t)CHUNK * D;
             Frag* gt = reinterpret_cast<Frag*>(reinterpret_cast<T*>(p.gs) + slot2);
 #pragma unroll
             for (int b = 0; b < DB; ++b) {
-                Frag gb[SPB];
-                pack_block<T>(Gm[b], gb);
-                const f32x16 tr = transpose32<T>(gb, idf);       // rows q, lane b
                 Frag fr[SPB];
-                pack_block<T>(tr, fr);
+                pack_block<T>(Gm[b], fr);
 #pragma unroll
-                for (int s2 = 0; s2 < SPB; ++s2) __builtin_nontemporal_store(fr[s2], &gt[((size_t)b * QS + qb * SPB + s2) * 64 + lane]);
+                for (int s2 = 0; s2 < SPB; ++s2) __builtin_nontemporal_store(fr[s2], &gt[((size_t)qb * DS + b * SPB + s2) * 64 + tile_lane<T>(lane, s2)]);
             }
         }
     }

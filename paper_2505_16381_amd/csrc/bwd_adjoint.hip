@@ -5,8 +5,8 @@
 //     S^T = Kb_j Xs^T,   dP^T = V_j dO^T,   dS^T = scale P o (dP^T - delta),   P = exp(scale S^T - lse)
 //     g^T <- (I - dP_block) g^T   where a block starts,       g^T += Kb_j^T dS^T
 //
-// The state after a block is also left, transposed through the matrix unit, as the tile gT (rows b, contraction q) of
-// the pair (i, next block) for the key-side kernels; what stands at the end is dQb.
+// The state after a block is also left, as a tile like the query states' (rows q, contraction b), of
+// the pair (i, next block) for the key-side kernels, which read it transposed; what stands at the end is dQb.
 //
 // One workgroup takes four query chunks with eight waves, two per SIMD, that meet at one barrier per 32 keys:
 //   waves 0..3  one chunk each (states and dO resident): logits, dP, the element-wise part; dS leaves as operand
@@ -47,7 +47,7 @@ __global__ __launch_bounds__(512, 2) void bwd_adjoint_kernel(BwdParams p) {
     using T = typename C::T;
     using Frag = typename Tr<T>::Frag;
     using FragV = typename Tr<TIO>::Frag;
-    constexpr int KW = Tr<T>::KW, SPB = 32 / KW, DB = D / 32, DS = D / KW, QS = CHUNK / KW;
+    constexpr int KW = Tr<T>::KW, SPB = 32 / KW, DB = D / 32, DS = D / KW;
     constexpr int KVF = C::KVF, DPF = C::DPF, STF = C::STF, HSF = C::HSF;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     Frag* const stages = reinterpret_cast<Frag*>(smem);
@@ -279,20 +279,16 @@ __global__ __launch_bounds__(512, 2) void bwd_adjoint_kernel(BwdParams p) {
         issue(j + 2);
         if (mine) add(1);
         copies_landed();
-        if (active && j + 1 < cq && block_start(j + 1)) {             // g after this block: tile gT (rows b, contraction q) of the pair (cq, next block)
-            Frag idf[SPB];
-            identity_frags<T>(idf, l32, h);
+        if (active && j + 1 < cq && block_start(j + 1)) {             // g after this block: tile (rows q, contraction b) of the pair (cq, next block)
             Frag* gt = reinterpret_cast<Frag*>(reinterpret_cast<T*>(p.gs) + tile_of(j + 1));
 #pragma unroll
             for (int b = 0; b < DB; ++b)
 #pragma unroll
                 for (int qb = 0; qb < 2; ++qb) {
-                    Frag gb[SPB], fr[SPB];
-                    pack_block<T>(Gm[b][qb], gb);
-                    const f32x16 tr = transpose32<T>(gb, idf);       // rows q, lane b
-                    pack_block<T>(tr, fr);
+                    Frag fr[SPB];
+                    pack_block<T>(Gm[b][qb], fr);
 #pragma unroll
-                    for (int s2 = 0; s2 < SPB; ++s2) __builtin_nontemporal_store(fr[s2], &gt[((size_t)b * QS + qb * SPB + s2) * 64 + lane]);
+                    for (int s2 = 0; s2 < SPB; ++s2) __builtin_nontemporal_store(fr[s2], &gt[((size_t)qb * DS + b * SPB + s2) * 64 + tile_lane<T>(lane, s2)]);
                 }
         }
         if (j + 1 < nj) lds_barrier();

@@ -34,10 +34,10 @@ namespace path {
 template <typename TIO, int D> struct FarCfg {
     typedef typename Compute<TIO>::type T;
     static constexpr int KVF = CHUNK * D / Tr<T>::FE;                 // fragments of a tile
-    static constexpr int GF = CHUNK / Tr<T>::KW * 64;                 // ... of 32 rows of a g tile
+    static constexpr int GF = CHUNK / Tr<T>::KW * 64;                 // ... of 32 columns of a g tile
     typedef FarBlocks<SBC, D> Blocks;
     static constexpr int GTF = Blocks::COLS * GF;
-    static constexpr int STF = 2 * KVF + GTF + 32;                    // a stage: xs | doq | the workgroup's rows of gT | lse2, delta
+    static constexpr int STF = 2 * KVF + GTF + 32;                    // a stage: xs | doq | the workgroup's columns of g | lse2, delta
     static constexpr int PDF = 2 * 4 * 2 * 64;                        // a hand-over buffer: (P | dS) x 4 key blocks x 2 slabs
     static constexpr size_t smem_bytes = (size_t)(3 * STF + 2 * PDF) * 16;
     static_assert(smem_bytes <= 160 * 1024, "LDS budget");
@@ -49,8 +49,8 @@ __global__ __launch_bounds__(512, 2) void bwd_far_kernel(BwdParams p) {
     using T = typename C::T;
     using Frag = typename Tr<T>::Frag;
     using FragV = typename Tr<TIO>::Frag;
-    constexpr int KW = Tr<T>::KW, SPB = 32 / KW, DB = D / 32, DS = D / KW, QS = CHUNK / KW;
-    constexpr int KVF = C::KVF, GF = C::GF, GTF = C::GTF, STF = C::STF, PDF = C::PDF;
+    constexpr int KW = Tr<T>::KW, SPB = 32 / KW, DB = D / 32, DS = D / KW;
+    constexpr int KVF = C::KVF, GTF = C::GTF, STF = C::STF, PDF = C::PDF;
     using Blocks = typename C::Blocks;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     Frag* const stages = reinterpret_cast<Frag*>(smem);
@@ -212,7 +212,7 @@ __global__ __launch_bounds__(512, 2) void bwd_far_kernel(BwdParams p) {
 #pragma unroll
                 for (int b = 0; b < NCB; ++b)
 #pragma unroll
-                    for (int u = 0; u < SPB; ++u) gf[b * SPB + u] = stages[st * STF + 2 * KVF + b * GF + (qh * SPB + u) * 64 + lane];
+                    for (int u = 0; u < SPB; ++u) gf[b * SPB + u] = ld_tile_frag_tr<T, 2 * NCB>(reinterpret_cast<const T*>(stages + st * STF + 2 * KVF), qh * SPB + u, b, l32, h);
 #pragma unroll
                 for (int a = 0; a < NR; ++a)
 #pragma unroll
@@ -262,11 +262,17 @@ __global__ __launch_bounds__(512, 2) void bwd_far_kernel(BwdParams p) {
                                                  (__attribute__((address_space(3))) void*)(buf + 2 * KVF + GTF), 16, 0, 0);
             }
         };
-        auto issue_b = [&](int i, int st) {               // doq, gT
+        auto issue_b = [&](int i, int st) {               // doq, g
             if (i >= i1) return;
             Frag* buf = stages + st * STF;
             async_copy_tile<256, KVF>(reinterpret_cast<const Frag*>(reinterpret_cast<const TIO*>(p.doq) + ((size_t)bh * NC + i) * CHUNK * D), buf + KVF, tid4, wv4);
-            async_copy_tile<256, GTF>(reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(p.gs) + slot_of(i)) + bb * GF, buf + 2 * KVF, tid4, wv4);
+            const Frag* g = reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(p.gs) + slot_of(i)) + 2 * bb * 64;      // two slabs per column block of either half
+#pragma unroll
+            for (int k = 0; k < NCB; ++k) {
+                const int n = wv4 * NCB + k;
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(g + ((n / (2 * NCB)) * DS + n % (2 * NCB)) * 64 + lane),
+                                                 (__attribute__((address_space(3))) void*)(buf + 2 * KVF + n * 64), 16, 0, 0);
+            }
         };
         issue_a(i0, 0);
         issue_b(i0, 0);

@@ -56,7 +56,7 @@ constexpr int CA_NT = 512;       // threads per workgroup (8 waves)
 template <typename TIO, int D> struct NearCfg {
     typedef typename Compute<TIO>::type T;
     static constexpr int KVF = CHUNK * D / Tr<T>::FE;                 // fragments of a tile
-    static constexpr int STF = 3 * KVF + 32;                          // a stage: xs | doq | gT | lse2, delta
+    static constexpr int STF = 3 * KVF + 32;                          // a stage: xs | doq | g | lse2, delta
     static constexpr int PDF = 2 * 2 * 4 * 64;                        // a hand-over buffer: (P | dS) x 2 key halves x 4 slabs
     // d = 64: one hand-over buffer (and a second barrier per pair), so that two workgroups share a CU.  (Of the 128 registers
     // that this leaves 6 lie in scratch, with gates up to 26, none of them inside the loop over pairs.)
@@ -357,7 +357,7 @@ __device__ __forceinline__ void near_sums(const ChunkFusedArgs& a, unsigned char
 #pragma unroll
             for (int s = 0; s < QS; ++s) {
                 xt[a * QS + s] = ld_tile_frag_tr<T, DS>(reinterpret_cast<const T*>(sX), s, NA * rb + a, l32, h);
-                gf[a * QS + s] = sX[2 * KVF + ((NA * kb + a) * QS + s) * 64 + lane];
+                gf[a * QS + s] = ld_tile_frag_tr<T, DS>(reinterpret_cast<const T*>(sX + 2 * KVF), s, NA * kb + a, l32, h);
             }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
