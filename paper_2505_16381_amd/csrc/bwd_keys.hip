@@ -255,7 +255,7 @@ __global__ __launch_bounds__(512, 2) void bwd_far_kernel(BwdParams p) {
         auto issue_a = [&](int i, int st) {               // xs, row constants
             if (i >= i1) return;
             Frag* buf = stages + st * STF;
-            async_copy_tile<256, KVF>(reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(p.xs) + slot_of(i)), buf, tid4, wv4);
+            async_copy_tile<256, KVF, false>(reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(p.xs) + slot_of(i)), buf, tid4, wv4);
             if (tid4 < 32) {    // 64 floats of lse2 (lanes 0-15) and of delta (lanes 16-31): 16 bytes per lane
                 const float* src = (tid4 < 16 ? p.lse2p : p.delta) + (size_t)bh * Lp + (size_t)i * CHUNK + 4 * (tid4 & 15);
                 __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
@@ -265,7 +265,7 @@ __global__ __launch_bounds__(512, 2) void bwd_far_kernel(BwdParams p) {
         auto issue_b = [&](int i, int st) {               // doq, g
             if (i >= i1) return;
             Frag* buf = stages + st * STF;
-            async_copy_tile<256, KVF>(reinterpret_cast<const Frag*>(reinterpret_cast<const TIO*>(p.doq) + ((size_t)bh * NC + i) * CHUNK * D), buf + KVF, tid4, wv4);
+            async_copy_tile<256, KVF, false>(reinterpret_cast<const Frag*>(reinterpret_cast<const TIO*>(p.doq) + ((size_t)bh * NC + i) * CHUNK * D), buf + KVF, tid4, wv4);
             const Frag* g = reinterpret_cast<const Frag*>(reinterpret_cast<const T*>(p.gs) + slot_of(i)) + 2 * bb * 64;      // two slabs per column block of either half
 #pragma unroll
             for (int k = 0; k < NCB; ++k) {
