@@ -15,7 +15,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-fno-honor-nans", "-mno-amdgpu-ieee",      # infinities are used, NaNs never: no canonicalisation of max operands
          "-Wno-unused-command-line-argument"]
 # per-file extras: the sweep keeps MFMA results in architectural VGPRs (two waves per SIMD, 256 registers each)
-PER_FILE = {"attn_fwd2.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+PER_FILE = {f: ["-mllvm", "-amdgpu-mfma-vgpr-form"] for f in ("attn_fwd2.hip", "attn_few.hip")}
 
 
 def build(verbose: bool = True, extra=()) -> str:

@@ -23,6 +23,7 @@
 #include <type_traits>
 
 #include "path_common.h"
+#include "sweep_parts.h"
 
 namespace path {
 
@@ -37,7 +38,6 @@ template <typename TIO, int D> struct Fwd2Cfg {
     static constexpr int HALF_FRAGS = 32 * D / FE;      // fragments of 32 keys of a key tile / V^T tile
     static constexpr int DP_FRAGS = D * D / FE;         // fragments per -dP tile
     static constexpr size_t smem_bytes = (size_t)(4 * HALF_FRAGS + DP_FRAGS) * 16 + 256;   // 2 stages x (K|V) + dP + 2 x 32 gate sums
-    static constexpr size_t smem_bytes_few = (size_t)(8 * HALF_FRAGS + 2 * DP_FRAGS) * 16 + 512;      // FEW: 4 stages, 2 x dP
 };
 
 __device__ __forceinline__ void wait_tiles_and_sync() {
@@ -59,31 +59,22 @@ __device__ __forceinline__ void wait_tiles_and_sync() {
 // edge, ready for the keys of the segment before) and stores its registers instead of writing o and lse.
 // 2 = one hop: the registers are loaded, all chunks of an earlier segment are swept as "far" blocks (second-level
 // keys, one product per super-block, the first one's included), and the registers are stored again.
-//
-// FEW (no more workgroups than CUs, 16-bit operands, ring or not): four more waves make the tile copies, three stages ahead, where
-// otherwise every wave makes them one stage ahead, 70 cycles a copy, and waits: a stage is then as long as the latency of a
-// copy, with nothing else on the SIMD.  The sweep of 16 heads of 1000 tokens, d = 128: 46 -> 36 us; forward of 8 heads of 4000
-// tokens 183 -> 160.  Not with more workgroups than CUs: at d = 128 its LDS leaves room for one on a CU, and for two of the other
-// form.  (One head's 128 workgroups on the 32 CUs of one XCD, while one XCD had all of a head: 16384 tokens 679 us, 602 in the other
-// form.)  A ring's own segment and hop gain alike: transforms and own segment of 8 heads of 2048 tokens, d = 128, 119.4 -> 105.1, its
-// hop 50.8 -> 43.4; of one head of 8192, d = 64, 163 -> 133 and 130 -> 102; 32 of 1024, d = 128, 112 -> 103 and 34.1 -> 30.8.
-template <typename TIO, int D, bool FOX, bool EMIT, int RING = 0, bool FEW = false>
-__global__ __launch_bounds__((FEW ? 2 * FWD2_THREADS : FWD2_THREADS), (512 / FWD2_THREADS)) void attn_fwd2_kernel(FwdParams p) {
+// (Few workgroups: attn_few.hip, the same bits.)
+template <typename TIO, int D, bool FOX, bool EMIT, int RING = 0>
+__global__ __launch_bounds__(FWD2_THREADS, (512 / FWD2_THREADS)) void attn_fwd2_kernel(FwdParams p) {
     using C = Fwd2Cfg<TIO, D>;
     using T = typename C::T;
     using Frag = typename Tr<T>::Frag;
     using FragV = typename Tr<TIO>::Frag;
-    using Vec4 = typename Tr<TIO>::Vec4;
     constexpr int KW = Tr<T>::KW;
     constexpr int SPB = 32 / KW, DB = D / 32, DS = D / KW;
     constexpr int HF = C::HALF_FRAGS, DPF = C::DP_FRAGS;
     constexpr bool HAS_MASTER = sizeof(T) == 2;      // fp32 operands are their own master copy
 
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    constexpr int NST = FEW ? 4 : 2, NP = FEW ? 2 : 1;
-    Frag* sKV = reinterpret_cast<Frag*>(smem);                  // [NST stages][K half | V half]
-    Frag* sP = sKV + 2 * NST * HF;                              // [NP] -dP tile
-    float* sC = reinterpret_cast<float*>(sP + NP * DPF);        // FOX: [NST stages][32] gate sums of the stage's keys
+    Frag* sKV = reinterpret_cast<Frag*>(smem);                  // [2 stages][K half | V half]
+    Frag* sP = sKV + 4 * HF;                                    // -dP tile
+    float* sC = reinterpret_cast<float*>(sP + DPF);             // FOX: [2 stages][32] gate sums of the stage's keys
 
     const int BH = p.B * p.H, NC = p.NC;            // NC: chunks per head in the workspace arrays and in the grid's numbering
     const int NCq = RING == 2 ? p.NCq : NC;         // chunks of the query side (a hop's keys belong to another segment)
@@ -99,7 +90,7 @@ __global__ __launch_bounds__((FEW ? 2 * FWD2_THREADS : FWD2_THREADS), (512 / FWD
     if (tile * FWD2_CPT >= NCown) return;
     const int cq = tile * FWD2_CPT + (wv >> 1);     // this wave's chunk
     const int qb = wv & 1;                          // ... and which 32-query half of it
-    const bool active = cq < NCown && (!FEW || wv < 4);
+    const bool active = cq < NCown;
     // (a hop sweeps every chunk of the other segment, all of them as far blocks)
     const int jtop = RING == 2 ? NC - 1 : ((tile * FWD2_CPT + FWD2_CPT - 1 < NCown) ? tile * FWD2_CPT + FWD2_CPT - 1 : NCown - 1);
     static_assert(SBC % FWD2_CPT == 0, "a tile must lie in one super-block");
@@ -152,97 +143,39 @@ __global__ __launch_bounds__((FEW ? 2 * FWD2_THREADS : FWD2_THREADS), (512 / FWD
     const T* dpg = reinterpret_cast<const T*>(p.dp) + (size_t)bh * NC * D * D;
     const T* dp2g = reinterpret_cast<const T*>(p.dp2) + (size_t)bh * nsb * D * D;
 
-    // Stage u = 0, 1, ...: chunk j = jtop - u/2, key half kb = u % 2, LDS buffer u % NST.
+    // Stage u = 0, 1, ...: chunk j = jtop - u/2, key half kb = u % 2, LDS buffer u % 2.
     const int nstage = 2 * (jtop + 1);
-    const int ctid = FEW ? tid - FWD2_THREADS : tid, cwv = FEW ? wv - FWD2_THREADS / 64 : wv;      // among the threads that copy
     auto issue_kv = [&](int u) {
         const int j = jtop - (u >> 1), kb = u & 1;
-        Frag* buf = sKV + (size_t)(u & (NST - 1)) * 2 * HF;
+        Frag* buf = sKV + (size_t)(u & 1) * 2 * HF;
         const T* kg = (j >= jsb ? ktg : kt2g) + (size_t)j * CHUNK * D;
-        async_copy_tile<FWD2_THREADS, HF>(reinterpret_cast<const Frag*>(kg) + kb * HF, buf, ctid, cwv);
-        async_copy_tile<FWD2_THREADS, HF>(reinterpret_cast<const Frag*>(vtg + (size_t)j * CHUNK * D) + kb * HF, buf + HF, ctid, cwv);
-        if (FOX && FEW) {        // 8 floats per wave: every wave makes as many copies
-            if (lane < 2)
-                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(p.cum + (size_t)bh * NC * CHUNK + (size_t)j * CHUNK + 32 * kb + 8 * cwv + 4 * lane),
-                                                 (__attribute__((address_space(3))) void*)(sC + (u & (NST - 1)) * 32 + 8 * cwv), 16, 0, 0);
-        } else if (FOX && ctid < 8)      // 32 floats, 16 bytes per lane
+        async_copy_tile<FWD2_THREADS, HF>(reinterpret_cast<const Frag*>(kg) + kb * HF, buf, tid, wv);
+        async_copy_tile<FWD2_THREADS, HF>(reinterpret_cast<const Frag*>(vtg + (size_t)j * CHUNK * D) + kb * HF, buf + HF, tid, wv);
+        if (FOX && tid < 8)      // 32 floats, 16 bytes per lane
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(p.cum + (size_t)bh * NC * CHUNK + (size_t)j * CHUNK + 32 * kb + 4 * tid),
                                              (__attribute__((address_space(3))) void*)(sC + (u & 1) * 32), 16, 0, 0);
     };
     // the product applied after chunk j (if any): loaded while the chunk's first half is
     // processed (sP is free then: the previous update ended before this stage's barrier)
     auto issue_dp = [&](int j) {
-        Frag* dst = FEW ? sP + ((jtop - j) & 1) * DPF : sP;
         if (j >= jsb) {
-            if (j < jtop && (j > 0 || RING)) async_copy_tile<FWD2_THREADS, DPF>(reinterpret_cast<const Frag*>(dpg + (size_t)j * D * D), dst, ctid, cwv);
+            if (j < jtop && (j > 0 || RING)) async_copy_tile<FWD2_THREADS, DPF>(reinterpret_cast<const Frag*>(dpg + (size_t)j * D * D), sP, tid, wv);
         } else if (j % SBC == 0 && (j > 0 || RING)) {
-            async_copy_tile<FWD2_THREADS, DPF>(reinterpret_cast<const Frag*>(dp2g + (size_t)(j / SBC) * D * D), dst, ctid, cwv);
+            async_copy_tile<FWD2_THREADS, DPF>(reinterpret_cast<const Frag*>(dp2g + (size_t)(j / SBC) * D * D), sP, tid, wv);
         }
     };
-    if constexpr (FEW) {
-        if (wv >= FWD2_THREADS / 64) {
-            // The copies, three stages ahead; a chunk's product with its second half: its place is free by then.
-            constexpr int CS = 2 * HF / FWD2_THREADS + (FOX ? 1 : 0), CP = DPF / FWD2_THREADS;      // a wave's copies per stage, per product
-            static_assert(HF % FWD2_THREADS == 0 && DPF % FWD2_THREADS == 0, "every wave makes as many copies");
-            auto issue = [&](int u) {
-                if (u >= nstage) return;
-                issue_kv(u);
-                if (u & 1) issue_dp(jtop - (u >> 1));
-            };
-            auto has_dp = [&](int j) { return (j > 0 || RING) && (j >= jsb ? j < jtop : j % SBC == 0); };
-            auto copies = [&](int u) { return u < nstage ? CS + ((u & 1) && has_dp(jtop - (u >> 1)) ? CP : 0) : 0; };
-            for (int u = 0; u < NST - 1; ++u) issue(u);
-            for (int u = 0; u < nstage; ++u) {
-                // stage u has landed: what may be on its way is the two behind it
-                const int n = copies(u + 1) + copies(u + 2);
-                if (n >= 2 * CS + CP) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * CS + CP) : "memory");
-                else if (n >= 2 * CS) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * CS) : "memory");
-                else if (n >= CS) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(CS) : "memory");
-                else copies_landed();
-                lds_barrier();               // ... for everybody, and stage u - 1 has been read
-                issue(u + NST - 1);
-            }
-            return;
-        }
-    }
-    // FEW: the raw logits of the own chunk, which a wave would otherwise wait for when it gets there
-    f32x4 diag_pre[FEW && RING != 2 ? 2 : 1][4];
-    if (FEW && RING != 2 && active) {
-#pragma unroll
-        for (int kb = 0; kb < (FEW && RING != 2 ? 2 : 1); ++kb)
-#pragma unroll
-            for (int g = 0; g < 4; ++g)
-                diag_pre[kb][g] = *reinterpret_cast<const f32x4*>(p.sd + ((size_t)bh * NC + cq) * 4096 + ((size_t)qb * 2 + kb) * 1024 + g * 256 + lane * 4);
-    }
-
     // One stage of an active wave (chunk j <= cq).  DIAG: the wave's own chunk (precomputed logits, causal mask,
-    // no state update after it), first or second half (tag 0, 1) or either (tag 2); otherwise
-    // (tag 3) a chunk further left.
+    // no state update after it); otherwise a chunk further left.
     auto stage = [&](int u, auto tag) {
-        constexpr bool DIAG = decltype(tag)::value < 3;
-        const int j = jtop - (u >> 1), kb = decltype(tag)::value < 2 ? decltype(tag)::value : u & 1;
-        const Frag* sK = sKV + (size_t)(u & (NST - 1)) * 2 * HF;
+        constexpr bool DIAG = decltype(tag)::value;
+        const int j = jtop - (u >> 1), kb = u & 1;
+        const Frag* sK = sKV + (size_t)(u & 1) * 2 * HF;
         const FragV* sV = reinterpret_cast<const FragV*>(sK + HF);
         if (!DIAG) {
             if (EMIT && kb == 0 && (j >= jsb || (j % SBC) == SBC - 1)) {
                 constexpr int QS = CHUNK / KW;
                 const size_t slot = ((size_t)bh * num_block_slots(NC) + block_slot(cq, j >= jsb ? j : j - (SBC - 1), NC)) * (size_t)CHUNK * D;
-                Frag* xd = reinterpret_cast<Frag*>(reinterpret_cast<T*>(p.xs) + slot);
-#pragma unroll
-                for (int s = 0; s < DS; ++s) __builtin_nontemporal_store(Xh[s], &xd[((size_t)qb * DS + s) * 64 + tile_lane<T>(lane, s)]);     // streamed: keep the key/value tiles in L2
-                if (sizeof(T) == 4) {                // (16-bit operands: the consumers transpose xs themselves)
-                    Frag* xt = reinterpret_cast<Frag*>(reinterpret_cast<T*>(p.xsT) + slot);
-                    Frag idf[SPB];
-                    identity_frags<T>(idf, l32, h);
-#pragma unroll
-                    for (int b = 0; b < DB; ++b) {
-                        const f32x16 tr = transpose32<T>(Xh + b * SPB, idf);     // rows q, lane c (block b)
-                        Frag fr[SPB];
-                        pack_block<T>(tr, fr);
-#pragma unroll
-                        for (int s2 = 0; s2 < SPB; ++s2) __builtin_nontemporal_store(fr[s2], &xt[((size_t)b * QS + qb * SPB + s2) * 64 + lane]);
-                    }
-                }
+                emit_state<T, D>(reinterpret_cast<T*>(p.xs) + slot, reinterpret_cast<T*>(p.xsT) + slot, Xh, qb, lane);
             }
         }
 
@@ -252,9 +185,7 @@ __global__ __launch_bounds__((FEW ? 2 * FWD2_THREADS : FWD2_THREADS), (512 / FWD
             const float* diag = p.sd + ((size_t)bh * NC + j) * 4096 + ((size_t)qb * 2 + kb) * 1024;
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
-                f32x4 v4;
-                if constexpr (FEW && RING != 2) v4 = diag_pre[decltype(tag)::value & 1][g];
-                else v4 = *reinterpret_cast<const f32x4*>(diag + g * 256 + lane * 4);
+                const f32x4 v4 = *reinterpret_cast<const f32x4*>(diag + g * 256 + lane * 4);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const int sk = 32 * kb + 8 * g + 4 * h + r, tq = 32 * qb + l32;
@@ -278,58 +209,8 @@ __global__ __launch_bounds__((FEW ? 2 * FWD2_THREADS : FWD2_THREADS), (512 / FWD
             }
         }
 
-        // ---- online softmax.  Fast path: exponentiate against the current reference maximum
-        // without looking at the block's own maximum; only if a lane's partial row sum is not
-        // below 2^16 (a logit beat the reference by more than ~16 bits, or overflowed), or on
-        // the wave's first block, take the slow path: find the block maximum, move the
-        // reference, rescale O and l, and exponentiate again.  Probabilities may thus be as
-        // large as 2^16, which bf16/fp32 operands and the fp32 sums hold without loss.
-        {
-            f32x16 E;
-            float rs = 0.f;
-            if (FOX) {            // T = logit in base-2 units minus the key's gate sum; then as below with scale 1
-                const float* ck = sC + (u & (NST - 1)) * 32 + 4 * h;
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const f32x4 c4 = *reinterpret_cast<const f32x4*>(ck + 8 * g);
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) S[4 * g + r] = __builtin_fmaf(S[4 * g + r], sl2, (RING == 2 ? koff : 0.f) - c4[r]);
-                }
-            }
-            const float sl = FOX ? 1.f : sl2;
-            bool slow = DIAG && kb == 0;                // first block of this wave: no reference yet
-            if (!slow) {
-                const float mneg = -m_run;
-#pragma unroll
-                for (int jj = 0; jj < 16; ++jj) {
-                    E[jj] = __builtin_amdgcn_exp2f(FOX ? S[jj] + mneg : __builtin_fmaf(S[jj], sl2, mneg));
-                    rs += E[jj];
-                }
-                slow = __builtin_amdgcn_ballot_w64(!(rs < 65536.f)) != 0;
-            }
-            if (slow) {
-                float mloc = fmaxf(S[0], S[1]);
-#pragma unroll
-                for (int jj = 2; jj < 16; jj += 2) mloc = fmaxf(mloc, fmaxf(S[jj], S[jj + 1]));
-                mloc = fmaxf(mloc, __shfl_xor(mloc, 32)) * sl;
-                const float m_new = fmaxf(m_run, mloc);     // finite: the first block holds the diagonal
-                const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
-                m_run = m_new;
-                l_run *= alpha;
-#pragma unroll
-                for (int b = 0; b < DB; ++b)
-#pragma unroll
-                    for (int jj = 0; jj < 16; ++jj) O[b][jj] *= alpha;
-                rs = 0.f;
-#pragma unroll
-                for (int jj = 0; jj < 16; ++jj) {
-                    E[jj] = __builtin_amdgcn_exp2f(FOX ? S[jj] - m_new : __builtin_fmaf(S[jj], sl2, -m_new));
-                    rs += E[jj];
-                }
-            }
-            l_run += rs;
-            S = E;
-        }
+        if (FOX) gate_logits<RING>(S, sC + (u & 1) * 32 + 4 * h, sl2, koff);
+        softmax_step<FOX, DB>(S, O, m_run, l_run, sl2, DIAG && kb == 0);
         FragV Pb[SPB];
         pack_block<TIO>(S, Pb);
 
@@ -343,7 +224,6 @@ __global__ __launch_bounds__((FEW ? 2 * FWD2_THREADS : FWD2_THREADS), (512 / FWD
             // ---- X <- X (I - dP) after the chunk (phase A) / after the super-block (phase B) -------
             const bool upd = kb == 1 && (j > 0 || RING) && (j >= jsb || (j % SBC) == 0);
             if (upd) {
-                const Frag* sPu = sP + (FEW ? (u >> 1) & 1 : 0) * DPF;
                 f32x16 Xn[DB];
 #pragma unroll
                 for (int b = 0; b < DB; ++b) {
@@ -355,7 +235,7 @@ __global__ __launch_bounds__((FEW ? 2 * FWD2_THREADS : FWD2_THREADS), (512 / FWD
 #pragma unroll
                 for (int b = 0; b < DB; ++b)
 #pragma unroll
-                    for (int s = 0; s < DS; ++s) Xn[b] = Tr<T>::mma(sPu[(b * DS + s) * 64 + tile_lane<T>(lane, s)], Xh[s], Xn[b]);
+                    for (int s = 0; s < DS; ++s) Xn[b] = Tr<T>::mma(sP[(b * DS + s) * 64 + tile_lane<T>(lane, s)], Xh[s], Xn[b]);
 #pragma unroll
                 for (int b = 0; b < DB; ++b) {
                     if (HAS_MASTER) Xm[b] = Xn[b];
@@ -367,23 +247,22 @@ __global__ __launch_bounds__((FEW ? 2 * FWD2_THREADS : FWD2_THREADS), (512 / FWD
     // Every wave passes the same nstage barriers: as a bystander (stages right of its own chunk: it only helps
     // with the tile copies), through its own chunk (two stages), then the steady state.
     auto top_of_stage = [&](int u) {
-        if (FEW) { lds_barrier(); return; }
         wait_tiles_and_sync();            // stage u has landed; everyone is done with stage u-1
         if (u + 1 < nstage) issue_kv(u + 1);
         if ((u & 1) == 0) issue_dp(jtop - (u >> 1));
     };
     const int u0 = RING == 2 ? (active ? 0 : nstage) : (active ? 2 * (jtop - cq) : nstage);      // this wave's first stage
-    if (!FEW) issue_kv(0);
+    issue_kv(0);
     int u = 0;
     for (; u < u0; ++u) top_of_stage(u);
     if (active) {
         if (RING != 2) {
-            top_of_stage(u); stage(u, std::integral_constant<int, FEW ? 0 : 2>{}); ++u;
-            top_of_stage(u); stage(u, std::integral_constant<int, FEW ? 1 : 2>{}); ++u;
+            top_of_stage(u); stage(u, std::true_type{}); ++u;
+            top_of_stage(u); stage(u, std::true_type{}); ++u;
         }
         for (; u < nstage; ++u) {
             top_of_stage(u);
-            stage(u, std::integral_constant<int, 3>{});
+            stage(u, std::false_type{});
         }
     }
     if (RING) {
@@ -409,68 +288,23 @@ __global__ __launch_bounds__((FEW ? 2 * FWD2_THREADS : FWD2_THREADS), (512 / FWD
         return;
     }
 
-    // ---- epilogue: normalise, store o and lse (paper Sec. 3.3, last step) ---------------------
     if (!active) return;
-    const float l_tot = l_run + __shfl_xor(l_run, 32);
-    const float inv = 1.f / l_tot;
-    const int tq = cq * CHUNK + 32 * qb + l32;
-    // A lane holds pieces of four components, 4h of every eight; with 16-bit results the two halves of the wave exchange
-    // every other one, so that each stores eight at a time (16 bytes: half as many stores.  Whole forward, 512 heads of 300
-    // tokens, d = 128 211.4 -> 207.7 us; 128 heads of 2048, d = 64 273.0 -> 270.1, within what two runs differ by).
-    typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-    union { Vec4 v4[4]; u32x4 v8[2]; unsigned w[8]; } out[DB];
-#pragma unroll
-    for (int b = 0; b < DB; ++b) {
-#pragma unroll
-        for (int g = 0; g < 4; ++g)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) out[b].v4[g][r] = (TIO)(O[b][4 * g + r] * inv);
-        if constexpr (sizeof(TIO) == 2) {
-#pragma unroll
-            for (int g = 0; g < 2; ++g) {
-                unsigned* w = out[b].w + 4 * g;
-#pragma unroll
-                for (int e = 0; e < 2; ++e) {
-                    const auto x = __builtin_amdgcn_permlane32_swap(w[e], w[2 + e], false, false);
-                    w[e] = x[0]; w[2 + e] = x[1];
-                }
-            }
-        }
-    }
-    if (tq < L) {
-        TIO* orow = reinterpret_cast<TIO*>(p.o) + user_vec(p.ul, bh, tq);
-#pragma unroll
-        for (int b = 0; b < DB; ++b) {
-            if constexpr (sizeof(TIO) == 2) {
-#pragma unroll
-                for (int g = 0; g < 2; ++g) *reinterpret_cast<u32x4*>(orow + 32 * b + 16 * g + 8 * h) = out[b].v8[g];
-            } else {
-#pragma unroll
-                for (int g = 0; g < 4; ++g) *reinterpret_cast<Vec4*>(orow + 32 * b + 8 * g + 4 * h) = out[b].v4[g];
-            }
-        }
-        const float ci = FOX ? p.cum[(size_t)bh * NC * CHUNK + tq] : 0.f;
-        if (h == 0) p.lse[user_scl(p.ul, bh, tq)] = (m_run + __builtin_amdgcn_logf(l_tot) + ci) * 0.69314718055994530942f;
-    }
+    store_result<TIO, D, FOX>(p, O, m_run, l_run, bh, cq * CHUNK + 32 * qb + l32, L, h);
 }
 
-template <typename TIO, int D, bool FOX, bool EMIT, int RING = 0, bool FEW = false>
+template <typename TIO, int D, bool FOX, bool EMIT, int RING = 0>
 hipError_t launch_attn_fwd2_f(const FwdParams& p, hipStream_t stream) {
     using C = Fwd2Cfg<TIO, D>;
-    constexpr size_t bytes = FEW ? C::smem_bytes_few : C::smem_bytes;
+    constexpr size_t bytes = C::smem_bytes;
     static_assert(bytes <= 160 * 1024, "LDS budget");
     // set once per process; a function-local static is initialised under the language's own lock
-    static const hipError_t attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_fwd2_kernel<TIO, D, FOX, EMIT, RING, FEW>),
+    static const hipError_t attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_fwd2_kernel<TIO, D, FOX, EMIT, RING>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
     if (attr_err != hipSuccess) return attr_err;
     const int ntiles = ((RING == 2 ? p.NCq : p.NC) + FWD2_CPT - 1) / FWD2_CPT;
     const int BH = p.B * p.H;
     dim3 grid(xcd_deal_grid(ntiles, BH));
-    if constexpr (!FEW && sizeof(TIO) == 2) {
-        // one workgroup or none for each of the 32 CUs of an XCD
-        if (grid.x <= 256) return launch_attn_fwd2_f<TIO, D, FOX, EMIT, RING, true>(p, stream);
-    }
-    hipLaunchKernelGGL((attn_fwd2_kernel<TIO, D, FOX, EMIT, RING, FEW>), grid, dim3(FEW ? 2 * FWD2_THREADS : FWD2_THREADS), bytes, stream, p);
+    hipLaunchKernelGGL((attn_fwd2_kernel<TIO, D, FOX, EMIT, RING>), grid, dim3(FWD2_THREADS), bytes, stream, p);
     return hipGetLastError();
 }
 template <typename TIO, int D>
@@ -535,7 +369,10 @@ hipError_t launch_ring_finish(const FwdParams& p, int d, int is_bf16, hipStream_
     return d == 64 ? launch_ring_finish_t<float, 64>(p, stream) : launch_ring_finish_t<float, 128>(p, stream);
 }
 
+bool attn_few_runs(const FwdParams& p, int d, int is_bf16);
+hipError_t launch_attn_few(const FwdParams& p, int d, int is_bf16, hipStream_t stream);
 hipError_t launch_attn_fwd2(const FwdParams& p, int d, int is_bf16, hipStream_t stream) {
+    if (attn_few_runs(p, d, is_bf16)) return launch_attn_few(p, d, is_bf16, stream);
     if (is_bf16) return d == 64 ? launch_attn_fwd2_t<bf16_t, 64>(p, stream) : launch_attn_fwd2_t<bf16_t, 128>(p, stream);
     return d == 64 ? launch_attn_fwd2_t<float, 64>(p, stream) : launch_attn_fwd2_t<float, 128>(p, stream);
 }
