@@ -175,12 +175,12 @@ __global__ __launch_bounds__(512, 2) void attn_few_kernel(FwdParams p) {
                 return n > 0 || RING ? n : -1;
             };
             Frag pa[HB][DS];                              // fragments of a product: each block's in the place of its predecessor's
-            auto read_dp = [&](int j, int block) {
+            auto read_dp = [&](int j, int block, bool used) {
                 const Frag* src = (j >= jsb ? reinterpret_cast<const Frag*>(p.dp) + ((size_t)bh * NC + j) * (D * D / C::FE)
                                             : reinterpret_cast<const Frag*>(p.dp2) + ((size_t)bh * nsb + j / SBC) * (D * D / C::FE)) + (HX * HB + block) * DS * 64;
 #pragma unroll
                 for (int s = 0; s < DS; ++s) pa[block][s] = *reinterpret_cast<const Frag*>(scalar_base(src + (s & ~3) * 64, tile_lane<T>(lane, s) * 16) + (s & 3) * 1024);
-                last += DS;
+                if (used) last += DS;                     // (requests that nobody waits for may have gone)
             };
             auto mul = [&](int block) {
 #pragma unroll
@@ -205,7 +205,7 @@ __global__ __launch_bounds__(512, 2) void attn_few_kernel(FwdParams p) {
             const int first = next(j + 1);
             if (first >= 0) {
 #pragma unroll
-                for (int b = 0; b < HB; ++b) read_dp(first, b);
+                for (int b = 0; b < HB; ++b) read_dp(first, b, true);
             }
             last = 0;
             while (iter < 2 * (jtop - j) - 2) next_iteration();      // (stages of the chunk to the right)
@@ -223,13 +223,13 @@ __global__ __launch_bounds__(512, 2) void attn_few_kernel(FwdParams p) {
                 read_other();
                 mul(0);
                 __builtin_amdgcn_sched_barrier(0);
-                read_dp(js, 0);
+                read_dp(js, 0, jl >= 0);
                 if (decltype(near)::value) emit(j);
                 next_iteration();
                 if constexpr (HB == 2) {
                     mul(1);
                     __builtin_amdgcn_sched_barrier(0);
-                    read_dp(js, 1);
+                    read_dp(js, 1, jl >= 0);
                 }
                 pack();
                 publish();
