@@ -120,6 +120,18 @@ template <> struct Tr<float> {
 template <typename TIO> struct Compute { typedef TIO type; };
 template <> struct Compute<bf16_t> { typedef half_t type; };
 
+// a * b, element by element, rounded once, to 16 bits.  (Written as a product and a conversion, four at a time, it is rounded to 32 bits first: 6e-5
+// of the results then are the other neighbour of a tie.)
+__device__ __forceinline__ halfx4 mul_once(f32x4 a, f32x4 b) {
+    union { unsigned w[2]; halfx4 v; } u;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(u.w[i]) : "v"(a[2 * i]), "v"(b[2 * i]));
+        asm("v_fma_mixhi_f16 %0, %1, %2, 0" : "+v"(u.w[i]) : "v"(a[2 * i + 1]), "v"(b[2 * i + 1]));
+    }
+    return u.v;
+}
+
 template <typename TO, typename TI>
 __device__ __forceinline__ typename Tr<TO>::Frag cvt_frag(const typename Tr<TI>::Frag& f) {
     typename Tr<TO>::Frag o;

@@ -245,10 +245,10 @@ __global__ __launch_bounds__(256, (Prep16Cfg<TIO, D>::WGS_PER_CU)) void prep16_f
 #pragma unroll
         for (int it = 0; it < 4; ++it) {
             const int t = (tid >> 4) + 16 * it;
-            Vec4 n4, x4;
+            Vec4 x4;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) { n4[r] = (T)(v[it][r] * b[r]); x4[r] = (T)v[it][r]; }
-            *reinterpret_cast<Vec4*>(Nt + t * LDC + c) = n4;
+            for (int r = 0; r < 4; ++r) x4[r] = (T)v[it][r];
+            *reinterpret_cast<Vec4*>(Nt + t * LDC + c) = mul_once(v[it], b);
             if (BWD) __builtin_nontemporal_store(x4, reinterpret_cast<Vec4*>(reinterpret_cast<T*>(p.aim) + bhc * 4096 + t * 64 + c));
         }
     }
