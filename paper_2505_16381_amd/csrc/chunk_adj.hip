@@ -796,20 +796,38 @@ __global__ __launch_bounds__(CA_NT, 2 * (CaCfg<TIO, D>::WGS_PER_CU)) void chunk_
         mmt<T, D, false, D, false, D>(gacc, XW, 32 * cb6, XW, 32 * mb6, tl);          // G = W W^T, as the transform forms it
         const int m = 32 * mb6 + l32;
         const float bm = beta_s[m];
-        float sum = 0.f;
+        float mv[16], mg[16];
 #pragma unroll
         for (int jj = 0; jj < 16; ++jj) {
-            const float mv = (32 * cb6 + acc_row(jj, h) >= m) ? 0.f : -acc[jj];
-            sum += gacc[jj] * mv;
-            acc[jj] = bm * mv;
+            mv[jj] = (32 * cb6 + acc_row(jj, h) >= m) ? 0.f : -acc[jj];
+            mg[jj] = gacc[jj] * mv[jj];
         }
-        sum += __shfl_xor(sum, 32);
-        if (h == 0) rowsum[cb6 * CHUNK + m] = sum;
-        st_block_t<T, 64>(Y2, 32 * mb6, 32 * cb6, acc, tl);
+        {       // the row's sum by halves, columns 16 apart first; products are rounded before they are added
+#pragma clang fp contract(off)
 #pragma unroll
-        for (int jj = 0; jj < 16; ++jj) {                 // ... and its mirror image, right of the diagonal
+            for (int jj = 0; jj < 8; ++jj) mg[jj] = mg[jj] + mg[jj + 8];
+#pragma unroll
+            for (int jj = 0; jj < 4; ++jj) {
+                mg[jj] = mg[jj] + mg[jj + 4];
+                mg[jj] = mg[jj] + __shfl_xor(mg[jj], 32);
+            }
+            const float sum = (mg[0] + mg[2]) + (mg[1] + mg[3]);
+            if (h == 0) rowsum[cb6 * CHUNK + m] = sum;
+        }
+        // left of the diagonal beta M is rounded once, its mirror image to 32 bits first
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const f32x4 m4 = {mv[4 * g], mv[4 * g + 1], mv[4 * g + 2], mv[4 * g + 3]};
+            const f32x4 b4 = {bm, bm, bm, bm};
+            if constexpr (sizeof(T) == 4) *reinterpret_cast<f32x4*>(Y2 + C::TileC::at(m, 32 * cb6 + 8 * g + 4 * h)) = b4 * m4;
+            else lds_write(lds_addr(Y2) + tl.of<64>().vec_at(32 * mb6, 32 * cb6 + 8 * g), mul_once(m4, b4));
+        }
+#pragma unroll
+        for (int jj = 0; jj < 16; ++jj) {
             const int n = 32 * cb6 + acc_row(jj, h);
-            if (n < m) Y2[C::TileC::at(n, m)] = (T)acc[jj];
+            float bmv = bm * mv[jj];
+            asm("" : "+v"(bmv));
+            if (n < m) Y2[C::TileC::at(n, m)] = (T)bmv;
         }
     }
     __syncthreads();
