@@ -179,7 +179,7 @@ __global__ __launch_bounds__(512, 2) void attn_few_kernel(FwdParams p) {
                 const Frag* src = (j >= jsb ? reinterpret_cast<const Frag*>(p.dp) + ((size_t)bh * NC + j) * (D * D / C::FE)
                                             : reinterpret_cast<const Frag*>(p.dp2) + ((size_t)bh * nsb + j / SBC) * (D * D / C::FE)) + (HX * HB + block) * DS * 64;
 #pragma unroll
-                for (int s = 0; s < DS; ++s) pa[block][s] = *reinterpret_cast<const Frag*>(scalar_base(src + (s & ~3) * 64, tile_lane<T>(lane, s) * 16) + (s & 3) * 1024);
+                for (int s = 0; s < DS; ++s) pa[block][s] = *(const __attribute__((address_space(1))) Frag*)(scalar_base(src + (s & ~3) * 64, tile_lane<T>(lane, s) * 16) + (s & 3) * 1024);
                 if (used) last += DS;                     // (requests that nobody waits for may have gone)
             };
             auto mul = [&](int block) {

@@ -338,15 +338,18 @@ __device__ __forceinline__ void ld_tile_frags_tr(const TileTr& a, typename Tr<E>
 }
 
 // p, the same for the whole wave, plus a lane's 32-bit offset, as an access takes it from scalar registers and one vector register.  (Left
-// to itself the compiler keeps per-lane 64-bit pointers across loops: vector arithmetic, and two address registers per lane.  With the copies
+// to itself the compiler keeps per-lane 64-bit pointers across loops: vector arithmetic, and two address registers per lane.  A pointer to
+// global memory: rebuilt from an integer it would otherwise be a generic one, and an access through it FLAT, which has no scalar base,
+// counts among the LDS accesses too and is in no order with the copies to LDS.  With the copies
 // to LDS this way, us: forward of 128 heads of 4096 tokens, d = 64, 649 -> 614, 64 of 8192, d = 128, 1818 -> 1780, 16 of 1000 51.5 ->
 // 50.2; adjoint scan 1919 -> 1903, chunk stage 1472 -> 1447 at the second shape.  Not in the far key sums, whose copying waves have vector
 // issue to spare: 64 heads of 8192 tokens, d = 64, 1177 -> 1198, d = 128 1838 -> 1856.)
-__device__ __forceinline__ const char* scalar_base(const void* p, unsigned lane_offset) {
+typedef const __attribute__((address_space(1))) char* GlobalBytes;
+__device__ __forceinline__ GlobalBytes scalar_base(const void* p, unsigned lane_offset) {
     const unsigned long long a = reinterpret_cast<unsigned long long>(p);
     const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)a), hi = __builtin_amdgcn_readfirstlane((unsigned)(a >> 32));
     asm volatile("" : "+v"(lane_offset));        // (its extension to 64 bits stays here, where the access absorbs it)
-    return reinterpret_cast<const char*>((unsigned long long)hi << 32 | lo) + lane_offset;
+    return reinterpret_cast<GlobalBytes>((unsigned long long)hi << 32 | lo) + lane_offset;
 }
 
 // Linear copy of NFRAG 16-byte fragments global -> LDS, asynchronous (direct-to-LDS), by a workgroup of
@@ -358,7 +361,7 @@ template <int NT, int NFRAG, bool SCALAR = true, typename Frag>
 __device__ __forceinline__ void async_copy_tile(const Frag* g, Frag* s, int tid, int wv) {
     static_assert(sizeof(Frag) == 16 && NFRAG % 64 == 0 && (NFRAG % NT == 0 || NFRAG < NT), "whole groups of fragments");
     const unsigned lane = (tid & 63) * 16;
-    auto at = [&](const Frag* p) { return SCALAR ? scalar_base(p, lane) : reinterpret_cast<const char*>(p) + lane; };
+    auto at = [&](const Frag* p) { return SCALAR ? scalar_base(p, lane) : (GlobalBytes)(reinterpret_cast<const char*>(p) + lane); };
     if (NFRAG < NT) {          // fewer groups than waves: the first NFRAG/64 waves take one each (wave-uniform test)
         if (wv * 64 < NFRAG)
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(at(g + wv * 64)),
@@ -368,7 +371,7 @@ __device__ __forceinline__ void async_copy_tile(const Frag* g, Frag* s, int tid,
     constexpr int NPT = NFRAG / NT > 0 ? NFRAG / NT : 1;
 #pragma unroll
     for (int i0 = 0; i0 < NPT; i0 += 4) {
-        const char* ga = at(g + (wv * NPT + i0) * 64);
+        const GlobalBytes ga = at(g + (wv * NPT + i0) * 64);
         Frag* sa = s + (wv * NPT + i0) * 64;
         __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)ga, (__attribute__((address_space(3))) void*)sa, 16, 0, 0);
         if (i0 + 1 < NPT) __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)ga, (__attribute__((address_space(3))) void*)sa, 16, 1024, 0);
