@@ -19,6 +19,7 @@
 #include <type_traits>
 
 #include "path_common.h"
+#include "sweep_form.h"
 #include "sweep_parts.h"
 
 namespace path {
@@ -412,18 +413,7 @@ __global__ __launch_bounds__(512, 2) void attn_few_kernel(FwdParams p) {
     store_result<TIO, D, FOX>(p, O, m_run, l_run, bh, cq * CHUNK + 32 * qb + l32, L, h);
 }
 
-// Query chunks per workgroup, 0: the general form.  One where every chunk has a CU, and for two rounds of them, which the chains' different
-// lengths fill evenly if they are not too short: forward, d = 128, us with one / two / general form: 16 heads of 1400 tokens 75 / 84 / 94, of 2000
-// 99 / 108 / 128, 128 of 250 43 / 40 / 44; not in a ring, whose chains have one length (d = 64, 32 heads of 1024 85 / 77 / 78).  Two where every tile
-// of two has a CU, and for three rounds if the chains are long: 32 heads of 2048 167 (general 178), 16 of 4000 191 / 217, of 6000 303 / 321, but of 8000
-// 462 / 459; 64 of 1024 118 / 113; ring, 16 of 4096 376 / 408, d = 64 16 of 3072 164 / 164, 32 of 2048 170 / 153.  With more workgroups the two
-// unsynchronised ones that the general form has on a CU fill its pipes better (64 of 8192 tokens 1817 / 1766, d = 64, 128 of 4096 733 / 606).
-static int few_chunks(const FwdParams& p) {
-    const int n = p.ring == 2 ? p.NCq : p.NC;
-    const unsigned one = xcd_deal_grid(n, p.B * p.H), two = xcd_deal_grid((n + 1) / 2, p.B * p.H);
-    if (one <= 256 || (one <= 512 && !p.ring && n >= 8)) return 1;
-    return two <= 256 || (two <= 768 && p.NC >= (p.ring ? 48 : 32)) ? 2 : 0;
-}
+static int few_chunks(const FwdParams& p) { return sweep_form(p.ring == 2 ? p.NCq : p.NC, p.NC, p.B * p.H, p.ring != 0); }
 
 template <typename TIO, int D, bool FOX, bool EMIT, int RING, int CPT>
 hipError_t launch_attn_few_c(const FwdParams& p, hipStream_t stream) {
