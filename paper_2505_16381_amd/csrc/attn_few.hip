@@ -8,13 +8,13 @@
 //   two waves    32 queries each: logits, online softmax, O.  In a stage of 32 keys they have the softmax of these keys between the products
 //                of the logits of the next 32 and of P V of the 32 before, one exponential and one read from LDS per product.
 //   two waves    half of the columns of the query state each, a stage and a half ahead; its operand copy goes to the former, and to the other
-//                one, through LDS.  The fragments of the chunk products come straight from memory, each read once per workgroup.  They
+//                one, through LDS.  The fragments of the chunk products come straight from memory, each read once per query chunk.  They
 //                also write the states that a training pair's backward starts from.
 //   waves 4..7   the copies of keys and values to LDS, two stages ahead (with two chunks per workgroup these are the states' waves).
 // One barrier per stage.  The form of attn_fwd2.hip with copying waves that ran before, with at most 256 tiles of two chunks, took,
-// us: sweep of 16 heads of 1000 tokens, d = 128, 33.2, now 23.0, d = 64 20.9 / 14.6; one head of 8000, d = 128, 139 / 94; fp32 (general
+// us: sweep of 16 heads of 1000 tokens, d = 128, 33.2, now 21.0, d = 64 20.9 / 14.6; one head of 8000, d = 128, 139 / 94; fp32 (general
 // form), d = 64, 4 heads of 900, 90 / 64.  Whole forward, against the general form: two heads of 14000 tokens, d = 128, 364 / 218, d = 64
-// 248 / 150; 16 of 4000 235 / 191 and 141 / 113.  Of the 23 us 6 are the start (arguments, first tiles, own chunk), then 0.7 to 1.1 a chunk, of which
+// 248 / 150; 16 of 4000 235 / 191 and 141 / 113.  Of the 21 us 6 are the start (arguments, first tiles, own chunk), then 0.7 to 1.1 a chunk, of which
 // the products alone would take 0.5: reads and writes of LDS (1150 cycles a chunk) and L2 are what is left.
 #include <type_traits>
 
@@ -132,7 +132,7 @@ __global__ __launch_bounds__(512, 2) void attn_few_kernel(FwdParams p) {
 
     if (wv >= 2 * CPT) {
         // ---- the query state: fp32 master; its operand copy, in registers, and in LDS for the logits and for the other wave, which has the
-        // other half of the columns.  The products' fragments come straight from memory, a chunk ahead: each is read once.
+        // other half of the columns.  The products' fragments come straight from memory, a chunk ahead: each is read once per query chunk.
         auto state = [&](auto second) {
             constexpr int HX = decltype(second)::value, HB = DB / 2, HS = DS / 2;      // this wave's half; blocks and slabs of a half
             int iter = W0, before = 0, last = 0;          // CPT 2: requests behind the copies of the iteration before the last, in the last one

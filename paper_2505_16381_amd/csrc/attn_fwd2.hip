@@ -173,7 +173,6 @@ __global__ __launch_bounds__(FWD2_THREADS, (512 / FWD2_THREADS)) void attn_fwd2_
         const FragV* sV = reinterpret_cast<const FragV*>(sK + HF);
         if (!DIAG) {
             if (EMIT && kb == 0 && (j >= jsb || (j % SBC) == SBC - 1)) {
-                constexpr int QS = CHUNK / KW;
                 const size_t slot = ((size_t)bh * num_block_slots(NC) + block_slot(cq, j >= jsb ? j : j - (SBC - 1), NC)) * (size_t)CHUNK * D;
                 emit_state<T, D>(reinterpret_cast<T*>(p.xs) + slot, reinterpret_cast<T*>(p.xsT) + slot, Xh, qb, lane);
             }

@@ -340,7 +340,7 @@ __global__ __launch_bounds__(256, 2) void bwd_adjoint2_lite_kernel(BwdParams p) 
     using Frag = typename Tr<T>::Frag;
     using FragV = typename Tr<TIO>::Frag;
     static_assert(sizeof(T) == 2, "16-bit operands");
-    constexpr int KW = Tr<T>::KW, SPB = 32 / KW, DB = D / 32, DS = D / KW, QS = CHUNK / KW;
+    constexpr int KW = Tr<T>::KW, SPB = 32 / KW, DB = D / 32, DS = D / KW;
     constexpr int KVF = C::KV_FRAGS, DPF = C::DP_FRAGS;
     constexpr bool AHEAD = LiteCfg<TIO, D>::AHEAD;
     constexpr int STF = LiteCfg<TIO, D>::STF;

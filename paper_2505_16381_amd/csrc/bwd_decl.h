@@ -12,7 +12,8 @@ struct BwdParams {
     const void *kt2, *kt2T, *dpt2;     // second-level tiles: keys per chunk, -(I - P_superblock) per super-block
     const void *xs, *xsT;              // per-(chunk, key block) query-state tiles from the states sweep
     void *doq, *doT;                   // per-chunk dO tiles (I/O type)
-    void* gs;                          // per-pair adjoint-state tiles gT (rows b, contraction q): g(i,j-1) at slot (i,j)
+    void* gs;                          // per-pair adjoint-state tiles, g(i,j-1) at slot (i,j): 16-bit operands as xs (rows q, contraction b, lanes
+                                       // as tile_lane() has them), fp32 operands gT (rows b, contraction q)
     float *delta;             // [BH][Lp]
     float *lse2p;             // [BH][Lp]: lse * log2(e), zero past L
     float *dqb, *dkb, *dvp;   // [BH][Lp][d] fp32: dQb, dKb, dV (off-diagonal part)

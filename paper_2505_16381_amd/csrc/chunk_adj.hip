@@ -36,7 +36,8 @@
 // d=64, packed batch of 64 sequences of 256 .. 2048 tokens (8 heads, d = 128) 700 + 1267 -> 1460.  (Near sums alone 681 us, the
 // rest alone 892, at the first of these shapes.  With a third stage of states for the pairs the near sums take as long, and at
 // d = 64 longer.)  Of what follows the near sums most is vector instructions, in a chain: addresses, conversions, LDS stores of two
-// bytes.  With tiles turned instead of padded (lds_tile.h; no bank conflicts), addresses that leave one exclusive or per access,
+// bytes.  With tiles turned instead of padded (lds_tile.h; 64 heads of 8192 tokens, d = 128: 60 million cycles of bank conflicts, now
+// 11), addresses that leave one exclusive or per access,
 // 64 x 64 results multiplied out transposed, so that they are stored four at a time, dGs formed where M is and whole chunks stored without
 // checks of the row, the chunk stage (with sb_chain_kernel) went, us, at d = 128 from 1594 to 1499 (64 heads of 8192 tokens), 1288 to 1163
 // (512 of 1024), 42.2 to 38.2 (8 of 1000), at d = 64 from 711 to 675 (128 of 4096).  The turned tiles alone, with addresses left to the compiler,
@@ -58,8 +59,8 @@ template <typename TIO, int D> struct NearCfg {
     static constexpr int KVF = CHUNK * D / Tr<T>::FE;                 // fragments of a tile
     static constexpr int STF = 3 * KVF + 32;                          // a stage: xs | doq | g | lse2, delta
     static constexpr int PDF = 2 * 2 * 4 * 64;                        // a hand-over buffer: (P | dS) x 2 key halves x 4 slabs
-    // d = 64: one hand-over buffer (and a second barrier per pair), so that two workgroups share a CU.  (Of the 128 registers
-    // that this leaves 6 lie in scratch, with gates up to 26, none of them inside the loop over pairs.)
+    // d = 64: one hand-over buffer (and a second barrier per pair), so that two workgroups share a CU.  (The 128 registers that
+    // this leaves do; with gates 16 more, 17 with interleaved heads, lie in scratch, none of them inside the loop over pairs.)
     static constexpr int HB = D == 64 ? 1 : 2;
     static constexpr int smem_bytes = (2 * STF + HB * PDF) * 16;
     // dV | dKb on their way to the waves that go on with them, fp32 [key][D + 4]

@@ -14,7 +14,7 @@
 //
 // What bounds it: memory, where there are several workgroups per CU (512 heads of 1024 tokens, d = 128: 1.4 GB in 286 us = 4.9 TB/s,
 // what a plain copy of such blocks reaches; d = 64 153 us), the chain of its phases where there are few (16 heads of 1000 tokens
-// 14.3 us, d = 64 10.8).  With operand fragments of Q and K read from global memory by each wave that needs them -- 32 rows per
+// 14.3 us, launch after launch; d = 64 10.8.  A single launch among others takes 17 to 18).  With operand fragments of Q and K read from global memory by each wave that needs them -- 32 rows per
 // request -- and V element by element, 426, 195, 18.6 and 14.0 us: requests, not bytes, were what it waited for.
 #include "path_common.h"
 
